@@ -11,7 +11,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libst.so")
 PROBE_LIB = os.path.join(HERE, "libst_probe.so")
 
-SOURCES = ["st_error.hip", "st_rope.hip", "st_plan.hip", "st_prefill.hip", "st_prefill_bwd.hip", "st_cache.hip", "st_decode.hip", "st_sched.hip"]
+SOURCES = ["st_error.hip", "st_rope.hip", "st_plan.hip", "st_prefill.hip", "st_prefill_bwd.hip", "st_attn_f32.hip", "st_cache.hip", "st_decode.hip", "st_sched.hip"]
 PROBE_SOURCES = ["st_probe.hip"]            # (linked with st_error.o for the error text)
 
 FLAGS = [
@@ -25,8 +25,9 @@ FLAGS = [
 # per-file extras.  The backward kernels run one wave per SIMD and keep their big accumulators in place; with
 # the matrix instructions writing ordinary vector registers the compiler stops shuttling score blocks
 # through the accumulation registers (12 % on the query-side kernel).  The forward file manages its
-# accumulation registers by hand and must not get this.
-EXTRA_FLAGS = {"st_prefill_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+# accumulation registers by hand and must not get this.  (The fp32 query-side kernel fits two waves per SIMD with it.)
+EXTRA_FLAGS = {"st_prefill_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+               "st_attn_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _hipcc():

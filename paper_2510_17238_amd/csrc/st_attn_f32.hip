@@ -1,0 +1,597 @@
+// Streaming-mask attention in fp32 on the matrix cores: forward and backward (the fp32 side of st_attn_prefill and
+// st_attn_prefill_bwd; Sec. 3.2, Eq. 2).
+//
+// v_mfma_f32_32x32x2_f32 multiplies fp32 operands and accumulates in fp32 -- no precision is given up -- at twice the
+// rate of the vector ALUs and leaves them free for the exponentials.  With two k-values per instruction the operand
+// layouts are so simple that no shuffle is ever needed:
+//   * first-type products (S^T = K Q^T and the like, contraction over the head dims): step (jj, e) contracts the dims
+//     8 jj + e (lanes 0-31) and 8 jj + 4 + e (lanes 32-63), so a lane's operands of four steps are ONE 16-byte load of a
+//     row as it lies in memory;
+//   * accumulator register i of a lane holds row r(i) = 8 (i / 4) + 4 (lane / 32) + i % 4 of the result's 32 rows -- and
+//     that is exactly the B operand of step i of a second-type product (O^T = V^T P^T and the like) whose k-values are
+//     those rows; its A operand is element (row r(i), dim 32 db + lane % 32): 128 contiguous bytes per half wave.
+// So every operand comes straight from the caller's tensors through the caches (rows gathered by token index): no packed
+// copies, no workspace for the forward, and no LDS in the loops beyond the 32 rows a workgroup shares.
+//
+// Work: a workgroup owns 32 rows (query rows; keys for dK / dV) of a work item and one head; its FOUR WAVES take the
+// 32-row blocks of the other side in turn and their results meet in LDS at the end.  A wave's chain of blocks is a
+// quarter of the row's -- what a small problem is bound by -- and the waves never wait for each other inside the loop.
+// Bound by the fp32 matrix rate (157 TFLOP/s); one block of 32 x 32 x 128 is 128 instructions of 64 cycles in the
+// forward, so the memory latency of the next block's operands, requested a phase ahead, is covered by one wave.
+// Two sequences of about 900 tokens, 16 / 8 heads of 128 dims: forward 2.86 ms (one thread per row, vector ALUs) -> 0.090 ms
+// (58 TFLOP/s of unmasked flop), gradients 19.8 -> 0.35 ms; 128 tokens, 2 heads of 64 dims: 200 -> 8 us.
+#include <math.h>
+
+#include <type_traits>
+
+#include "st_plan.h"
+
+namespace st {
+
+constexpr int kF32Waves = 4, kF32Rows = 32;
+
+// accumulator register i <-> row of the 32-row block
+__device__ __forceinline__ int acc_row(int i, int hg) { return 8 * (i >> 2) + 4 * hg + (i & 3); }
+
+// the rows a workgroup owns: 32-row part `sub` of a work item
+struct OwnRows {
+    int first, count;        // first row relative to the row's stream, rows (<= 32)
+};
+__device__ __forceinline__ OwnRows own_rows(const WorkItem& it, int sub) {
+    return OwnRows{it.row0 + kF32Rows * sub, min(kF32Rows, it.n_rows - kF32Rows * sub)};
+}
+
+// [32][D] block of rows in LDS; four floats of padding send 16 consecutive rows to 16 different 16-byte columns
+template <int D>
+struct RowsLds {
+    float x[kF32Rows][D + 4];
+};
+
+// What the four waves of a workgroup merge at the end
+template <int D>
+struct MergeLds {
+    float o[kF32Waves][kF32Rows][D + 4];
+};
+
+// accumulator blocks (lane = row, dims along the registers) -> LDS rows
+template <int D>
+__device__ __forceinline__ void park(float (&rows)[kF32Rows][D + 4], const f32x16 (&acc)[D / 32], int n, int hg) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+            *reinterpret_cast<f32x4*>(&rows[n][32 * db + 8 * q4 + 4 * hg]) =
+                f32x4{acc[db][4 * q4], acc[db][4 * q4 + 1], acc[db][4 * q4 + 2], acc[db][4 * q4 + 3]};
+}
+
+// --------------------------------------------------------------------------
+// Forward
+// --------------------------------------------------------------------------
+template <int D>
+struct FwdF32Smem {
+    MergeLds<D> merge;
+    float m[kF32Waves][kF32Rows], l[kF32Waves][kF32Rows];
+};
+
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves, 2) void prefill_f32_kernel(float* __restrict__ out, float* __restrict__ lse,
+                                                                        const float* __restrict__ q, const float* __restrict__ k,
+                                                                        const float* __restrict__ v, PlanView pv, int n_q_heads,
+                                                                        int n_kv_heads, float scale) {
+    constexpr int JJ = D / 8, DB = D / 32;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    FwdF32Smem<D>& sm = *reinterpret_cast<FwdF32Smem<D>*>(smem_raw);
+    const unsigned per_item = unsigned(n_q_heads) * (kTileM / kF32Rows);
+    const int rank = int(blockIdx.x / per_item);
+    const unsigned rest = blockIdx.x % per_item;
+    const int hh = int(rest % unsigned(n_q_heads)), sub = int(rest / unsigned(n_q_heads));
+    const int hk = hh % n_kv_heads, hq = hk * (n_q_heads / n_kv_heads) + hh / n_kv_heads;     // consecutive workgroups -> consecutive KV heads
+    const WorkItem it = pv.sorted[rank];
+    const OwnRows own = own_rows(it, sub);
+    if (own.count <= 0) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, hg = lane >> 5;
+    const int my_row = own.first + min(n, own.count - 1), last_row = own.first + own.count - 1;
+    const int my_vis = pv.vis[it.a_base + my_row];
+    const int64_t my_tok = pv.perm[it.a_base + my_row];
+    // 32-column blocks of the two runs: the own stream up to the last row, for reasoning rows the source prefix it sees
+    const int blocks_a = last_row / kF32Rows + 1;
+    const int blocks_b = it.kind == ST_SOURCE ? 0 : (pv.vis[it.a_base + last_row] + kF32Rows - 1) / kF32Rows;
+    const int first_vis = pv.vis[it.a_base + own.first];
+    const int n_blocks = blocks_a + blocks_b;
+
+    f32x4 qf[JJ];
+    {
+        const float* qp = q + (my_tok * n_q_heads + hq) * D + 4 * hg;
+#pragma unroll
+        for (int jj = 0; jj < JJ; ++jj) qf[jj] = *reinterpret_cast<const f32x4*>(qp + 8 * jj);
+    }
+    f32x16 o_acc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o_acc[db][i] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+
+    // token of this lane's key row in block t (columns past the end of the stream: the last one, masked below)
+    auto key_token = [&](int t) {
+        t = min(t, n_blocks - 1);
+        const bool in_a = t < blocks_a;
+        const int col = min((in_a ? t : t - blocks_a) * kF32Rows + n, (in_a ? it.n_stream : it.n_src) - 1);
+        return pv.perm[(in_a ? it.a_base : it.b_base) + col];
+    };
+    const int64_t stride = int64_t(n_kv_heads) * D;
+    const float* k_lane = k + int64_t(hk) * D + 4 * hg;
+    const float* v_lane = v + int64_t(hk) * D + n;
+    f32x4 kf[JJ];
+    int tok = 0;
+    if (wave < n_blocks) {
+        tok = key_token(wave);
+        const float* kp = k_lane + tok * stride;
+#pragma unroll
+        for (int jj = 0; jj < JJ; ++jj) kf[jj] = *reinterpret_cast<const f32x4*>(kp + 8 * jj);
+    }
+    for (int t = wave; t < n_blocks; t += kF32Waves) {
+        const int tok_next = key_token(t + kF32Waves);
+        // ---- S^T = K Q^T; the value rows of the block are requested beside it ----
+        f32x16 s;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+        float vf[16][DB];
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+            const float* vp = v_lane + __shfl(tok, acc_row(g, hg)) * stride;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) vf[g][db] = vp[32 * db];
+#pragma unroll
+            for (int jj = g * JJ / 16; jj < (g + 1) * JJ / 16; ++jj)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[jj][e], qf[jj][e], s, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // ---- softmax over the block: lane = query row, register i = column acc_row(i, hg) ----
+        const bool in_a = t < blocks_a;
+        const int c0 = (in_a ? t : t - blocks_a) * kF32Rows;
+        const int limit = in_a ? my_row + 1 : my_vis;                      // columns < limit are visible
+        const int limit_min = in_a ? own.first + 1 : first_vis;            // ... to every row
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] *= scale;
+        if (c0 + kF32Rows > limit_min) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = c0 + acc_row(i, hg) < limit ? s[i] : -INFINITY;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m_run, mx);
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;              // (a row that sees nothing yet)
+        if (__any(m_new > m_run)) {
+            const float alpha = expf(m_run - m_use);
+            l_run *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o_acc[db][i] *= alpha;
+        }
+        m_run = m_new;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            s[i] = expf(s[i] - m_use);
+            l_run += s[i];
+        }
+        // ---- O^T += V^T P^T; the next block's keys are requested beside it ----
+        tok = tok_next;
+        const float* kp = k_lane + tok * stride;
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db) o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[g][db], s[g], o_acc[db], 0, 0, 0);
+#pragma unroll
+            for (int jj = g * JJ / 16; jj < (g + 1) * JJ / 16; ++jj) kf[jj] = *reinterpret_cast<const f32x4*>(kp + 8 * jj);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // ---- merge of the four waves' states ----
+    park<D>(sm.merge.o[wave], o_acc, n, hg);
+    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    if (hg == 0) {
+        sm.m[wave][n] = m_run;
+        sm.l[wave][n] = l_tot;
+    }
+    __syncthreads();
+    const int row = threadIdx.x >> 3, part = threadIdx.x & 7;              // eight threads per row
+    if (row >= own.count) return;
+    float m_all = -INFINITY, wt[kF32Waves], den = 0.f;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) m_all = fmaxf(m_all, sm.m[w][row]);           // finite: column 0 of the own stream is visible
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {
+        wt[w] = expf(sm.m[w][row] - m_all);                                // (0 for a wave that saw nothing)
+        den = fmaf(wt[w], sm.l[w][row], den);
+    }
+    const float inv = 1.f / den;
+    const int64_t rowhead = int64_t(pv.perm[it.a_base + own.first + row]) * n_q_heads + hq;
+    float* op = out + rowhead * D;
+#pragma unroll
+    for (int d = 4 * part; d < D; d += 32) {
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kF32Waves; ++w) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][d]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = fmaf(wt[w], x[e], a[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] *= inv;
+        *reinterpret_cast<f32x4*>(op + d) = a;
+    }
+    if (lse && part == 0) lse[rowhead] = m_all + logf(den);
+}
+
+// --------------------------------------------------------------------------
+// Backward, query side: delta_i = dO_i . O_i, dQ_i = scale sum_j dS_ij K_j
+// --------------------------------------------------------------------------
+template <int D>
+struct DqF32Smem {
+    union {                       // the rows are read in the loop, the merge comes after it
+        struct {
+            RowsLds<D> q, d_out;
+        };
+        MergeLds<D> merge;
+    };
+    float lse[kF32Rows], delta[kF32Rows];
+};
+
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves, 2) void bwd_dq_f32_kernel(float* __restrict__ dq, float* __restrict__ delta_out,
+                                                                       const float* __restrict__ d_out, const float* __restrict__ q,
+                                                                       const float* __restrict__ k, const float* __restrict__ v,
+                                                                       const float* __restrict__ out, const float* __restrict__ lse,
+                                                                       PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
+    constexpr int JJ = D / 8, DB = D / 32;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    DqF32Smem<D>& sm = *reinterpret_cast<DqF32Smem<D>*>(smem_raw);
+    const unsigned per_item = unsigned(n_q_heads) * (kTileM / kF32Rows);
+    const int rank = int(blockIdx.x / per_item);
+    const unsigned rest = blockIdx.x % per_item;
+    const int hh = int(rest % unsigned(n_q_heads)), sub = int(rest / unsigned(n_q_heads));
+    const int hk = hh % n_kv_heads, hq = hk * (n_q_heads / n_kv_heads) + hh / n_kv_heads;
+    const WorkItem it = pv.sorted[rank];
+    const OwnRows own = own_rows(it, sub);
+    if (own.count <= 0) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, hg = lane >> 5;
+    const int my_row = own.first + min(n, own.count - 1), last_row = own.first + own.count - 1;
+    const int my_vis = pv.vis[it.a_base + my_row];
+    const int blocks_a = last_row / kF32Rows + 1;
+    const int blocks_b = it.kind == ST_SOURCE ? 0 : (pv.vis[it.a_base + last_row] + kF32Rows - 1) / kF32Rows;
+    const int first_vis = pv.vis[it.a_base + own.first];
+    const int n_blocks = blocks_a + blocks_b;
+
+    // the workgroup's rows of q and dO into LDS (operands of every wave), their delta on the way
+    const int row = threadIdx.x >> 3, part = threadIdx.x & 7;
+    const int64_t rowhead = int64_t(pv.perm[it.a_base + own.first + min(row, own.count - 1)]) * n_q_heads + hq;
+    {
+        float dl = 0.f;
+#pragma unroll
+        for (int d = 4 * part; d < D; d += 32) {
+            const f32x4 a = *reinterpret_cast<const f32x4*>(d_out + rowhead * D + d), o = *reinterpret_cast<const f32x4*>(out + rowhead * D + d);
+            *reinterpret_cast<f32x4*>(&sm.q.x[row][d]) = *reinterpret_cast<const f32x4*>(q + rowhead * D + d);
+            *reinterpret_cast<f32x4*>(&sm.d_out.x[row][d]) = a;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dl = fmaf(a[e], o[e], dl);
+        }
+        dl += __shfl_xor(dl, 1);
+        dl += __shfl_xor(dl, 2);
+        dl += __shfl_xor(dl, 4);
+        if (part == 0) {
+            sm.lse[row] = lse[rowhead];
+            sm.delta[row] = dl;
+            if (row < own.count) delta_out[rowhead] = dl;
+        }
+    }
+    __syncthreads();
+    const float my_lse = sm.lse[n], my_delta = sm.delta[n];
+
+    auto key_token = [&](int t) {
+        t = min(t, n_blocks - 1);
+        const bool in_a = t < blocks_a;
+        const int col = min((in_a ? t : t - blocks_a) * kF32Rows + n, (in_a ? it.n_stream : it.n_src) - 1);
+        return pv.perm[(in_a ? it.a_base : it.b_base) + col];
+    };
+    const int64_t stride = int64_t(n_kv_heads) * D;
+    const float* k_rows = k + int64_t(hk) * D + 4 * hg;
+    const float* v_rows = v + int64_t(hk) * D + 4 * hg;
+    const float* k_cols = k + int64_t(hk) * D + n;
+    f32x16 acc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
+    f32x4 kf[JJ], vf[JJ];
+    int tok = 0;
+    if (wave < n_blocks) {
+        tok = key_token(wave);
+#pragma unroll
+        for (int jj = 0; jj < JJ; ++jj) kf[jj] = *reinterpret_cast<const f32x4*>(k_rows + tok * stride + 8 * jj);
+#pragma unroll
+        for (int jj = 0; jj < JJ; ++jj) vf[jj] = *reinterpret_cast<const f32x4*>(v_rows + tok * stride + 8 * jj);
+    }
+    for (int t = wave; t < n_blocks; t += kF32Waves) {
+        const int tok_next = key_token(t + kF32Waves);
+        // ---- S^T = K Q^T, dP^T = V dO^T; K as the second product's operand is requested beside them ----
+        f32x16 s, dp;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+        float kt[16][DB];
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+            const float* kp = k_cols + __shfl(tok, acc_row(g, hg)) * stride;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) kt[g][db] = kp[32 * db];
+#pragma unroll
+            for (int jj = g * JJ / 16; jj < (g + 1) * JJ / 16; ++jj) {
+                const f32x4 qv = *reinterpret_cast<const f32x4*>(&sm.q.x[n][8 * jj + 4 * hg]);
+                const f32x4 ov = *reinterpret_cast<const f32x4*>(&sm.d_out.x[n][8 * jj + 4 * hg]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[jj][e], qv[e], s, 0, 0, 0);
+                    dp = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[jj][e], ov[e], dp, 0, 0, 0);
+                }
+            }
+        }
+        const bool in_a = t < blocks_a;
+        const int c0 = (in_a ? t : t - blocks_a) * kF32Rows;
+        const int limit = in_a ? my_row + 1 : my_vis, limit_min = in_a ? own.first + 1 : first_vis;
+        const bool partial = c0 + kF32Rows > limit_min;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            float p = expf(s[i] * scale - my_lse);
+            if (partial) p = c0 + acc_row(i, hg) < limit ? p : 0.f;
+            s[i] = p * (dp[i] - my_delta) * scale;
+        }
+        // ---- dQ^T += K^T dS^T; the next block's rows are requested beside it ----
+        tok = tok_next;
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db) acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(kt[g][db], s[g], acc[db], 0, 0, 0);
+#pragma unroll
+            for (int jj = g * JJ / 16; jj < (g + 1) * JJ / 16; ++jj) {
+                kf[jj] = *reinterpret_cast<const f32x4*>(k_rows + tok * stride + 8 * jj);
+                vf[jj] = *reinterpret_cast<const f32x4*>(v_rows + tok * stride + 8 * jj);
+            }
+        }
+    }
+    __syncthreads();
+    park<D>(sm.merge.o[wave], acc, n, hg);
+    __syncthreads();
+    if (row >= own.count) return;
+#pragma unroll
+    for (int d = 4 * part; d < D; d += 32) {
+        f32x4 a = *reinterpret_cast<const f32x4*>(&sm.merge.o[0][row][d]);
+#pragma unroll
+        for (int w = 1; w < kF32Waves; ++w) a += *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][d]);
+        *reinterpret_cast<f32x4*>(dq + rowhead * D + d) = a;
+    }
+}
+
+// --------------------------------------------------------------------------
+// Backward, key side: dV_j = sum_i P_ij dO_i, dK_j = scale sum_i dS_ij Q_i over the query rows i that see key j, summed
+// over the query heads of the KV head.  A workgroup owns 32 keys of one KV head; the (32-row query block, query head)
+// pairs are dealt out to its four waves.  Products not transposed (S = Q K^T): a lane owns a key, rows run along the
+// accumulator registers.
+// --------------------------------------------------------------------------
+template <int D>
+union DkvF32Smem {                // the rows are read in the loop, the merge comes after it
+    struct {
+        RowsLds<D> k, v;
+    };
+    MergeLds<D> merge;
+};
+
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* __restrict__ dk, float* __restrict__ dv,
+                                                                        const float* __restrict__ delta, const float* __restrict__ d_out,
+                                                                        const float* __restrict__ q, const float* __restrict__ k,
+                                                                        const float* __restrict__ v, const float* __restrict__ lse,
+                                                                        PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
+    constexpr int JJ = D / 8, DB = D / 32;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    DkvF32Smem<D>& sm = *reinterpret_cast<DkvF32Smem<D>*>(smem_raw);
+    const unsigned per_item = unsigned(n_kv_heads) * (kTileM / kF32Rows);
+    // (early keys are seen by the most rows: the table, sorted by the forward's cost, is walked backwards)
+    const int rank = pv.m_max - 1 - int(blockIdx.x / per_item);
+    const unsigned rest = blockIdx.x % per_item;
+    const int hk = int(rest % unsigned(n_kv_heads)), sub = int(rest / unsigned(n_kv_heads));
+    const int group = n_q_heads / n_kv_heads;
+    const WorkItem it = pv.sorted[rank];
+    const OwnRows own = own_rows(it, sub);
+    if (own.count <= 0) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, hg = lane >> 5;
+    const int my_key = own.first + min(n, own.count - 1), last_key = own.first + own.count - 1;
+
+    const int row = threadIdx.x >> 3, part = threadIdx.x & 7;
+    const int64_t keyhead = int64_t(pv.perm[it.a_base + own.first + min(row, own.count - 1)]) * n_kv_heads + hk;
+#pragma unroll
+    for (int d = 4 * part; d < D; d += 32) {
+        *reinterpret_cast<f32x4*>(&sm.k.x[row][d]) = *reinterpret_cast<const f32x4*>(k + keyhead * D + d);
+        *reinterpret_cast<f32x4*>(&sm.v.x[row][d]) = *reinterpret_cast<const f32x4*>(v + keyhead * D + d);
+    }
+    __syncthreads();
+
+    // the rows that see the block's first key: the own stream from it on; for source keys also the reasoning rows from the
+    // first one whose visible-source count exceeds it (counts do not decrease along the stream)
+    const int S = it.n_src;
+    const bool src = it.kind == ST_SOURCE;
+    const int rsn_base = it.b_base + S;
+    const int n_rsn = src ? pv.cu[it.seq + 1] - pv.cu[it.seq] - S : it.n_stream;
+    int rsn_first = 0;
+    if (src) {
+        int lo = 0, hi = n_rsn;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (pv.vis[rsn_base + mid] > own.first) hi = mid; else lo = mid + 1;
+        }
+        rsn_first = lo;
+    }
+    const int blocks_a = (it.n_stream - own.first + kF32Rows - 1) / kF32Rows;
+    const int blocks_b = src ? (n_rsn - rsn_first + kF32Rows - 1) / kF32Rows : 0;
+    const int n_iter = (blocks_a + blocks_b) * group;
+
+    // iteration x: query head x % group, block x / group
+    struct Iter { int base, row0, end, hq; bool rs; };
+    auto iter_at = [&](int x) {
+        x = min(x, n_iter - 1);
+        const int t = x / group;
+        Iter r;
+        r.hq = hk * group + x % group;
+        r.rs = t >= blocks_a;                                    // (rows of the other stream: visible by their source count)
+        r.base = r.rs ? rsn_base : it.a_base;
+        r.row0 = r.rs ? rsn_first + (t - blocks_a) * kF32Rows : own.first + t * kF32Rows;
+        r.end = r.rs ? n_rsn : it.n_stream;
+        return r;
+    };
+    f32x16 dk_acc[DB], dv_acc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dk_acc[db][i] = dv_acc[db][i] = 0.f;
+    f32x4 qf[JJ], of[JJ];
+    Iter cur = iter_at(wave);
+    int tok = 0, lim = 0;                                        // of this lane's row: token, keys it sees (index below lim)
+    float l_row = 0.f, d_row = 0.f;
+    auto row_info = [&](const Iter& r) {
+        const int i = min(r.row0 + n, r.end - 1);
+        tok = pv.perm[r.base + i];
+        lim = r.row0 + n < r.end ? (r.rs ? pv.vis[r.base + i] : i + 1) : 0;          // rows past the end see nothing
+        const int64_t rh = int64_t(tok) * n_q_heads + r.hq;
+        l_row = lse[rh];
+        d_row = delta[rh];
+    };
+    auto load_rows = [&](const Iter& r, int jj0, int jj1) {
+        const int64_t off = (int64_t(tok) * n_q_heads + r.hq) * D + 4 * hg;
+#pragma unroll
+        for (int jj = jj0; jj < jj1; ++jj) {
+            qf[jj] = *reinterpret_cast<const f32x4*>(q + off + 8 * jj);
+            of[jj] = *reinterpret_cast<const f32x4*>(d_out + off + 8 * jj);
+        }
+    };
+    if (wave < n_iter) {
+        row_info(cur);
+        load_rows(cur, 0, JJ);
+    }
+    for (int x = wave; x < n_iter; x += kF32Waves) {
+        // ---- S = Q K^T, dP = dO V^T; Q and dO as the second products' operands are requested beside them ----
+        f32x16 s, dp;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+        float qt[16][DB], ot[16][DB];
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+            const int64_t off = (int64_t(__shfl(tok, acc_row(g, hg))) * n_q_heads + cur.hq) * D + n;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                qt[g][db] = q[off + 32 * db];
+                ot[g][db] = d_out[off + 32 * db];
+            }
+#pragma unroll
+            for (int jj = g * JJ / 16; jj < (g + 1) * JJ / 16; ++jj) {
+                const f32x4 kv = *reinterpret_cast<const f32x4*>(&sm.k.x[n][8 * jj + 4 * hg]);
+                const f32x4 vv = *reinterpret_cast<const f32x4*>(&sm.v.x[n][8 * jj + 4 * hg]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(qf[jj][e], kv[e], s, 0, 0, 0);
+                    dp = __builtin_amdgcn_mfma_f32_32x32x2f32(of[jj][e], vv[e], dp, 0, 0, 0);
+                }
+            }
+        }
+        // register i <-> row acc_row(i, hg) of the block
+        const bool full = __builtin_amdgcn_readfirstlane(lim) > last_key && cur.row0 + kF32Rows <= cur.end;    // (limits do not decrease along the rows)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = acc_row(i, hg);
+            float p = expf(s[i] * scale - __shfl(l_row, r));
+            if (!full) p = my_key < __shfl(lim, r) ? p : 0.f;
+            s[i] = p;
+            dp[i] = p * (dp[i] - __shfl(d_row, r)) * scale;
+        }
+        // ---- dV^T += dO^T P, dK^T += Q^T dS; the next rows are requested beside them ----
+        cur = iter_at(x + kF32Waves);
+        row_info(cur);
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                dv_acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(ot[g][db], s[g], dv_acc[db], 0, 0, 0);
+                dk_acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(qt[g][db], dp[g], dk_acc[db], 0, 0, 0);
+            }
+            load_rows(cur, g * JJ / 16, (g + 1) * JJ / 16);
+        }
+    }
+    // ---- sums of the four waves, in a fixed order ----
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+        __syncthreads();
+        park<D>(sm.merge.o[wave], which == 0 ? dv_acc : dk_acc, n, hg);
+        __syncthreads();
+        if (row < own.count) {
+            float* dst = (which == 0 ? dv : dk) + keyhead * D;
+#pragma unroll
+            for (int d = 4 * part; d < D; d += 32) {
+                f32x4 a = *reinterpret_cast<const f32x4*>(&sm.merge.o[0][row][d]);
+#pragma unroll
+                for (int w = 1; w < kF32Waves; ++w) a += *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][d]);
+                *reinterpret_cast<f32x4*>(dst + d) = a;
+            }
+        }
+    }
+}
+
+// ---- launches (arguments have been checked by the callers) ----
+template <typename K>
+static st_status with_smem(K kernel, size_t bytes) {
+    ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
+    return ST_OK;
+}
+
+st_status launch_prefill_f32(float* out, float* lse, const float* q, const float* k, const float* v, const PlanView& pv, int n_q_heads,
+                             int n_kv_heads, int head_dim, float scale, hipStream_t s) {
+    const int64_t blocks = int64_t(pv.m_max) * n_q_heads * (kTileM / kF32Rows);
+    if (blocks > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_prefill: grid too large");
+    auto run = [&](auto dtag) -> st_status {
+        constexpr int D = decltype(dtag)::value;
+        const st_status r = with_smem(&prefill_f32_kernel<D>, sizeof(FwdF32Smem<D>));
+        if (r != ST_OK) return r;
+        hipLaunchKernelGGL((prefill_f32_kernel<D>), dim3((unsigned)blocks), dim3(64 * kF32Waves), sizeof(FwdF32Smem<D>), s, out, lse, q, k, v, pv,
+                           n_q_heads, n_kv_heads, scale);
+        ST_LAUNCH_CHECK("prefill_f32_kernel");
+        return ST_OK;
+    };
+    return head_dim == 64 ? run(std::integral_constant<int, 64>{}) : run(std::integral_constant<int, 128>{});
+}
+
+st_status launch_bwd_f32(float* dq, float* dk, float* dv, float* delta, const float* d_out, const float* q, const float* k, const float* v,
+                         const float* out, const float* lse, const PlanView& pv, int n_q_heads, int n_kv_heads, int head_dim, float scale,
+                         hipStream_t s) {
+    const int64_t qblocks = int64_t(pv.m_max) * n_q_heads * (kTileM / kF32Rows), kblocks = int64_t(pv.m_max) * n_kv_heads * (kTileM / kF32Rows);
+    if (qblocks > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_prefill_bwd: grid too large");
+    auto run = [&](auto dtag) -> st_status {
+        constexpr int D = decltype(dtag)::value;
+        st_status r = with_smem(&bwd_dq_f32_kernel<D>, sizeof(DqF32Smem<D>));
+        if (r != ST_OK) return r;
+        r = with_smem(&bwd_dkv_f32_kernel<D>, sizeof(DkvF32Smem<D>));
+        if (r != ST_OK) return r;
+        hipLaunchKernelGGL((bwd_dq_f32_kernel<D>), dim3((unsigned)qblocks), dim3(64 * kF32Waves), sizeof(DqF32Smem<D>), s, dq, delta, d_out, q, k, v,
+                           out, lse, pv, n_q_heads, n_kv_heads, scale);
+        hipLaunchKernelGGL((bwd_dkv_f32_kernel<D>), dim3((unsigned)kblocks), dim3(64 * kF32Waves), sizeof(DkvF32Smem<D>), s, dk, dv, delta, d_out, q,
+                           k, v, lse, pv, n_q_heads, n_kv_heads, scale);
+        ST_LAUNCH_CHECK("bwd_dq_f32_kernel / bwd_dkv_f32_kernel");
+        return ST_OK;
+    };
+    return head_dim == 64 ? run(std::integral_constant<int, 64>{}) : run(std::integral_constant<int, 128>{});
+}
+
+}  // namespace st

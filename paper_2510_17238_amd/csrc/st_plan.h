@@ -53,6 +53,13 @@ __device__ __forceinline__ int find_seq(const int32_t* table, int batch, int c) 
     return lo;
 }
 
+// fp32 attention (st_attn_f32.hip); the callers have checked the arguments and ordered `s` behind the plan
+st_status launch_prefill_f32(float* out, float* lse, const float* q, const float* k, const float* v, const PlanView& pv, int n_q_heads,
+                             int n_kv_heads, int head_dim, float scale, hipStream_t s);
+st_status launch_bwd_f32(float* dq, float* dk, float* dv, float* delta, const float* d_out, const float* q, const float* k, const float* v,
+                         const float* out, const float* lse, const PlanView& pv, int n_q_heads, int n_kv_heads, int head_dim, float scale,
+                         hipStream_t s);
+
 }  // namespace st
 
 struct st_plan {

@@ -25,120 +25,12 @@
 //   rope_table_kernel, tile_pack_rope_kernel
 //                         the fused rotation of st_attn_prefill_rope: (cos, sin) of every token once, keys rotated
 //                         on their way into the key tiles; the attention kernel's ROPE form rotates its query rows.
-//   prefill_simple_kernel any dtype, one thread per query row, plain fp32 arithmetic.  It is
-//                         the fp32 path (tolerance 1e-4) and walks the same work items.
+// (fp32 tensors take the kernel of st_attn_f32.hip, over the same work items.)
 #include <type_traits>
 
 #include "st_tiles.h"
 
 namespace st {
-
-struct ItemGeom {
-    int S;           // source tokens
-    int n_stream;    // tokens of the row's own stream
-    int a_base;      // compact row of column 0 of block A
-    int b_base;      // compact row of column 0 of block B (the source stream)
-};
-
-__device__ __forceinline__ ItemGeom item_geom(const PlanView&, const WorkItem& it) {
-    return ItemGeom{it.n_src, it.n_stream, it.a_base, it.b_base};
-}
-
-// --------------------------------------------------------------------------
-// Plain kernel: one thread per query row.
-// --------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ float load_f32(const T* p);
-template <>
-__device__ __forceinline__ float load_f32<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float load_f32<uint16_t>(const uint16_t* p) { return bf16_bits_to_f32(*p); }
-template <typename T>
-__device__ __forceinline__ void store_f32(T* p, float x);
-template <>
-__device__ __forceinline__ void store_f32<float>(float* p, float x) { *p = x; }
-template <>
-__device__ __forceinline__ void store_f32<uint16_t>(uint16_t* p, float x) { *p = f32_to_bf16_bits(x); }
-
-template <typename T, int D>
-__global__ __launch_bounds__(kTileM) void prefill_simple_kernel(T* __restrict__ out, float* __restrict__ lse,
-                                                               const T* __restrict__ q, const T* __restrict__ k,
-                                                               const T* __restrict__ v, PlanView pv, int n_q_heads,
-                                                               int n_kv_heads, float scale) {
-    constexpr int CH = 16;  // keys per softmax update
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    float (*s_q)[D + 1] = reinterpret_cast<float (*)[D + 1]>(smem_raw);
-    const int rank = blockIdx.x / n_q_heads;
-    const int hq = blockIdx.x % n_q_heads;
-    const int hk = hq / (n_q_heads / n_kv_heads);
-    const WorkItem it = pv.sorted[rank];
-    if (it.n_rows == 0) return;
-    const ItemGeom g = item_geom(pv, it);
-    const int r = threadIdx.x;
-    const bool active = r < it.n_rows;
-    const int my_row = it.row0 + min(r, it.n_rows - 1);        // relative to the row's stream
-    const int tok_q = pv.perm[g.a_base + my_row];
-    for (int d = 0; d < D; ++d) s_q[r][d] = load_f32(q + (int64_t(tok_q) * n_q_heads + hq) * D + d);
-    const int my_vis = pv.vis[g.a_base + my_row];
-
-    float o[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) o[d] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
-
-    const int n_tiles = it.a_total + it.b_total;
-    for (int ti = 0; ti < n_tiles; ++ti) {
-        const bool in_a = ti < it.a_total;
-        const int kt = in_a ? ti : ti - it.a_total;
-        const bool partial = kt >= (in_a ? it.a_full : it.b_full);
-        const int base = in_a ? g.a_base : g.b_base;
-        const int n_cols = in_a ? g.n_stream : g.S;
-        const int limit = in_a ? my_row + 1 : my_vis;          // columns < limit are visible
-        const int c_end = min((kt + 1) * kTileN, n_cols);
-        for (int c0 = kt * kTileN; c0 < c_end; c0 += CH) {
-            float s[CH];
-            float mx = -INFINITY;
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                const int col = c0 + u;
-                s[u] = -INFINITY;
-                if (col < c_end) {
-                    const int tok_k = pv.perm[base + col];
-                    const T* kp = k + (int64_t(tok_k) * n_kv_heads + hk) * D;
-                    float acc = 0.f;
-                    for (int d = 0; d < D; ++d) acc = fmaf(s_q[r][d], load_f32(kp + d), acc);
-                    if (!partial || col < limit) s[u] = acc * scale;
-                }
-                mx = fmaxf(mx, s[u]);
-            }
-            if (mx == -INFINITY) continue;
-            const float m_new = fmaxf(m_run, mx);
-            const float alpha = expf(m_run - m_new);
-            l_run *= alpha;
-#pragma unroll
-            for (int d = 0; d < D; ++d) o[d] *= alpha;
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                const int col = c0 + u;
-                if (col < c_end && s[u] != -INFINITY) {
-                    const float p = expf(s[u] - m_new);
-                    l_run += p;
-                    const int tok_k = pv.perm[base + col];
-                    const T* vp = v + (int64_t(tok_k) * n_kv_heads + hk) * D;
-#pragma unroll
-                    for (int d = 0; d < D; ++d) o[d] = fmaf(p, load_f32(vp + d), o[d]);
-                }
-            }
-            m_run = m_new;
-        }
-    }
-    if (!active) return;
-    const float inv = 1.f / l_run;
-    T* op = out + (int64_t(tok_q) * n_q_heads + hq) * D;
-#pragma unroll
-    for (int d = 0; d < D; ++d) store_f32(op + d, o[d] * inv);
-    if (lse) lse[int64_t(tok_q) * n_q_heads + hq] = m_run + logf(l_run);
-}
 
 // --------------------------------------------------------------------------
 // MFMA kernel (bf16): NH = 1 or 2 query heads of one KV head per workgroup.
@@ -815,22 +707,9 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     ST_HIP(plan->wait_built(s));
     const PlanView pv = plan->view();
-    if (dt == ST_F32) {
-        const size_t smem = sizeof(float) * kTileM * (head_dim + 1);
-        if (head_dim == 64) {
-            ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_simple_kernel<float, 64>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(smem)));
-            hipLaunchKernelGGL((prefill_simple_kernel<float, 64>), dim3((unsigned)blocks), dim3(kTileM), smem, s, (float*)out, lse,
-                               (const float*)q, (const float*)k, (const float*)v, pv, n_q_heads, n_kv_heads, scale);
-        } else {
-            ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_simple_kernel<float, 128>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(smem)));
-            hipLaunchKernelGGL((prefill_simple_kernel<float, 128>), dim3((unsigned)blocks), dim3(kTileM), smem, s, (float*)out, lse,
-                               (const float*)q, (const float*)k, (const float*)v, pv, n_q_heads, n_kv_heads, scale);
-        }
-        ST_LAUNCH_CHECK("prefill_simple_kernel");
-        return ST_OK;
-    }
+    if (dt == ST_F32)
+        return launch_prefill_f32(static_cast<float*>(out), lse, static_cast<const float*>(q), static_cast<const float*>(k),
+                                  static_cast<const float*>(v), pv, n_q_heads, n_kv_heads, head_dim, scale, s);
     const size_t tile_bytes = prefill_tile_bytes(plan, n_kv_heads, head_dim);
     uint16_t* kc = static_cast<uint16_t*>(workspace);
     uint16_t* vc = kc + tile_bytes / (2 * sizeof(uint16_t));

@@ -1,0 +1,64 @@
+"""GPU: attention and its gradients at the edges of the kernels' row blocks -- streams one token short of, exactly and one
+token past a multiple of the 32 rows a wave owns, single tokens, and rows whose visible source prefix ends inside a block --
+against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import streaming_attention as O
+
+from gpu_helpers import DEV, ids_to_dev, to_dev, to_f64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def st():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2510_17238_amd as st_
+    st_.load_library()
+    return st_
+
+
+# per sequence: (source segment lengths, reasoning segment lengths)
+EDGES = [(np.array([1]), np.array([1])), (np.array([31, 1]), np.array([32, 1])), (np.array([33]), np.array([63])),
+         (np.array([30, 35]), np.array([1, 96])), (np.array([127, 1, 1]), np.array([31, 97, 1])), (np.array([0]), np.array([161]))]
+
+
+def _case(dtype, hq, hkv, d, layout):
+    return W._assemble("edges", dtype, hq, hkv, d, EDGES, layout, 21)
+
+
+def _forward_and_backward(st, cfg, heads=0):
+    q, k, v = cfg.tensors()
+    g = W.normal(np.random.Generator(np.random.PCG64(22)), q.shape, cfg.dtype)
+    tq, tk, tv, tg = (to_dev(x, cfg.dtype) for x in (q, k, v, g))
+    plan = st.st_plan_create(*ids_to_dev(cfg), cfg.cu_seqlens).heads_per_workgroup(heads)
+    lse = torch.empty((cfg.n_tokens, cfg.n_q_heads), dtype=torch.float32, device=DEV)
+    out = st.st_attn_prefill(tq, tk, tv, plan, lse=lse)
+    grads = st.st_attn_prefill_bwd(tg, tq, tk, tv, out, lse, plan)
+    torch.cuda.synchronize()
+    refs = O.attention_varlen_backward(q, k, v, g, cfg.stream_ids, cfg.segment_ids, cfg.positions, cfg.cu_seqlens)
+    return (q, k, v), out, lse, grads, refs
+
+
+def _check(cfg, inputs, out, lse, grads, refs):
+    # forward: the bounds of the parity suite (1e-4 for fp32 inputs, 2e-2 for bf16).  Gradients: an entry sums at most
+    # 161 x 8 terms; fp32 rounds each to 6e-8 of its size (2e-4 is far above), bf16 rounds P, dS and the result to 4e-3.
+    q, k, v = inputs
+    tol, tol_g = (1e-4, 2e-4) if cfg.dtype == "f32" else (2e-2, 6e-2)
+    for b in range(cfg.batch):
+        sl = slice(int(cfg.cu_seqlens[b]), int(cfg.cu_seqlens[b + 1]))
+        ref, ref_lse = O.attention_dense(q[sl], k[sl], v[sl], cfg.stream_ids[sl], cfg.segment_ids[sl], cfg.positions[sl])
+        assert np.abs(to_f64(out[sl]) - ref).max() <= tol, b
+        assert np.abs(to_f64(lse[sl]) - ref_lse).max() <= tol, b
+    for name, got, ref in zip(("dq", "dk", "dv"), grads, refs):
+        assert np.abs(to_f64(got) - ref).max() <= tol_g * max(1.0, np.abs(ref).max()), name
+
+
+@pytest.mark.parametrize("hq,hkv,d,layout", [(2, 1, 64, "interleaved"), (4, 4, 128, "grouped"), (8, 2, 128, "interleaved"), (8, 1, 64, "grouped")])
+def test_fp32_row_blocks(st, hq, hkv, d, layout):
+    cfg = _case("f32", hq, hkv, d, layout)
+    _check(cfg, *_forward_and_backward(st, cfg))
