@@ -11,6 +11,7 @@
 // bf16 here; fp32 tensors take the kernels of st_attn_f32.hip.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "st_tiles.h"
@@ -295,12 +296,15 @@ struct BwdDkvSmem {
     float stats[2][256];
 };
 
+// parts > 1: the query heads of a KV head are dealt out to `parts` workgroups (a divisor of the group), which leave fp32
+// sums in `partial` ([2: dK, dV][parts][N][n_kv_heads][D]) for bwd_dkv_sum_kernel instead of writing dk / dv -- see dkv_parts.
 template <int D>
 __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                                                               const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                               const uint16_t* __restrict__ qrows, const uint16_t* __restrict__ dorows,
                                                               const float* __restrict__ stats, PlanView pv, int n_q_heads,
-                                                              int n_kv_heads, float scale) {
+                                                              int n_kv_heads, float scale, int parts, float* __restrict__ partial,
+                                                              int64_t partial_stride) {
     constexpr int KS = D / 16, DB = D / 32, SB = kTileN / 32;
     constexpr int TILE = kTileN * D;
     constexpr int NL = TILE * 2 / 1024 / 4;
@@ -309,9 +313,12 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
 
     // The table is sorted by the FORWARD's cost (late rows first); a key's cost runs the other way (early keys
     // are seen by the most rows), so walk the table backwards: longest first again, unused slots at once.
-    const int rank = pv.m_max - 1 - int(blockIdx.x / n_kv_heads);
+    const int per_item = n_kv_heads * parts;
+    const int rank = pv.m_max - 1 - int(blockIdx.x / per_item);
     const int hk = blockIdx.x % n_kv_heads;
-    const int group = n_q_heads / n_kv_heads;
+    const int part = int(blockIdx.x % per_item) / n_kv_heads;
+    const int group = n_q_heads / n_kv_heads / parts;           // query heads of this workgroup: hq0 .. hq0 + group - 1
+    const int hq0 = (hk * parts + part) * group;
     const WorkItem it = pv.sorted[rank];
     if (it.n_rows == 0) return;
     const int tid = threadIdx.x;
@@ -384,7 +391,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
     struct Iter { int tile; int hq; int row0; bool rs; };
     auto iter_at = [&](int t, int g) {                          // (tile count t of the walk, head g of the group)
         Iter r;
-        r.hq = hk * group + g;
+        r.hq = hq0 + g;
         if (t < n_a) {
             r.tile = tile_own0 + a_first + t;
             r.row0 = (a_first + t) * kTileN;
@@ -609,6 +616,18 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
     // cycles before an ordinary instruction may read them)
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     if (!active) return;
+    if (parts > 1) {
+        float* pk = partial + part * partial_stride + keyhead * D + 4 * hg;
+        float* pvv = pk + parts * partial_stride;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                *reinterpret_cast<f32x4*>(pk + 32 * db + 8 * q4) = f32x4{dk_acc[db][4 * q4], dk_acc[db][4 * q4 + 1], dk_acc[db][4 * q4 + 2], dk_acc[db][4 * q4 + 3]};
+                *reinterpret_cast<f32x4*>(pvv + 32 * db + 8 * q4) = f32x4{dv_acc[db][4 * q4], dv_acc[db][4 * q4 + 1], dv_acc[db][4 * q4 + 2], dv_acc[db][4 * q4 + 3]};
+            }
+        return;
+    }
     uint16_t* pk = dk + keyhead * D;
     uint16_t* pvv = dv + keyhead * D;
     // lane (n, hg), block db, register i  <->  d = 32 db + 8 (i/4) + 4 hg + i%4
@@ -627,15 +646,56 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
         }
 }
 
+// dK (blockIdx.y = 0) or dV (1) from the partial sums of the key-side kernel, in a fixed order; n8 groups of eight elements
+__global__ __launch_bounds__(256) void bwd_dkv_sum_kernel(uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, const float* __restrict__ partial,
+                                                          int64_t partial_stride, int parts, int n8, float scale) {
+    const int i = int(blockIdx.x) * 256 + int(threadIdx.x);
+    if (i >= n8) return;
+    const float* p = partial + blockIdx.y * parts * partial_stride + int64_t(i) * 8;
+    f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
+    for (int x = 1; x < parts; ++x) {
+        a += *reinterpret_cast<const f32x4*>(p + x * partial_stride);
+        b += *reinterpret_cast<const f32x4*>(p + x * partial_stride + 4);
+    }
+    const float f = blockIdx.y == 0 ? scale : 1.f;
+    bf16x8 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        r[e] = (__bf16)(a[e] * f);
+        r[4 + e] = (__bf16)(b[e] * f);
+    }
+    *reinterpret_cast<bf16x8*>((blockIdx.y == 0 ? dk : dv) + int64_t(i) * 8) = r;
+}
+
 }  // namespace st
 
 using namespace st;
 
 namespace {
 inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
-// workspace of the bf16 path: delta (token order) | row statistics | K rows | V rows | Q rows | dO rows
+// Workgroups per (128 keys, KV head) of the key-side kernel.  Its work items are KEYS: with few KV heads and many query heads
+// over each, a small batch leaves compute units idle and its few long workgroups end far apart.  The query heads of a group
+// are then split into parts, each with a fp32 partial dK / dV of its own, as few as give two workgroups per slot of the chip
+// (one per compute unit at 128 dims, two at 64): measured for the whole training step, 10 x 1.7K tokens, 16 / 2 heads of 64
+// dims (288 workgroups) 693 us -> 406 us with four parts; 1 x 6.1K, 16 / 2 of 128 (98) 1661 -> 674 with eight; 2 x 2.5K,
+// 32 / 8 of 128 (330) 593 -> 520 with two.  From there on the partial sums cost more than the balance gives (4 x 4K, 16 / 8
+// of 128, 1036 workgroups: 1244 -> 1318 us), and on sequences of a few tiles the second launch does (17 x 150 tokens: 129 ->
+// 143 us; 1 x 650: 141 -> 126).
+int dkv_parts(const st_plan* plan, int n_q_heads, int n_kv_heads, int head_dim) {
+    const int group = n_q_heads / n_kv_heads;
+    if (plan->n_tokens < int64_t(512) * plan->batch) return 1;
+    const int64_t workgroups = (plan->n_tokens / kTileM + plan->batch) * n_kv_heads;
+    const int64_t wanted = 2 * 256 * (head_dim == 64 ? 2 : 1);
+    int parts = 1;
+    for (int p = 2; p <= std::min(group, 8) && workgroups * parts < wanted; ++p)
+        if (group % p == 0) parts = p;
+    return parts;
+}
+// workspace of the bf16 path: delta (token order) | row statistics | K rows | V rows | Q rows | dO rows | partial dK, dV
 struct BwdLayout {
-    size_t delta, stats, krows, vrows, qrows, dorows, total;
+    size_t delta, stats, krows, vrows, qrows, dorows, partial, total;
+    int parts;
+    int64_t partial_stride;       // elements of one part
 };
 BwdLayout bwd_layout(const st_plan* plan, int n_q_heads, int n_kv_heads, int head_dim, st_dtype dt) {
     BwdLayout L{};
@@ -650,6 +710,9 @@ BwdLayout bwd_layout(const st_plan* plan, int n_q_heads, int n_kv_heads, int hea
         L.vrows = take(kvt);
         L.qrows = take(qt);
         L.dorows = take(qt);
+        L.parts = dkv_parts(plan, n_q_heads, n_kv_heads, head_dim);
+        L.partial_stride = plan->n_tokens * n_kv_heads * head_dim;
+        if (L.parts > 1) L.partial = take(2 * size_t(L.parts) * size_t(L.partial_stride) * sizeof(float));
     }
     L.total = off + 256;
     return L;
@@ -682,7 +745,7 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
     if (workspace_bytes < need) return fail(ST_ERR_CAPACITY, "st_attn_prefill_bwd: workspace has %zu bytes, needs %zu", workspace_bytes, need);
     if (scale <= 0.f) scale = 1.f / sqrtf(float(head_dim));
     const int64_t qblocks = int64_t(plan->m_max) * n_q_heads, kblocks = int64_t(plan->m_max) * n_kv_heads;
-    if (qblocks > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_prefill_bwd: grid too large");
+    if (qblocks > 0x7fffffff || kblocks * 8 > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_prefill_bwd: grid too large");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     ST_HIP(plan->wait_built(s));
     const PlanView pv = plan->view();
@@ -693,6 +756,7 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
         unsigned char* w = static_cast<unsigned char*>(workspace);
         auto at = [&](size_t o) { return reinterpret_cast<uint16_t*>(w + o); };
         float* stats = reinterpret_cast<float*>(w + L.stats);
+        float* partial = reinterpret_cast<float*>(w + L.partial);
         const unsigned kv_tiles = unsigned(plan->pack_tiles) * n_kv_heads, q_tiles = unsigned(plan->pack_tiles) * n_q_heads;
         hipLaunchKernelGGL((tile_pack_kernel<HD>), dim3(kv_tiles), dim3(256), 0, s, at(L.krows), (uint16_t*)nullptr, (const uint16_t*)k,
                            (const uint16_t*)k, pv, n_kv_heads);
@@ -714,10 +778,15 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
         prof_end(kProfBwdDq, s);
         prof_begin(kProfBwdDkv, s);
         for (int rep = 0; rep < prof_repeat(); ++rep)
-        hipLaunchKernelGGL((bwd_dkv_mfma_kernel<HD>), dim3((unsigned)kblocks), dim3(256), smem_k, s, (uint16_t*)dk, (uint16_t*)dv,
+        hipLaunchKernelGGL((bwd_dkv_mfma_kernel<HD>), dim3((unsigned)(kblocks * L.parts)), dim3(256), smem_k, s, (uint16_t*)dk, (uint16_t*)dv,
                            (const uint16_t*)k, (const uint16_t*)v, at(L.qrows), at(L.dorows), stats, pv,
-                           n_q_heads, n_kv_heads, scale);
+                           n_q_heads, n_kv_heads, scale, L.parts, partial, L.partial_stride);
         prof_end(kProfBwdDkv, s);
+        if (L.parts > 1) {
+            const int n8 = int(L.partial_stride / 8);
+            hipLaunchKernelGGL(bwd_dkv_sum_kernel, dim3((unsigned)((n8 + 255) / 256), 2), dim3(256), 0, s, (uint16_t*)dk, (uint16_t*)dv, partial,
+                               L.partial_stride, L.parts, n8, scale);
+        }
         return ST_OK;
     };
     st_status r;

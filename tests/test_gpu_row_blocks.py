@@ -62,3 +62,12 @@ def _check(cfg, inputs, out, lse, grads, refs):
 def test_fp32_row_blocks(st, hq, hkv, d, layout):
     cfg = _case("f32", hq, hkv, d, layout)
     _check(cfg, *_forward_and_backward(st, cfg))
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(16, 2, 64), (4, 2, 128), (6, 1, 128), (3, 3, 64)])
+def test_key_side_split_over_query_heads(st, hq, hkv, d):
+    """Few KV heads under sequences of 512 tokens and more: the key side of the backward splits the query heads of a group
+    over several workgroups (8, 2 and 6 ways here, and not at all with one head per group) and adds their sums."""
+    lists = [(np.array([127, 130]), np.array([129, 200])), (np.array([300]), np.array([260]))]
+    cfg = W._assemble("split", "bf16", hq, hkv, d, lists, "interleaved", 23)
+    _check(cfg, *_forward_and_backward(st, cfg))
