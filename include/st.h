@@ -382,8 +382,7 @@ typedef struct st_dual_lens {
     int32_t unit_tokens;            /* tokens per work unit of the step, see below; 0 = chosen by launch size */
 } st_dual_lens;
 
-/* Work units.  A step with q_len * (n_q_heads / n_kv_heads) <= 16 cuts each cache into units of
- * lens->unit_tokens tokens, one wave each: 0 chooses by launch size -- 1024 for large batches down
+/* Work units.  A step cuts each cache into units of lens->unit_tokens tokens, one wave each: 0 chooses by launch size -- 1024 for large batches down
  * to 128 for a few sequences, whose step is bound by a wave's serial walk over its unit --, 128,
  * 256, 512 or 1024 pins it (tests, tuning); other values give ST_ERR_INVALID_ARG.  Results agree
  * within rounding.  st_decode_workspace_bytes takes the same value and answers for it (and always

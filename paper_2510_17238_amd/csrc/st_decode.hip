@@ -2,7 +2,7 @@
 // slice with the reasoning cache, then decode).
 //
 // Nothing is merged in memory.  The two caches are cut into work units of 128 to 1,024 tokens
-// (decode_unit_tokens; 512 for the 32-row kernel); one WAVE takes one (sequence, KV head, unit),
+// (decode_unit_tokens); one WAVE takes one (sequence, KV head, unit),
 // streams that unit's K and V pages from HBM exactly once for all query heads of the group, and
 // emits an un-normalised partial (o, m, l).  A second kernel merges all partials of BOTH caches per (sequence, query
 // row, head) by log-sum-exp -- identical to a softmax over the concatenated cache.
@@ -104,139 +104,153 @@ __device__ __forceinline__ void rotate_query(bf16x8 (&qf)[KS], int off, int pos,
         }
 }
 
-// The decode step with 17 .. 32 query rows q_len * G per sequence and KV head, both caches: four waves per
-// workgroup, each with a unit of its own.
-template <int D>
-__global__ __launch_bounds__(256) void decode_split_kernel(DecodeArgs a) {
+// The decode step with 17 .. 32 query rows q_len * G per sequence and KV head (several tokens in one call, or wide groups):
+// ONE WAVE per workgroup and work unit on v_mfma_f32_32x32x16_bf16, whose 32 columns are the query rows.  As in the 16-row
+// kernel below the bytes in flight are what counts -- 4 D bytes per token against 128 flop per byte: the page ids of the unit
+// are fetched once, the 16 KB of the next 32 tokens are requested before the present ones are multiplied (two register
+// sets), whole 128-byte lines per instruction, value loads with the non-temporal hint.  That only fits two waves per SIMD
+// with the queries in LDS, in fragment order (each fragment is read back right before its matrix instruction).  A lane owns
+// a query row: no running maximum, the row's reference exponent moves out of line when a step exceeds it by 2^kLazyRise.
+// 64 sequences of up to 8K + 16K tokens, 8 tokens x 4 heads, 8 KV heads of 128 dims (3.78 GB of cache): 1.44 ms with loads
+// requested when they were needed and 512-token units (and 57 us for the merge of their partial results) -> 0.84 ms (37 us).
+template <int D, bool STREAM_KEYS>
+__global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
     constexpr int KS = D / 16, DB = D / 32, KCH = D / 8;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr float kLazyRise = 8.f;
+    __shared__ bf16x8 s_q[KS][64];
+    const int lane = threadIdx.x;
     const int nc = a.ncs + a.ncr;
-    int64_t unit = int64_t(blockIdx.x) * 4 + wave;
-    const int c = int(unit % nc);
-    unit /= nc;
-    const int h = int(unit % a.n_kv_heads);
-    const int b = int(unit / a.n_kv_heads);
-    if (b >= a.batch) return;
+    const int c = int(blockIdx.x % unsigned(nc));
+    const unsigned bh = blockIdx.x / unsigned(nc);
+    const int h = int(bh % unsigned(a.n_kv_heads));
+    const int b = int(bh / unsigned(a.n_kv_heads));
     const bool is_src = c < a.ncs;
     const CacheView& cv = is_src ? a.src : a.rsn;
-    const int cc = is_src ? c : c - a.ncs;
     const int len = min(max(is_src ? a.src_len[b] : a.rsn_len[b], 0), cv.max_pages * kPage);
-    const int tok0 = cc * kChunk;
+    const int tok0 = (is_src ? c : c - a.ncs) * a.chunk;
     if (tok0 >= len) return;
+    const int tok_end = min(len, tok0 + a.chunk);
+    const int n_steps = (tok_end - tok0 + 31) / 32;
 
     const int n = lane & 31, hg = lane >> 5;
-    const int q_len = a.q_len;
-    const int r = n;                                // query row of this (sequence, KV head): token r / G, head r % G
-    const int t_row = r / a.group;
-    const bool valid_row = r < q_len * a.group;
-    const int hq = h * a.group + r % a.group;
-    const int tok_end = min(len, tok0 + kChunk);
+    const bool valid_row = n < a.rows;                  // row of this (sequence, KV head): token n / G, head n % G
+    const int nr = min(n, a.rows - 1);                  // rows past the end repeat the last one (never stored)
+    const int t_row = nr / a.group;
+    const int hq = h * a.group + nr % a.group;
     // visible reasoning tokens of query row t: [0, len - q_len + t]; the source slice is seen whole
-    const int limit = !valid_row ? 0 : (is_src ? len : max(len - q_len + t_row + 1, 0));
+    const int limit = is_src ? len : min(max(len - a.q_len + t_row + 1, 0), len);
+    const int limit_min = is_src ? len : min(max(len - a.q_len + 1, 0), len);
 
-    bf16x8 qf[KS];
+    // the page ids of the unit, one per lane (units hold 64 pages at most)
+    const int last_page = (tok_end - 1) / kPage - tok0 / kPage;
+    int my_page = cv.page_table[int64_t(b) * cv.max_pages + tok0 / kPage + min(lane, last_page)];
+    my_page = min(max(my_page, 0), cv.n_pages - 1);
+    const int64_t page_k = int64_t(cv.n_kv_heads) * KCH * (kPage * 8);
+    const int64_t page_v = int64_t(cv.n_kv_heads) * D * kPage;
+    // K: lane (m = n, hg) reads slot swap23(m % 16) of page m / 16, d-chunk 2 j + hg; V: lane (m = n, hg) reads slots
+    // 8 hg .. + 7 of row d = 32 db + m
+    const uint16_t* k_lane = cv.k_pool + int64_t(h) * KCH * (kPage * 8) + hg * (kPage * 8) + swap23(n & 15) * 8;
+    const uint16_t* v_lane = cv.v_pool + int64_t(h) * D * kPage + n * kPage + 8 * hg;
+    auto load = [&](int s, u32x4 (&kk)[KS], u32x4 (&vv)[2][DB]) {
+        const int id0 = __builtin_amdgcn_readlane(my_page, min(2 * s, last_page));        // (past the visible length: the last visible page)
+        const int id1 = __builtin_amdgcn_readlane(my_page, min(2 * s + 1, last_page));
+        const uint16_t* kp = k_lane + int64_t(n >> 4 ? id1 : id0) * page_k;
 #pragma unroll
-    for (int j = 0; j < KS; ++j) {
-        u32x4 z = {0u, 0u, 0u, 0u};
-        if (valid_row)
-            z = *reinterpret_cast<const u32x4*>(a.q + ((int64_t(b) * a.q_len + t_row) * a.n_q_heads + hq) * D + 16 * j + 8 * hg);
-        qf[j] = __builtin_bit_cast(bf16x8, z);
-    }
-    if (a.rope) {
-        // the row's position id: its index in the reasoning stream
-        const int len_own = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
-        rotate_query<KS, 16>(qf, 8 * hg, max(len_own - q_len + t_row, 0), a.freq);
+        for (int j = 0; j < KS; ++j) kk[j] = key_load<STREAM_KEYS>(kp + 2 * j * (kPage * 8));
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) vv[t][db] = stream_load(v_lane + int64_t(t ? id1 : id0) * page_v + db * 32 * kPage);
+    };
+    u32x4 ka[KS], va[2][DB], kb[KS], vb[2][DB];
+    load(0, ka, va);
+    {
+        bf16x8 qf[KS];
+        const uint16_t* qp = a.q + ((int64_t(b) * a.q_len + t_row) * a.n_q_heads + hq) * D + 8 * hg;
+#pragma unroll
+        for (int j = 0; j < KS; ++j) qf[j] = *reinterpret_cast<const bf16x8*>(qp + 16 * j);
+        if (a.rope) {
+            // the row's position id: its index in the reasoning stream
+            const int len_own = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
+            rotate_query<KS, 16>(qf, 8 * hg, max(len_own - a.q_len + t_row, 0), a.freq);
+        }
+#pragma unroll
+        for (int j = 0; j < KS; ++j) s_q[j][lane] = qf[j];                 // (read back by the same lane only)
     }
     f32x16 o_acc[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o_acc[db][i] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_ref = 0.f, l_run = 0.f;
+    bool has_ref = false;
 
-    const int32_t* table = cv.page_table + int64_t(b) * cv.max_pages;
-    const int64_t head_k = int64_t(h) * KCH * (kPage * 8);
-    const int64_t page_k = int64_t(cv.n_kv_heads) * KCH * (kPage * 8);
-    const int64_t head_v = int64_t(h) * D * kPage;
-    const int64_t page_v = int64_t(cv.n_kv_heads) * D * kPage;
-    const int k_slot = swap23(n & 15);
-
-    for (int tok = tok0; tok < tok_end; tok += 32) {
-        // ---- K operand: lane (m = n, hg) -> page tok/16 + m/16, slot swap23(m % 16) ----
-        const int pg_k = tok / kPage + (n >> 4);
-        int id_k = -1;
-        if (pg_k * kPage < tok_end) id_k = table[pg_k];
-        const bool ok_k = id_k >= 0 && id_k < cv.n_pages;
-        f32x16 s_acc;
+    auto compute = [&](int s, const u32x4 (&kk)[KS], u32x4 (&vv)[2][DB]) {
+        const int tok = tok0 + 32 * s;
+        f32x16 t;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s_acc[i] = 0.f;
-        {
-            const uint16_t* kp = cv.k_pool + int64_t(ok_k ? id_k : 0) * page_k + head_k + k_slot * 8;
-            bf16x8 ak[KS];
+        for (int i = 0; i < 16; ++i) t[i] = 0.f;
 #pragma unroll
-            for (int j = 0; j < KS; ++j) {
-                u32x4 z = {0u, 0u, 0u, 0u};
-                if (ok_k) z = *reinterpret_cast<const u32x4*>(kp + (2 * j + hg) * (kPage * 8));
-                ak[j] = __builtin_bit_cast(bf16x8, z);
-            }
+        for (int j = 0; j < KS; ++j) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kk[j]), s_q[j][lane], t, 0, 0, 0);
+        // register i <-> token tok + 16 (i/8) + 8 hg + i%8
 #pragma unroll
-            for (int j = 0; j < KS; ++j) s_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[j], qf[j], s_acc, 0, 0, 0);
+        for (int i = 0; i < 16; ++i) t[i] = fmaf(t[i], a.scale_log2, -m_ref);
+        if (tok + 32 > limit_min) {                     // uniform: a step that reaches some row's limit
+#pragma unroll
+            for (int i = 0; i < 16; ++i) t[i] = tok + 16 * (i >> 3) + 8 * hg + (i & 7) < limit ? t[i] : -INFINITY;
         }
-        // ---- V operand: page t, lane (d = 32 db + n, hg) -> slots 8 hg .. 8 hg + 7 ----
-        bf16x8 av[2][DB];
+        float mx = t[0];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int pg_v = tok / kPage + t;
-            int id_v = -1;
-            if (pg_v * kPage < tok_end) id_v = table[pg_v];
-            const bool ok_v = id_v >= 0 && id_v < cv.n_pages;
-            const uint16_t* vp = cv.v_pool + int64_t(ok_v ? id_v : 0) * page_v + head_v + n * kPage + 8 * hg;
-            const int first = tok + 16 * t + 8 * hg;     // token held in element 0
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, t[i]);
+        if (__any(mx > kLazyRise || (!has_ref && mx > -INFINITY))) {
+            // out of line: move the reference of the rows that need it (a row lives in lanes n and n + 32)
+            const float rise = fmaxf(mx, __shfl_xor(mx, 32));
+            const bool move = has_ref ? rise > 0.f : rise > -INFINITY;
+            const float shift = move ? rise : 0.f;
+            const float alpha = has_ref ? __builtin_amdgcn_exp2f(-shift) : 1.f;
 #pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                u32x4 z = {0u, 0u, 0u, 0u};
-                if (ok_v) z = *reinterpret_cast<const u32x4*>(vp + db * 32 * kPage);
-                if (first + 8 > len) {
-                    // slots past the visible length may hold anything: select them away
+            for (int i = 0; i < 16; ++i) t[i] -= shift;
+            l_run *= alpha;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t keep_lo = first + 2 * e < len ? 0x0000ffffu : 0u;
-                        const uint32_t keep_hi = first + 2 * e + 1 < len ? 0xffff0000u : 0u;
-                        z[e] &= keep_lo | keep_hi;
-                    }
-                }
-                av[t][db] = __builtin_bit_cast(bf16x8, z);
-            }
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o_acc[db][i] *= alpha;
+            m_ref += shift;
+            has_ref = has_ref || move;
         }
-        // ---- mask + online softmax; register i <-> token tok + 16 (i/8) + 8 hg + i%8 ----
-        float mx = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int kv = tok + 16 * (i >> 3) + 8 * hg + (i & 7);
-            s_acc[i] = kv < limit ? s_acc[i] : -INFINITY;
-            mx = fmaxf(mx, s_acc[i]);
-        }
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m_run, mx * a.scale_log2);
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
-        m_run = m_new;
-        float psum = 0.f;
         bf16x8 pb[2];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const float p = __builtin_amdgcn_exp2f(fmaf(s_acc[i], a.scale_log2, -m_use));
-            psum += p;
+            const float p = __builtin_amdgcn_exp2f(t[i]);
+            l_run += p;
             pb[i >> 3][i & 7] = (__bf16)p;
         }
-        l_run = l_run * alpha + psum;
+        if (tok + 32 > len) {                           // uniform: slots past the visible length may hold anything
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
+            for (int u = 0; u < 2; ++u) {
+                const int first = tok + 16 * u + 8 * hg;
+                u32x4 keep;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) o_acc[db][i] *= alpha;
+                for (int e = 0; e < 4; ++e)
+                    keep[e] = (first + 2 * e < len ? 0x0000ffffu : 0u) | (first + 2 * e + 1 < len ? 0xffff0000u : 0u);
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
-                o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[t][db], pb[t], o_acc[db], 0, 0, 0);
+                for (int db = 0; db < DB; ++db) vv[u][db] &= keep;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+                o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv[u][db]), pb[u], o_acc[db], 0, 0, 0);
+    };
+    for (int s = 0; s < n_steps; s += 2) {
+        if (s + 1 < n_steps) load(s + 1, kb, vb);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(s, ka, va);
+        if (s + 1 < n_steps) {
+            if (s + 2 < n_steps) load(s + 2, ka, va);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(s + 1, kb, vb);
         }
     }
 
@@ -254,7 +268,7 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeArgs a) {
             *reinterpret_cast<f32x4*>(po + 32 * db + 8 * q4 + 4 * hg) = o4;
         }
     if (hg == 0) {
-        a.part_ml[slot * 2] = m_run;
+        a.part_ml[slot * 2] = has_ref ? m_ref : -INFINITY;
         a.part_ml[slot * 2 + 1] = l_tot;
     }
 }
@@ -1362,13 +1376,12 @@ static inline size_t decode_partial_bytes(int unit, int64_t batch, int hkv, int 
     const size_t slots = size_t(batch) * hkv * nc * rows;
     return align256(slots * d * sizeof(float)) + align256(slots * 2 * sizeof(float)) + 256;
 }
-// Tokens per work unit of the one-wave decode kernels (<= 16 query rows): a wave walks its unit serially, one
+// Tokens per work unit of the one-wave decode kernels: a wave walks its unit serially, one
 // memory round trip per 32 tokens, so the unit is as long as still leaves enough units -- 1024 tokens when that
 // gives four thousand (fewest partial results; measured best on 64 streams of 36 layers), else 512 if that gives a
 // thousand (measured best on configs[2]: 32 streams), down to 128 for a few sequences, where the step is bound by
 // that serial walk and not by bandwidth.
 static inline int decode_unit_tokens(int64_t batch, int hkv, int rows, int max_src, int max_rsn, int pinned, bool fp8 = false) {
-    if (rows > 16) return kChunk;
     if (pinned) return pinned;               // the caller's choice (st_dual_lens::unit_tokens)
     auto units = [&](int unit) { return batch * hkv * ((max_src + unit - 1) / unit + (max_rsn + unit - 1) / unit); };
     // (counted with the length BOUNDS: about half are real; the 8-bit kernel, which walks 64 tokens per step and
@@ -1533,20 +1546,18 @@ static st_status decode_dual_impl(void* out, float* lse, const void* q, const st
     }
     const int64_t units = int64_t(batch) * hkv * (a.ncs + a.ncr + a.append);
     const int64_t out_units = int64_t(batch) * a.q_len * n_q_heads;
-    if (units / 4 + 1 > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_decode_dual: grid too large");
+    if (units > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_decode_dual: grid too large");
     if (units > 0) {
-        const dim3 grid((unsigned)((units + 3) / 4)), block(256);
+        // (bytes of the launch from the length bounds: about half are real)
+        const double bound_bytes = double(batch) * hkv * (double(lens->max_src_len) + lens->max_rsn_len) * 4.0 * d;
+        const bool stream_keys = bound_bytes <= 4.0e9;
         if (a.rows <= 16) {
-            if (units > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_decode_dual: grid too large");
             if (!no_alloc) prof_begin(kProfDecodeSplit, s);      // (the timing hooks create events)
             for (int rep = 0, n_rep = no_alloc ? 1 : prof_repeat(); rep < n_rep; ++rep)
             if (fp8) {
                 if (d == 64) hipLaunchKernelGGL((decode_split16_fp8_kernel<64>), dim3((unsigned)units), dim3(64), 0, s, a);
                 else hipLaunchKernelGGL((decode_split16_fp8_kernel<128>), dim3((unsigned)units), dim3(64), 0, s, a);
             } else {
-                // (bytes of the launch from the length bounds: about half are real)
-                const double bound_bytes = double(batch) * hkv * (double(lens->max_src_len) + lens->max_rsn_len) * 4.0 * d;
-                const bool stream_keys = bound_bytes <= 4.0e9;
                 if (d == 64) {
                     if (stream_keys) hipLaunchKernelGGL((decode_split16_kernel<64, true>), dim3((unsigned)units), dim3(64), 0, s, a);
                     else hipLaunchKernelGGL((decode_split16_kernel<64, false>), dim3((unsigned)units), dim3(64), 0, s, a);
@@ -1557,8 +1568,13 @@ static st_status decode_dual_impl(void* out, float* lse, const void* q, const st
             }
             if (!no_alloc) prof_end(kProfDecodeSplit, s);
         } else {
-            if (d == 64) hipLaunchKernelGGL((decode_split_kernel<64>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((decode_split_kernel<128>), grid, block, 0, s, a);
+            if (d == 64) {
+                if (stream_keys) hipLaunchKernelGGL((decode_split32_kernel<64, true>), dim3((unsigned)units), dim3(64), 0, s, a);
+                else hipLaunchKernelGGL((decode_split32_kernel<64, false>), dim3((unsigned)units), dim3(64), 0, s, a);
+            } else {
+                if (stream_keys) hipLaunchKernelGGL((decode_split32_kernel<128, true>), dim3((unsigned)units), dim3(64), 0, s, a);
+                else hipLaunchKernelGGL((decode_split32_kernel<128, false>), dim3((unsigned)units), dim3(64), 0, s, a);
+            }
         }
         ST_LAUNCH_CHECK("decode_split_kernel");
     }
