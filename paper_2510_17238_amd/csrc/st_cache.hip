@@ -32,6 +32,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(CacheView cache, const u
                                                         int pages_per_seq_touched, RopeFreq freq) {
     constexpr int KCH = D / 8;
     __shared__ uint16_t s_v[kPage][D + 2];
+    __shared__ float2 s_rot[ROPE ? kPage * (D / 2) : 1];
     const int pi = blockIdx.x % pages_per_seq_touched;
     const int h = (blockIdx.x / pages_per_seq_touched) % cache.n_kv_heads;
     const int b = blockIdx.x / (pages_per_seq_touched * cache.n_kv_heads);
@@ -50,6 +51,8 @@ __global__ __launch_bounds__(256) void kv_append_kernel(CacheView cache, const u
     const int tid = threadIdx.x;
 
     if (ROPE) {
+        rope_table_to_lds<D>(s_rot, lo, cnt, freq, 256);         // index in this cache == position id
+        __syncthreads();
         // K: a thread takes the two 16-byte pieces d = 8 c .. + 7 and D/2 + 8 c .. + 7 of one token --
         // the two halves of eight rotation pairs
         for (int w = tid; w < (KCH / 2) * kPage; w += 256) {
@@ -58,14 +61,12 @@ __global__ __launch_bounds__(256) void kv_append_kernel(CacheView cache, const u
             const uint16_t* src = k_new + (row0 + s) * row_stride + h * D + c8 * 8;
             const Piece lo_in = *reinterpret_cast<const Piece*>(src), hi_in = *reinterpret_cast<const Piece*>(src + D / 2);
             Piece lo_out, hi_out;
-            const int pos = lo + s;                              // index in this cache == position id
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float cs, sn;
-                rope_cos_sin(pos, freq.f[c8 * 8 + e], &cs, &sn);
+                const float2 r = s_rot[s * (D / 2) + c8 * 8 + e];
                 const float a = bf16_bits_to_f32(lo_in.v[e]), b2 = bf16_bits_to_f32(hi_in.v[e]);
-                lo_out.v[e] = f32_to_bf16_bits(a * cs - b2 * sn);
-                hi_out.v[e] = f32_to_bf16_bits(b2 * cs + a * sn);
+                lo_out.v[e] = f32_to_bf16_bits(a * r.x - b2 * r.y);
+                hi_out.v[e] = f32_to_bf16_bits(b2 * r.x + a * r.y);
             }
             uint16_t* dst = cache.k_pool + ((int64_t(id) * cache.n_kv_heads + h) * KCH + c8) * (kPage * 8) + (slot_lo + s) * 8;
             *reinterpret_cast<Piece*>(dst) = lo_out;
@@ -115,6 +116,7 @@ __global__ __launch_bounds__(256) void kv_append_token_kernel(CacheView cache, c
                                                               const int32_t* __restrict__ n_new,
                                                               const int32_t* __restrict__ len_after, RopeFreq freq) {
     constexpr int KCH = D / 8;
+    __shared__ float2 s_rot[D / 2];
     const int b = blockIdx.x;
     const int capacity = cache.max_pages * kPage;
     // the token's index: the cache's own length, or -- len_after given -- the caller's length INCLUDING the token
@@ -125,6 +127,10 @@ __global__ __launch_bounds__(256) void kv_append_token_kernel(CacheView cache, c
     n = min(n, capacity - start);
     __syncthreads();                                     // every thread has read the old length
     if (n == 0) return;
+    if (ROPE) {
+        rope_table_to_lds<D>(s_rot, start, 1, freq, 256);        // index in this cache == position id
+        __syncthreads();
+    }
     const int id = cache.page_table[int64_t(b) * cache.max_pages + start / kPage];
     if (id >= 0 && id < cache.n_pages) {                 // never write outside the pool
         const int slot = start % kPage;
@@ -142,11 +148,10 @@ __global__ __launch_bounds__(256) void kv_append_token_kernel(CacheView cache, c
                     Piece lo_out, hi_out;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        float cs, sn;
-                        rope_cos_sin(start, freq.f[c8 * 8 + e], &cs, &sn);      // index in this cache == position id
+                        const float2 r = s_rot[c8 * 8 + e];
                         const float a = bf16_bits_to_f32(lo_in.v[e]), b2 = bf16_bits_to_f32(hi_in.v[e]);
-                        lo_out.v[e] = f32_to_bf16_bits(a * cs - b2 * sn);
-                        hi_out.v[e] = f32_to_bf16_bits(b2 * cs + a * sn);
+                        lo_out.v[e] = f32_to_bf16_bits(a * r.x - b2 * r.y);
+                        hi_out.v[e] = f32_to_bf16_bits(b2 * r.x + a * r.y);
                     }
                     *reinterpret_cast<Piece*>(kdst) = lo_out;
                     *reinterpret_cast<Piece*>(kdst + (KCH / 2) * (kPage * 8)) = hi_out;

@@ -88,20 +88,22 @@ struct WaveStamp {
     }
 };
 
-// Fused query rotation (Sec. 3.2, stream-local position ids): fragments j and j + KS/2 of a lane hold the
-// two halves of eight rotation pairs, head dims STRIDE j + off + e and D/2 + the same.
+// Fused query rotation (Sec. 3.2, stream-local position ids): fragments j and j + KS/2 of a lane hold the two halves of
+// eight rotation pairs, head dims STRIDE j + off + e and D/2 + the same; `row` holds (cos, sin) of the pairs at the row's
+// position (rope_table_to_lds).
 template <int KS, int STRIDE>
-__device__ __forceinline__ void rotate_query(bf16x8 (&qf)[KS], int off, int pos, const RopeFreq& fr) {
+__device__ __forceinline__ void rotate_fragments(bf16x8 (&f)[KS], int off, const float2* row) {
 #pragma unroll
-    for (int j = 0; j < KS / 2; ++j)
+    for (int j = 0; j < KS / 2; ++j) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            float cs, sn;
-            rope_cos_sin(pos, fr.f[STRIDE * j + off + e], &cs, &sn);
-            const float x = float(qf[j][e]), y = float(qf[j + KS / 2][e]);
-            qf[j][e] = (__bf16)(x * cs - y * sn);
-            qf[j + KS / 2][e] = (__bf16)(y * cs + x * sn);
+            const float2 r = row[STRIDE * j + off + e];
+            const float x = float(f[j][e]), y = float(f[j + KS / 2][e]);
+            f[j][e] = (__bf16)(x * r.x - y * r.y);
+            f[j + KS / 2][e] = (__bf16)(y * r.x + x * r.y);
         }
+        __builtin_amdgcn_sched_barrier(0);               // (all table reads at once would take 128 registers)
+    }
 }
 
 // The decode step with 17 .. 32 query rows q_len * G per sequence and KV head (several tokens in one call, or wide groups):
@@ -117,7 +119,11 @@ template <int D, bool STREAM_KEYS>
 __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
     constexpr int KS = D / 16, DB = D / 32, KCH = D / 8;
     constexpr float kLazyRise = 8.f;
-    __shared__ bf16x8 s_q[KS][64];
+    // first the (cos, sin) of the q_len query positions, then the query fragments (16 KB: eight workgroups fit a compute unit)
+    __shared__ union {
+        float2 rot[32 * (D / 2)];
+        bf16x8 q[KS][64];
+    } sm;
     const int lane = threadIdx.x;
     const int nc = a.ncs + a.ncr;
     const int c = int(blockIdx.x % unsigned(nc));
@@ -172,10 +178,13 @@ __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
         if (a.rope) {
             // the row's position id: its index in the reasoning stream
             const int len_own = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
-            rotate_query<KS, 16>(qf, 8 * hg, max(len_own - a.q_len + t_row, 0), a.freq);
+            rope_table_to_lds<D>(sm.rot, len_own - a.q_len, a.q_len, a.freq, 64);
+            __syncthreads();
+            rotate_fragments<KS, 16>(qf, 8 * hg, sm.rot + t_row * (D / 2));
+            __syncthreads();
         }
 #pragma unroll
-        for (int j = 0; j < KS; ++j) s_q[j][lane] = qf[j];                 // (read back by the same lane only)
+        for (int j = 0; j < KS; ++j) sm.q[j][lane] = qf[j];                // (read back by the same lane only)
     }
     f32x16 o_acc[DB];
 #pragma unroll
@@ -191,7 +200,7 @@ __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) t[i] = 0.f;
 #pragma unroll
-        for (int j = 0; j < KS; ++j) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kk[j]), s_q[j][lane], t, 0, 0, 0);
+        for (int j = 0; j < KS; ++j) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kk[j]), sm.q[j][lane], t, 0, 0, 0);
         // register i <-> token tok + 16 (i/8) + 8 hg + i%8
 #pragma unroll
         for (int i = 0; i < 16; ++i) t[i] = fmaf(t[i], a.scale_log2, -m_ref);
@@ -435,6 +444,7 @@ __device__ __forceinline__ void scan_unit16(const CacheView& cv, int b, int h, i
 template <int D, bool STREAM_KEYS>
 __global__ __launch_bounds__(64, 2) void decode_split16_kernel(DecodeArgs a) {
     constexpr int KS = D / 32, DB = D / 16, KCH = D / 8;
+    __shared__ float2 s_rot[16 * (D / 2)];              // (cos, sin) of the q_len query positions
     const WaveStamp stamp(a);
     const int lane = threadIdx.x;
     const int nc = a.ncs + a.ncr + a.append;             // (append: one more slot per sequence and head, the new token's)
@@ -467,7 +477,9 @@ __global__ __launch_bounds__(64, 2) void decode_split16_kernel(DecodeArgs a) {
     }
     if (a.rope) {
         const int len_r = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
-        rotate_query<KS, 32>(qf, 8 * g4, max(len_r - a.q_len + t_row, 0), a.freq);
+        rope_table_to_lds<D>(s_rot, len_r - a.q_len, a.q_len, a.freq, 64);
+        __syncthreads();
+        rotate_fragments<KS, 32>(qf, 8 * g4, s_rot + t_row * (D / 2));
     }
     f32x4 o_acc[DB];
 #pragma unroll
@@ -481,7 +493,7 @@ __global__ __launch_bounds__(64, 2) void decode_split16_kernel(DecodeArgs a) {
         const uint16_t* kp = a.k_new + (int64_t(b) * a.n_kv_heads + h) * D + 8 * g4;
 #pragma unroll
         for (int j = 0; j < KS; ++j) kf[j] = *reinterpret_cast<const bf16x8*>(kp + 32 * j);
-        if (a.rope) rotate_query<KS, 32>(kf, 8 * g4, idx, a.freq);
+        if (a.rope) rotate_fragments<KS, 32>(kf, 8 * g4, s_rot);         // (q_len = 1: the query's position)
         float dot = 0.f;
 #pragma unroll
         for (int j = 0; j < KS; ++j)
@@ -537,21 +549,6 @@ __global__ __launch_bounds__(64, 2) void decode_split16_kernel(DecodeArgs a) {
 // (log-sum-exp, fixed order) and write the finished rows.
 constexpr int kSmallWaves = 8, kSmallUnit = 64;
 
-// Rotation of a fragment set (layout of rotate_query<KS, 32>) by cos / sin values parked in LDS: entry i belongs
-// to head dims i and D/2 + i.
-template <int KS>
-__device__ __forceinline__ void rotate_fragments(bf16x8 (&f)[KS], int off, const float* cs, const float* sn) {
-#pragma unroll
-    for (int j = 0; j < KS / 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float c = cs[32 * j + off + e], s_ = sn[32 * j + off + e];
-            const float x = float(f[j][e]), y = float(f[j + KS / 2][e]);
-            f[j][e] = (__bf16)(x * c - y * s_);
-            f[j + KS / 2][e] = (__bf16)(y * c + x * s_);
-        }
-}
-
 // APPEND (one new token per sequence, q_len = 1): k_new / v_new [batch][Hkv][D] is the token at index
 // rsn_len[b] - 1 of the reasoning stream.  The workgroup of (sequence, KV head) stores its head's key (rotated by
 // that index if a.rope) and value in the reasoning cache, folds the token in from registers -- score in fp32 from
@@ -564,12 +561,11 @@ __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(Decode
     constexpr int W = kSmallWaves, UNIT = kSmallUnit;
     constexpr int WP = APPEND ? W + 1 : W;            // states to merge: the waves' and the new token's
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    // [WP][rows][D] partial outputs, [WP][rows] reference exponents, [WP][rows] sums, [D/2] cos, [D/2] sin
+    // [WP][rows][D] partial outputs, [WP][rows] reference exponents, [WP][rows] sums, [q_len][D/2] (cos, sin)
     float* sm_o = reinterpret_cast<float*>(smem_raw);
     float* sm_m = sm_o + WP * a.rows * D;
     float* sm_l = sm_m + WP * a.rows;
-    float* sm_cs = sm_l + WP * a.rows;
-    float* sm_sn = sm_cs + D / 2;
+    float2* sm_rot = reinterpret_cast<float2*>(sm_l + WP * a.rows);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int h = int(blockIdx.x % unsigned(a.n_kv_heads));
     const int b = int(blockIdx.x / unsigned(a.n_kv_heads));
@@ -585,9 +581,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(Decode
     const int units_s = (len_s + UNIT - 1) / UNIT, units = units_s + (len_r + UNIT - 1) / UNIT;
 
     if (a.rope) {
-        // q_len rows at consecutive positions: the workgroup evaluates the D/2 (cos, sin) pairs of the LAST row's
-        // position once; other rows (q_len > 1 only) rotate by their own position the slow way
-        if (threadIdx.x < D / 2) rope_cos_sin(max(len_all - 1, 0), a.freq.f[threadIdx.x], &sm_cs[threadIdx.x], &sm_sn[threadIdx.x]);
+        rope_table_to_lds<D>(sm_rot, len_all - a.q_len, a.q_len, a.freq, 64 * W);
         __syncthreads();
     }
     f32x4 o_acc[DB];
@@ -602,17 +596,14 @@ __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(Decode
 #pragma unroll
             for (int j = 0; j < KS; ++j) qf[j] = *reinterpret_cast<const bf16x8*>(qp + 32 * j);
         }
-        if (a.rope) {
-            if (a.q_len == 1) rotate_fragments<KS>(qf, 8 * g4, sm_cs, sm_sn);
-            else rotate_query<KS, 32>(qf, 8 * g4, max(len_all - a.q_len + t_row, 0), a.freq);
-        }
+        if (a.rope) rotate_fragments<KS, 32>(qf, 8 * g4, sm_rot + t_row * (D / 2));
         if (APPEND && wave == W - 1 && add) {
             // the new token: key fragments in the query's layout (piece 4 j + g4 of the row), the same for every row
             bf16x8 kf[KS];
             const uint16_t* kp = k_new + (int64_t(b) * a.n_kv_heads + h) * D + 8 * g4;
 #pragma unroll
             for (int j = 0; j < KS; ++j) kf[j] = *reinterpret_cast<const bf16x8*>(kp + 32 * j);
-            if (a.rope) rotate_fragments<KS>(kf, 8 * g4, sm_cs, sm_sn);
+            if (a.rope) rotate_fragments<KS, 32>(kf, 8 * g4, sm_rot);
             float dot = 0.f;
 #pragma unroll
             for (int j = 0; j < KS; ++j)
@@ -721,6 +712,7 @@ __device__ __forceinline__ bf16x8 e4m3x8_to_bf16(uint32_t lo, uint32_t hi) {
 template <int D>
 __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a) {
     constexpr int KS = D / 32, KP = D / 64, DB = D / 16, C16 = D / 16;
+    __shared__ float2 s_rot[16 * (D / 2)];              // (cos, sin) of the q_len query positions
     const int lane = threadIdx.x;
     const int nc = a.ncs + a.ncr;
     const int c = int(blockIdx.x % unsigned(nc));
@@ -753,8 +745,11 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
     bf16x8 qf[KS];
     {
         const uint16_t* qp = a.q + ((int64_t(b) * a.q_len + t_row) * a.n_q_heads + hq) * D;
-        const int len_r = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
-        const int pos = max(len_r - a.q_len + t_row, 0);
+        if (a.rope) {
+            const int len_r = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
+            rope_table_to_lds<D>(s_rot, len_r - a.q_len, a.q_len, a.freq, 64);
+            __syncthreads();
+        }
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
             const int d0 = 64 * (j >> 1) + 16 * g4 + 8 * (j & 1);
@@ -765,10 +760,9 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
                 const bf16x8 other = *reinterpret_cast<const bf16x8*>(qp + (upper ? d0 - D / 2 : d0 + D / 2));
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    float cs, sn;
-                    rope_cos_sin(pos, a.freq.f[(upper ? d0 - D / 2 : d0) + e], &cs, &sn);
+                    const float2 r = s_rot[t_row * (D / 2) + (upper ? d0 - D / 2 : d0) + e];
                     const float x = float(qf[j][e]), y = float(other[e]);
-                    qf[j][e] = (__bf16)(upper ? x * cs + y * sn : x * cs - y * sn);
+                    qf[j][e] = (__bf16)(upper ? x * r.x + y * r.y : x * r.x - y * r.y);
                 }
             }
         }
@@ -1108,12 +1102,28 @@ __global__ __launch_bounds__(256, 2) void chunk_split_lds_kernel(DecodeArgs a) {
 #pragma unroll
     for (int j = 0; j < KS; ++j)
         qf[j] = *reinterpret_cast<const bf16x8*>(a.q + ((int64_t(b) * a.max_new + t_row) * a.n_q_heads + hq) * D + 16 * j + 8 * hg);
-    if (a.rope) rotate_query<KS, 16>(qf, 8 * hg, max(len - q_len + t_row, 0), a.freq);
+    if (a.rope) {
+        // the positions of the group's 128 rows, at most 128 of them: they fit the (still unused) tile buffers exactly
+        static_assert(sizeof(ChunkSmem<D, STAGES, TOK>) >= 128 * (D / 2) * sizeof(float2), "rotation table over the tile buffers");
+        float2* s_rot = reinterpret_cast<float2*>(smem_raw);
+        const int t_first = rbg * 128 / a.group;
+        rope_table_to_lds<D>(s_rot, len - q_len + t_first, group_last_t - t_first + 1, a.freq, 256);
+        __syncthreads();
+        // (rows past the group's end repeat the last row of the sequence: it is this group's last or a later one)
+        rotate_fragments<KS, 16>(qf, 8 * hg, s_rot + (min(t_row, group_last_t) - t_first) * (D / 2));
+        __syncthreads();                             // read by everybody before the first copies land
+    }
     // queries times scale * log2(e), rounded to bf16 again: K q' is the exponent of the softmax weight
 #pragma unroll
     for (int j = 0; j < KS; ++j)
 #pragma unroll
         for (int e = 0; e < 8; ++e) qf[j][e] = (__bf16)(float(qf[j][e]) * a.scale_log2);
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+        u32x4 t = __builtin_bit_cast(u32x4, qf[j]);
+        asm volatile("" : "+v"(t));
+        qf[j] = __builtin_bit_cast(bf16x8, t);
+    }
 
     // Copies.  A step is PG pages of K and PG pages of V; the four waves share them out, PER_WAVE page copies each:
     // copy number x = wave * PER_WAVE + u is page x % PG of K (x < PG) or of V.
@@ -1200,9 +1210,12 @@ __global__ __launch_bounds__(256, 2) void chunk_split_lds_kernel(DecodeArgs a) {
             s_acc[f % SBN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[f], qf[f / SBN], f < SBN ? s_acc[SBN - 1] : s_acc[f % SBN], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         u32x4 fv[PG * DB];
+        auto load_v = [&](int f0, int f1) {
 #pragma unroll
-        for (int f = 0; f < PG * DB; ++f)
-            fv[f] = *reinterpret_cast<const u32x4*>(vb + (f / DB) * PAGE + 32 * (f % DB) * kPage + v_off);
+            for (int f = f0; f < f1; ++f)
+                fv[f] = *reinterpret_cast<const u32x4*>(vb + (f / DB) * PAGE + 32 * (f % DB) * kPage + v_off);
+        };
+        load_v(0, PG * DB / 2);
         __builtin_amdgcn_sched_barrier(0);
         // block sb, register i  <->  token tok + 32 sb + 16 (i/8) + 8 hg + i%8.  The scores leave the matrix pipe as
         // exponents relative to the row's reference (queries prescaled, -m_ref where the accumulators start).
@@ -1258,6 +1271,9 @@ __global__ __launch_bounds__(256, 2) void chunk_split_lds_kernel(DecodeArgs a) {
             has_ref = has_ref || move;
             weights();
         }
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(PG * DB / 2, PG * DB);
+        __builtin_amdgcn_sched_barrier(0);
         // the last score block is where the next step's accumulators start: -m_ref again
 #pragma unroll
         for (int i = 0; i < 16; ++i) s_acc[SBN - 1][i] = -m_ref;
@@ -1525,7 +1541,7 @@ static st_status decode_dual_impl(void* out, float* lse, const void* q, const st
     // Short caches: one wave per (sequence, KV head) does everything (no partials, no merge launch) -- when the
     // serial walk of both caches is short and there are too few sequences for the split to pay anyway.
     if (!fp8 && a.rows <= 16 && lens->max_src_len + lens->max_rsn_len <= kSmallDecodeTokens && int64_t(batch) * hkv <= 0x7fffffff) {
-        const size_t smem = (size_t(kSmallWaves + (append ? 1 : 0)) * a.rows * (d + 2) + d) * sizeof(float);
+        const size_t smem = (size_t(kSmallWaves + (append ? 1 : 0)) * a.rows * (d + 2) + size_t(a.q_len) * d) * sizeof(float);
         auto launch = [&](auto kernel) -> st_status {
             if (smem > 64 * 1024)                       // beyond the default limit (16 rows of 128 dims only)
                 ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem)));
