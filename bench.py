@@ -557,7 +557,7 @@ def _wave_timeline(st, torch, launch, reset, n_pairs=1 << 16, bin_us=10.0):
     while lo < span:
         bins.append(int(((start < lo + bin_us) & (end > lo) & real).sum()))
         lo += bin_us
-    return {"note": "one launch, every workgroup (one wave, one work unit) stamped at start and end with the 100 MHz wall clock (st_profile_wave_trace)",
+    return {"note": "one launch, every workgroup (four waves, one work unit) stamped at start and end with the 100 MHz wall clock (st_profile_wave_trace)",
             "workgroups": int(len(a)), "units_with_tokens": int(real.sum()), "first_start_to_last_end_us": round(span, 1),
             "events_around_this_single_launch_us": round(ev_ms * 1e3, 1),
             "unit_duration_us": {"mean": round(float(dur[real].mean()), 1), "p10": round(float(np.percentile(dur[real], 10)), 1),

@@ -81,7 +81,7 @@ enum { ST_PROF_PREFILL_ATTN = 0, ST_PROF_DECODE_SPLIT = 1, ST_PROF_BWD_DQ = 2, S
 void st_profile_enable(int32_t on);
 st_status st_profile_repeat(int32_t launches);
 /* Wave timeline of the decode split kernel (<= 16 query rows per sequence and KV head, bf16 caches), for the calling
- * thread's calls while timing is enabled: workgroup i of a launch (one wave: one work unit of one cache of one
+ * thread's calls while timing is enabled: workgroup i of a launch (four waves: one work unit of one cache of one
  * sequence and KV head, in the order sequence, head, unit; units past a cache's length end at once) writes the
  * 100 MHz wall clock at its start and at its end to device_buffer[2 i], device_buffer[2 i + 1] (uint64; device
  * memory of the caller, 16-byte aligned, n_pairs pairs; workgroups beyond n_pairs write nothing).  Every launch
@@ -382,9 +382,10 @@ typedef struct st_dual_lens {
     int32_t unit_tokens;            /* tokens per work unit of the step, see below; 0 = chosen by launch size */
 } st_dual_lens;
 
-/* Work units.  A step cuts each cache into units of lens->unit_tokens tokens, one wave each: 0 chooses by launch size -- 1024 for large batches down
- * to 128 for a few sequences, whose step is bound by a wave's serial walk over its unit --, 128,
- * 256, 512 or 1024 pins it (tests, tuning); other values give ST_ERR_INVALID_ARG.  Results agree
+/* Work units.  A step cuts each cache into units of lens->unit_tokens tokens, one workgroup each: 0
+ * chooses by launch size -- up to 4096 for large batches, down to 128 for a few sequences, whose step
+ * is bound by the serial walk over a unit --, 128, 256, 512 or 1024 pins it (tests, tuning); other
+ * values give ST_ERR_INVALID_ARG.  Results agree
  * within rounding.  st_decode_workspace_bytes takes the same value and answers for it (and always
  * provides for 512-token units).  A workspace sized for other length bounds or another unit is
  * accepted as long as it holds 512-token units; the call then uses the smallest unit not below the
@@ -436,7 +437,7 @@ st_status st_attn_decode_dual_rope(void* out, float* lse, const void* q,
  *   k_new, v_new : [batch, 1, n_kv_heads, head_dim] bf16 device, 16-byte aligned
  *   theta_base   : > 0: q and k_new are UNROTATED and are rotated by the token's position id
  *                  rsn_len[b] - 1 (Sec. 3.2); 0: both are already rotated
- * When both caches are short (max_src_len + max_rsn_len <= 1024) the step is ONE kernel launch:
+ * When both caches are short (max_src_len + max_rsn_len <= 1024; for a few sequences 640) the step is ONE kernel launch:
  * the workgroup that attends for a KV head also stores that head's key and value, and takes the
  * new token from registers.  Longer caches take two launches (the split kernel stores the token
  * through one more work unit per sequence and KV head and merges it as one more partial state;

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(CacheView cache, const u
     const int tid = threadIdx.x;
 
     if (ROPE) {
-        rope_table_to_lds<D>(s_rot, lo, cnt, freq, 256);         // index in this cache == position id
+        rope_table_to_lds<D>(s_rot, lo, cnt, rope_frequency<D>(freq), 256);         // index in this cache == position id
         __syncthreads();
         // K: a thread takes the two 16-byte pieces d = 8 c .. + 7 and D/2 + 8 c .. + 7 of one token --
         // the two halves of eight rotation pairs
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256) void kv_append_token_kernel(CacheView cache, c
     __syncthreads();                                     // every thread has read the old length
     if (n == 0) return;
     if (ROPE) {
-        rope_table_to_lds<D>(s_rot, start, 1, freq, 256);        // index in this cache == position id
+        rope_table_to_lds<D>(s_rot, start, 1, rope_frequency<D>(freq), 256);        // index in this cache == position id
         __syncthreads();
     }
     const int id = cache.page_table[int64_t(b) * cache.max_pages + start / kPage];

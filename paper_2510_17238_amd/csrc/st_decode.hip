@@ -1,11 +1,11 @@
 // Dual-cache decode (Sec. 3.3 "Parallel KV caches"; Alg. 1: merge the visible source
 // slice with the reasoning cache, then decode).
 //
-// Nothing is merged in memory.  The two caches are cut into work units of 128 to 1,024 tokens
-// (decode_unit_tokens); one WAVE takes one (sequence, KV head, unit),
-// streams that unit's K and V pages from HBM exactly once for all query heads of the group, and
-// emits an un-normalised partial (o, m, l).  A second kernel merges all partials of BOTH caches per (sequence, query
-// row, head) by log-sum-exp -- identical to a softmax over the concatenated cache.
+// Nothing is merged in memory.  The two caches are cut into work units of 128 to 4,096 tokens
+// (decode_unit_tokens); a workgroup of four waves takes one (sequence, KV head, unit), streams that unit's K and V
+// pages from HBM exactly once for all query heads of the group, and emits an un-normalised partial (o, m, l).  A second
+// kernel merges all partials of BOTH caches per (sequence, query row, head) by log-sum-exp -- identical to a softmax over
+// the concatenated cache.
 //
 // HBM-bound: 4 * D bytes per cached token and KV head, 2 * G * D useful flops for it.
 // The arithmetic rides on the matrix cores only to keep the vector ALUs out of the
@@ -24,9 +24,9 @@
 namespace st {
 
 constexpr int kChunk = 512;                 // tokens per work unit
-constexpr int kSmallDecodeTokens = 1024;    // both caches together: below this one wave per (sequence, KV head) finishes the rows itself
-constexpr int kChunkMin = 128;              // ... of the one-token decode step of a few sequences
-constexpr int kChunkLong = 1024;            // ... of the one-token decode step when there is plenty of work (64 pages: one id per lane)
+constexpr int kSmallDecodeTokens = 1024;    // both caches together: up to here one workgroup per (sequence, KV head) finishes the rows itself (small_decode)
+constexpr int kChunkMin = 128;              // ... of a decode step of a few sequences
+constexpr int kChunkLong = 4096;            // ... of a decode step when there is plenty of work (a wave's quarter is 64 pages: one id per lane)
 
 // 16 bytes of a pool that this launch reads once and never again, taken in whole 128-byte lines per instruction: the
 // load carries the non-temporal hint.  Value loads always do (measured on the decode step of 28 layers: 3 to 4 %
@@ -49,7 +49,7 @@ struct DecodeArgs {
     float* part_ml;    // [B][Hkv][nc][rows][2]
     int batch, q_len, n_q_heads, n_kv_heads, group, rows;
     int ncs, ncr;      // chunk slots per (sequence, head) for the two caches
-    int chunk;         // tokens per work unit (kChunk; kChunkMin .. kChunkLong for the one-wave decode kernels)
+    int chunk;         // tokens per work unit (kChunkMin .. kChunkLong)
     float scale_log2;
     // source-chunk prefill only: ragged query counts and 32-row blocks
     const int32_t* n_new;   // [B] query tokens per sequence, or null for max_new everywhere
@@ -70,6 +70,10 @@ struct DecodeArgs {
     int trace_cap;
 };
 
+// A barrier for data exchanged through LDS alone: __syncthreads() also waits for every global load in flight -- here the first
+// keys and values, requested before the queries are rotated.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Stamps the workgroup's start and end into the timeline buffer, whichever way the kernel is left.
 struct WaveStamp {
     unsigned long long* slot;
@@ -87,6 +91,52 @@ struct WaveStamp {
         }
     }
 };
+
+// The split kernels: a workgroup of FOUR WAVES takes one work unit (one cache of one sequence and KV head, a.chunk tokens)
+// and deals its steps out to the waves in turn; their states meet in LDS and ONE partial result leaves the
+// workgroup.  A partial is rows x D floats, written and read back by the merge kernel: with a wave per unit either the units
+// were short and the partials cost more than the bytes alone say (64 sequences of up to 24K tokens, 32 rows: 512-token units
+// 910 us, 1,024-token units 852), or they were long and the launch ended with a few of them.
+constexpr int kSplitWaves = 4;
+
+// what the waves of a workgroup leave for the merge: [4][rows][D] un-normalised outputs, [4][rows] reference exponents and sums
+template <int D>
+struct SplitLds {
+    float *o, *m, *l;
+    __device__ __forceinline__ SplitLds(unsigned char* smem, int rows)
+        : o(reinterpret_cast<float*>(smem)), m(o + kSplitWaves * rows * D), l(m + kSplitWaves * rows) {}
+};
+inline size_t split_lds_bytes(int rows, int d) { return sizeof(float) * size_t(kSplitWaves) * rows * (d + 2); }
+
+// log-sum-exp merge of the waves' states into the unit's partial result at row slot `slot`
+template <int D>
+__device__ __forceinline__ void merge_waves(const SplitLds<D>& sm, const DecodeArgs& a, int64_t slot) {
+    for (int e = int(threadIdx.x) * 4; e < a.rows * D; e += 64 * kSplitWaves * 4) {
+        const int row = e / D, d0 = e % D;
+        float m_all = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kSplitWaves; ++w) m_all = fmaxf(m_all, sm.m[w * a.rows + row]);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float den = 0.f;
+        if (m_all != -INFINITY) {
+#pragma unroll
+            for (int w = 0; w < kSplitWaves; ++w) {
+                const float mw = sm.m[w * a.rows + row];
+                if (mw == -INFINITY) continue;                        // a wave that holds nothing for this row
+                const float wt = __builtin_amdgcn_exp2f(mw - m_all);
+                den = fmaf(wt, sm.l[w * a.rows + row], den);
+                const f32x4 o = *reinterpret_cast<const f32x4*>(sm.o + (w * a.rows + row) * D + d0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] = fmaf(wt, o[i], acc[i]);
+            }
+        }
+        *reinterpret_cast<f32x4*>(a.part_o + (slot + row) * D + d0) = acc;
+        if (d0 == 0) {
+            a.part_ml[(slot + row) * 2] = m_all;
+            a.part_ml[(slot + row) * 2 + 1] = den;
+        }
+    }
+}
 
 // Fused query rotation (Sec. 3.2, stream-local position ids): fragments j and j + KS/2 of a lane hold the two halves of
 // eight rotation pairs, head dims STRIDE j + off + e and D/2 + the same; `row` holds (cos, sin) of the pairs at the row's
@@ -106,25 +156,24 @@ __device__ __forceinline__ void rotate_fragments(bf16x8 (&f)[KS], int off, const
     }
 }
 
-// The decode step with 17 .. 32 query rows q_len * G per sequence and KV head (several tokens in one call, or wide groups):
-// ONE WAVE per workgroup and work unit on v_mfma_f32_32x32x16_bf16, whose 32 columns are the query rows.  As in the 16-row
-// kernel below the bytes in flight are what counts -- 4 D bytes per token against 128 flop per byte: the page ids of the unit
-// are fetched once, the 16 KB of the next 32 tokens are requested before the present ones are multiplied (two register
-// sets), whole 128-byte lines per instruction, value loads with the non-temporal hint.  That only fits two waves per SIMD
-// with the queries in LDS, in fragment order (each fragment is read back right before its matrix instruction).  A lane owns
-// a query row: no running maximum, the row's reference exponent moves out of line when a step exceeds it by 2^kLazyRise.
-// 64 sequences of up to 8K + 16K tokens, 8 tokens x 4 heads, 8 KV heads of 128 dims (3.78 GB of cache): 1.44 ms with loads
-// requested when they were needed and 512-token units (and 57 us for the merge of their partial results) -> 0.84 ms (37 us).
+// The decode step with 17 .. 32 query rows q_len * G per sequence and KV head (several tokens in one call, or wide groups) on
+// v_mfma_f32_32x32x16_bf16, whose 32 columns are the query rows.  As in the 16-row kernel below the bytes in flight are what
+// counts -- 4 D bytes per token against 128 flop per byte: the page ids of a wave's run are fetched once, the 16 KB of the next
+// 32 tokens are requested before the present ones are multiplied (two register sets), whole 128-byte lines per instruction,
+// value loads with the non-temporal hint.  That only fits two waves per SIMD with the queries in LDS, in fragment order (one
+// copy for the four waves; each fragment is read back right before its matrix instruction).  A lane owns a query row: no
+// running maximum, the row's reference exponent moves out of line when a step exceeds it by 2^kLazyRise.
+// 64 sequences of up to 8K + 16K tokens, 8 tokens x 4 heads, 8 KV heads of 128 dims (3.78 GB of cache), with the merge
+// of the partial results: 1.50 ms with loads requested when they were needed, 0.89 with a wave per unit of 1,024 tokens, 0.75 ms.
 template <int D, bool STREAM_KEYS>
-__global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(64 * kSplitWaves, 2) void decode_split32_kernel(DecodeArgs a) {
     constexpr int KS = D / 16, DB = D / 32, KCH = D / 8;
     constexpr float kLazyRise = 8.f;
-    // first the (cos, sin) of the q_len query positions, then the query fragments (16 KB: eight workgroups fit a compute unit)
-    __shared__ union {
-        float2 rot[32 * (D / 2)];
-        bf16x8 q[KS][64];
-    } sm;
-    const int lane = threadIdx.x;
+    // query fragments [KS][64 lanes], behind them the (cos, sin) of the q_len query positions; after the loop: SplitLds
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    bf16x8* s_q = reinterpret_cast<bf16x8*>(smem_raw);
+    float2* s_rot = reinterpret_cast<float2*>(s_q + KS * 64);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nc = a.ncs + a.ncr;
     const int c = int(blockIdx.x % unsigned(nc));
     const unsigned bh = blockIdx.x / unsigned(nc);
@@ -132,11 +181,14 @@ __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
     const int b = int(bh / unsigned(a.n_kv_heads));
     const bool is_src = c < a.ncs;
     const CacheView& cv = is_src ? a.src : a.rsn;
+    const int unit0 = (is_src ? c : c - a.ncs) * a.chunk;
+    // wave w takes the 32-token steps w, w + 4, ...; the page ids of all of them (one per lane, 32 steps at most) are asked for
+    // before the length is known, as in Pages16
+    int my_page = cv.page_table[int64_t(b) * cv.max_pages + min(unit0 / kPage + 2 * (kSplitWaves * (lane >> 1) + wave) + (lane & 1), cv.max_pages - 1)];
+    my_page = min(max(my_page, 0), cv.n_pages - 1);
     const int len = min(max(is_src ? a.src_len[b] : a.rsn_len[b], 0), cv.max_pages * kPage);
-    const int tok0 = (is_src ? c : c - a.ncs) * a.chunk;
-    if (tok0 >= len) return;
-    const int tok_end = min(len, tok0 + a.chunk);
-    const int n_steps = (tok_end - tok0 + 31) / 32;
+    if (unit0 >= len) return;
+    const int n_steps = (min(len - unit0, a.chunk) - 32 * wave + 32 * kSplitWaves - 1) / (32 * kSplitWaves);
 
     const int n = lane & 31, hg = lane >> 5;
     const bool valid_row = n < a.rows;                  // row of this (sequence, KV head): token n / G, head n % G
@@ -147,10 +199,6 @@ __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
     const int limit = is_src ? len : min(max(len - a.q_len + t_row + 1, 0), len);
     const int limit_min = is_src ? len : min(max(len - a.q_len + 1, 0), len);
 
-    // the page ids of the unit, one per lane (units hold 64 pages at most)
-    const int last_page = (tok_end - 1) / kPage - tok0 / kPage;
-    int my_page = cv.page_table[int64_t(b) * cv.max_pages + tok0 / kPage + min(lane, last_page)];
-    my_page = min(max(my_page, 0), cv.n_pages - 1);
     const int64_t page_k = int64_t(cv.n_kv_heads) * KCH * (kPage * 8);
     const int64_t page_v = int64_t(cv.n_kv_heads) * D * kPage;
     // K: lane (m = n, hg) reads slot swap23(m % 16) of page m / 16, d-chunk 2 j + hg; V: lane (m = n, hg) reads slots
@@ -158,8 +206,7 @@ __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
     const uint16_t* k_lane = cv.k_pool + int64_t(h) * KCH * (kPage * 8) + hg * (kPage * 8) + swap23(n & 15) * 8;
     const uint16_t* v_lane = cv.v_pool + int64_t(h) * D * kPage + n * kPage + 8 * hg;
     auto load = [&](int s, u32x4 (&kk)[KS], u32x4 (&vv)[2][DB]) {
-        const int id0 = __builtin_amdgcn_readlane(my_page, min(2 * s, last_page));        // (past the visible length: the last visible page)
-        const int id1 = __builtin_amdgcn_readlane(my_page, min(2 * s + 1, last_page));
+        const int id0 = __builtin_amdgcn_readlane(my_page, 2 * s), id1 = __builtin_amdgcn_readlane(my_page, 2 * s + 1);
         const uint16_t* kp = k_lane + int64_t(n >> 4 ? id1 : id0) * page_k;
 #pragma unroll
         for (int j = 0; j < KS; ++j) kk[j] = key_load<STREAM_KEYS>(kp + 2 * j * (kPage * 8));
@@ -169,23 +216,19 @@ __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
             for (int db = 0; db < DB; ++db) vv[t][db] = stream_load(v_lane + int64_t(t ? id1 : id0) * page_v + db * 32 * kPage);
     };
     u32x4 ka[KS], va[2][DB], kb[KS], vb[2][DB];
-    load(0, ka, va);
-    {
-        bf16x8 qf[KS];
-        const uint16_t* qp = a.q + ((int64_t(b) * a.q_len + t_row) * a.n_q_heads + hq) * D + 8 * hg;
-#pragma unroll
-        for (int j = 0; j < KS; ++j) qf[j] = *reinterpret_cast<const bf16x8*>(qp + 16 * j);
-        if (a.rope) {
-            // the row's position id: its index in the reasoning stream
-            const int len_own = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
-            rope_table_to_lds<D>(sm.rot, len_own - a.q_len, a.q_len, a.freq, 64);
-            __syncthreads();
-            rotate_fragments<KS, 16>(qf, 8 * hg, sm.rot + t_row * (D / 2));
-            __syncthreads();
-        }
-#pragma unroll
-        for (int j = 0; j < KS; ++j) sm.q[j][lane] = qf[j];                // (read back by the same lane only)
+    if (n_steps > 0) load(0, ka, va);
+    // the queries: wave w takes fragments w and w + KS / 2 (the two halves of their rotation pairs), rotates them by the
+    // row's position -- its index in the reasoning stream -- and leaves them for all four
+    if (a.rope) rope_table_to_lds<D>(s_rot, min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage) - a.q_len, a.q_len, rope_frequency<D>(a.freq), 64 * kSplitWaves);
+    lds_barrier();
+    if (wave < KS / 2) {
+        const uint16_t* qp = a.q + ((int64_t(b) * a.q_len + t_row) * a.n_q_heads + hq) * D + 8 * hg + 16 * wave;
+        bf16x8 qf[2] = {*reinterpret_cast<const bf16x8*>(qp), *reinterpret_cast<const bf16x8*>(qp + D / 2)};
+        if (a.rope) rotate_fragments<2, 16>(qf, 8 * hg + 16 * wave, s_rot + t_row * (D / 2));
+        s_q[wave * 64 + lane] = qf[0];
+        s_q[(wave + KS / 2) * 64 + lane] = qf[1];
     }
+    lds_barrier();
     f32x16 o_acc[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -195,12 +238,12 @@ __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
     bool has_ref = false;
 
     auto compute = [&](int s, const u32x4 (&kk)[KS], u32x4 (&vv)[2][DB]) {
-        const int tok = tok0 + 32 * s;
+        const int tok = unit0 + 32 * (kSplitWaves * s + wave);
         f32x16 t;
 #pragma unroll
         for (int i = 0; i < 16; ++i) t[i] = 0.f;
 #pragma unroll
-        for (int j = 0; j < KS; ++j) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kk[j]), sm.q[j][lane], t, 0, 0, 0);
+        for (int j = 0; j < KS; ++j) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kk[j]), s_q[j * 64 + lane], t, 0, 0, 0);
         // register i <-> token tok + 16 (i/8) + 8 hg + i%8
 #pragma unroll
         for (int i = 0; i < 16; ++i) t[i] = fmaf(t[i], a.scale_log2, -m_ref);
@@ -264,29 +307,31 @@ __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
     }
 
     const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (!valid_row) return;
-    const int64_t slot = ((int64_t(b) * a.n_kv_heads + h) * nc + c) * a.rows + n;
-    float* po = a.part_o + slot * D;
+    __syncthreads();                                    // everybody is done with the query fragments
+    const SplitLds<D> sm(smem_raw, a.rows);
+    if (valid_row) {
+        float* po = sm.o + (wave * a.rows + n) * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            f32x4 o4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o4[e] = o_acc[db][4 * q4 + e];
-            *reinterpret_cast<f32x4*>(po + 32 * db + 8 * q4 + 4 * hg) = o4;
+            for (int q4 = 0; q4 < 4; ++q4)
+                *reinterpret_cast<f32x4*>(po + 32 * db + 8 * q4 + 4 * hg) =
+                    f32x4{o_acc[db][4 * q4], o_acc[db][4 * q4 + 1], o_acc[db][4 * q4 + 2], o_acc[db][4 * q4 + 3]};
+        if (hg == 0) {
+            sm.m[wave * a.rows + n] = has_ref ? m_ref : -INFINITY;
+            sm.l[wave * a.rows + n] = l_tot;
         }
-    if (hg == 0) {
-        a.part_ml[slot * 2] = has_ref ? m_ref : -INFINITY;
-        a.part_ml[slot * 2 + 1] = l_tot;
     }
+    __syncthreads();
+    merge_waves<D>(sm, a, ((int64_t(b) * a.n_kv_heads + h) * nc + c) * a.rows);
+}
+// LDS of a workgroup: the loop's part (queries, rotations) and the merge's share the space
+inline size_t split32_lds_bytes(int rows, int q_len, int d) {
+    const size_t loop = size_t(d / 16) * 64 * 16 + size_t(q_len) * (d / 2) * sizeof(float2), merge = split_lds_bytes(rows, d);
+    return loop > merge ? loop : merge;
 }
 
-// Variant for q_len * G <= 16 query rows (the one-token decode step): the same scheme on
-// v_mfma_f32_16x16x32_bf16, ONE WAVE PER WORKGROUP.  With a single wave everything that selects
-// the work unit is uniform (scalar registers, scalar branches), a finished unit frees its slot
-// at once, and at <= 128 VGPRs sixteen such waves share a CU, each with 16 KB of loads in flight.
-//
+// Variant for q_len * G <= 16 query rows (the one-token decode step): the same scheme on v_mfma_f32_16x16x32_bf16.
 // A wave takes 32 tokens (two pages) per step with two first-product MFMAs X and Y whose 16 key
 // rows are chosen so that afterwards quarter-wave g4 (lanes 16 g4 .. 16 g4 + 15) holds, for its
 // query column, the 8 CONSECUTIVE slots 8 (g4 % 2) .. + 7 of page g4 / 2: X gives slots +0..3,
@@ -294,68 +339,92 @@ __global__ __launch_bounds__(64, 2) void decode_split32_kernel(DecodeArgs a) {
 // whose A operand (V^T) is then one contiguous 16-byte load.  All loads are unconditional (page
 // ids are clamped into the pool); what lies beyond the visible length is removed afterwards by
 // index: scores by select, V by bit mask.
-// One unit (tokens [tok0, tok_end) of one cache) folded into the running state of a query column: the step loop of the
-// one-wave kernels.  State in base-2 exponent units: m_ref is the column's reference exponent (the same in its four
-// lanes); it starts at 0 with has_ref = false and is moved, out of line, only when a step brings an exponent more
-// than kLazyRise above it (or the first finite score): the common step then needs no exchange between lanes and no
-// rescale of the accumulator -- probabilities are bounded by 2^kLazyRise instead of 1, which fp32 and bf16 do not
-// mind, and whoever finishes the row divides by l anyway.
-template <int D, bool PREFETCH = false, bool STREAM_KEYS = false>
-__device__ __forceinline__ void scan_unit16(const CacheView& cv, int b, int h, int lane, int tok0, int tok_end, int len, int limit,
-                                            int limit_min, float scale_log2, const bf16x8 (&qf)[D / 32], f32x4 (&o_acc)[D / 16],
-                                            float& m_ref, float& l_run, bool& has_ref) {
-    constexpr int KS = D / 32, DB = D / 16, KCH = D / 8;
-    constexpr float kLazyRise = 8.f;
-    const int n = lane & 15, g4 = lane >> 4;
-    const int n_steps = (tok_end - tok0 + 31) / 32;
-    bf16x2 ones2;
-    ones2[0] = (__bf16)1.f;
-    ones2[1] = (__bf16)1.f;
-    // the page ids of the whole unit, one per lane, fetched once: no dependent scalar load per step
-    const int last_page = (tok_end - 1) / kPage - tok0 / kPage;      // last page of the chunk that holds visible tokens
-    int my_page = cv.page_table[int64_t(b) * cv.max_pages + tok0 / kPage + min(lane, last_page)];
-    my_page = min(max(my_page, 0), cv.n_pages - 1);
-    const int64_t page_k = int64_t(cv.n_kv_heads) * KCH * (kPage * 8);
-    const int64_t page_v = int64_t(cv.n_kv_heads) * D * kPage;
-    // K: lane (m = n, g4) reads d-chunk 4 j + g4 of key row m; row m lives in page m / 8, slot m % 8 for X and
-    // + 8 for Y -- the 64 lanes of one load instruction take whole 128-byte lines (eight slots of a d-chunk), none
-    // shared with another instruction
-    const bool k_second_page = (n >> 3) != 0;
-    const uint16_t* k_lane = cv.k_pool + int64_t(h) * KCH * (kPage * 8) + g4 * (kPage * 8) + (n & 7) * 8;
-    // V: lane (m = n, g4) reads slots 8 (g4 % 2) .. + 7 of row d = 16 db + m in page g4 / 2
-    const bool v_second_page = (g4 >> 1) != 0;
-    const uint16_t* v_lane = cv.v_pool + int64_t(h) * D * kPage + n * kPage + 8 * (g4 & 1);
+// 32 sequences of 2K + 1K to 6K tokens, 16 / 8 heads of 128 dims, the new token stored in the same launch, with the merge of
+// the partial results: 130 us per layer with one wave per unit, 125 us with four (5.8 TB/s; a copy of that size runs at 4.9).
+// One step of the 16-row kernels: 32 tokens (two pages), 8 key loads and 8 value loads of 16 bytes per lane at D = 128.
+template <int D>
+struct Tokens16 {
+    u32x4 kx[D / 32], ky[D / 32], vv[D / 16];
+};
 
+// A wave's steps of one cache: every `stride`-th step from token tok0 on.  Under load a memory round trip takes microseconds,
+// so what precedes the first keys is kept to one: the page ids of all the wave's steps (one per lane, 32 steps at most) are
+// asked for without waiting for the cache's length; pages past the end are read like any other (ids clamped into the pool)
+// and removed by index.
+// K: lane (m = n, g4) reads d-chunk 4 j + g4 of key row m; row m lives in page m / 8, slot m % 8 for X and + 8 for Y --
+//    the 64 lanes of one load instruction take whole 128-byte lines (eight slots of a d-chunk), none shared with another
+// V: lane (m = n, g4) reads slots 8 (g4 % 2) .. + 7 of row d = 16 db + m in page g4 / 2
+template <int D, bool STREAM_KEYS>
+struct Pages16 {
+    static constexpr int KS = D / 32, DB = D / 16, KCH = D / 8;
+    int my_page;
+    const uint16_t *k_lane, *v_lane;
+    int64_t page_k, page_v;
+    __device__ __forceinline__ Pages16(const CacheView& cv, int b, int h, int lane, int tok0, int stride) {
+        const int n = lane & 15, g4 = lane >> 4;
+        const int page = tok0 / kPage + 2 * stride * (lane >> 1) + (lane & 1);
+        const int id = cv.page_table[int64_t(b) * cv.max_pages + min(page, cv.max_pages - 1)];
+        k_lane = cv.k_pool + int64_t(h) * KCH * (kPage * 8) + g4 * (kPage * 8) + (n & 7) * 8;
+        v_lane = cv.v_pool + int64_t(h) * D * kPage + n * kPage + 8 * (g4 & 1);
+        page_k = int64_t(cv.n_kv_heads) * KCH * (kPage * 8);
+        page_v = int64_t(cv.n_kv_heads) * D * kPage;
+        my_page = min(max(id, 0), cv.n_pages - 1);
+    }
+    __device__ __forceinline__ void load(int s, Tokens16<D>& t32) const {
+        const int lane = int(threadIdx.x & 63);
+        const int id0 = __builtin_amdgcn_readlane(my_page, 2 * s), id1 = __builtin_amdgcn_readlane(my_page, 2 * s + 1);
+        const uint16_t* kp = k_lane + int64_t(lane & 8 ? id1 : id0) * page_k;
+        const uint16_t* vp = v_lane + int64_t(lane & 32 ? id1 : id0) * page_v;
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+            t32.kx[j] = key_load<STREAM_KEYS>(kp + 4 * j * (kPage * 8));
+            t32.ky[j] = key_load<STREAM_KEYS>(kp + 4 * j * (kPage * 8) + 8 * 8);
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) t32.vv[db] = stream_load(vp + db * 16 * kPage);
+    }
+};
+
+// The running state of a query column (lane (n, g4): column n), in base-2 exponent units: m_ref is the column's reference
+// exponent (the same in its four lanes); it starts at 0 with has_ref = false and is moved, out of line, only when a step brings
+// an exponent more than kLazyRise above it (or the first finite score): the common step then needs no exchange between lanes
+// and no rescale of the accumulator -- probabilities are bounded by 2^kLazyRise instead of 1, which fp32 and bf16 do not mind,
+// and whoever finishes the row divides by l anyway.
+template <int D>
+struct State16 {
+    static constexpr int KS = D / 32, DB = D / 16;
+    static constexpr float kLazyRise = 8.f;
+    bf16x8 qf[KS];
+    f32x4 o_acc[DB];
+    float m_ref = 0.f, l_run = 0.f;
+    bool has_ref = false;
+    __device__ __forceinline__ State16() {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o_acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     // value of the three other lanes of a query column folded in (lanes n, n + 16, n + 32, n + 48):
     // v_permlane16_swap / v_permlane32_swap exchange 16- / 32-lane rows between their two operands; with
     // both operands set to x, every lane finds x of lane ^ 16 (^ 32) in one of the two results
-    auto column_max = [&](float x) {
+    static __device__ __forceinline__ float column_max(float x) {
         float a1 = x, b1 = x;
         asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a1), "+v"(b1));
         float a2 = fmaxf(a1, b1), b2 = a2;
         asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a2), "+v"(b2));
         return fmaxf(a2, b2);
-    };
-
-    // one step = 32 tokens (two pages): 8 key loads and 8 value loads of 16 bytes per lane
-    auto load = [&](int s, u32x4 (&kx)[KS], u32x4 (&ky)[KS], u32x4 (&vv)[DB]) {
-        // page ids of this step (uniform); pages past the visible length fall back to the last visible one
-        const int id0 = __builtin_amdgcn_readlane(my_page, min(2 * s, last_page));
-        const int id1 = __builtin_amdgcn_readlane(my_page, min(2 * s + 1, last_page));
-        const uint16_t* kp = k_lane + int64_t(k_second_page ? id1 : id0) * page_k;
-        const uint16_t* vp = v_lane + int64_t(v_second_page ? id1 : id0) * page_v;
-#pragma unroll
-        for (int j = 0; j < KS; ++j) {
-            kx[j] = key_load<STREAM_KEYS>(kp + 4 * j * (kPage * 8));
-            ky[j] = key_load<STREAM_KEYS>(kp + 4 * j * (kPage * 8) + 8 * 8);
-        }
-#pragma unroll
-        for (int db = 0; db < DB; ++db) vv[db] = stream_load(vp + db * 16 * kPage);
-    };
-    auto compute = [&](int s, const u32x4 (&kx)[KS], const u32x4 (&ky)[KS], u32x4 (&vv)[DB]) {
-        const int first = tok0 + 32 * s + 8 * g4;       // token of this lane's first VALUE slot
+    }
+    // one step: 32 tokens from token `tok` of a cache of `len` visible tokens, of which this lane's row sees [0, limit) and every
+    // row [0, limit_min)
+    __device__ __forceinline__ void step(Tokens16<D>& t32, int tok, int len, int limit, int limit_min, float scale_log2) {
+        u32x4 (&kx)[KS] = t32.kx;
+        u32x4 (&ky)[KS] = t32.ky;
+        u32x4 (&vv)[DB] = t32.vv;
+        const int g4 = int(threadIdx.x & 63) >> 4;
+        bf16x2 ones2;
+        ones2[0] = (__bf16)1.f;
+        ones2[1] = (__bf16)1.f;
+        const int first = tok + 8 * g4;       // token of this lane's first VALUE slot
         // scores of this lane: X rows 4 g4 .. + 3 and the Y rows eight slots further on
-        const int first_k = tok0 + 32 * s + 16 * (g4 >> 1) + 4 * (g4 & 1);
+        const int first_k = tok + 16 * (g4 >> 1) + 4 * (g4 & 1);
         f32x4 sx = {0.f, 0.f, 0.f, 0.f}, sy = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
@@ -365,7 +434,7 @@ __device__ __forceinline__ void scan_unit16(const CacheView& cv, int b, int h, i
         float t[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) t[e] = fmaf(e < 4 ? sx[e] : sy[e - 4], scale_log2, -m_ref);
-        if (tok0 + 32 * s + 32 > limit_min) {           // uniform: a step that reaches some row's limit
+        if (tok + 32 > limit_min) {           // uniform: a step that reaches some row's limit
 #pragma unroll
             for (int e = 0; e < 8; ++e) t[e] = first_k + (e & 3) + 8 * (e >> 2) < limit ? t[e] : -INFINITY;
         }
@@ -405,7 +474,7 @@ __device__ __forceinline__ void scan_unit16(const CacheView& cv, int b, int h, i
         for (int r = 0; r < 2; ++r)
             asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(pw[r]), "+v"(pw[2 + r]));
         const bf16x8 pb = __builtin_bit_cast(bf16x8, pw);
-        if (tok0 + 32 * s + 32 > len) {                 // uniform: only the step that holds the end of the cache
+        if (tok + 32 > len) {                 // uniform: only the step that holds the end of the cache
             u32x4 keep;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -416,37 +485,17 @@ __device__ __forceinline__ void scan_unit16(const CacheView& cv, int b, int h, i
 #pragma unroll
         for (int db = 0; db < DB; ++db)
             o_acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv[db]), pb, o_acc[db], 0, 0, 0);
-    };
-    if (PREFETCH) {
-        // The loads of step s + 1 are issued before step s is computed (two register sets, used in turn): a wave
-        // has up to two steps' worth of bytes in flight, and a load's latency is covered by the step before it.
-        u32x4 kxa[KS], kya[KS], vva[DB], kxb[KS], kyb[KS], vvb[DB];
-        if (n_steps > 0) load(0, kxa, kya, vva);
-        for (int s = 0; s < n_steps; s += 2) {
-            if (s + 1 < n_steps) load(s + 1, kxb, kyb, vvb);
-            __builtin_amdgcn_sched_barrier(0);
-            compute(s, kxa, kya, vva);
-            if (s + 1 < n_steps) {
-                if (s + 2 < n_steps) load(s + 2, kxa, kya, vva);
-                __builtin_amdgcn_sched_barrier(0);
-                compute(s + 1, kxb, kyb, vvb);
-            }
-        }
-    } else {
-        for (int s = 0; s < n_steps; ++s) {
-            u32x4 kx[KS], ky[KS], vv[DB];
-            load(s, kx, ky, vv);
-            compute(s, kx, ky, vv);
-        }
     }
-}
+};
 
 template <int D, bool STREAM_KEYS>
-__global__ __launch_bounds__(64, 2) void decode_split16_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(64 * kSplitWaves, 2) void decode_split16_kernel(DecodeArgs a) {
     constexpr int KS = D / 32, DB = D / 16, KCH = D / 8;
-    __shared__ float2 s_rot[16 * (D / 2)];              // (cos, sin) of the q_len query positions
+    // (cos, sin) of the q_len query positions; after the loop: SplitLds
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    float2* s_rot = reinterpret_cast<float2*>(smem_raw);
     const WaveStamp stamp(a);
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nc = a.ncs + a.ncr + a.append;             // (append: one more slot per sequence and head, the new token's)
     const int c = int(blockIdx.x % unsigned(nc));
     const unsigned bh = blockIdx.x / unsigned(nc);
@@ -456,37 +505,38 @@ __global__ __launch_bounds__(64, 2) void decode_split16_kernel(DecodeArgs a) {
     const bool is_tok = c == a.ncs + a.ncr;
     const CacheView& cv = is_src ? a.src : a.rsn;
     const int cc = is_src ? c : c - a.ncs;
-    const int len_all = min(max(is_src ? a.src_len[b] : a.rsn_len[b], 0), cv.max_pages * kPage);
-    const int len = (a.append && !is_src && len_all > 0) ? len_all - 1 : len_all;     // cached tokens to walk
-    const int tok0 = is_tok ? 0 : cc * a.chunk;
-    if (is_tok ? len_all == 0 : tok0 >= len) return;
-    const int tok_end = min(len, tok0 + a.chunk);
-
+    const int unit0 = is_tok ? 0 : cc * a.chunk;
     const int n = lane & 15, g4 = lane >> 4;
     const bool valid_row = n < a.rows;
     const int nr = min(n, a.rows - 1);                  // rows past the end repeat the last one (never stored)
     const int t_row = nr / a.group;
     const int hq = h * a.group + nr % a.group;
-    const int limit = is_src ? len : max(len - a.q_len + t_row + 1, 0);
-    const int limit_min = is_src ? len : max(len - a.q_len + 1, 0);     // the smallest limit of any row (row 0's)
-    bf16x8 qf[KS];
+    // asked for at once: the page ids, the queries, a rotation frequency (rope_table_to_lds), the lengths
+    const Pages16<D, STREAM_KEYS> pages(cv, b, h, lane, unit0 + 32 * wave, kSplitWaves);
+    State16<D> st;
     {
         const uint16_t* qp = a.q + ((int64_t(b) * a.q_len + t_row) * a.n_q_heads + hq) * D + 8 * g4;
 #pragma unroll
-        for (int j = 0; j < KS; ++j) qf[j] = *reinterpret_cast<const bf16x8*>(qp + 32 * j);
+        for (int j = 0; j < KS; ++j) st.qf[j] = *reinterpret_cast<const bf16x8*>(qp + 32 * j);
     }
+    const int len_all = min(max(is_src ? a.src_len[b] : a.rsn_len[b], 0), cv.max_pages * kPage);
+    const int len = (a.append && !is_src && len_all > 0) ? len_all - 1 : len_all;     // cached tokens to walk
+    if (is_tok ? len_all == 0 : unit0 >= len) return;
+    // this wave's steps: every fourth one of the unit's
+    const int n_steps = is_tok ? 0 : (min(len - unit0, a.chunk) - 32 * wave + 32 * kSplitWaves - 1) / (32 * kSplitWaves);
+    const int limit = is_src ? len : min(max(len - a.q_len + t_row + 1, 0), len);
+    const int limit_min = is_src ? len : min(max(len - a.q_len + 1, 0), len);         // the smallest limit of any row (row 0's)
+    Tokens16<D> ta, tb;
+    if (n_steps > 0) pages.load(0, ta);
     if (a.rope) {
         const int len_r = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
-        rope_table_to_lds<D>(s_rot, len_r - a.q_len, a.q_len, a.freq, 64);
-        __syncthreads();
-        rotate_fragments<KS, 32>(qf, 8 * g4, s_rot + t_row * (D / 2));
+        rope_table_to_lds<D>(s_rot, len_r - a.q_len, a.q_len, rope_frequency<D>(a.freq), 64 * kSplitWaves);
+        lds_barrier();
+        rotate_fragments<KS, 32>(st.qf, 8 * g4, s_rot + t_row * (D / 2));
     }
-    f32x4 o_acc[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db) o_acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_ref = 0.f, l_run = 0.f;
-    bool has_ref = false;
-    if (is_tok) {
+    if (is_tok && wave > 0) {
+        // (the new token is one wave's work; the others hold nothing)
+    } else if (is_tok) {
         // the new token: key fragments in the query's layout (piece 4 j + g4 of the row), rotated by the token's index
         const int idx = len_all - 1;
         bf16x8 kf[KS];
@@ -498,17 +548,17 @@ __global__ __launch_bounds__(64, 2) void decode_split16_kernel(DecodeArgs a) {
 #pragma unroll
         for (int j = 0; j < KS; ++j)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) dot = fmaf(float(qf[j][e]), float(kf[j][e]), dot);
+            for (int e = 0; e < 8; ++e) dot = fmaf(float(st.qf[j][e]), float(kf[j][e]), dot);
         dot += __shfl_xor(dot, 16);
         dot += __shfl_xor(dot, 32);
-        m_ref = dot * a.scale_log2;
-        has_ref = true;
-        l_run = g4 == 0 ? 1.f : 0.f;                                  // (summed over the four lanes of a row below)
+        st.m_ref = dot * a.scale_log2;
+        st.has_ref = true;
+        st.l_run = g4 == 0 ? 1.f : 0.f;                                  // (summed over the four lanes of a row below)
         const uint16_t* vp = a.v_new + (int64_t(b) * a.n_kv_heads + h) * D;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o_acc[db][i] = bf16_bits_to_f32(vp[16 * db + 4 * g4 + i]);
+            for (int i = 0; i < 4; ++i) st.o_acc[db][i] = bf16_bits_to_f32(vp[16 * db + 4 * g4 + i]);
         // into the cache: this head's key and value at index idx; the workgroup of head 0 writes the new length
         const int id = a.rsn.page_table[int64_t(b) * a.rsn.max_pages + idx / kPage];
         const int slot_in_page = idx % kPage;
@@ -523,31 +573,51 @@ __global__ __launch_bounds__(64, 2) void decode_split16_kernel(DecodeArgs a) {
         }
         if (h == 0 && lane == 0) a.rsn.appended_len[b] = len_all;
     } else {
-        scan_unit16<D, true, STREAM_KEYS>(cv, b, h, lane, tok0, tok_end, len, min(limit, len), min(limit_min, len), a.scale_log2, qf, o_acc, m_ref, l_run,
-                                                has_ref);
+        // The loads of step x + 1 are issued before step x is computed (two register sets, used in turn): a wave has up to two
+        // steps' worth of bytes in flight, and a load's latency is covered by the step before it.
+        const int tok0 = unit0 + 32 * wave;
+        for (int x = 0; x < n_steps; x += 2) {
+            if (x + 1 < n_steps) pages.load(x + 1, tb);
+            __builtin_amdgcn_sched_barrier(0);
+            st.step(ta, tok0 + 32 * kSplitWaves * x, len, limit, limit_min, a.scale_log2);
+            if (x + 1 < n_steps) {
+                if (x + 2 < n_steps) pages.load(x + 2, ta);
+                __builtin_amdgcn_sched_barrier(0);
+                st.step(tb, tok0 + 32 * kSplitWaves * (x + 1), len, limit, limit_min, a.scale_log2);
+            }
+        }
     }
 
-    float l_tot = l_run + __shfl_xor(l_run, 16);
+    float l_tot = st.l_run + __shfl_xor(st.l_run, 16);
     l_tot += __shfl_xor(l_tot, 32);
-    if (!valid_row) return;
-    const int64_t slot = ((int64_t(b) * a.n_kv_heads + h) * nc + c) * a.rows + n;
-    float* po = a.part_o + slot * D;
-    // lane (n, g4), block db, register i  <->  d = 16 db + 4 g4 + i
+    __syncthreads();                                    // everybody is done with the rotations
+    const SplitLds<D> sm(smem_raw, a.rows);
+    if (valid_row) {
+        // lane (n, g4), block db, register i  <->  d = 16 db + 4 g4 + i
+        float* po = sm.o + (wave * a.rows + n) * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(po + 16 * db + 4 * g4) = o_acc[db];
-    if (g4 == 0) {
-        a.part_ml[slot * 2] = has_ref ? m_ref : -INFINITY;
-        a.part_ml[slot * 2 + 1] = l_tot;
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(po + 16 * db + 4 * g4) = st.o_acc[db];
+        if (g4 == 0) {
+            sm.m[wave * a.rows + n] = st.has_ref ? st.m_ref : -INFINITY;
+            sm.l[wave * a.rows + n] = l_tot;
+        }
     }
+    __syncthreads();
+    merge_waves<D>(sm, a, ((int64_t(b) * a.n_kv_heads + h) * nc + c) * a.rows);
+}
+// LDS of a workgroup: the rotations and the merge share the space
+inline size_t split16_lds_bytes(int rows, int q_len, int d) {
+    const size_t loop = size_t(q_len) * (d / 2) * sizeof(float2), merge = split_lds_bytes(rows, d);
+    return loop > merge ? loop : merge;
 }
 
 // Short caches (the streaming session of one listener: a hundred source tokens, a few hundred reasoning tokens): one
 // workgroup per (sequence, KV head) does everything -- no partial results in memory, no merge kernel, one launch per
 // layer and token instead of two.  Such a step is bound by the chain of memory round trips a wave makes walking its
-// tokens, so the tokens of BOTH caches are dealt out in short units to the waves of the workgroup (wave w folds
-// units w, w + W, ... into one running state), and the waves' states meet in LDS, where all threads merge them
-// (log-sum-exp, fixed order) and write the finished rows.
-constexpr int kSmallWaves = 8, kSmallUnit = 64;
+// tokens, so the tokens of BOTH caches are dealt out in steps of 32 to the waves of the workgroup (reasoning steps from the
+// first wave up, source steps from the last one down -- who takes what is known before the lengths are), and the waves' states
+// meet in LDS, where all threads merge them (log-sum-exp, fixed order) and write the finished rows.
+constexpr int kSmallWaves = 8, kTokenWave = 4;
 
 // APPEND (one new token per sequence, q_len = 1): k_new / v_new [batch][Hkv][D] is the token at index
 // rsn_len[b] - 1 of the reasoning stream.  The workgroup of (sequence, KV head) stores its head's key (rotated by
@@ -558,7 +628,7 @@ template <int D, bool APPEND>
 __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(DecodeArgs a, uint16_t* __restrict__ out, float* __restrict__ lse,
                                                                           const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new) {
     constexpr int KS = D / 32, DB = D / 16, KCH = D / 8;
-    constexpr int W = kSmallWaves, UNIT = kSmallUnit;
+    constexpr int W = kSmallWaves;
     constexpr int WP = APPEND ? W + 1 : W;            // states to merge: the waves' and the new token's
     extern __shared__ __align__(16) unsigned char smem_raw[];
     // [WP][rows][D] partial outputs, [WP][rows] reference exponents, [WP][rows] sums, [q_len][D/2] (cos, sin)
@@ -566,7 +636,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(Decode
     float* sm_m = sm_o + WP * a.rows * D;
     float* sm_l = sm_m + WP * a.rows;
     float2* sm_rot = reinterpret_cast<float2*>(sm_l + WP * a.rows);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = int(blockIdx.x % unsigned(a.n_kv_heads));
     const int b = int(blockIdx.x / unsigned(a.n_kv_heads));
     const int n = lane & 15, g4 = lane >> 4;
@@ -574,87 +644,96 @@ __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(Decode
     const int nr = min(n, a.rows - 1);
     const int t_row = nr / a.group;
     const int hq = h * a.group + nr % a.group;
+    // asked for at once: the page ids of both caches, the queries, the new token (wave kTokenWave), a rotation frequency, the
+    // lengths
+    const Pages16<D, false> pages_s(a.src, b, h, lane, 32 * (W - 1 - wave), W), pages_r(a.rsn, b, h, lane, 32 * wave, W);
+    State16<D> st;
+    {
+        const uint16_t* qp = a.q + ((int64_t(b) * a.q_len + t_row) * a.n_q_heads + hq) * D + 8 * g4;
+#pragma unroll
+        for (int j = 0; j < KS; ++j) st.qf[j] = *reinterpret_cast<const bf16x8*>(qp + 32 * j);
+    }
+    const bool token_wave = APPEND && wave == kTokenWave;
+    bf16x8 kf[KS];                                   // key fragments in the query's layout (piece 4 j + g4 of the row)
+    uint16_t vf[D / 64];                             // value elements lane, lane + 64
+    if (token_wave) {
+        const uint16_t* kp = k_new + (int64_t(b) * a.n_kv_heads + h) * D + 8 * g4;
+#pragma unroll
+        for (int j = 0; j < KS; ++j) kf[j] = *reinterpret_cast<const bf16x8*>(kp + 32 * j);
+#pragma unroll
+        for (int u = 0; u < D / 64; ++u) vf[u] = v_new[(int64_t(b) * a.n_kv_heads + h) * D + 64 * u + lane];
+    }
+    const double freq = a.rope ? rope_frequency<D>(a.freq) : 0.0;
     const int len_s = min(max(a.src_len[b], 0), a.src.max_pages * kPage);
     const int len_all = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
     const bool add = APPEND && len_all > 0;          // (rsn_len 0: an idle sequence, nothing to store)
     const int len_r = add ? len_all - 1 : len_all;   // cached reasoning tokens to walk
-    const int units_s = (len_s + UNIT - 1) / UNIT, units = units_s + (len_r + UNIT - 1) / UNIT;
-
+    // this wave's steps of 32 tokens: reasoning steps from wave 0 up, then source steps from the last wave down
+    const int steps_s = (len_s - 32 * (W - 1 - wave) + 32 * W - 1) / (32 * W), steps_r = (len_r - 32 * wave + 32 * W - 1) / (32 * W);
+    const int n_steps = steps_r + steps_s;
+    auto load = [&](int x, Tokens16<D>& t) {
+        if (x < steps_r) pages_r.load(x, t);
+        else pages_s.load(x - steps_r, t);
+    };
+    // the source slice is seen whole; reasoning token j by rows t with j <= len_all - q_len + t
+    const int limit = min(max(len_all - a.q_len + t_row + 1, 0), len_r), limit_min = min(max(len_all - a.q_len + 1, 0), len_r);
+    auto step = [&](int x, Tokens16<D>& t) {
+        const bool r = x < steps_r;
+        st.step(t, r ? 32 * (wave + W * x) : 32 * (W - 1 - wave + W * (x - steps_r)), r ? len_r : len_s, r ? limit : len_s, r ? limit_min : len_s,
+                a.scale_log2);
+    };
+    const int new_page = token_wave && add ? a.rsn.page_table[int64_t(b) * a.rsn.max_pages + (len_all - 1) / kPage] : -1;
     if (a.rope) {
-        rope_table_to_lds<D>(sm_rot, len_all - a.q_len, a.q_len, a.freq, 64 * W);
-        __syncthreads();
+        rope_table_to_lds<D>(sm_rot, len_all - a.q_len, a.q_len, freq, 64 * W);
+        lds_barrier();
+        rotate_fragments<KS, 32>(st.qf, 8 * g4, sm_rot + t_row * (D / 2));
     }
-    f32x4 o_acc[DB];
+    if (token_wave && add) {
+        // the new token: the same key for every row; its value row is its partial output
+        if (a.rope) rotate_fragments<KS, 32>(kf, 8 * g4, sm_rot);
+        float dot = 0.f;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) o_acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_ref = 0.f, l_run = 0.f;
-    bool has_ref = false;
-    if (wave < units || (APPEND && wave == W - 1)) {      // (uniform per wave)
-        bf16x8 qf[KS];
-        {
-            const uint16_t* qp = a.q + ((int64_t(b) * a.q_len + t_row) * a.n_q_heads + hq) * D + 8 * g4;
+        for (int j = 0; j < KS; ++j)
 #pragma unroll
-            for (int j = 0; j < KS; ++j) qf[j] = *reinterpret_cast<const bf16x8*>(qp + 32 * j);
+            for (int e = 0; e < 8; ++e) dot = fmaf(float(st.qf[j][e]), float(kf[j][e]), dot);
+        dot += __shfl_xor(dot, 16);
+        dot += __shfl_xor(dot, 32);
+        if (valid_row && g4 == 0) {
+            sm_m[W * a.rows + n] = dot * a.scale_log2;
+            sm_l[W * a.rows + n] = 1.f;
         }
-        if (a.rope) rotate_fragments<KS, 32>(qf, 8 * g4, sm_rot + t_row * (D / 2));
-        if (APPEND && wave == W - 1 && add) {
-            // the new token: key fragments in the query's layout (piece 4 j + g4 of the row), the same for every row
-            bf16x8 kf[KS];
-            const uint16_t* kp = k_new + (int64_t(b) * a.n_kv_heads + h) * D + 8 * g4;
+        for (int r = 0; r < a.rows; ++r)
 #pragma unroll
-            for (int j = 0; j < KS; ++j) kf[j] = *reinterpret_cast<const bf16x8*>(kp + 32 * j);
-            if (a.rope) rotate_fragments<KS, 32>(kf, 8 * g4, sm_rot);
-            float dot = 0.f;
+            for (int u = 0; u < D / 64; ++u) sm_o[(W * a.rows + r) * D + 64 * u + lane] = bf16_bits_to_f32(vf[u]);
+        // into the cache: page of index len_all - 1, this head
+        const int slot = (len_all - 1) % kPage;
+        if (new_page >= 0 && new_page < a.rsn.n_pages) {         // never write outside the pool
+            if (n == 0) {
+                uint16_t* kdst = a.rsn.k_pool + (int64_t(new_page) * a.n_kv_heads + h) * KCH * (kPage * 8) + slot * 8;
 #pragma unroll
-            for (int j = 0; j < KS; ++j)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) dot = fmaf(float(qf[j][e]), float(kf[j][e]), dot);
-            dot += __shfl_xor(dot, 16);
-            dot += __shfl_xor(dot, 32);
-            if (valid_row && g4 == 0) {
-                sm_m[W * a.rows + n] = dot * a.scale_log2;
-                sm_l[W * a.rows + n] = 1.f;
+                for (int j = 0; j < KS; ++j) *reinterpret_cast<bf16x8*>(kdst + (4 * j + g4) * (kPage * 8)) = kf[j];
             }
-            // into the cache: page of index len_all - 1, this head
-            const int idx = len_all - 1;
-            const int id = a.rsn.page_table[int64_t(b) * a.rsn.max_pages + idx / kPage];
-            const int slot = idx % kPage;
-            const uint16_t* vp = v_new + (int64_t(b) * a.n_kv_heads + h) * D;
-            if (id >= 0 && id < a.rsn.n_pages) {             // never write outside the pool
-                if (n == 0) {
-                    uint16_t* kdst = a.rsn.k_pool + (int64_t(id) * a.n_kv_heads + h) * KCH * (kPage * 8) + slot * 8;
+            uint16_t* vdst = a.rsn.v_pool + (int64_t(new_page) * a.n_kv_heads + h) * (D * kPage) + slot;
 #pragma unroll
-                    for (int j = 0; j < KS; ++j) *reinterpret_cast<bf16x8*>(kdst + (4 * j + g4) * (kPage * 8)) = kf[j];
-                }
-                uint16_t* vdst = a.rsn.v_pool + (int64_t(id) * a.n_kv_heads + h) * (D * kPage) + slot;
-                for (int d0 = lane; d0 < D; d0 += 64) vdst[d0 * kPage] = vp[d0];
-            }
-            // the token's value row is its partial output, the same for every row
-            for (int e = lane; e < a.rows * D; e += 64) sm_o[W * a.rows * D + e] = bf16_bits_to_f32(vp[e % D]);
-            if (h == 0 && lane == 0) a.rsn.appended_len[b] = len_all;
+            for (int u = 0; u < D / 64; ++u) vdst[(64 * u + lane) * kPage] = vf[u];
         }
-        // the source slice is seen whole; reasoning token j by rows t with j <= len_all - q_len + t
-        const int limit = min(max(len_all - a.q_len + t_row + 1, 0), len_r), limit_min = min(max(len_all - a.q_len + 1, 0), len_r);
-        for (int u = wave; u < units; u += W) {
-            if (u < units_s) {
-                const int tok0 = u * UNIT;
-                scan_unit16<D>(a.src, b, h, lane, tok0, min(len_s, tok0 + UNIT), len_s, len_s, len_s, a.scale_log2, qf, o_acc, m_ref, l_run, has_ref);
-            } else {
-                const int tok0 = (u - units_s) * UNIT;
-                scan_unit16<D>(a.rsn, b, h, lane, tok0, min(len_r, tok0 + UNIT), len_r, limit, limit_min, a.scale_log2, qf, o_acc, m_ref, l_run, has_ref);
-            }
-        }
+        if (h == 0 && lane == 0) a.rsn.appended_len[b] = len_all;
     }
-    if (APPEND && !add && wave == W - 1 && lane < a.rows) sm_m[W * a.rows + lane] = -INFINITY;
-    float l_tot = l_run + __shfl_xor(l_run, 16);
+    for (int x = 0; x < n_steps; ++x) {
+        Tokens16<D> t;
+        load(x, t);
+        step(x, t);
+    }
+    if (token_wave && !add && lane < a.rows) sm_m[W * a.rows + lane] = -INFINITY;
+    float l_tot = st.l_run + __shfl_xor(st.l_run, 16);
     l_tot += __shfl_xor(l_tot, 32);
     if (valid_row) {
         // lane (n, g4), block db, register i  <->  d = 16 db + 4 g4 + i
         float* po = sm_o + (wave * a.rows + n) * D;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(po + 16 * db + 4 * g4) = o_acc[db];
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(po + 16 * db + 4 * g4) = st.o_acc[db];
         if (g4 == 0) {
-            sm_m[wave * a.rows + n] = has_ref ? m_ref : -INFINITY;
+            sm_m[wave * a.rows + n] = st.has_ref ? st.m_ref : -INFINITY;
             sm_l[wave * a.rows + n] = l_tot;
         }
     }
@@ -710,10 +789,12 @@ __device__ __forceinline__ bf16x8 e4m3x8_to_bf16(uint32_t lo, uint32_t hi) {
 }
 
 template <int D>
-__global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(64 * kSplitWaves, 3) void decode_split16_fp8_kernel(DecodeArgs a) {
     constexpr int KS = D / 32, KP = D / 64, DB = D / 16, C16 = D / 16;
-    __shared__ float2 s_rot[16 * (D / 2)];              // (cos, sin) of the q_len query positions
-    const int lane = threadIdx.x;
+    // (cos, sin) of the q_len query positions; after the loop: SplitLds
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    float2* s_rot = reinterpret_cast<float2*>(smem_raw);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nc = a.ncs + a.ncr;
     const int c = int(blockIdx.x % unsigned(nc));
     const unsigned bh = blockIdx.x / unsigned(nc);
@@ -722,13 +803,16 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
     const bool is_src = c < a.ncs;
     const CacheView& cv = is_src ? a.src : a.rsn;
     const int cc = is_src ? c : c - a.ncs;
-    const int len = min(max(is_src ? a.src_len[b] : a.rsn_len[b], 0), cv.max_pages * kPage);
-    const int tok0 = cc * a.chunk;
-    if (tok0 >= len) return;
-    const int tok_end = min(len, tok0 + a.chunk);
+    const int unit0 = cc * a.chunk;
     // With half the bytes per token, a wave takes 64 tokens (four pages) per step to keep as many bytes in flight
-    // as the bf16 kernel does with 32.
-    const int n_steps = (tok_end - tok0 + 63) / 64;
+    // as the bf16 kernel does with 32; wave w takes steps w, w + 4, ...  Page ids (four lanes per step, 16 steps at most)
+    // are asked for before the length is known, as in Pages16.
+    int my_page = cv.page_table[int64_t(b) * cv.max_pages + min(unit0 / kPage + 4 * (kSplitWaves * (lane >> 2) + wave) + (lane & 3), cv.max_pages - 1)];
+    my_page = min(max(my_page, 0), cv.n_pages - 1);
+    const int len = min(max(is_src ? a.src_len[b] : a.rsn_len[b], 0), cv.max_pages * kPage);
+    if (unit0 >= len) return;
+    const int n_steps = (min(len - unit0, a.chunk) - 64 * wave + 64 * kSplitWaves - 1) / (64 * kSplitWaves);
+    const int tok0 = unit0 + 64 * wave;
 
     const int n = lane & 15, g4 = lane >> 4;
     const bool valid_row = n < a.rows;
@@ -747,8 +831,8 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
         const uint16_t* qp = a.q + ((int64_t(b) * a.q_len + t_row) * a.n_q_heads + hq) * D;
         if (a.rope) {
             const int len_r = min(max(a.rsn_len[b], 0), a.rsn.max_pages * kPage);
-            rope_table_to_lds<D>(s_rot, len_r - a.q_len, a.q_len, a.freq, 64);
-            __syncthreads();
+            rope_table_to_lds<D>(s_rot, len_r - a.q_len, a.q_len, rope_frequency<D>(a.freq), 64 * kSplitWaves);
+            lds_barrier();
         }
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
@@ -774,9 +858,6 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
     float m_ref = 0.f, l_run = 0.f;
     bool has_ref = false;
 
-    const int last_page = (tok_end - 1) / kPage - tok0 / kPage;
-    int my_page = cv.page_table[int64_t(b) * cv.max_pages + tok0 / kPage + min(lane, last_page)];
-    my_page = min(max(my_page, 0), cv.n_pages - 1);
     const int64_t page_k = int64_t(cv.n_kv_heads) * C16 * (kPage * 16);      // bytes
     const int64_t page_v = int64_t(cv.n_kv_heads) * D * kPage;
     const int64_t page_s = int64_t(cv.n_kv_heads) * kPage;                   // floats
@@ -801,7 +882,7 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
     for (int s = 0; s < n_steps; ++s) {
         int id[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) id[u] = __builtin_amdgcn_readlane(my_page, min(4 * s + u, last_page));
+        for (int u = 0; u < 4; ++u) id[u] = __builtin_amdgcn_readlane(my_page, 4 * s + u);
         const int id_k = k_page_sel == 0 ? id[0] : k_page_sel == 1 ? id[1] : k_page_sel == 2 ? id[2] : id[3];
         const int id_g = g4 == 0 ? id[0] : g4 == 1 ? id[1] : g4 == 2 ? id[2] : id[3];
         const uint8_t* kp = k_lane + int64_t(id_k) * page_k;
@@ -821,7 +902,7 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
             vs[u] = *reinterpret_cast<const f32x4*>(cv.v_scale + sp + 4 * u);
         }
 
-        const int first = tok0 + 64 * s + 16 * g4;      // token of this lane's slot 0
+        const int first = tok0 + 64 * kSplitWaves * s + 16 * g4;      // token of this lane's slot 0
         f32x4 sc[4];
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
@@ -832,7 +913,7 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
                 sc[st] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e4m3x8_to_bf16(k8[st][jj][2 * u], k8[st][jj][2 * u + 1]), qf[j], sc[st], 0, 0, 0);
             }
         }
-        const bool reaches_limit = tok0 + 64 * s + 64 > limit_min;      // uniform
+        const bool reaches_limit = tok0 + 64 * kSplitWaves * s + 64 > limit_min;      // uniform
         float t[16], vsc[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {                  // slot e = 4 set + register
@@ -878,7 +959,7 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
         }
         u32x4 keep[2];
         keep[0] = keep[1] = u32x4{0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-        if (tok0 + 64 * s + 64 > len) {
+        if (tok0 + 64 * kSplitWaves * s + 64 > len) {
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
@@ -896,15 +977,20 @@ __global__ __launch_bounds__(64, 3) void decode_split16_fp8_kernel(DecodeArgs a)
 
     float l_tot = l_run + __shfl_xor(l_run, 16);
     l_tot += __shfl_xor(l_tot, 32);
-    if (!valid_row) return;
-    const int64_t slot = ((int64_t(b) * a.n_kv_heads + h) * nc + c) * a.rows + n;
-    float* po = a.part_o + slot * D;
+    __syncthreads();                                    // everybody is done with the rotations
+    const SplitLds<D> sm(smem_raw, a.rows);
+    if (valid_row) {
+        // lane (n, g4), block db, register i  <->  d = 16 db + 4 g4 + i
+        float* po = sm.o + (wave * a.rows + n) * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(po + 16 * db + 4 * g4) = o_acc[db];
-    if (g4 == 0) {
-        a.part_ml[slot * 2] = has_ref ? m_ref : -INFINITY;
-        a.part_ml[slot * 2 + 1] = l_tot;
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(po + 16 * db + 4 * g4) = o_acc[db];
+        if (g4 == 0) {
+            sm.m[wave * a.rows + n] = has_ref ? m_ref : -INFINITY;
+            sm.l[wave * a.rows + n] = l_tot;
+        }
     }
+    __syncthreads();
+    merge_waves<D>(sm, a, ((int64_t(b) * a.n_kv_heads + h) * nc + c) * a.rows);
 }
 
 // One wave (one workgroup) per (sequence, query row, query head): log-sum-exp merge of the
@@ -1107,7 +1193,7 @@ __global__ __launch_bounds__(256, 2) void chunk_split_lds_kernel(DecodeArgs a) {
         static_assert(sizeof(ChunkSmem<D, STAGES, TOK>) >= 128 * (D / 2) * sizeof(float2), "rotation table over the tile buffers");
         float2* s_rot = reinterpret_cast<float2*>(smem_raw);
         const int t_first = rbg * 128 / a.group;
-        rope_table_to_lds<D>(s_rot, len - q_len + t_first, group_last_t - t_first + 1, a.freq, 256);
+        rope_table_to_lds<D>(s_rot, len - q_len + t_first, group_last_t - t_first + 1, rope_frequency<D>(a.freq), 256);
         __syncthreads();
         // (rows past the group's end repeat the last row of the sequence: it is this group's last or a later one)
         rotate_fragments<KS, 16>(qf, 8 * hg, s_rot + (min(t_row, group_last_t) - t_first) * (D / 2));
@@ -1392,20 +1478,32 @@ static inline size_t decode_partial_bytes(int unit, int64_t batch, int hkv, int 
     const size_t slots = size_t(batch) * hkv * nc * rows;
     return align256(slots * d * sizeof(float)) + align256(slots * 2 * sizeof(float)) + 256;
 }
-// Tokens per work unit of the one-wave decode kernels: a wave walks its unit serially, one
-// memory round trip per 32 tokens, so the unit is as long as still leaves enough units -- 1024 tokens when that
-// gives four thousand (fewest partial results; measured best on 64 streams of 36 layers), else 512 if that gives a
-// thousand (measured best on configs[2]: 32 streams), down to 128 for a few sequences, where the step is bound by
-// that serial walk and not by bandwidth.
+// Short caches: one workgroup per (sequence, KV head) does everything (no partial results, no merge launch).  A compute unit
+// takes in a cache at about 9 ns per token, so for a few (sequence, KV head) pairs, which leave most of the chip idle, the split
+// and its second launch win from some 640 tokens on (one sequence, 8 KV heads of 128 dims: 400 tokens 8.6 us here, 10.9 split;
+// 1,000 tokens 14.5 here, 11.1 split); larger batches keep it up to 1,024 (16 sequences of up to 900: 15.7 against 21.3).
+static inline bool small_decode(int64_t batch, int hkv, int max_src, int max_rsn) {
+    return max_src + max_rsn <= (batch * hkv <= 32 ? 640 : kSmallDecodeTokens);
+}
+
+// Tokens per work unit of a split kernel's workgroup.  Every unit pays a prologue (a chain of memory round trips, microseconds
+// each under load) and a partial result, so a unit is as long as still leaves enough of them to fill the chip (512 workgroups
+// at a time) and to end evenly: with the length BOUNDS (about half the units they give are real) the longest of 4,096 .. 1,024
+// tokens that gives 2,048 units -- us per layer, 16 / 8 heads of 128 dims: 64 sequences of up to 24K tokens 622 with 2,048
+// against 777 with 512; 16 of up to 16K 134 with 1,024 against 141 with 512; 48 of 2K 73 with 512 against 91 with 1,024 --, 1,024
+// units for 8-bit caches (32 sequences of up to 8K tokens: 82 with 2,048 against 88 with 512).  With more than 8 query rows
+// the partial results weigh so much (4.2 to 16 KB each) that 192 units of 4,096 tokens are enough (8 sequences of up to 12K
+// tokens, 32 rows: 63 against 67 with 512; 32 of them 214 against 264).  A few sequences are bound by the walk over a unit and
+// not by bandwidth: 256 tokens below 256 units of 512 (one sequence of 4K tokens: 13.5 against 15.3), 128 from 32 units down
+// (2K tokens: 11.7 against 15.3).
 static inline int decode_unit_tokens(int64_t batch, int hkv, int rows, int max_src, int max_rsn, int pinned, bool fp8 = false) {
     if (pinned) return pinned;               // the caller's choice (st_dual_lens::unit_tokens)
     auto units = [&](int unit) { return batch * hkv * ((max_src + unit - 1) / unit + (max_rsn + unit - 1) / unit); };
-    // (counted with the length BOUNDS: about half are real; the 8-bit kernel, which walks 64 tokens per step and
-    // keeps four waves per SIMD, is best with the long unit from a thousand on)
-    if (units(kChunkLong) >= (fp8 ? 1024 : 4096)) return kChunkLong;
-    int unit = kChunk;
-    while (unit > kChunkMin && units(unit) < 1024) unit /= 2;
-    return unit;
+    if (rows > 8 && units(kChunkLong) >= 192) return kChunkLong;
+    const int64_t enough = fp8 ? 1024 : 2048;
+    for (int unit = kChunkLong; unit > kChunk; unit /= 2)
+        if (units(unit) >= enough) return unit;
+    return units(kChunk) > 256 ? kChunk : units(kChunk) > 32 ? kChunk / 2 : kChunkMin;
 }
 
 }  // namespace st
@@ -1538,9 +1636,7 @@ static st_status decode_dual_impl(void* out, float* lse, const void* q, const st
     a.part_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + align256(slots * d * sizeof(float)));
 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    // Short caches: one wave per (sequence, KV head) does everything (no partials, no merge launch) -- when the
-    // serial walk of both caches is short and there are too few sequences for the split to pay anyway.
-    if (!fp8 && a.rows <= 16 && lens->max_src_len + lens->max_rsn_len <= kSmallDecodeTokens && int64_t(batch) * hkv <= 0x7fffffff) {
+    if (!fp8 && a.rows <= 16 && small_decode(batch, hkv, lens->max_src_len, lens->max_rsn_len) && int64_t(batch) * hkv <= 0x7fffffff) {
         const size_t smem = (size_t(kSmallWaves + (append ? 1 : 0)) * a.rows * (d + 2) + size_t(a.q_len) * d) * sizeof(float);
         auto launch = [&](auto kernel) -> st_status {
             if (smem > 64 * 1024)                       // beyond the default limit (16 rows of 128 dims only)
@@ -1567,30 +1663,23 @@ static st_status decode_dual_impl(void* out, float* lse, const void* q, const st
         // (bytes of the launch from the length bounds: about half are real)
         const double bound_bytes = double(batch) * hkv * (double(lens->max_src_len) + lens->max_rsn_len) * 4.0 * d;
         const bool stream_keys = bound_bytes <= 4.0e9;
+        auto go = [&](void (*kern)(DecodeArgs), size_t smem) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)units), dim3(64 * kSplitWaves), smem, s, a);
+        };
         if (a.rows <= 16) {
             if (!no_alloc) prof_begin(kProfDecodeSplit, s);      // (the timing hooks create events)
             for (int rep = 0, n_rep = no_alloc ? 1 : prof_repeat(); rep < n_rep; ++rep)
-            if (fp8) {
-                if (d == 64) hipLaunchKernelGGL((decode_split16_fp8_kernel<64>), dim3((unsigned)units), dim3(64), 0, s, a);
-                else hipLaunchKernelGGL((decode_split16_fp8_kernel<128>), dim3((unsigned)units), dim3(64), 0, s, a);
-            } else {
-                if (d == 64) {
-                    if (stream_keys) hipLaunchKernelGGL((decode_split16_kernel<64, true>), dim3((unsigned)units), dim3(64), 0, s, a);
-                    else hipLaunchKernelGGL((decode_split16_kernel<64, false>), dim3((unsigned)units), dim3(64), 0, s, a);
-                } else {
-                    if (stream_keys) hipLaunchKernelGGL((decode_split16_kernel<128, true>), dim3((unsigned)units), dim3(64), 0, s, a);
-                    else hipLaunchKernelGGL((decode_split16_kernel<128, false>), dim3((unsigned)units), dim3(64), 0, s, a);
-                }
-            }
+            if (fp8) go(d == 64 ? decode_split16_fp8_kernel<64> : decode_split16_fp8_kernel<128>, split16_lds_bytes(a.rows, a.q_len, d));
+            else if (d == 64) go(stream_keys ? decode_split16_kernel<64, true> : decode_split16_kernel<64, false>, split16_lds_bytes(a.rows, a.q_len, d));
+            else go(stream_keys ? decode_split16_kernel<128, true> : decode_split16_kernel<128, false>, split16_lds_bytes(a.rows, a.q_len, d));
             if (!no_alloc) prof_end(kProfDecodeSplit, s);
         } else {
-            if (d == 64) {
-                if (stream_keys) hipLaunchKernelGGL((decode_split32_kernel<64, true>), dim3((unsigned)units), dim3(64), 0, s, a);
-                else hipLaunchKernelGGL((decode_split32_kernel<64, false>), dim3((unsigned)units), dim3(64), 0, s, a);
-            } else {
-                if (stream_keys) hipLaunchKernelGGL((decode_split32_kernel<128, true>), dim3((unsigned)units), dim3(64), 0, s, a);
-                else hipLaunchKernelGGL((decode_split32_kernel<128, false>), dim3((unsigned)units), dim3(64), 0, s, a);
-            }
+            const size_t smem = split32_lds_bytes(a.rows, a.q_len, d);
+            auto kern = d == 64 ? (stream_keys ? decode_split32_kernel<64, true> : decode_split32_kernel<64, false>)
+                                : (stream_keys ? decode_split32_kernel<128, true> : decode_split32_kernel<128, false>);
+            if (smem > 64 * 1024)                       // beyond the default limit (32 rows of 128 dims)
+                ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem)));
+            go(kern, smem);
         }
         ST_LAUNCH_CHECK("decode_split_kernel");
     }

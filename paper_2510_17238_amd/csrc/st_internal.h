@@ -98,12 +98,13 @@ __device__ __forceinline__ void rope_cos_sin(int pos, double f, float* c, float*
 
 // (cos, sin) of the D / 2 rotation pairs at `count` consecutive positions from pos0 on, evaluated once by the `threads`
 // threads of a workgroup (a multiple of D / 2) into LDS: tab[t * D / 2 + i].  A thread evaluates ONE pair at its positions,
-// so it reads one frequency (the array is a kernel argument; indexed per lane it is a memory access) -- rotating a fragment
+// so it reads one frequency (rope_frequency: the array is a kernel argument; indexed per lane it is a memory access) -- rotating a fragment
 // pair by pair where it is held took a frequency load and an evaluation per element, one behind the other, in every wave.
 template <int D>
-__device__ __forceinline__ void rope_table_to_lds(float2* tab, int pos0, int count, const RopeFreq& fr, int threads) {
+__device__ __forceinline__ double rope_frequency(const RopeFreq& fr) { return fr.f[int(threadIdx.x) % (D / 2)]; }
+template <int D>
+__device__ __forceinline__ void rope_table_to_lds(float2* tab, int pos0, int count, double f, int threads) {
     const int i = int(threadIdx.x) % (D / 2);
-    const double f = fr.f[i];
     for (int t = int(threadIdx.x) / (D / 2); t < count; t += threads / (D / 2)) {
         float cs, sn;
         rope_cos_sin(max(pos0 + t, 0), f, &cs, &sn);
