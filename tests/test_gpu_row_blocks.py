@@ -71,3 +71,12 @@ def test_key_side_split_over_query_heads(st, hq, hkv, d):
     lists = [(np.array([127, 130]), np.array([129, 200])), (np.array([300]), np.array([260]))]
     cfg = W._assemble("split", "bf16", hq, hkv, d, lists, "interleaved", 23)
     _check(cfg, *_forward_and_backward(st, cfg))
+
+
+@pytest.mark.parametrize("heads", [1, 2])
+@pytest.mark.parametrize("hq,hkv,d", [(3, 3, 128), (4, 2, 64), (8, 2, 128), (16, 2, 64), (12, 2, 128)])
+def test_query_heads_over_waves(st, hq, hkv, d, heads):
+    """The waves of a workgroup take one, two or four sets of one or two query heads of a KV head and 128, 64 or 32 rows of
+    an item (groups of 1, 2, 4, 8 and 6 heads), rows and visible prefixes ending inside the parts."""
+    cfg = _case("bf16", hq, hkv, d, "interleaved")
+    _check(cfg, *_forward_and_backward(st, cfg, heads))
