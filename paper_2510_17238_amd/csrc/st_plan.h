@@ -29,6 +29,11 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 64, "WorkItem is one 64-byte record");
 
+// A packed key tile: compact row of its first row, rows (0: a spare tile, never read).
+struct TileInfo {
+    int32_t base, valid;
+};
+
 struct PlanView {  // what kernels need
     const int32_t* cu;       // [B+1] token offsets
     const int32_t* n_src;    // [B]
@@ -36,22 +41,11 @@ struct PlanView {  // what kernels need
     const int32_t* vis;      // [N] visible source count per compact row
     const WorkItem* sorted;  // [m_max] work items, longest first (unused slots last)
     int32_t m_max;
-    // Packed K / V^T buffers (bf16 path): sequence b owns key tiles [pack_base[b], pack_base[b+1]) of
-    // kTileN rows each: first ceil(S / kTileN) source tiles, then the reasoning tiles.
-    const int32_t* pack_base;  // [B+1]
-    int32_t pack_tiles;        // = pack_base[B]
-    int32_t batch;
+    // Packed K / V^T buffers (bf16 path): key tiles of kTileN rows each -- per sequence first ceil(S / kTileN) source tiles,
+    // then the reasoning tiles, then spare ones.
+    const TileInfo* tiles;     // [pack_tiles]
+    int32_t pack_tiles;
 };
-
-// largest b in [0, batch) with table[b] <= c, for a non-decreasing table of batch + 1 offsets
-__device__ __forceinline__ int find_seq(const int32_t* table, int batch, int c) {
-    int lo = 0, hi = batch;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (table[mid] <= c) lo = mid; else hi = mid;
-    }
-    return lo;
-}
 
 // fp32 attention (st_attn_f32.hip); the callers have checked the arguments and ordered `s` behind the plan
 st_status launch_prefill_f32(float* out, float* lse, const float* q, const float* k, const float* v, const PlanView& pv, int n_q_heads,
@@ -67,20 +61,21 @@ struct st_plan {
     int64_t n_tokens = 0;
     int32_t m_max = 0;
     int32_t heads_per_workgroup = 0;   // bf16 attention kernel: 0 = chosen by problem size, 1, 2 (st_plan_heads_per_workgroup)
-    std::vector<int32_t> cu_host, slot_base_host, pack_base_host;
+    std::vector<int32_t> cu_host, slot_base_host;
     int32_t pack_tiles = 0;
     void* ws = nullptr;
     bool owns_ws = false;
     hipStream_t stream = nullptr;
     hipEvent_t built = nullptr;        // recorded on `stream` behind the kernels that build the tables
-    int32_t *cu = nullptr, *slot_base = nullptr, *pack_base = nullptr, *n_src = nullptr, *n_rsn = nullptr;
+    int32_t *cu = nullptr, *n_src = nullptr, *n_rsn = nullptr;
     int32_t *perm = nullptr, *seg_c = nullptr, *vis = nullptr, *cost = nullptr, *flag = nullptr;
     unsigned long long* pairs = nullptr;
     st::WorkItem* items = nullptr;    // slot order (sequence by sequence)
     st::WorkItem* sorted = nullptr;   // longest first
+    st::TileInfo* tiles = nullptr;    // packed key tiles
 
     // Orders `s` behind the build of the tables (nothing to do on the stream that built them).
     hipError_t wait_built(hipStream_t s) const { return (s == stream || !built) ? hipSuccess : hipStreamWaitEvent(s, built, 0); }
 
-    st::PlanView view() const { return st::PlanView{cu, n_src, perm, vis, sorted, m_max, pack_base, pack_tiles, batch}; }
+    st::PlanView view() const { return st::PlanView{cu, n_src, perm, vis, sorted, m_max, tiles, pack_tiles}; }
 };

@@ -60,15 +60,9 @@ __global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ ta
                                                          RopeFreq freq) {
     constexpr int HALF = D / 2;
     const int tile = blockIdx.x;
-    const int b = find_seq(pv.pack_base, pv.batch, tile);
-    const int lt = tile - pv.pack_base[b];
-    const int t0 = pv.cu[b], S = pv.n_src[b], R = pv.cu[b + 1] - t0 - S;
-    const int ts = (S + kTileN - 1) / kTileN, tr = (R + kTileN - 1) / kTileN;
-    if (lt >= ts + tr) return;                      // spare tile of this sequence: never read
-    const bool src = lt < ts;
-    const int kt = src ? lt : lt - ts;
-    const int base = t0 + (src ? 0 : S) + kt * kTileN;
-    const int valid = min(kTileN, (src ? S : R) - kt * kTileN);
+    const TileInfo info = pv.tiles[tile];
+    if (info.valid == 0) return;                    // spare tile of a sequence: never read
+    const int base = info.base, valid = info.valid;
     for (int w = threadIdx.x; w < valid * HALF; w += 256) {
         const int row = w / HALF, i = w % HALF;
         float cs, sn;
@@ -87,15 +81,9 @@ __global__ __launch_bounds__(256) void tile_pack_rope_kernel(uint16_t* __restric
     constexpr int PER_THREAD = kTileN * CP / 256;
     const int tile = blockIdx.x / n_kv_heads;
     const int h = blockIdx.x % n_kv_heads;
-    const int b = find_seq(pv.pack_base, pv.batch, tile);
-    const int lt = tile - pv.pack_base[b];
-    const int t0 = pv.cu[b], S = pv.n_src[b], R = pv.cu[b + 1] - t0 - S;
-    const int ts = (S + kTileN - 1) / kTileN, tr = (R + kTileN - 1) / kTileN;
-    if (lt >= ts + tr) return;                      // spare tile of this sequence: never read
-    const bool src = lt < ts;
-    const int kt = src ? lt : lt - ts;
-    const int base = t0 + (src ? 0 : S) + kt * kTileN;
-    const int valid = min(kTileN, (src ? S : R) - kt * kTileN);
+    const TileInfo info = pv.tiles[tile];
+    if (info.valid == 0) return;                    // spare tile of a sequence: never read
+    const int base = info.base, valid = info.valid;
     const int tid = threadIdx.x;
     const uint32_t row_stride = uint32_t(n_kv_heads) * D;
     uint16_t* kdst = kc + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);

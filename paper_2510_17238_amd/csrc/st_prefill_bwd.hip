@@ -232,15 +232,9 @@ __global__ __launch_bounds__(256) void bwd_rowstats_kernel(float* __restrict__ s
     constexpr int PER = D / 4;                                   // elements per thread: 4 threads share a row
     const int tile = blockIdx.x / n_q_heads;
     const int h = blockIdx.x % n_q_heads;
-    const int b = find_seq(pv.pack_base, pv.batch, tile);
-    const int lt = tile - pv.pack_base[b];
-    const int t0 = pv.cu[b], S = pv.n_src[b], R = pv.cu[b + 1] - t0 - S;
-    const int ts = (S + kTileN - 1) / kTileN, tr = (R + kTileN - 1) / kTileN;
-    if (lt >= ts + tr) return;
-    const bool src = lt < ts;
-    const int kt = src ? lt : lt - ts;
-    const int base = t0 + (src ? 0 : S) + kt * kTileN;
-    const int valid = min(kTileN, (src ? S : R) - kt * kTileN);
+    const TileInfo info = pv.tiles[tile];
+    if (info.valid == 0) return;                    // spare tile of a sequence: never read
+    const int base = info.base, valid = info.valid;
     const int r = threadIdx.x >> 2, part = threadIdx.x & 3;
     float l2 = INFINITY, dl = 0.f;
     int vs = 0;
