@@ -51,23 +51,41 @@ namespace st {
 // with ONE barrier per key tile.  There is no running maximum of a row (see the list at the kernel): the reference
 // exponent m_ref is the row maximum of the first tile and only moves when a tile's weights sum beyond 2^kRiseLog2,
 // an out-of-line block.
-// Fused rotation (Sec. 3.2), step 1: the (cos, sin) pairs of every packed row -- `tab` [packed tile][64 rows][D/2]
-// float2, row r of a stream's tile t at (tile t) * 64 + r -- evaluated ONCE per token (not once per head): the key
-// pack below and the attention kernel's query load both rotate with them.  The angle position * theta^(-2i/D) is
-// reduced in fp64, cos / sin are fp32 (rope_cos_sin).  One workgroup per packed tile.
+// Fused rotation (Sec. 3.2), step 1: the (cos, sin) pairs of every packed row, evaluated ONCE per token (not once per head):
+// the key pack below and the attention kernel's query load both rotate with them.  Laid out for the latter, whose lane (n, hg)
+// holds the dims 16 j + 8 hg .. + 7 of row n: per 32 rows of a packed tile [j][w][hg][n] pairs 16 j + 8 hg + 2 w and + 1, so
+// that a load instruction takes 1 KB in one piece (row by row it took 16 bytes of each of 32 rows, and the rotation was a
+// quarter of the kernel on short sequences).  The angle position * theta^(-2i/D) is reduced in fp64, cos / sin are fp32
+// (rope_cos_sin).  One workgroup per packed tile.
+template <int D>
+__device__ __forceinline__ size_t rope_table_at(size_t packed_row, int j, int w, int hg) {       // in f32x4 units
+    return (packed_row >> 5) * (32 * D / 4) + ((j * 4 + w) * 2 + hg) * 32 + (packed_row & 31);
+}
 template <int D>
 __global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ tab, const int32_t* __restrict__ positions, PlanView pv,
                                                          RopeFreq freq) {
     constexpr int HALF = D / 2;
+    __shared__ double s_freq[HALF];
+    __shared__ int s_pos[kTileN];
     const int tile = blockIdx.x;
     const TileInfo info = pv.tiles[tile];
     if (info.valid == 0) return;                    // spare tile of a sequence: never read
-    const int base = info.base, valid = info.valid;
-    for (int w = threadIdx.x; w < valid * HALF; w += 256) {
-        const int row = w / HALF, i = w % HALF;
-        float cs, sn;
-        rope_cos_sin(positions[pv.perm[base + row]], freq.f[i], &cs, &sn);
-        tab[(size_t(tile) * kTileN + row) * HALF + i] = float2{cs, sn};
+    if (threadIdx.x < kTileN) s_pos[threadIdx.x] = positions[pv.perm[info.base + min(int(threadIdx.x), info.valid - 1)]];
+    else if (threadIdx.x < kTileN + HALF) s_freq[threadIdx.x - kTileN] = freq.f[threadIdx.x - kTileN];
+    __syncthreads();
+    f32x4* out = reinterpret_cast<f32x4*>(tab) + rope_table_at<D>(size_t(tile) * kTileN, 0, 0, 0);
+    for (int x = threadIdx.x; x < kTileN * D / 4; x += 256) {        // in the order of the layout, two pairs each
+        const int n = x & 31, hg = (x >> 5) & 1, jw = (x >> 6) % (D / 8), blk = x / (32 * D / 4);
+        const int i = 16 * (jw >> 2) + 8 * hg + 2 * (jw & 3);
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            float cs, sn;
+            rope_cos_sin(s_pos[32 * blk + n], s_freq[i + e], &cs, &sn);
+            v[2 * e] = cs;
+            v[2 * e + 1] = sn;
+        }
+        out[x] = v;
     }
 }
 
@@ -96,10 +114,10 @@ __global__ __launch_bounds__(256) void tile_pack_rope_kernel(uint16_t* __restric
         if (row < valid) {
             const uint16_t* kr = k + (uint32_t(pv.perm[base + row]) * row_stride + uint32_t(h) * D + cp * 8);
             const u32x4 lo_in = *reinterpret_cast<const u32x4*>(kr), hi_in = *reinterpret_cast<const u32x4*>(kr + D / 2);
-            const f32x4* trow = reinterpret_cast<const f32x4*>(tab + (size_t(tile) * kTileN + row) * (D / 2) + cp * 8);
+            const f32x4* tab4 = reinterpret_cast<const f32x4*>(tab);
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                const f32x4 t = trow[w];                                  // (cos, sin) of pairs 2 w and 2 w + 1
+                const f32x4 t = tab4[rope_table_at<D>(size_t(tile) * kTileN + row, cp >> 1, w, cp & 1)];      // (cos, sin) of pairs 8 cp + 2 w and + 1
                 uint32_t out_lo = 0, out_hi = 0;
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
@@ -253,17 +271,9 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     const uint32_t lds_v0 = uint32_t(uintptr_t(&sm.vt[0][0])) + uint32_t(wave) * (NL * 1024);
     auto issue_k = [&](int ti, int stage) { async_copy_rows<NL>(kc_head + size_t(tile_of(ti)) * TILE, lane_off, lds_k0 + stage * (TILE * 2)); };
     auto issue_v = [&](int ti, int stage) { async_copy_rows<NL>(vc_head + size_t(tile_of(ti)) * TILE, lane_off, lds_v0 + stage * (TILE * 2)); };
-    // copy order (tile x lives in buffer x % STAGES):
-    //   three buffers: K0 V0 K1 K2 V1 | K3 V2 | K4 V3 | ...   K two tiles ahead, V^T one
-    //   two buffers:   K0 V0 K1       | V1 K2 | V2 K3 | ...   one tile ahead
-    issue_k(0, 0);
-    issue_v(0, 0);
-    issue_k(1, 1);
-    if (STAGES == 3) {
-        issue_k(2, 2);
-        issue_v(1, 1);
-    }
-
+    // The rows' tokens, then their queries and the first key tile, then the other copies: a wait for an ordinary load also waits
+    // for the copies in flight (they are counted alike), so only what the first scores need is asked for before the queries
+    // are there.
     const int row_in_tile = (wave / head_waves) * 32 + n;
     const bool active = row_in_tile < it.n_rows;
     const int my_row = it.row0 + min(row_in_tile, it.n_rows - 1);
@@ -278,13 +288,32 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
 #pragma unroll
             for (int j = 0; j < KS; ++j) qf[h][j] = *reinterpret_cast<const bf16x8*>(qp + h * D + 16 * j);
     }
+    // copy order (tile x lives in buffer x % STAGES):
+    //   three buffers: K0 | V0 K1 K2 V1 | K3 V2 | K4 V3 | ...   K two tiles ahead, V^T one
+    //   two buffers:   K0 | V0 K1       | V1 K2 | V2 K3 | ...   one tile ahead
+    issue_k(0, 0);
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+            u32x4 t = __builtin_bit_cast(u32x4, qf[h][j]);
+            asm volatile("" : "+v"(t));
+            qf[h][j] = __builtin_bit_cast(bf16x8, t);
+        }
+    issue_v(0, 0);
+    issue_k(1, 1);
+    if (STAGES == 3) {
+        issue_k(2, 2);
+        issue_v(1, 1);
+    }
+
     if (ROPE) {
-        const float2* trow = rope_tab + (size_t(it.tile_a0) * kTileN + my_row) * (D / 2) + 8 * hg;
+        const f32x4* tab4 = reinterpret_cast<const f32x4*>(rope_tab);
 #pragma unroll
         for (int j = 0; j < KS / 2; ++j) {
             f32x4 cs4[4];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) cs4[w] = *reinterpret_cast<const f32x4*>(trow + 16 * j + 2 * w);
+            for (int w = 0; w < 4; ++w) cs4[w] = tab4[rope_table_at<D>(size_t(it.tile_a0) * kTileN + my_row, j, w, hg)];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float cs = cs4[e / 2][2 * (e % 2)], sn = cs4[e / 2][2 * (e % 2) + 1];
@@ -651,20 +680,31 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
         const float l_tot = l_run[h] + __shfl_xor(l_run[h], 32);   // wave-wide exchange: inactive rows take part
-        if (!active) continue;
         const float inv = 1.f / l_tot;
         uint16_t* op = out + (int64_t(tok_q) * n_q_heads + hq0 + h) * D;
-        // lane (n, hg), block db, register i  <->  d = 32 db + 8 (i/4) + 4 hg + i%4
+        // lane (n, hg), block db, register i  <->  d = 32 db + 8 (i/4) + 4 hg + i%4: the two lanes of a row hold four dims each of
+        // every eight.  One exchange of 32-lane rows per word pair (the upper half of an even group's words against the lower
+        // half of the odd group's) leaves lane hg with all eight of group 2 g + hg: half as many stores, 16 bytes each
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                bf16x4 o4;
+            for (int g = 0; g < 2; ++g) {
+                u32x2 lo, hi;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) o4[c] = (__bf16)(o_acc[h][db][4 * q4 + c] * inv);
-                *reinterpret_cast<bf16x4*>(op + 32 * db + 8 * q4 + 4 * hg) = o4;
+                for (int c = 0; c < 2; ++c) {
+                    bf16x2 a, b;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        a[e] = (__bf16)(o_acc[h][db][8 * g + 2 * c + e] * inv);
+                        b[e] = (__bf16)(o_acc[h][db][8 * g + 4 + 2 * c + e] * inv);
+                    }
+                    lo[c] = __builtin_bit_cast(uint32_t, a);
+                    hi[c] = __builtin_bit_cast(uint32_t, b);
+                    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(lo[c]), "+v"(hi[c]));
+                }
+                if (active) *reinterpret_cast<u32x4*>(op + 32 * db + 16 * g + 8 * hg) = u32x4{lo[0], lo[1], hi[0], hi[1]};
             }
-        if (lse && hg == 0) lse[int64_t(tok_q) * n_q_heads + hq0 + h] = (m_ref[h] + __builtin_amdgcn_logf(l_tot)) * kLn2;
+        if (lse && active && hg == 0) lse[int64_t(tok_q) * n_q_heads + hq0 + h] = (m_ref[h] + __builtin_amdgcn_logf(l_tot)) * kLn2;
     }
 }
 
