@@ -1520,7 +1520,9 @@ extern "C" size_t st_decode_workspace_bytes(int32_t batch, int32_t n_q_heads, in
     const int rows = q_len * (n_q_heads / n_kv_heads);
     // enough for 512-token units whatever the bounds of a later call, and for the unit this very call would use
     const size_t base = decode_partial_bytes(kChunk, batch, n_kv_heads, rows, head_dim, max_src_len, max_rsn_len);
-    const int unit = decode_unit_tokens(batch, n_kv_heads, rows, max_src_len, max_rsn_len, unit_tokens);
+    // (few sequences: for the shortest unit, which shorter caches than these may get in a later call)
+    int unit = decode_unit_tokens(batch, n_kv_heads, rows, max_src_len, max_rsn_len, unit_tokens);
+    if (!unit_tokens && unit < kChunk) unit = kChunkMin;
     const size_t own = decode_partial_bytes(unit, batch, n_kv_heads, rows, head_dim, max_src_len, max_rsn_len);
     return base > own ? base : own;
 }

@@ -86,7 +86,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
 struct RopeFreq {
     double f[64];  // theta^(-2 i / D), i < D/2 <= 64
 };
-RopeFreq make_rope_freq(double theta_base, int head_dim);
+const RopeFreq& make_rope_freq(double theta_base, int head_dim);      // valid until the thread's next call
 
 // cos / sin of position * f for the fused kernels: the angle (up to 1e5 rad at long contexts, where an
 // fp32 product would be off by 1e-3 rad) is reduced to [-pi, pi] in fp64, the functions themselves are fp32

@@ -53,6 +53,7 @@ static WsLayout ws_layout(int32_t batch, int64_t n_tokens) {
 constexpr int kPlanThreads = 1024;
 constexpr int kPre = 16;                 // tokens of a sequence that a thread keeps in registers through all passes (16,384 a sequence)
 constexpr int kSegLds = 8192;            // source tokens of a sequence whose segment ids are searched in LDS
+constexpr int kAloneMax = 256;           // work items up to which the workgroup of a single sequence orders them itself
 constexpr int kSmallTable = 64, kLargeTable = 512;      // up to this batch cu_seqlens travels as a kernel argument
 
 template <int CAP>
@@ -76,7 +77,7 @@ __device__ __forceinline__ int full_tiles(int limit, int n_cols) {
 struct PlanOut {                         // the tables of the workspace
     int32_t *cu, *n_src, *n_rsn, *perm, *seg_c, *vis, *flag, *cost;
     unsigned long long* pairs;
-    WorkItem* items;
+    WorkItem *items, *sorted;
     TileInfo* tiles;
 };
 
@@ -280,6 +281,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_sequence_kernel(const int32
     }
 
     // work items: the 128-row query tiles of the source stream, then those of the reasoning stream; spare slots are empty
+    const bool alone = batch == 1 && item_slots(n) <= kAloneMax;
     const int ts = (S + kTileM - 1) / kTileM, tr = (R + kTileM - 1) / kTileM;
     const int ps = (S + kTileN - 1) / kTileN, pr = (R + kTileN - 1) / kTileN;
     for (int local = threadIdx.x; local < item_slots(n); local += kPlanThreads) {
@@ -311,13 +313,27 @@ __global__ __launch_bounds__(kPlanThreads) void plan_sequence_kernel(const int32
             if (seq_major) cost = ((batch - 1 - b) << 20) + min(cost, (1 << 20) - 1);
         }
         o.items[slots_before + local] = it;
-        o.cost[slots_before + local] = cost;
+        if (alone) s_seg[local] = cost;                         // (the segment ids are done with)
+        else o.cost[slots_before + local] = cost;
     }
     // packed key tiles: the source tiles, then the reasoning tiles; spare ones hold no rows
     for (int local = threadIdx.x; local < tile_slots(n); local += kPlanThreads) {
         const bool src = local < ps;
         const int row = (src ? local : local - ps) * kTileN;
         o.tiles[tiles_before + local] = local < ps + pr ? TileInfo{t0 + (src ? 0 : S) + row, min(kTileN, (src ? S : R) - row)} : TileInfo{0, 0};
+    }
+    if (alone) {
+        // the only sequence: its workgroup orders the items itself (as plan_order_kernel does), no second launch
+        __threadfence_block();
+        __syncthreads();
+        const int m = item_slots(n);
+        for (int i = threadIdx.x; i < m; i += kPlanThreads) {
+            const int ci = s_seg[i];
+            int rank = 0;
+#pragma unroll 8
+            for (int k = 0; k < m; ++k) rank += int(s_seg[k] > ci || (s_seg[k] == ci && k < i));
+            o.sorted[rank] = o.items[i];
+        }
     }
 }
 
@@ -437,7 +453,7 @@ extern "C" st_status st_plan_create(st_plan** plan_out, const int32_t* segment_i
     // attention kernel's HBM fetch falls from 18 GB to 3.5 GB per launch and it runs 7 to 9 % faster; four sequences
     // of 4K tokens lose 2 to 6 % to the worse balance, hence the threshold).
     const bool seq_major = n_tokens >= 32768 && batch > 1 && batch < 2048;
-    const PlanOut o{p->cu, p->n_src, p->n_rsn, p->perm, p->seg_c, p->vis, p->flag, p->cost, p->pairs, p->items, p->tiles};
+    const PlanOut o{p->cu, p->n_src, p->n_rsn, p->perm, p->seg_c, p->vis, p->flag, p->cost, p->pairs, p->items, p->sorted, p->tiles};
     auto sequences = [&](auto cap_tag) {
         constexpr int CAP = decltype(cap_tag)::value;
         HostOffsets<CAP> h;
@@ -455,7 +471,8 @@ extern "C" st_status st_plan_create(st_plan** plan_out, const int32_t* segment_i
             return bail(e, "copy of cu_seqlens");
         sequences(std::integral_constant<int, 0>{});
     }
-    hipLaunchKernelGGL(plan_order_kernel, dim3((p->m_max + 63) / 64), dim3(256), 0, s, p->cost, p->m_max, p->items, p->sorted);
+    if (batch > 1 || p->m_max > kAloneMax)
+        hipLaunchKernelGGL(plan_order_kernel, dim3((p->m_max + 63) / 64), dim3(256), 0, s, p->cost, p->m_max, p->items, p->sorted);
     if ((e = hipGetLastError()) != hipSuccess) return bail(e, "launch of plan kernels");
     // calls that use the plan on another stream wait for this point
     if ((e = hipEventCreateWithFlags(&p->built, hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreateWithFlags");

@@ -11,9 +11,16 @@
 
 namespace st {
 
-RopeFreq make_rope_freq(double theta_base, int head_dim) {
-    RopeFreq freq;
-    for (int i = 0; i < 64; ++i) freq.f[i] = i < head_dim / 2 ? pow(theta_base, -2.0 * double(i) / double(head_dim)) : 0.0;
+// (64 pow calls are a tenth of a short call's host time, and a program uses one base: each thread keeps its last table)
+const RopeFreq& make_rope_freq(double theta_base, int head_dim) {
+    static thread_local RopeFreq freq;
+    static thread_local double for_base = 0.0;
+    static thread_local int for_dim = 0;
+    if (for_base != theta_base || for_dim != head_dim) {
+        for (int i = 0; i < 64; ++i) freq.f[i] = i < head_dim / 2 ? pow(theta_base, -2.0 * double(i) / double(head_dim)) : 0.0;
+        for_base = theta_base;
+        for_dim = head_dim;
+    }
     return freq;
 }
 
