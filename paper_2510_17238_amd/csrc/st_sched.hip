@@ -491,9 +491,10 @@ extern "C" st_status st_stream_run(const st_stream_job* job_in, int32_t mode, st
     Runner run{job, lay, ev, sh, vis_dev, len_dev, device, Clock::now(), c0.n_kv_heads, c0.head_dim, ps, ds, use_graph ? &staging : nullptr};
     for (int k = 0; k < job.n_sentences; ++k) report->waited[k] = report->sliced[k] = 0;
 
+    // the host clock is read right after the GPU's starting point: a first use of `ds` can take the host milliseconds
     ST_HIP(hipEventRecord(ev.start, ps));
-    ST_HIP(hipStreamWaitEvent(ds, ev.start, 0));
     run.t0 = Clock::now();
+    ST_HIP(hipStreamWaitEvent(ds, ev.start, 0));
     if (mode == ST_SCHED_STREAMING) {
         std::thread a([&] { run.prefill_loop(); });
         std::thread b([&] { run.decode_loop(report->waited, report->sliced); });
