@@ -993,19 +993,103 @@ __global__ __launch_bounds__(64 * kSplitWaves, 3) void decode_split16_fp8_kernel
     merge_waves<D>(sm, a, ((int64_t(b) * a.n_kv_heads + h) * nc + c) * a.rows);
 }
 
-// One wave (one workgroup) per (sequence, query row, query head): log-sum-exp merge of the
-// partials of both caches, in a fixed order (run-to-run identical results).  The partial rows are
-// fetched 32 at a time with independent loads -- one memory round trip per batch instead of one
-// per partial -- and folded with a running maximum across batches.
+// Merge of a row's partial results (both merge kernels): log-sum-exp in a fixed order, run-to-run identical.  D / 4 lanes take a
+// row, four head dims each, and fetch kMergeBatch partials per memory round trip; a row's partials are dealt out to `splits`
+// such groups of the workgroup (merge_splits), whose states meet in LDS.  Bound by the bytes of the partials and by the rate at
+// which workgroups start -- a wave per row, fetching 32 (8) partials whether there were that many or not, took 31 us for 16,384
+// rows of about 5 partials and 42 us for 65,536 rows of 1 to 3; so 12 and 27.
+constexpr int kMergeThreads = 256, kMergeBatch = 8;
 template <int D>
-__global__ __launch_bounds__(64) void decode_combine_kernel(DecodeArgs a, uint16_t* __restrict__ out,
-                                                            float* __restrict__ lse) {
-    constexpr int PER = D / 64;
-    constexpr int BATCH = 32;
-    const int lane = threadIdx.x;
-    const int hq = int(blockIdx.x % unsigned(a.n_q_heads));
-    const int t = int((blockIdx.x / unsigned(a.n_q_heads)) % unsigned(a.q_len));
-    const int b = int(blockIdx.x / unsigned(a.n_q_heads * a.q_len));
+struct MergeRow {
+    static constexpr int LANES = D / 4, GROUPS = kMergeThreads / LANES;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, den = 0.f;
+    // another state of the row: weight 0 for one that holds nothing
+    __device__ __forceinline__ void add(float w, float l, const f32x4& o) {
+        den = fmaf(w, l, den);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(w, o[e], acc[e]);
+    }
+    __device__ __forceinline__ bool raise(float to) {
+        if (to == -INFINITY) return false;                               // nothing visible so far
+        const float alpha = __builtin_amdgcn_exp2f(m - to);
+        m = to;
+        den *= alpha;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] *= alpha;
+        return true;
+    }
+    // partials first, first + stride, ... below n_tot; row_of(i): index of partial i's row
+    template <typename RowOf>
+    __device__ __forceinline__ void fold(const DecodeArgs& a, int first, int stride, int n_tot, int d0, RowOf row_of) {
+        for (int i0 = first; i0 < n_tot; i0 += kMergeBatch * stride) {
+            f32x2 ml[kMergeBatch];
+            f32x4 o[kMergeBatch];
+#pragma unroll
+            for (int u = 0; u < kMergeBatch; ++u) {
+                ml[u] = f32x2{-INFINITY, 0.f};
+                o[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (i0 + u * stride < n_tot) {
+                    const int64_t row = row_of(i0 + u * stride);
+                    ml[u] = *reinterpret_cast<const f32x2*>(a.part_ml + row * 2);
+                    o[u] = *reinterpret_cast<const f32x4*>(a.part_o + row * D + d0);
+                }
+            }
+            float top = m;
+#pragma unroll
+            for (int u = 0; u < kMergeBatch; ++u) top = fmaxf(top, ml[u][0]);
+            if (!raise(top)) continue;
+#pragma unroll
+            for (int u = 0; u < kMergeBatch; ++u) add(__builtin_amdgcn_exp2f(ml[u][0] - top), ml[u][1], o[u]);
+        }
+    }
+    // the states of `splits` neighbouring groups into the first one's (called by every thread of the workgroup)
+    __device__ __forceinline__ void meet(int splits) {
+        __shared__ f32x4 s_acc[kMergeThreads];
+        __shared__ f32x2 s_ml[GROUPS];
+        const int group = int(threadIdx.x) / LANES, lane = int(threadIdx.x) % LANES;
+        s_acc[threadIdx.x] = acc;
+        if (lane == 0) s_ml[group] = f32x2{m, den};
+        __syncthreads();
+        if (group % splits != 0) return;
+        float top = m;
+        for (int s = 1; s < splits; ++s) top = fmaxf(top, s_ml[group + s][0]);
+        if (!raise(top)) return;
+        for (int s = 1; s < splits; ++s)
+            add(__builtin_amdgcn_exp2f(s_ml[group + s][0] - top), s_ml[group + s][1], s_acc[(group + s) * LANES + lane]);
+    }
+    __device__ __forceinline__ void store(uint16_t* out, float* lse, int64_t row, int d0) const {
+        const float inv = den > 0.f ? 1.f / den : 0.f;
+        bf16x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = (__bf16)(acc[e] * inv);
+        *reinterpret_cast<bf16x4*>(out + row * D + d0) = r;
+        if (lse && d0 == 0) lse[row] = den > 0.f ? (m + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
+    }
+};
+// Groups per row: as few (a power of two, at most the 8 that a workgroup has at 128 dims) as fetch a row's partials in one round
+// trip; a single short unit of a long cache leaves hundreds of partials for a handful of rows.
+inline int merge_splits(int n_partials) {
+    int splits = 1;
+    while (splits < 8 && splits * kMergeBatch < n_partials) splits *= 2;
+    return splits;
+}
+inline int64_t merge_workgroups(int64_t rows, int d, int splits) {
+    const int per = kMergeThreads / (d / 4) / splits;
+    return (rows + per - 1) / per;
+}
+
+template <int D>
+__global__ __launch_bounds__(kMergeThreads) void decode_combine_kernel(DecodeArgs a, uint16_t* __restrict__ out,
+                                                                       float* __restrict__ lse, int splits) {
+    using Row = MergeRow<D>;
+    const int group = int(threadIdx.x) / Row::LANES, d0 = int(threadIdx.x) % Row::LANES * 4;
+    const int64_t n_rows = int64_t(a.batch) * a.q_len * a.n_q_heads;
+    const int64_t mine = int64_t(blockIdx.x) * (Row::GROUPS / splits) + group / splits;
+    const unsigned row = unsigned(min(mine, n_rows - 1));
+    const int hq = int(row % unsigned(a.n_q_heads));
+    const int t = int((row / unsigned(a.n_q_heads)) % unsigned(a.q_len));
+    const int b = int(row / (unsigned(a.n_q_heads) * unsigned(a.q_len)));
     const int h = hq / a.group, n = t * a.group + hq % a.group;
     const int nc = a.ncs + a.ncr + a.append;
     const int len_s = min(max(a.src_len[b], 0), a.src.max_pages * kPage);
@@ -1013,60 +1097,14 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(DecodeArgs a, uint16
     const int n_tok = (a.append && len_all > 0) ? 1 : 0;            // the new token's own partial (slot ncs + ncr)
     const int len_r = len_all - n_tok;                               // what the split kernel walked
     const int n_s = min((len_s + a.chunk - 1) / a.chunk, a.ncs), n_r = min((len_r + a.chunk - 1) / a.chunk, a.ncr);
-    const int n_tot = n_s + n_r + n_tok;
     const int64_t base = (int64_t(b) * a.n_kv_heads + h) * nc;
+    Row r;
     // partial i of the row -> slot: source units, reasoning units, then the token
-    auto slot_of = [&](int i) { return i < n_s ? i : i < n_s + n_r ? a.ncs + (i - n_s) : a.ncs + a.ncr; };
-
-    float acc[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-    float den = 0.f, m_run = -INFINITY;
-    for (int i0 = 0; i0 < n_tot; i0 += BATCH) {
-        const int cnt = min(BATCH, n_tot - i0);
-        // lane u < cnt owns (m, l) of partial i0 + u
-        float m_mine = -INFINITY, l_mine = 0.f;
-        if (lane < cnt) {
-            const int i = i0 + lane;
-            const int c = slot_of(i);
-            const f32x2 ml = *reinterpret_cast<const f32x2*>(a.part_ml + ((base + c) * a.rows + n) * 2);
-            m_mine = ml[0];
-            l_mine = ml[1];
-        }
-        float rows[BATCH][PER];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int i = i0 + min(u, cnt - 1);          // rows past the end repeat the last one, with weight 0
-            const int c = slot_of(i);
-            const float* po = a.part_o + ((base + c) * a.rows + n) * D + lane * PER;
-#pragma unroll
-            for (int e = 0; e < PER; ++e) rows[u][e] = po[e];
-        }
-        float bm = m_mine;
-        for (int o = 32; o > 0; o >>= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
-        const float m_new = fmaxf(m_run, bm);
-        if (m_new == -INFINITY) continue;                // nothing visible in this batch or before
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-        m_run = m_new;
-        const float w_mine = __builtin_amdgcn_exp2f(m_mine - m_new);     // 0 for lanes >= cnt
-        float wl = w_mine * l_mine;
-        for (int o = 32; o > 0; o >>= 1) wl += __shfl_xor(wl, o);
-        den = den * alpha + wl;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) acc[e] *= alpha;
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const float w = __shfl(w_mine, u);
-#pragma unroll
-            for (int e = 0; e < PER; ++e) acc[e] = fmaf(w, rows[u][e], acc[e]);
-        }
-    }
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-    uint16_t* op = out + ((int64_t(b) * a.q_len + t) * a.n_q_heads + hq) * D + lane * PER;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) op[e] = f32_to_bf16_bits(acc[e] * inv);
-    if (lse && lane == 0)
-        lse[(int64_t(b) * a.q_len + t) * a.n_q_heads + hq] = den > 0.f ? (m_run + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
+    r.fold(a, group % splits, splits, n_s + n_r + n_tok, d0, [&](int i) {
+        return (base + (i < n_s ? i : i < n_s + n_r ? a.ncs + (i - n_s) : a.ncs + a.ncr)) * a.rows + n;
+    });
+    if (splits > 1) r.meet(splits);
+    if (group % splits == 0 && mine < n_rows) r.store(out, lse, row, d0);
 }
 
 // Source-chunk prefill (Alg. 1, prefill loop) with the cache pages SHARED through LDS: one workgroup per
@@ -1403,70 +1441,31 @@ __global__ __launch_bounds__(256, 2) void chunk_split_lds_kernel(DecodeArgs a) {
     }
 }
 
-// Merge for the source-chunk prefill: one wave per (sequence, query token, query head).
+// Merge for the source-chunk prefill; rows past n_new[b] are left untouched.
 template <int D>
-__global__ __launch_bounds__(64) void chunk_combine_kernel(DecodeArgs a, uint16_t* __restrict__ out,
-                                                           float* __restrict__ lse) {
-    constexpr int PER = D / 64;
-    constexpr int BATCH = 8;                         // partial rows fetched per round trip (units are long: few partials per row)
-    const int lane = threadIdx.x;
-    const int hq = int(blockIdx.x % unsigned(a.n_q_heads));
-    const int t = int((blockIdx.x / unsigned(a.n_q_heads)) % unsigned(a.max_new));
-    const int b = int(blockIdx.x / unsigned(a.n_q_heads * a.max_new));
+__global__ __launch_bounds__(kMergeThreads) void chunk_combine_kernel(DecodeArgs a, uint16_t* __restrict__ out,
+                                                                      float* __restrict__ lse, int splits) {
+    using Row = MergeRow<D>;
+    const int group = int(threadIdx.x) / Row::LANES, d0 = int(threadIdx.x) % Row::LANES * 4;
+    const int64_t n_rows = int64_t(a.batch) * a.max_new * a.n_q_heads;
+    const int64_t mine = int64_t(blockIdx.x) * (Row::GROUPS / splits) + group / splits;
+    const unsigned row = unsigned(min(mine, n_rows - 1));
+    const int hq = int(row % unsigned(a.n_q_heads));
+    const int t = int((row / unsigned(a.n_q_heads)) % unsigned(a.max_new));
+    const int b = int(row / (unsigned(a.n_q_heads) * unsigned(a.max_new)));
     const int len = min(max(a.src_len[b], 0), a.src.max_pages * kPage);
     const int q_len = min(min(max(a.n_new ? a.n_new[b] : a.max_new, 0), a.max_new), len);
-    if (t >= q_len) return;                          // rows past n_new[b] are left untouched
     const int h = hq / a.group;
-    const int r = t * a.group + hq % a.group, rb = r / 32, n = r % 32;
+    const int rr = t * a.group + hq % a.group, rb = rr / 32, n = rr % 32;
     const int last_t = min(q_len - 1, (rb * 32 + 31) / a.group);
     const int unit_size = chunk_units(len, a.chunk).size;
-    const int n_tot = min((len - q_len + last_t + 1 + unit_size - 1) / unit_size, a.ncs);   // units the split kernel wrote for this block
+    // units the split kernel wrote for this block
+    const int n_tot = t < q_len ? min((len - q_len + last_t + 1 + unit_size - 1) / unit_size, a.ncs) : 0;
     const int64_t base = ((int64_t(b) * a.n_kv_heads + h) * a.row_blocks + rb) * a.ncs;
-
-    float acc[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-    float den = 0.f, m_run = -INFINITY;
-    for (int i0 = 0; i0 < n_tot; i0 += BATCH) {
-        const int cnt = min(BATCH, n_tot - i0);
-        float m_mine = -INFINITY, l_mine = 0.f;
-        if (lane < cnt) {
-            const f32x2 ml = *reinterpret_cast<const f32x2*>(a.part_ml + ((base + i0 + lane) * 32 + n) * 2);
-            m_mine = ml[0];
-            l_mine = ml[1];
-        }
-        float rows[BATCH][PER];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const float* po = a.part_o + ((base + i0 + min(u, cnt - 1)) * 32 + n) * D + lane * PER;
-#pragma unroll
-            for (int e = 0; e < PER; ++e) rows[u][e] = po[e];
-        }
-        float bm = m_mine;
-        for (int o = 32; o > 0; o >>= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
-        const float m_new = fmaxf(m_run, bm);
-        if (m_new == -INFINITY) continue;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-        m_run = m_new;
-        const float w_mine = __builtin_amdgcn_exp2f(m_mine - m_new);
-        float wl = w_mine * l_mine;
-        for (int o = 32; o > 0; o >>= 1) wl += __shfl_xor(wl, o);
-        den = den * alpha + wl;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) acc[e] *= alpha;
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const float w = __shfl(w_mine, u);
-#pragma unroll
-            for (int e = 0; e < PER; ++e) acc[e] = fmaf(w, rows[u][e], acc[e]);
-        }
-    }
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-    uint16_t* op = out + ((int64_t(b) * a.max_new + t) * a.n_q_heads + hq) * D + lane * PER;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) op[e] = f32_to_bf16_bits(acc[e] * inv);
-    if (lse && lane == 0)
-        lse[(int64_t(b) * a.max_new + t) * a.n_q_heads + hq] = den > 0.f ? (m_run + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
+    Row r;
+    r.fold(a, group % splits, splits, n_tot, d0, [&](int i) { return (base + i) * 32 + n; });
+    if (splits > 1) r.meet(splits);
+    if (group % splits == 0 && mine < n_rows && t < q_len) r.store(out, lse, row, d0);
 }
 
 static inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -1686,12 +1685,10 @@ static st_status decode_dual_impl(void* out, float* lse, const void* q, const st
         ST_LAUNCH_CHECK("decode_split_kernel");
     }
     if (out_units > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_decode_dual: grid too large");
-    if (d == 64)
-        hipLaunchKernelGGL((decode_combine_kernel<64>), dim3((unsigned)out_units), dim3(64), 0, s, a,
-                           static_cast<uint16_t*>(out), lse);
-    else
-        hipLaunchKernelGGL((decode_combine_kernel<128>), dim3((unsigned)out_units), dim3(64), 0, s, a,
-                           static_cast<uint16_t*>(out), lse);
+    const int splits = merge_splits(a.ncs + a.ncr + a.append);
+    const dim3 merge_grid((unsigned)merge_workgroups(out_units, d, splits));
+    if (d == 64) hipLaunchKernelGGL((decode_combine_kernel<64>), merge_grid, dim3(kMergeThreads), 0, s, a, static_cast<uint16_t*>(out), lse, splits);
+    else hipLaunchKernelGGL((decode_combine_kernel<128>), merge_grid, dim3(kMergeThreads), 0, s, a, static_cast<uint16_t*>(out), lse, splits);
     ST_LAUNCH_CHECK("decode_combine_kernel");
     return ST_OK;
 }
@@ -1831,8 +1828,10 @@ static st_status source_chunk_impl(void* out, float* lse, const void* q, const s
         if (lr != ST_OK) return lr;
         ST_LAUNCH_CHECK("chunk_split_lds_kernel");
     }
-    if (d == 64) hipLaunchKernelGGL((chunk_combine_kernel<64>), dim3((unsigned)out_units), dim3(64), 0, s, a, static_cast<uint16_t*>(out), lse);
-    else hipLaunchKernelGGL((chunk_combine_kernel<128>), dim3((unsigned)out_units), dim3(64), 0, s, a, static_cast<uint16_t*>(out), lse);
+    const int splits = merge_splits(a.ncs);
+    const dim3 merge_grid((unsigned)merge_workgroups(out_units, d, splits));
+    if (d == 64) hipLaunchKernelGGL((chunk_combine_kernel<64>), merge_grid, dim3(kMergeThreads), 0, s, a, static_cast<uint16_t*>(out), lse, splits);
+    else hipLaunchKernelGGL((chunk_combine_kernel<128>), merge_grid, dim3(kMergeThreads), 0, s, a, static_cast<uint16_t*>(out), lse, splits);
     ST_LAUNCH_CHECK("chunk_combine_kernel");
     return ST_OK;
 }
