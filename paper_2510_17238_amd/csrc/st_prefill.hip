@@ -240,21 +240,7 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     const int hk = hh0 % n_kv_heads;                // consecutive workgroups -> consecutive KV heads
     const int hq0 = hk * group + heads_here * (hh0 / n_kv_heads) + NH * (wave % head_waves);
     WorkItem it = pv.sorted[rank];
-    if (head_waves > 1) {
-        // the part's rows as an item of their own (the extents as the plan builds them)
-        const int part_rows = kTileM / head_waves;
-        it.row0 += sub * part_rows;
-        it.n_rows = min(part_rows, it.n_rows - sub * part_rows);
-        if (it.n_rows <= 0) return;
-        const int last = it.row0 + it.n_rows - 1;
-        it.a_total = last / kTileN + 1;
-        it.a_full = it.n_stream <= it.row0 + 1 ? (it.n_stream + kTileN - 1) / kTileN : (it.row0 + 1) / kTileN;
-        if (it.kind != ST_SOURCE) {
-            const int vmin = pv.vis[it.a_base + it.row0], vmax = pv.vis[it.a_base + last];
-            it.b_total = (vmax + kTileN - 1) / kTileN;
-            it.b_full = it.n_src <= vmin ? (it.n_src + kTileN - 1) / kTileN : vmin / kTileN;
-        }
-    }
+    if (head_waves > 1) it = item_part(it, pv, sub, kTileM / head_waves);
     if (it.n_rows <= 0) return;
     const int n_tiles = it.a_total + it.b_total;
 

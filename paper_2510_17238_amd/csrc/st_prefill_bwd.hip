@@ -41,22 +41,26 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
                                                              const uint16_t* __restrict__ q, const uint16_t* __restrict__ krows,
                                                              const uint16_t* __restrict__ vrows,
                                                              const float* __restrict__ lse, const float* __restrict__ delta,
-                                                             PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
+                                                             PlanView pv, int n_q_heads, int n_kv_heads, float scale, int head_waves) {
     constexpr int KS = D / 16, DB = D / 32, SB = kTileN / 32;
     constexpr int TILE = kTileN * D;
     constexpr int NL = TILE * 2 / 1024 / 4;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     BwdDqSmem<D>& sm = *reinterpret_cast<BwdDqSmem<D>*>(smem_raw);
 
-    const int rank = blockIdx.x / n_q_heads;
-    const int hh = blockIdx.x % n_q_heads;
-    const int group = n_q_heads / n_kv_heads;
-    const int hk = hh % n_kv_heads;
-    const int hq = hk * group + hh / n_kv_heads;
-    const WorkItem it = pv.sorted[rank];
-    if (it.n_rows == 0) return;
+    // workgroup -> (work item, part of its rows, set of head_waves query heads of one KV head), as in the forward
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_sets = n_q_heads / head_waves;
+    const int rank = blockIdx.x / n_q_heads;
+    const int rem = blockIdx.x % n_q_heads;
+    const int hh0 = rem % n_sets, sub = head_waves - 1 - rem / n_sets;              // (later rows have the longer loops: first)
+    const int group = n_q_heads / n_kv_heads;
+    const int hk = hh0 % n_kv_heads;
+    const int hq = hk * group + head_waves * (hh0 / n_kv_heads) + wave % head_waves;
+    WorkItem it = pv.sorted[rank];
+    if (head_waves > 1) it = item_part(it, pv, sub, kTileM / head_waves);
+    if (it.n_rows <= 0) return;
     const int n = lane & 31, hg = lane >> 5;
     const int n_tiles = it.a_total + it.b_total;
 
@@ -75,7 +79,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
     };
     issue_rows(0, 0);
 
-    const int row_in_tile = wave * 32 + n;
+    const int row_in_tile = (wave / head_waves) * 32 + n;
     const bool active = row_in_tile < it.n_rows;
     const int my_row = it.row0 + min(row_in_tile, it.n_rows - 1);
     const int tok_q = pv.perm[it.a_base + my_row];
@@ -765,10 +769,15 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
         const size_t smem_q = sizeof(BwdDqSmem<HD>), smem_k = sizeof(BwdDkvSmem<HD>);
         ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_dq_mfma_kernel<HD>), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem_q)));
         ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_dkv_mfma_kernel<HD>), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem_k)));
+        const int group = n_q_heads / n_kv_heads;
+        // the waves take as many heads as the group has, as in the forward and for the same reason: fewer rows end closer to
+        // their last visible column (training step, 4 x 4K tokens, 16 / 8 heads of 128 dims, 1195 -> 1181 us; 10 x 1.7K, 16 / 2
+        // of 64, 369 -> 364)
+        const int head_waves = group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
         prof_begin(kProfBwdDq, s);
         for (int rep = 0; rep < prof_repeat(); ++rep)
         hipLaunchKernelGGL((bwd_dq_mfma_kernel<HD>), dim3((unsigned)qblocks), dim3(256), smem_q, s, (uint16_t*)dq, (const uint16_t*)d_out,
-                           (const uint16_t*)q, at(L.krows), at(L.vrows), lse, delta, pv, n_q_heads, n_kv_heads, scale);
+                           (const uint16_t*)q, at(L.krows), at(L.vrows), lse, delta, pv, n_q_heads, n_kv_heads, scale, head_waves);
         prof_end(kProfBwdDq, s);
         prof_begin(kProfBwdDkv, s);
         for (int rep = 0; rep < prof_repeat(); ++rep)

@@ -105,6 +105,23 @@ struct TrOffsets {
     }
 };
 
+// Rows [sub * part_rows, + part_rows) of a work item as an item of their own, with the extents as the plan builds them
+// (n_rows <= 0: no such rows).
+__device__ __forceinline__ WorkItem item_part(WorkItem it, const PlanView& pv, int sub, int part_rows) {
+    it.row0 += sub * part_rows;
+    it.n_rows = min(part_rows, it.n_rows - sub * part_rows);
+    if (it.n_rows <= 0) return it;
+    const int last = it.row0 + it.n_rows - 1;
+    it.a_total = last / kTileN + 1;
+    it.a_full = it.n_stream <= it.row0 + 1 ? (it.n_stream + kTileN - 1) / kTileN : (it.row0 + 1) / kTileN;
+    if (it.kind != ST_SOURCE) {
+        const int vmin = pv.vis[it.a_base + it.row0], vmax = pv.vis[it.a_base + last];
+        it.b_total = (vmax + kTileN - 1) / kTileN;
+        it.b_full = it.n_src <= vmin ? (it.n_src + kTileN - 1) / kTileN : vmin / kTileN;
+    }
+    return it;
+}
+
 // swap bits 2 and 3: the row order in which K is parked in LDS, so that after the
 // first MFMA each half-wave holds 8 CONSECUTIVE keys per 16-key step
 __device__ __forceinline__ int swap23(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
