@@ -224,50 +224,65 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
 }
 
 
-// Row statistics of the backward in tile order: for every 64-row tile of a stream and every query head one
-// 1 KB block of 256 floats -- [0, 64) MINUS lse in base-2 units (-inf for rows past the end of the stream: their
-// probabilities become 0), [64, 128) MINUS delta, [128, 192) the visible-source count of the row (as int bits) --
-// so that the key-side kernel fetches them with ONE asynchronous copy per tile.  delta is also written in
-// token order for the query-side kernel.
+// Everything the two gradient kernels stream, in one pass: the row tiles of dO, Q, K and V and, in tile order, the row
+// statistics -- for every 64-row tile of a stream and every query head one 1 KB block of 256 floats: [0, 64) MINUS lse in base-2
+// units (-inf for rows past the end of the stream: their probabilities become 0), [64, 128) MINUS delta, [128, 192) the
+// visible-source count of the row (as int bits) -- so that the key-side kernel fetches them with ONE asynchronous copy per tile.
+// delta is also written in token order for the query-side kernel.
+// A workgroup takes one tile of one head of one tensor, the heads of all four side by side: 0 .. n_q_heads - 1 dO (and the
+// statistics), then Q, then K, then V.  Bound by its bytes (each tensor read and written once, the forward's output read once).
+// As five launches, dO read twice: training step, 4 x 4K tokens, 16 / 8 heads of 128 dims 1181 -> 1154 us; 10 x 1.7K, 16 / 2 of 64 364 -> 347.
+struct BwdPackArgs {
+    const uint16_t *d_out, *q, *k, *v, *out;
+    const float* lse;
+    uint16_t *dorows, *qrows, *krows, *vrows;
+    float *stats, *delta;
+    int n_q_heads, n_kv_heads;
+};
 template <int D>
-__global__ __launch_bounds__(256) void bwd_rowstats_kernel(float* __restrict__ stats, float* __restrict__ delta_tok,
-                                                          const uint16_t* __restrict__ d_out, const uint16_t* __restrict__ out,
-                                                          const float* __restrict__ lse, PlanView pv, int n_q_heads) {
-    constexpr int PER = D / 4;                                   // elements per thread: 4 threads share a row
-    const int tile = blockIdx.x / n_q_heads;
-    const int h = blockIdx.x % n_q_heads;
+__global__ __launch_bounds__(256) void bwd_pack_kernel(BwdPackArgs a, PlanView pv) {
+    const int n_slots = 2 * (a.n_q_heads + a.n_kv_heads);
+    const int tile = int(blockIdx.x) / n_slots;
+    int h = int(blockIdx.x) % n_slots;
     const TileInfo info = pv.tiles[tile];
     if (info.valid == 0) return;                    // spare tile of a sequence: never read
-    const int base = info.base, valid = info.valid;
-    const int r = threadIdx.x >> 2, part = threadIdx.x & 3;
-    float l2 = INFINITY, dl = 0.f;
-    int vs = 0;
-    int64_t rh = 0;
-    if (r < valid) {
-        const int tok = pv.perm[base + r];
-        rh = int64_t(tok) * n_q_heads + h;
-        const uint16_t* a = d_out + rh * D + part * PER;
-        const uint16_t* o = out + rh * D + part * PER;
+    const int32_t* perm = pv.perm + info.base;
+    if (h < a.n_q_heads) {
+        float* blk = a.stats + (size_t(h) * pv.pack_tiles + tile) * 256;
+        pack_rows<D>(a.dorows + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D), a.d_out, perm, info.valid, uint32_t(a.n_q_heads) * D, uint32_t(h),
+                     [&](int row, uint32_t at, const u32x4& piece) {
+                         float dl = 0.f;
+                         if (row < info.valid) {
+                             const bf16x8 x = __builtin_bit_cast(bf16x8, piece), o = *reinterpret_cast<const bf16x8*>(a.out + at);
 #pragma unroll
-        for (int c = 0; c < PER / 8; ++c) {
-            const bf16x8 x = *reinterpret_cast<const bf16x8*>(a + 8 * c), y = *reinterpret_cast<const bf16x8*>(o + 8 * c);
+                             for (int e = 0; e < 8; ++e) dl = fmaf(float(x[e]), float(o[e]), dl);
+                         }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) dl = fmaf(float(x[e]), float(y[e]), dl);
-        }
+                         for (int s = 1; s < D / 8; s *= 2) dl += __shfl_xor(dl, s);
+                         if (threadIdx.x % (D / 8) != 0) return;
+                         float l2 = INFINITY;
+                         int vs = 0;
+                         if (row < info.valid) {
+                             const int64_t rh = int64_t(perm[row]) * a.n_q_heads + h;
+                             l2 = a.lse[rh] * kLog2e;
+                             vs = pv.vis[info.base + row];
+                             a.delta[rh] = dl;
+                         }
+                         blk[row] = -l2;                             // (negated: where the key-side kernel's accumulators start)
+                         blk[64 + row] = -dl;
+                         blk[128 + row] = __int_as_float(vs);
+                         blk[192 + row] = 0.f;
+                     });
+        return;
     }
-    dl += __shfl_xor(dl, 1);
-    dl += __shfl_xor(dl, 2);
-    if (part != 0) return;
-    if (r < valid) {
-        l2 = lse[rh] * kLog2e;
-        vs = pv.vis[base + r];
-        delta_tok[rh] = dl;
-    }
-    float* blk = stats + (size_t(h) * pv.pack_tiles + tile) * 256;
-    blk[r] = -l2;                                                // (negated: where the key-side kernel's accumulators start)
-    blk[64 + r] = -dl;
-    blk[128 + r] = __int_as_float(vs);
-    blk[192 + r] = 0.f;
+    h -= a.n_q_heads;
+    const bool is_q = h < a.n_q_heads;
+    if (!is_q) h -= a.n_q_heads;
+    const bool is_v = !is_q && h >= a.n_kv_heads;
+    if (is_v) h -= a.n_kv_heads;
+    uint16_t* dst = (is_q ? a.qrows : is_v ? a.vrows : a.krows) + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
+    pack_rows<D>(dst, is_q ? a.q : is_v ? a.v : a.k, perm, info.valid, uint32_t(is_q ? a.n_q_heads : a.n_kv_heads) * D, uint32_t(h),
+                 [](int, uint32_t, const u32x4&) {});
 }
 
 // dK, dV: one workgroup per (128 keys of one stream of one sequence, KV head) -- the forward's work items read
@@ -743,29 +758,22 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
     if (workspace_bytes < need) return fail(ST_ERR_CAPACITY, "st_attn_prefill_bwd: workspace has %zu bytes, needs %zu", workspace_bytes, need);
     if (scale <= 0.f) scale = 1.f / sqrtf(float(head_dim));
     const int64_t qblocks = int64_t(plan->m_max) * n_q_heads, kblocks = int64_t(plan->m_max) * n_kv_heads;
-    if (qblocks > 0x7fffffff || kblocks * 8 > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_prefill_bwd: grid too large");
+    const int64_t pack_blocks = int64_t(plan->pack_tiles) * 2 * (n_q_heads + n_kv_heads);
+    if (qblocks > 0x7fffffff || kblocks * 8 > 0x7fffffff || pack_blocks > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_prefill_bwd: grid too large");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     ST_HIP(plan->wait_built(s));
     const PlanView pv = plan->view();
     float* delta = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + L.delta);
-    // bf16: every operand gathered once into 64-row row tiles, then two MFMA kernels
+    // bf16: every operand gathered once into 64-row row tiles (one kernel), then two MFMA kernels
     auto run_mfma = [&](auto dtag) -> st_status {
         constexpr int HD = decltype(dtag)::value;
         unsigned char* w = static_cast<unsigned char*>(workspace);
         auto at = [&](size_t o) { return reinterpret_cast<uint16_t*>(w + o); };
         float* stats = reinterpret_cast<float*>(w + L.stats);
         float* partial = reinterpret_cast<float*>(w + L.partial);
-        const unsigned kv_tiles = unsigned(plan->pack_tiles) * n_kv_heads, q_tiles = unsigned(plan->pack_tiles) * n_q_heads;
-        hipLaunchKernelGGL((tile_pack_kernel<HD>), dim3(kv_tiles), dim3(256), 0, s, at(L.krows), (uint16_t*)nullptr, (const uint16_t*)k,
-                           (const uint16_t*)k, pv, n_kv_heads);
-        hipLaunchKernelGGL((tile_pack_kernel<HD>), dim3(kv_tiles), dim3(256), 0, s, at(L.vrows), (uint16_t*)nullptr, (const uint16_t*)v,
-                           (const uint16_t*)v, pv, n_kv_heads);
-        hipLaunchKernelGGL((tile_pack_kernel<HD>), dim3(q_tiles), dim3(256), 0, s, at(L.qrows), (uint16_t*)nullptr, (const uint16_t*)q,
-                           (const uint16_t*)q, pv, n_q_heads);
-        hipLaunchKernelGGL((tile_pack_kernel<HD>), dim3(q_tiles), dim3(256), 0, s, at(L.dorows), (uint16_t*)nullptr, (const uint16_t*)d_out,
-                           (const uint16_t*)d_out, pv, n_q_heads);
-        hipLaunchKernelGGL((bwd_rowstats_kernel<HD>), dim3(q_tiles), dim3(256), 0, s, stats, delta, (const uint16_t*)d_out,
-                           (const uint16_t*)out, lse, pv, n_q_heads);
+        const BwdPackArgs pack{(const uint16_t*)d_out, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)out, lse,
+                               at(L.dorows), at(L.qrows), at(L.krows), at(L.vrows), stats, delta, n_q_heads, n_kv_heads};
+        hipLaunchKernelGGL((bwd_pack_kernel<HD>), dim3((unsigned)pack_blocks), dim3(256), 0, s, pack, pv);
         const size_t smem_q = sizeof(BwdDqSmem<HD>), smem_k = sizeof(BwdDkvSmem<HD>);
         ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_dq_mfma_kernel<HD>), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem_q)));
         ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_dkv_mfma_kernel<HD>), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem_k)));

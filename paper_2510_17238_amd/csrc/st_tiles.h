@@ -4,9 +4,8 @@
 // one tensor as a "row tile" ([64 rows][D], rows parked in the order the first-type MFMA wants, 16-byte chunks
 // XOR-swizzled) and the rows of a second tensor as a "transposed tile" ([D][64 rows], swizzled), 16 KB each at
 // D = 128, contiguous -- so that a kernel streams tiles with plain linear copies and needs no per-row token lookup
-// and no transpose in its inner loop.  Either destination may be null (that half is skipped).  The forward packs
-// (K rows, V^T); the backward packs row tiles only (K, V, Q, dO) and takes its transposed operands out of them with
-// transposing LDS reads (TrOffsets below).
+// and no transpose in its inner loop.  The forward packs (K rows, V^T); the backward packs row tiles only (K, V, Q, dO:
+// bwd_pack_kernel) and takes its transposed operands out of them with transposing LDS reads (TrOffsets below).
 #pragma once
 #include "st_plan.h"
 
@@ -126,13 +125,35 @@ __device__ __forceinline__ WorkItem item_part(WorkItem it, const PlanView& pv, i
 // first MFMA each half-wave holds 8 CONSECUTIVE keys per 16-key step
 __device__ __forceinline__ int swap23(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 
+// The rows of one tile and head, gathered by a workgroup of 256 threads into a row tile: parked in the row order the first MFMA
+// wants (bits 2 and 3 of the row swapped), with the chunk swizzle of the LDS tile; rows past the end of the stream are zero
+// (they are masked, but must be finite).  each(row, element offset of the piece, piece) sees every 16-byte piece on the way:
+// D / 8 neighbouring lanes hold a row.
+template <int D, typename Each>
+__device__ __forceinline__ void pack_rows(uint16_t* dst, const uint16_t* src, const int32_t* perm, int valid, uint32_t row_stride,
+                                          uint32_t head, Each each) {
+    constexpr int CH = D / 8;
+#pragma unroll
+    for (int u = 0; u < kTileN * CH / 256; ++u) {
+        const int c = int(threadIdx.x) + 256 * u;
+        const int row = c / CH, ch = c % CH;
+        u32x4 val = {0u, 0u, 0u, 0u};
+        uint32_t at = 0;
+        if (row < valid) {
+            at = uint32_t(perm[row]) * row_stride + head * D + ch * 8;
+            val = *reinterpret_cast<const u32x4*>(src + at);
+        }
+        each(row, at, val);
+        const int lr = swap23(row);                                    // row position in the tile
+        *reinterpret_cast<u32x4*>(dst + lr * D + (ch ^ swizzle_key<2 * D>(lr)) * 8) = val;
+    }
+}
+
 template <int D>
 __global__ __launch_bounds__(256) void tile_pack_kernel(uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
                                                            const uint16_t* __restrict__ k,
                                                            const uint16_t* __restrict__ v, PlanView pv,
                                                            int n_kv_heads) {
-    constexpr int KCH = D / 8;
-    constexpr int K_PER_THREAD = kTileN * KCH / 256;
     const int tile = blockIdx.x / n_kv_heads;
     const int h = blockIdx.x % n_kv_heads;
     const TileInfo info = pv.tiles[tile];
@@ -142,22 +163,10 @@ __global__ __launch_bounds__(256) void tile_pack_kernel(uint16_t* __restrict__ k
     const uint32_t row_stride = uint32_t(n_kv_heads) * D;
     uint16_t* kdst = kc + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
     uint16_t* vdst = vc + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
-    // K rows, parked in the row order the first MFMA wants (bits 2 and 3 of the row swapped) and with
-    // the chunk swizzle of the LDS tile; rows past the end of the stream are zero (they are masked,
-    // but must be finite)
-    if (kc != nullptr)
-#pragma unroll
-    for (int u = 0; u < K_PER_THREAD; ++u) {
-        const int c = tid + 256 * u;
-        const int row = c / KCH, ch = c % KCH;
-        u32x4 val = {0u, 0u, 0u, 0u};
-        if (row < valid) val = *reinterpret_cast<const u32x4*>(k + (uint32_t(pv.perm[base + row]) * row_stride + uint32_t(h) * D + ch * 8));
-        const int lr = swap23(row);                                    // row position in the tile
-        *reinterpret_cast<u32x4*>(kdst + lr * D + (ch ^ swizzle_key<2 * D>(lr)) * 8) = val;
-    }
+    pack_rows<D>(kdst, k, pv.perm + base, valid, row_stride, uint32_t(h), [](int, uint32_t, const u32x4&) {});
     // V: 8 keys x 8 d per thread (16-byte loads), transposed in registers to 8 d x 8 keys (16-byte stores)
     const int kvb = tid & 7, dq = tid >> 3;
-    if (vc != nullptr && dq < D / 8) {
+    if (dq < D / 8) {
         u32x4 vreg[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
