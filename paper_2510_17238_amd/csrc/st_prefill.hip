@@ -187,7 +187,8 @@ struct PipeSmem {
 //   * The queries are multiplied by scale * log2(e) once, when they are loaded (and rounded to bf16 again), and
 //     the first matrix instruction of a score block starts from -m_ref instead of 0: a score leaves the matrix
 //     pipe as the base-2 exponent of its probability relative to the row's reference exponent m_ref -- no
-//     multiply-add per element.  Between two tiles the -m_ref values are parked in the last score block.
+//     multiply-add per element.  (NH = 1 keeps -m_ref in registers of its own,
+//     NH = 2 parks it in the last score block between two tiles.)
 //   * No running maximum.  m_ref is the row maximum of the FIRST tile (every row sees column 0 of its own stream,
 //     so it is finite); bf16 and fp32 have the same exponent range, so probabilities may grow far beyond 1 without
 //     any loss.  Only when a tile's row sum exceeds 2^kRiseLog2 (or is not finite) -- seen right after the
@@ -293,32 +294,49 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
         issue_v(1, 1);
     }
 
+    // The queries times scale * log2(e), rounded to bf16 once: scores in base-2 exponent units straight out of the matrix pipe.
+    // Rotated ones (ROPE) take the factor with (cos, sin); two elements at a time, as they lie in a register (one by one the
+    // rotation was a sixth of all vector instructions on sequences of a few hundred tokens: 96 of 60 to 900 tokens 493 -> 487 us, with
+    // what the loop says of neg_ref below).
+    auto element = [](uint32_t word, int e) { return __builtin_bit_cast(float, e == 0 ? word << 16 : word & 0xffff0000u); };
+    auto rounded = [](float lo, float hi) {
+        bf16x2 r;
+        r[0] = (__bf16)lo;
+        r[1] = (__bf16)hi;
+        return __builtin_bit_cast(uint32_t, r);
+    };
     if (ROPE) {
         const f32x4* tab4 = reinterpret_cast<const f32x4*>(rope_tab);
 #pragma unroll
         for (int j = 0; j < KS / 2; ++j) {
             f32x4 cs4[4];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) cs4[w] = tab4[rope_table_at<D>(size_t(it.tile_a0) * kTileN + my_row, j, w, hg)];
+            for (int w = 0; w < 4; ++w) cs4[w] = tab4[rope_table_at<D>(size_t(it.tile_a0) * kTileN + my_row, j, w, hg)] * scale_log2;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float cs = cs4[e / 2][2 * (e % 2)], sn = cs4[e / 2][2 * (e % 2) + 1];
+            for (int h = 0; h < NH; ++h) {
+                u32x4 lo = __builtin_bit_cast(u32x4, qf[h][j]), hi = __builtin_bit_cast(u32x4, qf[h][j + KS / 2]);
 #pragma unroll
-                for (int h = 0; h < NH; ++h) {
-                    const float x = float(qf[h][j][e]), y = float(qf[h][j + KS / 2][e]);
-                    qf[h][j][e] = (__bf16)(x * cs - y * sn);
-                    qf[h][j + KS / 2][e] = (__bf16)(y * cs + x * sn);
+                for (int w = 0; w < 4; ++w) {                         // pairs 2 w and 2 w + 1
+                    const float x0 = element(lo[w], 0), x1 = element(lo[w], 1), y0 = element(hi[w], 0), y1 = element(hi[w], 1);
+                    const f32x4 r = cs4[w];
+                    lo[w] = rounded(x0 * r[0] - y0 * r[1], x1 * r[2] - y1 * r[3]);
+                    hi[w] = rounded(y0 * r[0] + x0 * r[1], y1 * r[2] + x1 * r[3]);
                 }
+                qf[h][j] = __builtin_bit_cast(bf16x8, lo);
+                qf[h][j + KS / 2] = __builtin_bit_cast(bf16x8, hi);
             }
         }
+    } else {
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+            for (int j = 0; j < KS; ++j) {
+                u32x4 x = __builtin_bit_cast(u32x4, qf[h][j]);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) x[w] = rounded(element(x[w], 0) * scale_log2, element(x[w], 1) * scale_log2);
+                qf[h][j] = __builtin_bit_cast(bf16x8, x);
+            }
     }
-    // scores in base-2 exponent units straight out of the matrix pipe
-#pragma unroll
-    for (int h = 0; h < NH; ++h)
-#pragma unroll
-        for (int j = 0; j < KS; ++j)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) qf[h][j][e] = (__bf16)(float(qf[h][j][e]) * scale_log2);
 
     f32x16 o_acc[NH][DB];
 #pragma unroll
@@ -361,12 +379,12 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     auto ld_k = [&](const uint16_t* kb, int f) { return *reinterpret_cast<const bf16x8*>(kb + 32 * (f % SB) * D + koff[f / SB]); };
     auto ld_v = [&](const uint16_t* vb, int f) { return *reinterpret_cast<const bf16x8*>(vb + 32 * (f % DB) * kTileN + voff[f / DB]); };
 
-    struct TileInfo { bool partial; int limit; int c0; };
+    struct TileInfo { bool partial; int room; };          // room: columns the row sees from this lane's first one of the tile on
     auto tile_info = [&](int ti) {
         const bool in_a = ti < it.a_total;
         const int kt = in_a ? ti : ti - it.a_total;
         const bool partial = kt >= (in_a ? it.a_full : it.b_full) || (kt + 1) * kTileN > (in_a ? it.n_stream : it.n_src);
-        return TileInfo{partial, in_a ? my_row + 1 : my_vis, kt * kTileN + 8 * hg};
+        return TileInfo{partial, (in_a ? my_row + 1 : my_vis) - (kt * kTileN + 8 * hg)};
     };
     auto max_with_partner = [&](float x) {
         float a = x, b = x;
@@ -396,14 +414,21 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     // the columns of a partial tile that a row may not see: exponent -inf, probability 0
     // lane (n, hg), block sb, register i  <->  key column kt*64 + 32 sb + 16 (i/8) + 8 hg + i%8
     auto mask_tile = [&](f32x16 (&sv)[NH][SB], const TileInfo& ti) {
+        uint32_t seen[SB];                               // bit i: register i of the block
+        const uint32_t none = 0xff800000u;               // -inf
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb)
+            seen[sb] = ((1u << min(max(ti.room - 32 * sb, 0), 8)) - 1u) | ((1u << min(max(ti.room - 32 * sb - 16, 0), 8)) - 1u) << 8;
 #pragma unroll
         for (int h = 0; h < NH; ++h)
 #pragma unroll
             for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int col = ti.c0 + 32 * sb + 16 * (i >> 3) + (i & 7);
-                    sv[h][sb][i] = col < ti.limit ? sv[h][sb][i] : -INFINITY;
+                    // (by bits: a compare and the select that reads it have to be kept apart by a wait state)
+                    const uint32_t keep = uint32_t(__builtin_amdgcn_sbfe(int(seen[sb]), i, 1));
+                    const float x = sv[h][sb][i];
+                    sv[h][sb][i] = __builtin_bit_cast(float, (keep & __builtin_bit_cast(uint32_t, x)) | (~keep & none));
                 }
     };
     // row maximum (both lanes of the row) of a tile's exponents
@@ -417,11 +442,14 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     };
 
     // ---- prologue: tile 0 gives every row its reference exponent ----
-    // sv: the exponents of the tile whose probabilities are formed next (vector registers); s_next: the score blocks
-    // the matrix pipe is filling.  Between two tiles the LAST block of s_next holds -m_ref in all its 16 registers:
-    // the first matrix instruction of every score block starts from it (the last block in place), so a score leaves
-    // the pipe as s - m_ref.
-    f32x16 sv[NH][SB], s_next[NH][SB];
+    // sv: the exponents of the tile whose probabilities are formed next; s_next: the score blocks the matrix pipe is
+    // filling.  The first matrix instruction of every score block starts from -m_ref, so a score leaves the pipe as
+    // s - m_ref.
+    //   NH = 1  neg_ref holds -m_ref for good; the scores are copied, two per instruction, beside the matrix instructions of
+    //           phase Y, which has no other vector work (4 x 4K tokens 273 -> 271.7 us: the chip's power is the limit there).
+    //   NH = 2  s_next lives in accumulation registers; between two tiles its LAST block holds -m_ref in all its 16 registers and
+    //           starts in place.
+    f32x16 sv[NH][SB], s_next[NH][SB], neg_ref;
     wait_vmcnt<(STAGES == 3 ? 4 : 2) * NL>();            // K0 has landed
     __syncthreads();
     {
@@ -454,11 +482,14 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
 #pragma unroll
                 for (int i = 0; i < 16; ++i) sv[h][sb][i] -= m_ref[h];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s_next[h][SB - 1][i] = -m_ref[h];
+            for (int i = 0; i < 16; ++i) {
+                if constexpr (NH == 2) s_next[h][SB - 1][i] = -m_ref[h];
+                else neg_ref[i] = -m_ref[h];
+            }
         }
     }
 
-    bf16x8 pb[NH][SB][2];                                // probabilities of the current tile, as the second product's operand
+    u32x4 pw[NH][SB][2];                                 // probabilities of the current tile (bf16 pairs), as the second product's operand
     float psum[NH];
     // slot m of NH SB KS: PER elements of the probabilities of the tile in sv, in the order (head, block, register)
     // (the two-head form sums the probabilities as the second product will see them, rounded to bf16, two per
@@ -479,8 +510,9 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
             p2[1] = (__bf16)pr1;
             if constexpr (NH == 2) psum[hh] = __builtin_amdgcn_fdot2_f32_bf16(p2, ones2, psum[hh], false);
             else psum[hh] += pr0 + pr1;
-            pb[hh][sb2][i >> 3][i & 7] = p2[0];
-            pb[hh][sb2][i >> 3][(i & 7) + 1] = p2[1];
+            uint32_t word = __builtin_bit_cast(uint32_t, p2);
+            if constexpr (NH == 1) asm volatile("" : "+v"(word));   // HERE, not behind the check of the row sums (NH = 2: 3 % slower)
+            pw[hh][sb2][i >> 3][(i & 7) / 2] = word;
         }
     };
     // A row sum beyond 2^kRiseLog2 (or not finite) means the tile's exponents outgrew the reference: move it to the
@@ -507,10 +539,11 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
 #pragma unroll
                 for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const float pr = __builtin_amdgcn_exp2f(sv[h][sb][i] - shift);
-                        psum[h] += pr;
-                        pb[h][sb][i >> 3][i & 7] = (__bf16)pr;
+                    for (int i = 0; i < 16; i += 2) {
+                        const float pr0 = __builtin_amdgcn_exp2f(sv[h][sb][i] - shift), pr1 = __builtin_amdgcn_exp2f(sv[h][sb][i + 1] - shift);
+                        psum[h] += pr0;
+                        psum[h] += pr1;
+                        pw[h][sb][i >> 3][(i & 7) / 2] = rounded(pr0, pr1);
                     }
                 l_run[h] *= alpha;
                 rescale_acc(h, alpha);
@@ -559,8 +592,8 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
                 const int sb = f % SB, j = f / SB;
 #pragma unroll
                 for (int h = 0; h < NH; ++h) {
-                    // k-step 0 starts from -m_ref, parked in the last block (which starts in place)
-                    s_next[h][sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f], qf[h][j], j == 0 ? s_next[h][SB - 1] : s_next[h][sb], 0, 0, 0);
+                    // k-step 0 starts from -m_ref
+                    s_next[h][sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f], qf[h][j], j > 0 ? s_next[h][sb] : NH == 2 ? s_next[h][SB - 1] : neg_ref, 0, 0, 0);
                     // the copies of this round go out behind the first matrix instructions
                     if (f * NH + h == 0) {
                         if (STAGES == 3) async_copy_rows<NL>(copy_k, lane_off, copy_k_lds);
@@ -577,7 +610,7 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
         }
         const bool moved = check_rise();
 
-        // ---- phase Y: O^T += V^T P^T of tile ti  |  the exponents of tile ti+1 leave the accumulation registers ----
+        // ---- phase Y: O^T += V^T P^T of tile ti  |  the exponents of tile ti+1 leave the registers of the scores ----
         // slot m of NH DB SB 2: PER fresh exponents, in the order (block, head, register); the last block is left
         // holding -m_ref for the next round
         float neg[NH];
@@ -585,27 +618,28 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
         for (int h = 0; h < NH; ++h) neg[h] = -m_ref[h];
         auto move_slot = [&](int m) {
 #pragma unroll
-            for (int u = 0; u < PER; ++u) {
+            for (int u = 0; u < PER; u += 2) {
                 const int e = m * PER + u;
                 const int sb2 = e / (NH * 16), hh = (e / 16) % NH, i = e % 16;
-                // ONE move out of the accumulation registers, HERE (a plain copy would be sunk to its use, into
-                // the crowded phase X); the producing matrix instruction retired at least three of them ago
-                float x;
+                // ONE move per register, HERE (a plain copy would be sunk to its use, into the crowded phase X); the producing
+                // matrix instruction retired at least two (NH = 1) or three of them ago
                 if constexpr (NH == 2) {
-                    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(s_next[hh][sb2][i]));
-                } else {
-                    x = s_next[hh][sb2][i];
-                    asm volatile("" : "+v"(x));
-                }
-                sv[hh][sb2][i] = x;
-                if (sb2 == SB - 1) {
-                    if constexpr (NH == 2) {
-                        float t;
-                        asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(t) : "v"(neg[hh]));
-                        s_next[hh][sb2][i] = t;
-                    } else {
-                        s_next[hh][sb2][i] = neg[hh];
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        float x;
+                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(s_next[hh][sb2][i + w]));
+                        sv[hh][sb2][i + w] = x;
+                        if (sb2 == SB - 1) {
+                            float t;
+                            asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(t) : "v"(neg[hh]));
+                            s_next[hh][sb2][i + w] = t;
+                        }
                     }
+                } else {
+                    f32x2 x;
+                    asm volatile("v_mov_b64 %0, %1" : "=v"(x) : "v"(f32x2{s_next[hh][sb2][i], s_next[hh][sb2][i + 1]}));
+                    sv[hh][sb2][i] = x[0];
+                    sv[hh][sb2][i + 1] = x[1];
                 }
             }
         };
@@ -621,7 +655,8 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
                 const int db = f % DB, st = f / DB;              // keys 16 st .. 16 st + 15
 #pragma unroll
                 for (int h = 0; h < NH; ++h) {
-                    o_acc[h][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f], pb[h][st >> 1][st & 1], o_acc[h][db], 0, 0, 0);
+                    o_acc[h][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f], __builtin_bit_cast(bf16x8, pw[h][st >> 1][st & 1]), o_acc[h][db], 0, 0, 0);
+                    if (NH == 1 && f == 0) __builtin_amdgcn_sched_barrier(0);        // (two matrix instructions behind the last one of block 0)
                     move_slot(f * NH + h);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -634,6 +669,10 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
                 for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) sv[h][sb][i] -= late[h];
+            if constexpr (NH == 1) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) neg_ref[i] = -m_ref[0];
+            }
         }
         const TileInfo fresh = tile_info(ti + 1);
         if (fresh.partial) mask_tile(sv, fresh);
@@ -659,7 +698,7 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
             const int db = f % DB, st = f / DB;
 #pragma unroll
             for (int h = 0; h < NH; ++h)
-                o_acc[h][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f], pb[h][st >> 1][st & 1], o_acc[h][db], 0, 0, 0);
+                o_acc[h][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f], __builtin_bit_cast(bf16x8, pw[h][st >> 1][st & 1]), o_acc[h][db], 0, 0, 0);
         }
     }
 
