@@ -380,7 +380,8 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void bwd_dq_f32_kernel(float* __
 // --------------------------------------------------------------------------
 // Backward, key side: dV_j = sum_i P_ij dO_i, dK_j = scale sum_i dS_ij Q_i over the query rows i that see key j, summed
 // over the query heads of the KV head.  A workgroup owns 32 keys of one KV head; the (32-row query block, query head)
-// pairs are dealt out to its four waves.  Products not transposed (S = Q K^T): a lane owns a key, rows run along the
+// pairs are dealt out to its four waves.  parts > 1: the query heads of a KV head are dealt out to `parts` workgroups (a divisor
+// of the group), which leave their sums in `partial` ([2: dK, dV][parts][N][n_kv_heads][D]) for bwd_dkv_sum_f32_kernel.  Products not transposed (S = Q K^T): a lane owns a key, rows run along the
 // accumulator registers.
 // --------------------------------------------------------------------------
 template <int D>
@@ -396,16 +397,17 @@ __global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* _
                                                                         const float* __restrict__ delta, const float* __restrict__ d_out,
                                                                         const float* __restrict__ q, const float* __restrict__ k,
                                                                         const float* __restrict__ v, const float* __restrict__ lse,
-                                                                        PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
+                                                                        PlanView pv, int n_q_heads, int n_kv_heads, float scale,
+                                                                        int parts, float* __restrict__ partial, int64_t partial_stride) {
     constexpr int JJ = D / 8, DB = D / 32;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     DkvF32Smem<D>& sm = *reinterpret_cast<DkvF32Smem<D>*>(smem_raw);
-    const unsigned per_item = unsigned(n_kv_heads) * (kTileM / kF32Rows);
+    const unsigned per_item = unsigned(n_kv_heads) * (kTileM / kF32Rows) * unsigned(parts);
     // (early keys are seen by the most rows: the table, sorted by the forward's cost, is walked backwards)
     const int rank = pv.m_max - 1 - int(blockIdx.x / per_item);
     const unsigned rest = blockIdx.x % per_item;
-    const int hk = int(rest % unsigned(n_kv_heads)), sub = int(rest / unsigned(n_kv_heads));
-    const int group = n_q_heads / n_kv_heads;
+    const int hk = int(rest % unsigned(n_kv_heads)), part_of = int(rest / unsigned(n_kv_heads)) % parts, sub = int(rest / (unsigned(n_kv_heads) * unsigned(parts)));
+    const int group = n_q_heads / n_kv_heads / parts, hq0 = (hk * parts + part_of) * group;      // this workgroup's query heads
     const WorkItem it = pv.sorted[rank];
     const OwnRows own = own_rows(it, sub);
     if (own.count <= 0) return;
@@ -430,10 +432,21 @@ __global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* _
     const int n_rsn = src ? pv.cu[it.seq + 1] - pv.cu[it.seq] - S : it.n_stream;
     int rsn_first = 0;
     if (src) {
-        int lo = 0, hi = n_rsn;
+        // searched by the whole wave: every lane tests the end of one 64th of the range
+        int lo = 0, hi = n_rsn;                                 // the answer lies in [lo, hi]; hi == n_rsn: no such row
         while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (pv.vis[rsn_base + mid] > own.first) hi = mid; else lo = mid + 1;
+            const int span = hi - lo, step = (span + 63) >> 6;
+            const int last = min(span - 1, lane * step + step - 1);                              // end of this lane's piece
+            const unsigned long long seen = __ballot(pv.vis[rsn_base + lo + last] > own.first);  // (monotone along the lanes)
+            if (seen == 0ull) {
+                lo = hi;
+            } else {
+                const int first = __ffsll((long long)seen) - 1;
+                hi = lo + min(span - 1, first * step + step - 1);                                // this row exceeds it ...
+                lo = lo + first * step;                                                          // ... and none before this piece does
+            }
+            lo = __builtin_amdgcn_readfirstlane(lo);
+            hi = __builtin_amdgcn_readfirstlane(hi);
         }
         rsn_first = lo;
     }
@@ -447,7 +460,7 @@ __global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* _
         x = min(x, n_iter - 1);
         const int t = x / group;
         Iter r;
-        r.hq = hk * group + x % group;
+        r.hq = hq0 + x % group;
         r.rs = t >= blocks_a;                                    // (rows of the other stream: visible by their source count)
         r.base = r.rs ? rsn_base : it.a_base;
         r.row0 = r.rs ? rsn_first + (t - blocks_a) * kF32Rows : own.first + t * kF32Rows;
@@ -538,7 +551,7 @@ __global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* _
         park<D>(sm.merge.o[wave], which == 0 ? dv_acc : dk_acc, n, hg);
         __syncthreads();
         if (row < own.count) {
-            float* dst = (which == 0 ? dv : dk) + keyhead * D;
+            float* dst = (parts > 1 ? partial + ((which == 0 ? parts : 0) + part_of) * partial_stride : which == 0 ? dv : dk) + keyhead * D;
 #pragma unroll
             for (int d = 4 * part; d < D; d += 32) {
                 f32x4 a = *reinterpret_cast<const f32x4*>(&sm.merge.o[0][row][d]);
@@ -548,6 +561,17 @@ __global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* _
             }
         }
     }
+}
+
+// dK (blockIdx.y = 0) or dV (1) from the partial sums of the key-side kernel, in a fixed order; n4 groups of four elements
+__global__ __launch_bounds__(256) void bwd_dkv_sum_f32_kernel(float* __restrict__ dk, float* __restrict__ dv, const float* __restrict__ partial,
+                                                              int64_t partial_stride, int parts, int64_t n4) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n4) return;
+    const float* p = partial + blockIdx.y * parts * partial_stride + i * 4;
+    f32x4 a = *reinterpret_cast<const f32x4*>(p);
+    for (int x = 1; x < parts; ++x) a += *reinterpret_cast<const f32x4*>(p + x * partial_stride);
+    *reinterpret_cast<f32x4*>((blockIdx.y == 0 ? dk : dv) + i * 4) = a;
 }
 
 // ---- launches (arguments have been checked by the callers) ----
@@ -575,8 +599,9 @@ st_status launch_prefill_f32(float* out, float* lse, const float* q, const float
 
 st_status launch_bwd_f32(float* dq, float* dk, float* dv, float* delta, const float* d_out, const float* q, const float* k, const float* v,
                          const float* out, const float* lse, const PlanView& pv, int n_q_heads, int n_kv_heads, int head_dim, float scale,
-                         hipStream_t s) {
-    const int64_t qblocks = int64_t(pv.m_max) * n_q_heads * (kTileM / kF32Rows), kblocks = int64_t(pv.m_max) * n_kv_heads * (kTileM / kF32Rows);
+                         int64_t n_tokens, int parts, float* partial, hipStream_t s) {
+    const int64_t qblocks = int64_t(pv.m_max) * n_q_heads * (kTileM / kF32Rows), kblocks = int64_t(pv.m_max) * n_kv_heads * parts * (kTileM / kF32Rows);
+    const int64_t partial_stride = n_tokens * n_kv_heads * head_dim;
     if (qblocks > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_prefill_bwd: grid too large");
     auto run = [&](auto dtag) -> st_status {
         constexpr int D = decltype(dtag)::value;
@@ -587,7 +612,11 @@ st_status launch_bwd_f32(float* dq, float* dk, float* dv, float* delta, const fl
         hipLaunchKernelGGL((bwd_dq_f32_kernel<D>), dim3((unsigned)qblocks), dim3(64 * kF32Waves), sizeof(DqF32Smem<D>), s, dq, delta, d_out, q, k, v,
                            out, lse, pv, n_q_heads, n_kv_heads, scale);
         hipLaunchKernelGGL((bwd_dkv_f32_kernel<D>), dim3((unsigned)kblocks), dim3(64 * kF32Waves), sizeof(DkvF32Smem<D>), s, dk, dv, delta, d_out, q,
-                           k, v, lse, pv, n_q_heads, n_kv_heads, scale);
+                           k, v, lse, pv, n_q_heads, n_kv_heads, scale, parts, partial, partial_stride);
+        if (parts > 1) {
+            const int64_t n4 = partial_stride / 4;
+            hipLaunchKernelGGL(bwd_dkv_sum_f32_kernel, dim3((unsigned)((n4 + 255) / 256), 2), dim3(256), 0, s, dk, dv, partial, partial_stride, parts, n4);
+        }
         ST_LAUNCH_CHECK("bwd_dq_f32_kernel / bwd_dkv_f32_kernel");
         return ST_OK;
     };

@@ -52,7 +52,7 @@ st_status launch_prefill_f32(float* out, float* lse, const float* q, const float
                              int n_kv_heads, int head_dim, float scale, hipStream_t s);
 st_status launch_bwd_f32(float* dq, float* dk, float* dv, float* delta, const float* d_out, const float* q, const float* k, const float* v,
                          const float* out, const float* lse, const PlanView& pv, int n_q_heads, int n_kv_heads, int head_dim, float scale,
-                         hipStream_t s);
+                         int64_t n_tokens, int parts, float* partial, hipStream_t s);
 
 }  // namespace st
 

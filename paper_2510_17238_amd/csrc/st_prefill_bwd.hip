@@ -704,7 +704,19 @@ int dkv_parts(const st_plan* plan, int n_q_heads, int n_kv_heads, int head_dim) 
         if (group % p == 0) parts = p;
     return parts;
 }
-// workspace of the bf16 path: delta (token order) | row statistics | K rows | V rows | Q rows | dO rows | partial dK, dV
+// The same for the fp32 key side, whose workgroups own 32 keys and keep a compute unit to themselves: parts only while there is
+// less than one workgroup per unit of the chip, at whatever length (a wave's chain of (row block, head) pairs is what a small
+// problem takes).  Whole training steps: 3 x 100 to 200 tokens, 8 / 4 heads of 128 dims (80 workgroups) 110 -> 90 us; 4 x 60 to
+// 120, 32 / 8 of 64 (152) 72 -> 64; but 2 x 900, 16 / 8 of 128 (480) 432 -> 438.
+int dkv_parts_f32(const st_plan* plan, int n_q_heads, int n_kv_heads) {
+    const int group = n_q_heads / n_kv_heads;
+    const int64_t workgroups = (plan->n_tokens / 32 + 2 * int64_t(plan->batch)) * n_kv_heads;
+    int parts = 1;
+    for (int p = 2; p <= std::min(group, 8) && workgroups * parts < 256; ++p)
+        if (group % p == 0) parts = p;
+    return parts;
+}
+// workspace of the fp32 path: delta | partial dK, dV; of the bf16 path: delta (token order) | row statistics | K rows | V rows | Q rows | dO rows | partial dK, dV
 struct BwdLayout {
     size_t delta, stats, krows, vrows, qrows, dorows, partial, total;
     int parts;
@@ -723,10 +735,10 @@ BwdLayout bwd_layout(const st_plan* plan, int n_q_heads, int n_kv_heads, int hea
         L.vrows = take(kvt);
         L.qrows = take(qt);
         L.dorows = take(qt);
-        L.parts = dkv_parts(plan, n_q_heads, n_kv_heads, head_dim);
-        L.partial_stride = plan->n_tokens * n_kv_heads * head_dim;
-        if (L.parts > 1) L.partial = take(2 * size_t(L.parts) * size_t(L.partial_stride) * sizeof(float));
     }
+    L.parts = dt == ST_BF16 ? dkv_parts(plan, n_q_heads, n_kv_heads, head_dim) : dkv_parts_f32(plan, n_q_heads, n_kv_heads);
+    L.partial_stride = plan->n_tokens * n_kv_heads * head_dim;
+    if (L.parts > 1) L.partial = take(2 * size_t(L.parts) * size_t(L.partial_stride) * sizeof(float));
     L.total = off + 256;
     return L;
 }
@@ -804,7 +816,8 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
     if (dt == ST_F32)
         r = launch_bwd_f32(static_cast<float*>(dq), static_cast<float*>(dk), static_cast<float*>(dv), delta, static_cast<const float*>(d_out),
                            static_cast<const float*>(q), static_cast<const float*>(k), static_cast<const float*>(v), static_cast<const float*>(out), lse,
-                           pv, n_q_heads, n_kv_heads, head_dim, scale, s);
+                           pv, n_q_heads, n_kv_heads, head_dim, scale, plan->n_tokens, L.parts,
+                           reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + L.partial), s);
     else r = head_dim == 64 ? run_mfma(std::integral_constant<int, 64>{}) : run_mfma(std::integral_constant<int, 128>{});
     if (r != ST_OK) return r;
     ST_LAUNCH_CHECK("st_attn_prefill_bwd kernels");

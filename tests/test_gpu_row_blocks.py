@@ -60,6 +60,7 @@ def _check(cfg, inputs, out, lse, grads, refs):
 
 @pytest.mark.parametrize("hq,hkv,d,layout", [(2, 1, 64, "interleaved"), (4, 4, 128, "grouped"), (8, 2, 128, "interleaved"), (8, 1, 64, "grouped")])
 def test_fp32_row_blocks(st, hq, hkv, d, layout):
+    """(The key side of the backward splits the query heads of a group two, one, four and eight ways here.)"""
     cfg = _case("f32", hq, hkv, d, layout)
     _check(cfg, *_forward_and_backward(st, cfg))
 
