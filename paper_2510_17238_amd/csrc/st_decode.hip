@@ -997,7 +997,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 3) void decode_split16_fp8_kernel
 // row, four head dims each, and fetch kMergeBatch partials per memory round trip; a row's partials are dealt out to `splits`
 // such groups of the workgroup (merge_splits), whose states meet in LDS.  Bound by the bytes of the partials and by the rate at
 // which workgroups start -- a wave per row, fetching 32 (8) partials whether there were that many or not, took 31 us for 16,384
-// rows of about 5 partials and 42 us for 65,536 rows of 1 to 3; so 12 and 27.
+// rows of about 5 partials and 42 us for 65,536 rows of 1 to 3; so 11 and 23.
 constexpr int kMergeThreads = 256, kMergeBatch = 8;
 template <int D>
 struct MergeRow {
