@@ -356,7 +356,7 @@ def bench_probes(st, torch):
     fsink = torch.zeros(4, dtype=torch.float32, device=dev)
     e0 = torch.cuda.Event(enable_timing=True); e1 = torch.cuda.Event(enable_timing=True)
     res = {}
-    # the decode kernel's launch on configs[2]: about 2,800 one-wave units of up to 1024 tokens x 4 KB;
+    # about the bytes of the decode kernel's launch on configs[2], in 2,816 waves of up to 16 steps;
     # and a launch four times as large
     for name, waves, steps in (("paged_read_decode_sized", 2816, 16), ("paged_read_large", 11264, 16)):
         for i in range(3):

@@ -770,7 +770,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(Decode
     }
 }
 
-// The one-wave kernel over 8-bit caches (E4M3 codes, one power-of-two fp32 scale per key row and per value
+// The 16-row kernel over 8-bit caches (E4M3 codes, one power-of-two fp32 scale per key row and per value
 // row): half the bytes per token.  Codes become bf16 in registers (exact: 3 mantissa bits) and feed the same
 // two bf16 products; the key scale multiplies the score (folded into the softmax scale factor), the value
 // scale multiplies the probability before the second product -- both exact, the scales being powers of two.
@@ -1621,7 +1621,7 @@ static st_status decode_dual_impl(void* out, float* lse, const void* q, const st
     a.row_blocks = 1;
     a.rope = rotate ? 1 : 0;
     a.freq = rotate ? make_rope_freq(theta_base, d) : RopeFreq{};
-    // long caches: the one-wave split kernel stores the token itself (one more slot per sequence and head); the
+    // long caches: the 16-row split kernel stores the token itself (one more slot per sequence and head); the
     // 32-row kernel does not, the token then goes in with a launch of its own
     const bool fuse_token = append && !fp8 && a.rows <= 16;
     a.append = fuse_token ? 1 : 0;
