@@ -108,6 +108,10 @@ struct SplitLds {
 };
 inline size_t split_lds_bytes(int rows, int d) { return sizeof(float) * size_t(kSplitWaves) * rows * (d + 2); }
 
+// A state (reference exponent m, sum l) without a finite score: nothing that its row sees -- or NaN scores alone, whose sum says
+// so and has to reach the row (its weight 2^(-inf) = 0 keeps a NaN one).
+__device__ __forceinline__ bool holds_nothing(float m, float l) { return m == -INFINITY && l == 0.f; }
+
 // log-sum-exp merge of the waves' states into the unit's partial result at row slot `slot`
 template <int D>
 __device__ __forceinline__ void merge_waves(const SplitLds<D>& sm, const DecodeArgs& a, int64_t slot) {
@@ -116,19 +120,18 @@ __device__ __forceinline__ void merge_waves(const SplitLds<D>& sm, const DecodeA
         float m_all = -INFINITY;
 #pragma unroll
         for (int w = 0; w < kSplitWaves; ++w) m_all = fmaxf(m_all, sm.m[w * a.rows + row]);
+        const float m_use = m_all == -INFINITY ? 0.f : m_all;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         float den = 0.f;
-        if (m_all != -INFINITY) {
 #pragma unroll
-            for (int w = 0; w < kSplitWaves; ++w) {
-                const float mw = sm.m[w * a.rows + row];
-                if (mw == -INFINITY) continue;                        // a wave that holds nothing for this row
-                const float wt = __builtin_amdgcn_exp2f(mw - m_all);
-                den = fmaf(wt, sm.l[w * a.rows + row], den);
-                const f32x4 o = *reinterpret_cast<const f32x4*>(sm.o + (w * a.rows + row) * D + d0);
+        for (int w = 0; w < kSplitWaves; ++w) {
+            const float mw = sm.m[w * a.rows + row], lw = sm.l[w * a.rows + row];
+            if (holds_nothing(mw, lw)) continue;
+            const float wt = __builtin_amdgcn_exp2f(mw - m_use);
+            den = fmaf(wt, lw, den);
+            const f32x4 o = *reinterpret_cast<const f32x4*>(sm.o + (w * a.rows + row) * D + d0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = fmaf(wt, o[i], acc[i]);
-            }
+            for (int i = 0; i < 4; ++i) acc[i] = fmaf(wt, o[i], acc[i]);
         }
         *reinterpret_cast<f32x4*>(a.part_o + (slot + row) * D + d0) = acc;
         if (d0 == 0) {
@@ -724,7 +727,10 @@ __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(Decode
         load(x, t);
         step(x, t);
     }
-    if (token_wave && !add && lane < a.rows) sm_m[W * a.rows + lane] = -INFINITY;
+    if (token_wave && !add && lane < a.rows) {
+        sm_m[W * a.rows + lane] = -INFINITY;
+        sm_l[W * a.rows + lane] = 0.f;
+    }
     float l_tot = st.l_run + __shfl_xor(st.l_run, 16);
     l_tot += __shfl_xor(l_tot, 32);
     if (valid_row) {
@@ -750,10 +756,10 @@ __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(Decode
         if (m_all != -INFINITY) {
 #pragma unroll
             for (int w = 0; w < WP; ++w) {
-                const float mw = sm_m[w * a.rows + row];
-                if (mw == -INFINITY) continue;                        // a state that holds nothing for this row
+                const float mw = sm_m[w * a.rows + row], lw = sm_l[w * a.rows + row];
+                if (holds_nothing(mw, lw)) continue;
                 const float wt = __builtin_amdgcn_exp2f(mw - m_all);
-                den = fmaf(wt, sm_l[w * a.rows + row], den);
+                den = fmaf(wt, lw, den);
                 const f32x4 o = *reinterpret_cast<const f32x4*>(sm_o + (w * a.rows + row) * D + d0);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[i] = fmaf(wt, o[i], acc[i]);
