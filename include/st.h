@@ -206,8 +206,11 @@ st_status st_plan_tile_classes(const st_plan* plan, int32_t seq, int32_t block,
  * fp32 accumulation and fp32 softmax state; the queries carry the softmax scale
  * (q * scale * log2(e), rounded to bf16 once more: a perturbation of q of at most
  * half a bf16 unit in the last place, the size of its own quantisation), the
- * probabilities are rounded to bf16 before the second product.  f32: plain fp32
- * arithmetic.
+ * probabilities are rounded to bf16 before the second product.  f32: fp32 products
+ * and sums.
+ * Inf and NaN: f32, a token's values reach the rows that see the token and no others.
+ * bf16: in a tile that a row sees in part, a non-finite v of a token that it does not
+ * see may reach it (0 x Inf is NaN); the same holds for the gradients.
  *
  * workspace (bf16 only): at least st_prefill_workspace_bytes(...) bytes, 256-byte
  * aligned; holds K and V^T regrouped into contiguous key tiles for the duration of
@@ -258,7 +261,8 @@ st_status st_attn_prefill_ids(void* out, float* lse, const void* q, const void* 
  * ST_BF16: products on the matrix cores (bf16 operands -- P and dS are rounded to bf16 before the
  * second products, as the forward rounds P -- fp32 accumulation); every operand is first gathered
  * into 64-row tiles in the workspace, which therefore holds about 1.1x the bytes of q, k, v, d_out.
- * ST_F32: fp32 products and sums (the matrix cores' fp32 instructions).
+ * ST_F32: fp32 products and sums (the matrix cores' fp32 instructions); Inf and NaN stay with the
+ * pairs that the mask allows, as in the forward.
  * workspace: at least st_prefill_bwd_workspace_bytes(plan, n_q_heads, n_kv_heads, head_dim, dt)
  * bytes, 256-byte aligned.  Errors as for st_attn_prefill.
  * ---------------------------------------------------------------------- */

@@ -64,6 +64,61 @@ __device__ __forceinline__ void park(float (&rows)[kF32Rows][D + 4], const f32x1
                 f32x4{acc[db][4 * q4], acc[db][4 * q4 + 1], acc[db][4 * q4 + 2], acc[db][4 * q4 + 3]};
 }
 
+// Masked pairs and values that are not finite.  A matrix instruction multiplies an operand row with the weights of all 32 columns of
+// the block, 0 for the pairs that the mask forbids, and 0 x Inf is NaN: a bad value of a token would reach rows that do not see
+// it.  A NaN stays, so the kernels walk their blocks without a look at this and check what comes out: a workgroup whose result
+// is not finite throws it away and walks again with care -- in blocks with masked pairs the operand rows that hold such
+// a value leave the product and are added to the columns that see them alone.  (Looking at the operands in every such block cost 4 %
+// of the forward and 4 to 14 % of the gradients, most of it in registers; looking at the result costs 1 %, 0.2 us of the
+// smallest forward.)
+
+// (z stays 0 as long as what is folded into it is finite: 0 x Inf = 0 x NaN = NaN)
+__device__ __forceinline__ float fold_finite(float z, const f32x4& x) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z = fmaf(x[e], 0.f, z);
+    return z;
+}
+// bad[w], written by wave w before a barrier: does any wave report something?
+__device__ __forceinline__ bool any_wave(const int (&bad)[kF32Waves]) {
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) any |= bad[w];
+    return any != 0;
+}
+// Sets the rows of an operand that hold a value that is not finite to zero; returned: bit r, row r of the block (x[g] holds row acc_row(g, hg)).
+template <int DB>
+__device__ __forceinline__ uint32_t take_out(float (&x)[16][DB], int hg) {
+    uint32_t rows = 0u;
+#pragma unroll
+    for (int g = 0; g < 16; ++g) {
+        float z = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) z = fmaf(x[g][db], 0.f, z);
+        const unsigned long long lanes = __ballot(z != z);
+        const bool lower = uint32_t(lanes) != 0u, upper = uint32_t(lanes >> 32) != 0u;
+        rows |= (lower ? 1u << acc_row(g, 0) : 0u) | (upper ? 1u << acc_row(g, 1) : 0u);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) x[g][db] = (hg ? upper : lower) ? 0.f : x[g][db];
+    }
+    return rows;
+}
+// weight x row r (uniform; `row` points at its dim 4 hg) added to the columns that see it; w: the block's weights
+template <int D>
+__device__ __forceinline__ void add_row(f32x16 (&acc)[D / 32], const f32x16& w, const float* row, int r, int n, bool seen) {
+    float weight = w[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) weight = i == 4 * (r >> 3) + (r & 3) ? w[i] : weight;
+    weight = __shfl(weight, n + 32 * ((r >> 2) & 1));
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(row + 32 * db + 8 * q4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[db][4 * q4 + c] = seen ? fmaf(weight, x[c], acc[db][4 * q4 + c]) : acc[db][4 * q4 + c];
+        }
+}
+
 // --------------------------------------------------------------------------
 // Forward
 // --------------------------------------------------------------------------
@@ -71,24 +126,25 @@ template <int D>
 struct FwdF32Smem {
     MergeLds<D> merge;
     float m[kF32Waves][kF32Rows], l[kF32Waves][kF32Rows];
+    int bad[kF32Waves];
 };
 
-template <int D>
-__global__ __launch_bounds__(64 * kF32Waves, 2) void prefill_f32_kernel(float* __restrict__ out, float* __restrict__ lse,
-                                                                        const float* __restrict__ q, const float* __restrict__ k,
-                                                                        const float* __restrict__ v, PlanView pv, int n_q_heads,
-                                                                        int n_kv_heads, float scale) {
+// false: the result is not finite, nothing has been stored
+template <int D, bool CAREFUL>
+__device__ __forceinline__ bool prefill_f32_walk(unsigned block, float* __restrict__ out, float* __restrict__ lse,
+                                                 const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+                                                 PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
     constexpr int JJ = D / 8, DB = D / 32;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     FwdF32Smem<D>& sm = *reinterpret_cast<FwdF32Smem<D>*>(smem_raw);
     const unsigned per_item = unsigned(n_q_heads) * (kTileM / kF32Rows);
-    const int rank = int(blockIdx.x / per_item);
-    const unsigned rest = blockIdx.x % per_item;
+    const int rank = int(block / per_item);
+    const unsigned rest = block % per_item;
     const int hh = int(rest % unsigned(n_q_heads)), sub = int(rest / unsigned(n_q_heads));
     const int hk = hh % n_kv_heads, hq = hk * (n_q_heads / n_kv_heads) + hh / n_kv_heads;     // consecutive workgroups -> consecutive KV heads
     const WorkItem it = pv.sorted[rank];
     const OwnRows own = own_rows(it, sub);
-    if (own.count <= 0) return;
+    if (own.count <= 0) return true;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, hg = lane >> 5;
     const int my_row = own.first + min(n, own.count - 1), last_row = own.first + own.count - 1;
@@ -100,6 +156,17 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void prefill_f32_kernel(float* _
     const int first_vis = pv.vis[it.a_base + own.first];
     const int n_blocks = blocks_a + blocks_b;
 
+    // token of this lane's key row in block t (columns past the end of the stream: the last one, masked below)
+    auto key_token = [&](int t) {
+        t = min(t, n_blocks - 1);
+        const bool in_a = t < blocks_a;
+        const int col = min((in_a ? t : t - blocks_a) * kF32Rows + n, (in_a ? it.n_stream : it.n_src) - 1);
+        return pv.perm[(in_a ? it.a_base : it.b_base) + col];
+    };
+    const int64_t stride = int64_t(n_kv_heads) * D;
+    const float* k_lane = k + int64_t(hk) * D + 4 * hg;
+    const float* v_lane = v + int64_t(hk) * D + n;
+    const int row = threadIdx.x >> 3, part = threadIdx.x & 7;              // of the merge: eight threads per row
     f32x4 qf[JJ];
     {
         const float* qp = q + (my_tok * n_q_heads + hq) * D + 4 * hg;
@@ -113,16 +180,6 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void prefill_f32_kernel(float* _
         for (int i = 0; i < 16; ++i) o_acc[db][i] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
 
-    // token of this lane's key row in block t (columns past the end of the stream: the last one, masked below)
-    auto key_token = [&](int t) {
-        t = min(t, n_blocks - 1);
-        const bool in_a = t < blocks_a;
-        const int col = min((in_a ? t : t - blocks_a) * kF32Rows + n, (in_a ? it.n_stream : it.n_src) - 1);
-        return pv.perm[(in_a ? it.a_base : it.b_base) + col];
-    };
-    const int64_t stride = int64_t(n_kv_heads) * D;
-    const float* k_lane = k + int64_t(hk) * D + 4 * hg;
-    const float* v_lane = v + int64_t(hk) * D + n;
     f32x4 kf[JJ];
     int tok = 0;
     if (wave < n_blocks) {
@@ -180,6 +237,12 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void prefill_f32_kernel(float* _
             s[i] = expf(s[i] - m_use);
             l_run += s[i];
         }
+        if (CAREFUL && c0 + kF32Rows > limit_min) {
+            for (uint32_t rows = take_out<DB>(vf, hg); rows != 0u; rows &= rows - 1u) {
+                const int r = __ffs(rows) - 1;
+                add_row<D>(o_acc, s, v + __shfl(tok, r) * stride + int64_t(hk) * D + 4 * hg, r, n, c0 + r < limit);
+            }
+        }
         // ---- O^T += V^T P^T; the next block's keys are requested beside it ----
         tok = tok_next;
         const float* kp = k_lane + tok * stride;
@@ -193,15 +256,25 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void prefill_f32_kernel(float* _
         }
     }
     // ---- merge of the four waves' states ----
+    bool bad = false;
+    if (!CAREFUL) {
+        float z = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) z = fmaf(o_acc[db][i], 0.f, z);
+        bad = __any(z != z);
+    }
     park<D>(sm.merge.o[wave], o_acc, n, hg);
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (hg == 0) {
         sm.m[wave][n] = m_run;
         sm.l[wave][n] = l_tot;
     }
+    if (!CAREFUL && lane == 0) sm.bad[wave] = bad;
     __syncthreads();
-    const int row = threadIdx.x >> 3, part = threadIdx.x & 7;              // eight threads per row
-    if (row >= own.count) return;
+    if (!CAREFUL && any_wave(sm.bad)) return false;
+    const int64_t rowhead = int64_t(pv.perm[it.a_base + own.first + min(row, own.count - 1)]) * n_q_heads + hq;
     float m_all = -INFINITY, wt[kF32Waves], den = 0.f;
 #pragma unroll
     for (int w = 0; w < kF32Waves; ++w) m_all = fmaxf(m_all, sm.m[w][row]);           // finite: column 0 of the own stream is visible
@@ -211,22 +284,36 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void prefill_f32_kernel(float* _
         den = fmaf(wt[w], sm.l[w][row], den);
     }
     const float inv = 1.f / den;
-    const int64_t rowhead = int64_t(pv.perm[it.a_base + own.first + row]) * n_q_heads + hq;
-    float* op = out + rowhead * D;
+    f32x4 a[DB];
 #pragma unroll
-    for (int d = 4 * part; d < D; d += 32) {
-        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+    for (int db = 0; db < DB; ++db) {
+        a[db] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < kF32Waves; ++w) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][d]);
+            const f32x4 x = *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][4 * part + 32 * db]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) a[e] = fmaf(wt[w], x[e], a[e]);
+            for (int e = 0; e < 4; ++e) a[db][e] = fmaf(wt[w], x[e], a[db][e]);
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) a[e] *= inv;
-        *reinterpret_cast<f32x4*>(op + d) = a;
+        for (int e = 0; e < 4; ++e) a[db][e] *= inv;
     }
-    if (lse && part == 0) lse[rowhead] = m_all + logf(den);
+    if (row < own.count) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(out + rowhead * D + 4 * part + 32 * db) = a[db];
+        if (lse && part == 0) lse[rowhead] = m_all + logf(den);
+    }
+    return true;
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves, 2) void prefill_f32_kernel(float* __restrict__ out, float* __restrict__ lse,
+                                                                        const float* __restrict__ q, const float* __restrict__ k,
+                                                                        const float* __restrict__ v, PlanView pv, int n_q_heads,
+                                                                        int n_kv_heads, float scale) {
+    unsigned block = blockIdx.x;
+    if (prefill_f32_walk<D, false>(block, out, lse, q, k, v, pv, n_q_heads, n_kv_heads, scale)) return;
+    asm volatile("" : "+s"(block));               // (nothing of the first walk is kept for the second: the registers are full)
+    prefill_f32_walk<D, true>(block, out, lse, q, k, v, pv, n_q_heads, n_kv_heads, scale);
 }
 
 // --------------------------------------------------------------------------
@@ -241,25 +328,26 @@ struct DqF32Smem {
         MergeLds<D> merge;
     };
     float lse[kF32Rows], delta[kF32Rows];
+    int bad[kF32Waves];
 };
 
-template <int D>
-__global__ __launch_bounds__(64 * kF32Waves, 2) void bwd_dq_f32_kernel(float* __restrict__ dq, float* __restrict__ delta_out,
-                                                                       const float* __restrict__ d_out, const float* __restrict__ q,
-                                                                       const float* __restrict__ k, const float* __restrict__ v,
-                                                                       const float* __restrict__ out, const float* __restrict__ lse,
-                                                                       PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
+// false: the result is not finite, nothing but delta has been stored
+template <int D, bool CAREFUL>
+__device__ __forceinline__ bool bwd_dq_f32_walk(unsigned block, float* __restrict__ dq, float* __restrict__ delta_out,
+                                                const float* __restrict__ d_out, const float* __restrict__ q, const float* __restrict__ k,
+                                                const float* __restrict__ v, const float* __restrict__ out, const float* __restrict__ lse,
+                                                PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
     constexpr int JJ = D / 8, DB = D / 32;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     DqF32Smem<D>& sm = *reinterpret_cast<DqF32Smem<D>*>(smem_raw);
     const unsigned per_item = unsigned(n_q_heads) * (kTileM / kF32Rows);
-    const int rank = int(blockIdx.x / per_item);
-    const unsigned rest = blockIdx.x % per_item;
+    const int rank = int(block / per_item);
+    const unsigned rest = block % per_item;
     const int hh = int(rest % unsigned(n_q_heads)), sub = int(rest / unsigned(n_q_heads));
     const int hk = hh % n_kv_heads, hq = hk * (n_q_heads / n_kv_heads) + hh / n_kv_heads;
     const WorkItem it = pv.sorted[rank];
     const OwnRows own = own_rows(it, sub);
-    if (own.count <= 0) return;
+    if (own.count <= 0) return true;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, hg = lane >> 5;
     const int my_row = own.first + min(n, own.count - 1), last_row = own.first + own.count - 1;
@@ -269,9 +357,19 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void bwd_dq_f32_kernel(float* __
     const int first_vis = pv.vis[it.a_base + own.first];
     const int n_blocks = blocks_a + blocks_b;
 
-    // the workgroup's rows of q and dO into LDS (operands of every wave), their delta on the way
     const int row = threadIdx.x >> 3, part = threadIdx.x & 7;
     const int64_t rowhead = int64_t(pv.perm[it.a_base + own.first + min(row, own.count - 1)]) * n_q_heads + hq;
+    auto key_token = [&](int t) {
+        t = min(t, n_blocks - 1);
+        const bool in_a = t < blocks_a;
+        const int col = min((in_a ? t : t - blocks_a) * kF32Rows + n, (in_a ? it.n_stream : it.n_src) - 1);
+        return pv.perm[(in_a ? it.a_base : it.b_base) + col];
+    };
+    const int64_t stride = int64_t(n_kv_heads) * D;
+    const float* k_rows = k + int64_t(hk) * D + 4 * hg;
+    const float* v_rows = v + int64_t(hk) * D + 4 * hg;
+    const float* k_cols = k + int64_t(hk) * D + n;
+    // the workgroup's rows of q and dO into LDS (operands of every wave), their delta on the way
     {
         float dl = 0.f;
 #pragma unroll
@@ -294,16 +392,6 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void bwd_dq_f32_kernel(float* __
     __syncthreads();
     const float my_lse = sm.lse[n], my_delta = sm.delta[n];
 
-    auto key_token = [&](int t) {
-        t = min(t, n_blocks - 1);
-        const bool in_a = t < blocks_a;
-        const int col = min((in_a ? t : t - blocks_a) * kF32Rows + n, (in_a ? it.n_stream : it.n_src) - 1);
-        return pv.perm[(in_a ? it.a_base : it.b_base) + col];
-    };
-    const int64_t stride = int64_t(n_kv_heads) * D;
-    const float* k_rows = k + int64_t(hk) * D + 4 * hg;
-    const float* v_rows = v + int64_t(hk) * D + 4 * hg;
-    const float* k_cols = k + int64_t(hk) * D + n;
     f32x16 acc[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -350,6 +438,13 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void bwd_dq_f32_kernel(float* __
             float p = expf(s[i] * scale - my_lse);
             if (partial) p = c0 + acc_row(i, hg) < limit ? p : 0.f;
             s[i] = p * (dp[i] - my_delta) * scale;
+            if (CAREFUL) s[i] = c0 + acc_row(i, hg) < limit ? s[i] : 0.f;
+        }
+        if (CAREFUL && partial) {
+            for (uint32_t rows = take_out<DB>(kt, hg); rows != 0u; rows &= rows - 1u) {
+                const int r = __ffs(rows) - 1;
+                add_row<D>(acc, s, k_rows + __shfl(tok, r) * stride, r, n, c0 + r < limit);
+            }
         }
         // ---- dQ^T += K^T dS^T; the next block's rows are requested beside it ----
         tok = tok_next;
@@ -367,63 +462,83 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void bwd_dq_f32_kernel(float* __
     __syncthreads();
     park<D>(sm.merge.o[wave], acc, n, hg);
     __syncthreads();
-    if (row >= own.count) return;
+    f32x4 a[DB];
+    float z = 0.f;
 #pragma unroll
-    for (int d = 4 * part; d < D; d += 32) {
-        f32x4 a = *reinterpret_cast<const f32x4*>(&sm.merge.o[0][row][d]);
+    for (int db = 0; db < DB; ++db) {
+        a[db] = *reinterpret_cast<const f32x4*>(&sm.merge.o[0][row][4 * part + 32 * db]);
 #pragma unroll
-        for (int w = 1; w < kF32Waves; ++w) a += *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][d]);
-        *reinterpret_cast<f32x4*>(dq + rowhead * D + d) = a;
+        for (int w = 1; w < kF32Waves; ++w) a[db] += *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][4 * part + 32 * db]);
+        z = fold_finite(z, a[db]);
     }
+    if (!CAREFUL) {
+        const bool bad = __any(z != z);
+        if (lane == 0) sm.bad[wave] = bad;
+        __syncthreads();
+        if (any_wave(sm.bad)) return false;
+    }
+    if (row < own.count) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(dq + rowhead * D + 4 * part + 32 * db) = a[db];
+    }
+    return true;
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves, 2) void bwd_dq_f32_kernel(float* __restrict__ dq, float* __restrict__ delta_out,
+                                                                       const float* __restrict__ d_out, const float* __restrict__ q,
+                                                                       const float* __restrict__ k, const float* __restrict__ v,
+                                                                       const float* __restrict__ out, const float* __restrict__ lse,
+                                                                       PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
+    unsigned block = blockIdx.x;
+    if (bwd_dq_f32_walk<D, false>(block, dq, delta_out, d_out, q, k, v, out, lse, pv, n_q_heads, n_kv_heads, scale)) return;
+    asm volatile("" : "+s"(block));               // (nothing of the first walk is kept for the second: the registers are full)
+    bwd_dq_f32_walk<D, true>(block, dq, delta_out, d_out, q, k, v, out, lse, pv, n_q_heads, n_kv_heads, scale);
 }
 
 // --------------------------------------------------------------------------
 // Backward, key side: dV_j = sum_i P_ij dO_i, dK_j = scale sum_i dS_ij Q_i over the query rows i that see key j, summed
 // over the query heads of the KV head.  A workgroup owns 32 keys of one KV head; the (32-row query block, query head)
 // pairs are dealt out to its four waves.  parts > 1: the query heads of a KV head are dealt out to `parts` workgroups (a divisor
-// of the group), which leave their sums in `partial` ([2: dK, dV][parts][N][n_kv_heads][D]) for bwd_dkv_sum_f32_kernel.  Products not transposed (S = Q K^T): a lane owns a key, rows run along the
-// accumulator registers.
+// of the group), which leave their sums in `partial` ([2: dK, dV][parts][N][n_kv_heads][D]) for bwd_dkv_sum_f32_kernel.
+// Products not transposed (S = Q K^T): a lane owns a key, rows run along the accumulator registers.
 // --------------------------------------------------------------------------
 template <int D>
-union DkvF32Smem {                // the rows are read in the loop, the merge comes after it
-    struct {
-        RowsLds<D> k, v;
+struct DkvF32Smem {
+    union {                       // the rows are read in the loop, the merge comes after it
+        struct {
+            RowsLds<D> k, v;
+        };
+        MergeLds<D> merge;
     };
-    MergeLds<D> merge;
+    int bad[kF32Waves];
 };
 
-template <int D>
-__global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* __restrict__ dk, float* __restrict__ dv,
-                                                                        const float* __restrict__ delta, const float* __restrict__ d_out,
-                                                                        const float* __restrict__ q, const float* __restrict__ k,
-                                                                        const float* __restrict__ v, const float* __restrict__ lse,
-                                                                        PlanView pv, int n_q_heads, int n_kv_heads, float scale,
-                                                                        int parts, float* __restrict__ partial, int64_t partial_stride) {
+// false: the result is not finite, nothing has been stored
+template <int D, bool CAREFUL>
+__device__ __forceinline__ bool bwd_dkv_f32_walk(unsigned block, float* __restrict__ dk, float* __restrict__ dv,
+                                                 const float* __restrict__ delta, const float* __restrict__ d_out,
+                                                 const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+                                                 const float* __restrict__ lse, PlanView pv, int n_q_heads, int n_kv_heads, float scale,
+                                                 int parts, float* __restrict__ partial, int64_t partial_stride) {
     constexpr int JJ = D / 8, DB = D / 32;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     DkvF32Smem<D>& sm = *reinterpret_cast<DkvF32Smem<D>*>(smem_raw);
     const unsigned per_item = unsigned(n_kv_heads) * (kTileM / kF32Rows) * unsigned(parts);
     // (early keys are seen by the most rows: the table, sorted by the forward's cost, is walked backwards)
-    const int rank = pv.m_max - 1 - int(blockIdx.x / per_item);
-    const unsigned rest = blockIdx.x % per_item;
+    const int rank = pv.m_max - 1 - int(block / per_item);
+    const unsigned rest = block % per_item;
     const int hk = int(rest % unsigned(n_kv_heads)), part_of = int(rest / unsigned(n_kv_heads)) % parts, sub = int(rest / (unsigned(n_kv_heads) * unsigned(parts)));
     const int group = n_q_heads / n_kv_heads / parts, hq0 = (hk * parts + part_of) * group;      // this workgroup's query heads
     const WorkItem it = pv.sorted[rank];
     const OwnRows own = own_rows(it, sub);
-    if (own.count <= 0) return;
+    if (own.count <= 0) return true;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, hg = lane >> 5;
     const int my_key = own.first + min(n, own.count - 1), last_key = own.first + own.count - 1;
 
     const int row = threadIdx.x >> 3, part = threadIdx.x & 7;
     const int64_t keyhead = int64_t(pv.perm[it.a_base + own.first + min(row, own.count - 1)]) * n_kv_heads + hk;
-#pragma unroll
-    for (int d = 4 * part; d < D; d += 32) {
-        *reinterpret_cast<f32x4*>(&sm.k.x[row][d]) = *reinterpret_cast<const f32x4*>(k + keyhead * D + d);
-        *reinterpret_cast<f32x4*>(&sm.v.x[row][d]) = *reinterpret_cast<const f32x4*>(v + keyhead * D + d);
-    }
-    __syncthreads();
-
     // the rows that see the block's first key: the own stream from it on; for source keys also the reasoning rows from the
     // first one whose visible-source count exceeds it (counts do not decrease along the stream)
     const int S = it.n_src;
@@ -467,6 +582,13 @@ __global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* _
         r.end = r.rs ? n_rsn : it.n_stream;
         return r;
     };
+#pragma unroll
+    for (int d = 4 * part; d < D; d += 32) {
+        *reinterpret_cast<f32x4*>(&sm.k.x[row][d]) = *reinterpret_cast<const f32x4*>(k + keyhead * D + d);
+        *reinterpret_cast<f32x4*>(&sm.v.x[row][d]) = *reinterpret_cast<const f32x4*>(v + keyhead * D + d);
+    }
+    __syncthreads();
+
     f32x16 dk_acc[DB], dv_acc[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -530,6 +652,18 @@ __global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* _
             if (!full) p = my_key < __shfl(lim, r) ? p : 0.f;
             s[i] = p;
             dp[i] = p * (dp[i] - __shfl(d_row, r)) * scale;
+            if (CAREFUL && !full) dp[i] = my_key < __shfl(lim, r) ? dp[i] : 0.f;
+        }
+        if (CAREFUL && !full) {
+            auto row_of = [&](const float* x, int r) { return x + (int64_t(__shfl(tok, r)) * n_q_heads + cur.hq) * D + 4 * hg; };
+            for (uint32_t rows = take_out<DB>(ot, hg); rows != 0u; rows &= rows - 1u) {
+                const int r = __ffs(rows) - 1;
+                add_row<D>(dv_acc, s, row_of(d_out, r), r, n, my_key < __shfl(lim, r));
+            }
+            for (uint32_t rows = take_out<DB>(qt, hg); rows != 0u; rows &= rows - 1u) {
+                const int r = __ffs(rows) - 1;
+                add_row<D>(dk_acc, dp, row_of(q, r), r, n, my_key < __shfl(lim, r));
+            }
         }
         // ---- dV^T += dO^T P, dK^T += Q^T dS; the next rows are requested beside them ----
         cur = iter_at(x + kF32Waves);
@@ -544,23 +678,50 @@ __global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* _
             load_rows(cur, g * JJ / 16, (g + 1) * JJ / 16);
         }
     }
-    // ---- sums of the four waves, in a fixed order ----
+    // ---- sums of the four waves, in a fixed order: dV, then dK ----
+    f32x4 a[2][DB];
+    float z = 0.f;
 #pragma unroll
     for (int which = 0; which < 2; ++which) {
         __syncthreads();
         park<D>(sm.merge.o[wave], which == 0 ? dv_acc : dk_acc, n, hg);
         __syncthreads();
-        if (row < own.count) {
-            float* dst = (parts > 1 ? partial + ((which == 0 ? parts : 0) + part_of) * partial_stride : which == 0 ? dv : dk) + keyhead * D;
 #pragma unroll
-            for (int d = 4 * part; d < D; d += 32) {
-                f32x4 a = *reinterpret_cast<const f32x4*>(&sm.merge.o[0][row][d]);
+        for (int db = 0; db < DB; ++db) {
+            a[which][db] = *reinterpret_cast<const f32x4*>(&sm.merge.o[0][row][4 * part + 32 * db]);
 #pragma unroll
-                for (int w = 1; w < kF32Waves; ++w) a += *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][d]);
-                *reinterpret_cast<f32x4*>(dst + d) = a;
-            }
+            for (int w = 1; w < kF32Waves; ++w) a[which][db] += *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][4 * part + 32 * db]);
+            z = fold_finite(z, a[which][db]);
         }
     }
+    if (!CAREFUL) {
+        const bool bad = __any(z != z);
+        if (lane == 0) sm.bad[wave] = bad;
+        __syncthreads();
+        if (any_wave(sm.bad)) return false;
+    }
+    if (row < own.count) {
+#pragma unroll
+        for (int which = 0; which < 2; ++which) {
+            float* dst = (parts > 1 ? partial + ((which == 0 ? parts : 0) + part_of) * partial_stride : which == 0 ? dv : dk) + keyhead * D;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(dst + 4 * part + 32 * db) = a[which][db];
+        }
+    }
+    return true;
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves, 1) void bwd_dkv_f32_kernel(float* __restrict__ dk, float* __restrict__ dv,
+                                                                        const float* __restrict__ delta, const float* __restrict__ d_out,
+                                                                        const float* __restrict__ q, const float* __restrict__ k,
+                                                                        const float* __restrict__ v, const float* __restrict__ lse,
+                                                                        PlanView pv, int n_q_heads, int n_kv_heads, float scale, int parts,
+                                                                        float* __restrict__ partial, int64_t partial_stride) {
+    unsigned block = blockIdx.x;
+    if (bwd_dkv_f32_walk<D, false>(block, dk, dv, delta, d_out, q, k, v, lse, pv, n_q_heads, n_kv_heads, scale, parts, partial, partial_stride)) return;
+    asm volatile("" : "+s"(block));               // (nothing of the first walk is kept for the second: the registers are full)
+    bwd_dkv_f32_walk<D, true>(block, dk, dv, delta, d_out, q, k, v, lse, pv, n_q_heads, n_kv_heads, scale, parts, partial, partial_stride);
 }
 
 // dK (blockIdx.y = 0) or dV (1) from the partial sums of the key-side kernel, in a fixed order; n4 groups of four elements
