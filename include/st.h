@@ -264,7 +264,8 @@ st_status st_attn_prefill_ids(void* out, float* lse, const void* q, const void* 
  * ST_F32: fp32 products and sums (the matrix cores' fp32 instructions); Inf and NaN stay with the
  * pairs that the mask allows, as in the forward.
  * workspace: at least st_prefill_bwd_workspace_bytes(plan, n_q_heads, n_kv_heads, head_dim, dt)
- * bytes, 256-byte aligned.  Errors as for st_attn_prefill.
+ * bytes, 256-byte aligned.  Errors as for st_attn_prefill, but the tensors need only be aligned to
+ * their elements here (gradients may be slices of a flat buffer).
  * ---------------------------------------------------------------------- */
 size_t st_prefill_bwd_workspace_bytes(const st_plan* plan, int32_t n_q_heads, int32_t n_kv_heads,
                                       int32_t head_dim, st_dtype dt);

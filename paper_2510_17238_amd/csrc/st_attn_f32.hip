@@ -113,7 +113,7 @@ __device__ __forceinline__ void add_row(f32x16 (&acc)[D / 32], const f32x16& w, 
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(row + 32 * db + 8 * q4);
+            const f32x4 x = *reinterpret_cast<const f32x4_a4*>(row + 32 * db + 8 * q4);
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[db][4 * q4 + c] = seen ? fmaf(weight, x[c], acc[db][4 * q4 + c]) : acc[db][4 * q4 + c];
         }
@@ -374,8 +374,8 @@ __device__ __forceinline__ bool bwd_dq_f32_walk(unsigned block, float* __restric
         float dl = 0.f;
 #pragma unroll
         for (int d = 4 * part; d < D; d += 32) {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(d_out + rowhead * D + d), o = *reinterpret_cast<const f32x4*>(out + rowhead * D + d);
-            *reinterpret_cast<f32x4*>(&sm.q.x[row][d]) = *reinterpret_cast<const f32x4*>(q + rowhead * D + d);
+            const f32x4 a = *reinterpret_cast<const f32x4_a4*>(d_out + rowhead * D + d), o = *reinterpret_cast<const f32x4_a4*>(out + rowhead * D + d);
+            *reinterpret_cast<f32x4*>(&sm.q.x[row][d]) = *reinterpret_cast<const f32x4_a4*>(q + rowhead * D + d);
             *reinterpret_cast<f32x4*>(&sm.d_out.x[row][d]) = a;
 #pragma unroll
             for (int e = 0; e < 4; ++e) dl = fmaf(a[e], o[e], dl);
@@ -402,9 +402,9 @@ __device__ __forceinline__ bool bwd_dq_f32_walk(unsigned block, float* __restric
     if (wave < n_blocks) {
         tok = key_token(wave);
 #pragma unroll
-        for (int jj = 0; jj < JJ; ++jj) kf[jj] = *reinterpret_cast<const f32x4*>(k_rows + tok * stride + 8 * jj);
+        for (int jj = 0; jj < JJ; ++jj) kf[jj] = *reinterpret_cast<const f32x4_a4*>(k_rows + tok * stride + 8 * jj);
 #pragma unroll
-        for (int jj = 0; jj < JJ; ++jj) vf[jj] = *reinterpret_cast<const f32x4*>(v_rows + tok * stride + 8 * jj);
+        for (int jj = 0; jj < JJ; ++jj) vf[jj] = *reinterpret_cast<const f32x4_a4*>(v_rows + tok * stride + 8 * jj);
     }
     for (int t = wave; t < n_blocks; t += kF32Waves) {
         const int tok_next = key_token(t + kF32Waves);
@@ -454,8 +454,8 @@ __device__ __forceinline__ bool bwd_dq_f32_walk(unsigned block, float* __restric
             for (int db = 0; db < DB; ++db) acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(kt[g][db], s[g], acc[db], 0, 0, 0);
 #pragma unroll
             for (int jj = g * JJ / 16; jj < (g + 1) * JJ / 16; ++jj) {
-                kf[jj] = *reinterpret_cast<const f32x4*>(k_rows + tok * stride + 8 * jj);
-                vf[jj] = *reinterpret_cast<const f32x4*>(v_rows + tok * stride + 8 * jj);
+                kf[jj] = *reinterpret_cast<const f32x4_a4*>(k_rows + tok * stride + 8 * jj);
+                vf[jj] = *reinterpret_cast<const f32x4_a4*>(v_rows + tok * stride + 8 * jj);
             }
         }
     }
@@ -479,7 +479,7 @@ __device__ __forceinline__ bool bwd_dq_f32_walk(unsigned block, float* __restric
     }
     if (row < own.count) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(dq + rowhead * D + 4 * part + 32 * db) = a[db];
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4_a4*>(dq + rowhead * D + 4 * part + 32 * db) = a[db];
     }
     return true;
 }
@@ -584,8 +584,8 @@ __device__ __forceinline__ bool bwd_dkv_f32_walk(unsigned block, float* __restri
     };
 #pragma unroll
     for (int d = 4 * part; d < D; d += 32) {
-        *reinterpret_cast<f32x4*>(&sm.k.x[row][d]) = *reinterpret_cast<const f32x4*>(k + keyhead * D + d);
-        *reinterpret_cast<f32x4*>(&sm.v.x[row][d]) = *reinterpret_cast<const f32x4*>(v + keyhead * D + d);
+        *reinterpret_cast<f32x4*>(&sm.k.x[row][d]) = *reinterpret_cast<const f32x4_a4*>(k + keyhead * D + d);
+        *reinterpret_cast<f32x4*>(&sm.v.x[row][d]) = *reinterpret_cast<const f32x4_a4*>(v + keyhead * D + d);
     }
     __syncthreads();
 
@@ -610,8 +610,8 @@ __device__ __forceinline__ bool bwd_dkv_f32_walk(unsigned block, float* __restri
         const int64_t off = (int64_t(tok) * n_q_heads + r.hq) * D + 4 * hg;
 #pragma unroll
         for (int jj = jj0; jj < jj1; ++jj) {
-            qf[jj] = *reinterpret_cast<const f32x4*>(q + off + 8 * jj);
-            of[jj] = *reinterpret_cast<const f32x4*>(d_out + off + 8 * jj);
+            qf[jj] = *reinterpret_cast<const f32x4_a4*>(q + off + 8 * jj);
+            of[jj] = *reinterpret_cast<const f32x4_a4*>(d_out + off + 8 * jj);
         }
     };
     if (wave < n_iter) {
@@ -705,7 +705,7 @@ __device__ __forceinline__ bool bwd_dkv_f32_walk(unsigned block, float* __restri
         for (int which = 0; which < 2; ++which) {
             float* dst = (parts > 1 ? partial + ((which == 0 ? parts : 0) + part_of) * partial_stride : which == 0 ? dv : dk) + keyhead * D;
 #pragma unroll
-            for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(dst + 4 * part + 32 * db) = a[which][db];
+            for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4_a4*>(dst + 4 * part + 32 * db) = a[which][db];
         }
     }
     return true;
@@ -732,7 +732,7 @@ __global__ __launch_bounds__(256) void bwd_dkv_sum_f32_kernel(float* __restrict_
     const float* p = partial + blockIdx.y * parts * partial_stride + i * 4;
     f32x4 a = *reinterpret_cast<const f32x4*>(p);
     for (int x = 1; x < parts; ++x) a += *reinterpret_cast<const f32x4*>(p + x * partial_stride);
-    *reinterpret_cast<f32x4*>((blockIdx.y == 0 ? dk : dv) + i * 4) = a;
+    *reinterpret_cast<f32x4_a4*>((blockIdx.y == 0 ? dk : dv) + i * 4) = a;
 }
 
 // ---- launches (arguments have been checked by the callers) ----

@@ -66,6 +66,12 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// The same as they lie in a tensor that is only aligned to its elements (a gradient may be a slice of a flat buffer): the compiler
+// may assume no more of it, and takes the same instructions -- global memory serves any address.
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+typedef bf16x8 bf16x8_a2 __attribute__((aligned(2)));
+typedef bf16x4 bf16x4_a2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 
 constexpr int kWave = 64;
 constexpr int kPage = 16;           // tokens per cache page

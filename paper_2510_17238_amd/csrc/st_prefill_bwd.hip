@@ -91,8 +91,8 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
     bf16x8 qf[KS], dof[KS];
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
-        qf[j] = *reinterpret_cast<const bf16x8*>(q + rowhead * D + 8 * hg + 16 * j);
-        dof[j] = *reinterpret_cast<const bf16x8*>(d_out + rowhead * D + 8 * hg + 16 * j);
+        qf[j] = *reinterpret_cast<const bf16x8_a2*>(q + rowhead * D + 8 * hg + 16 * j);
+        dof[j] = *reinterpret_cast<const bf16x8_a2*>(d_out + rowhead * D + 8 * hg + 16 * j);
     }
     // queries times scale * log2(e), rounded to bf16 again (as in the forward kernel): K q' is a score in exponent units
 #pragma unroll
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
             bf16x4 o4;
 #pragma unroll
             for (int c = 0; c < 4; ++c) o4[c] = (__bf16)(acc[db][4 * q4 + c] * scale);
-            *reinterpret_cast<bf16x4*>(op + 32 * db + 8 * q4 + 4 * hg) = o4;
+            *reinterpret_cast<bf16x4_a2*>(op + 32 * db + 8 * q4 + 4 * hg) = o4;
         }
 }
 
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(256) void bwd_pack_kernel(BwdPackArgs a, PlanView p
                      [&](int row, uint32_t at, const u32x4& piece) {
                          float dl = 0.f;
                          if (row < info.valid) {
-                             const bf16x8 x = __builtin_bit_cast(bf16x8, piece), o = *reinterpret_cast<const bf16x8*>(a.out + at);
+                             const bf16x8 x = __builtin_bit_cast(bf16x8, piece), o = *reinterpret_cast<const bf16x8_a2*>(a.out + at);
 #pragma unroll
                              for (int e = 0; e < 8; ++e) dl = fmaf(float(x[e]), float(o[e]), dl);
                          }
@@ -382,8 +382,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
     bf16x8 kf[KS], vf[KS];
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
-        kf[j] = *reinterpret_cast<const bf16x8*>(k + keyhead * D + 8 * hg + 16 * j);
-        vf[j] = *reinterpret_cast<const bf16x8*>(v + keyhead * D + 8 * hg + 16 * j);
+        kf[j] = *reinterpret_cast<const bf16x8_a2*>(k + keyhead * D + 8 * hg + 16 * j);
+        vf[j] = *reinterpret_cast<const bf16x8_a2*>(v + keyhead * D + 8 * hg + 16 * j);
     }
     // keys times scale * log2(e), rounded to bf16 again: Q k' is a score in exponent units (dK takes Q, not K)
 #pragma unroll
@@ -654,8 +654,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
                 a4[c] = (__bf16)(dk_acc[db][4 * q4 + c] * scale);
                 b4[c] = (__bf16)dv_acc[db][4 * q4 + c];
             }
-            *reinterpret_cast<bf16x4*>(pk + 32 * db + 8 * q4 + 4 * hg) = a4;
-            *reinterpret_cast<bf16x4*>(pvv + 32 * db + 8 * q4 + 4 * hg) = b4;
+            *reinterpret_cast<bf16x4_a2*>(pk + 32 * db + 8 * q4 + 4 * hg) = a4;
+            *reinterpret_cast<bf16x4_a2*>(pvv + 32 * db + 8 * q4 + 4 * hg) = b4;
         }
 }
 
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(256) void bwd_dkv_sum_kernel(uint16_t* __restrict__
         r[e] = (__bf16)(a[e] * f);
         r[4 + e] = (__bf16)(b[e] * f);
     }
-    *reinterpret_cast<bf16x8*>((blockIdx.y == 0 ? dk : dv) + int64_t(i) * 8) = r;
+    *reinterpret_cast<bf16x8_a2*>((blockIdx.y == 0 ? dk : dv) + int64_t(i) * 8) = r;
 }
 
 }  // namespace st

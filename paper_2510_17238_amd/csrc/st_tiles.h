@@ -141,7 +141,7 @@ __device__ __forceinline__ void pack_rows(uint16_t* dst, const uint16_t* src, co
         uint32_t at = 0;
         if (row < valid) {
             at = uint32_t(perm[row]) * row_stride + head * D + ch * 8;
-            val = *reinterpret_cast<const u32x4*>(src + at);
+            val = *reinterpret_cast<const u32x4_a2*>(src + at);
         }
         each(row, at, val);
         const int lr = swap23(row);                                    // row position in the tile
