@@ -1493,21 +1493,27 @@ static inline bool small_decode(int64_t batch, int hkv, int max_src, int max_rsn
 
 // Tokens per work unit of a split kernel's workgroup.  Every unit pays a prologue (a chain of memory round trips, microseconds
 // each under load) and a partial result, so a unit is as long as still leaves enough of them to fill the chip (512 workgroups
-// at a time) and to end evenly: with the length BOUNDS (about half the units they give are real) the longest of 4,096 .. 1,024
-// tokens that gives 2,048 units -- us per layer, 16 / 8 heads of 128 dims: 64 sequences of up to 24K tokens 622 with 2,048
-// against 777 with 512; 16 of up to 16K 134 with 1,024 against 141 with 512; 48 of 2K 73 with 512 against 91 with 1,024 --, 1,024
-// units for 8-bit caches (32 sequences of up to 8K tokens: 82 with 2,048 against 88 with 512).  With more than 8 query rows
-// the partial results weigh so much (4.2 to 16 KB each) that 192 units of 4,096 tokens are enough (8 sequences of up to 12K
-// tokens, 32 rows: 63 against 67 with 512; 32 of them 214 against 264).  A few sequences are bound by the walk over a unit and
-// not by bandwidth: 256 tokens below 256 units of 512 (one sequence of 4K tokens: 13.5 against 15.3), 128 from 32 units down
-// (2K tokens: 11.7 against 15.3).
+// at a time) and to end evenly: the longest of 4,096 .. 1,024 tokens that gives, with the length BOUNDS (about half the units
+// they give are real), 2,048 units -- us per layer, 16 / 8 heads of 128 dims: 64 sequences of up to 24K tokens 622 with 2,048
+// against 777 with 512; 16 of up to 16K 134 with 1,024 against 141 with 512; 48 of 2K 73 with 512 against 91 with 1,024.  Where
+// a partial result weighs more or a token less, fewer units are enough: 384 with 9 to 16 query rows (24 sequences of 2K + 2K
+// tokens, 32 / 8 heads of 128 dims 68 with 2,048 against 76 with 512), 768 for 8-bit caches (32 sequences of up to 8K tokens 82 with 2,048
+// against 88 with 512), 192 of 4,096 tokens with 17 to 32 rows (8 sequences of up to 12K tokens 63 against 67 with 512; 32 of
+// them 214 against 264).  And one that leaves the last units of the caches no more than a sixth empty between them: a cache a
+// little longer than a unit makes a long and a short workgroup, and the launch ends with the long ones -- 64 sequences of 5K + 5K
+// tokens, 8 heads of 128 dims 455 with 4,096, 398 with 1,024; 8-bit, 32 / 8 heads 271 and 228; 20 of 3,000 + 900 tokens, 16
+// rows 78 with 4,096, 60 with 1,024.
+// A few sequences are bound by the walk over a unit and not by bandwidth: 256 tokens up to 256 units of 512 (one sequence of 4K
+// tokens: 13.5 against 15.3), 128 up to 32 units (2K tokens: 11.7 against 15.3).
 static inline int decode_unit_tokens(int64_t batch, int hkv, int rows, int max_src, int max_rsn, int pinned, bool fp8 = false) {
     if (pinned) return pinned;               // the caller's choice (st_dual_lens::unit_tokens)
-    auto units = [&](int unit) { return batch * hkv * ((max_src + unit - 1) / unit + (max_rsn + unit - 1) / unit); };
-    if (rows > 8 && units(kChunkLong) >= 192) return kChunkLong;
-    const int64_t enough = fp8 ? 1024 : 2048;
+    auto per_head = [&](int unit) { return int64_t((max_src + unit - 1) / unit) + (max_rsn + unit - 1) / unit; };
+    auto units = [&](int unit) { return batch * hkv * per_head(unit); };
+    auto even = [&](int unit) { return 5 * per_head(unit) * unit <= 6 * (int64_t(max_src) + max_rsn); };
+    if (rows > 16 && units(kChunkLong) >= 192) return kChunkLong;
+    const int64_t enough = rows > 8 ? 384 : fp8 ? 768 : 2048;
     for (int unit = kChunkLong; unit > kChunk; unit /= 2)
-        if (units(unit) >= enough) return unit;
+        if (units(unit) >= enough && even(unit)) return unit;
     return units(kChunk) > 256 ? kChunk : units(kChunk) > 32 ? kChunk / 2 : kChunkMin;
 }
 
