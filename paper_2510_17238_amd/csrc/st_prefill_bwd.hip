@@ -688,20 +688,26 @@ namespace {
 inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 // Workgroups per (128 keys, KV head) of the key-side kernel.  Its work items are KEYS: with few KV heads and many query heads
 // over each, a small batch leaves compute units idle and its few long workgroups end far apart.  The query heads of a group
-// are then split into parts, each with a fp32 partial dK / dV of its own, as few as give two workgroups per slot of the chip
-// (one per compute unit at 128 dims, two at 64): measured for the whole training step, 10 x 1.7K tokens, 16 / 2 heads of 64
-// dims (288 workgroups) 693 us -> 406 us with four parts; 1 x 6.1K, 16 / 2 of 128 (98) 1661 -> 674 with eight; 2 x 2.5K,
-// 32 / 8 of 128 (330) 593 -> 520 with two.  From there on the partial sums cost more than the balance gives (4 x 4K, 16 / 8
-// of 128, 1036 workgroups: 1244 -> 1318 us), and on sequences of a few tiles the second launch does (17 x 150 tokens: 129 ->
-// 143 us; 1 x 650: 141 -> 126).
+// are then split into parts, each with a fp32 partial dK / dV of its own, as long as the launch is no more than so many
+// workgroups per slot of the chip (one per compute unit at 128 dims, two at 64): 2 if a workgroup walks 8,192 rows of its
+// query heads and more, 1.5 from 2,048 on, 1 below -- the shorter the walk, the more the partial sums weigh against it.  us for
+// the gradients, with 1 / 2 / 4 / 8 parts: 1 x 7.5K tokens, 16 / 8 heads of 128 dims (472 workgroups) 699 / 677; 2 x 2.7K (352)
+// 281 / 262; 3 x 2.4K (472) 295 / 314; 8 x 760 (440) 148 / 186; 4 x 3.1K, 16 / 2 of 128 (200) 953 / 615 / 547 / 571; 10 x 1.7K, 16 / 2
+// of 64 (292) 550 / 379 / 307 / 316; 10 x 0.9K, 16 / 8 of 64 (648) 125 / 135.  On sequences of a few tiles the second launch costs
+// more than it gives (17 x 150 tokens, whole step: 129 -> 143 us; 1 x 650: 141 -> 126).
 int dkv_parts(const st_plan* plan, int n_q_heads, int n_kv_heads, int head_dim) {
     const int group = n_q_heads / n_kv_heads;
     if (plan->n_tokens < int64_t(512) * plan->batch) return 1;
     const int64_t workgroups = (plan->n_tokens / kTileM + plan->batch) * n_kv_heads;
-    const int64_t wanted = 2 * 256 * (head_dim == 64 ? 2 : 1);
+    const int64_t slots = 256 * (head_dim == 64 ? 2 : 1);
     int parts = 1;
-    for (int p = 2; p <= std::min(group, 8) && workgroups * parts < wanted; ++p)
-        if (group % p == 0) parts = p;
+    for (int p = 2; p <= std::min(group, 8); ++p) {
+        if (group % p != 0) continue;
+        const int64_t walk = plan->n_tokens / plan->batch * group / parts;
+        const int half_rounds = walk < 2048 ? 2 : walk < 8192 ? 3 : 4;
+        if (2 * workgroups * parts > half_rounds * slots) break;
+        parts = p;
+    }
     return parts;
 }
 // The same for the fp32 key side, whose workgroups own 32 keys and keep a compute unit to themselves: parts only while there is
