@@ -14,6 +14,7 @@
 // a contiguous 16-byte load straight from global memory into MFMA registers:
 //   K [page][head][d/8][slot][8] : lane (m, hg) reads slot m of d-chunk 2 j + hg
 //   V [page][head][d][slot]      : lane (n, hg) reads slots 8 hg .. 8 hg + 7 of row d
+#include <algorithm>
 #include <type_traits>
 
 #include "st_cache.h"
@@ -1499,17 +1500,18 @@ static inline bool small_decode(int64_t batch, int hkv, int max_src, int max_rsn
 // a partial result weighs more or a token less, fewer units are enough: 384 with 9 to 16 query rows (24 sequences of 2K + 2K
 // tokens, 32 / 8 heads of 128 dims 68 with 2,048 against 76 with 512), 768 for 8-bit caches (32 sequences of up to 8K tokens 82 with 2,048
 // against 88 with 512), 192 of 4,096 tokens with 17 to 32 rows (8 sequences of up to 12K tokens 63 against 67 with 512; 32 of
-// them 214 against 264).  And one that leaves the last units of the caches no more than a sixth empty between them: a cache a
-// little longer than a unit makes a long and a short workgroup, and the launch ends with the long ones -- 64 sequences of 5K + 5K
-// tokens, 8 heads of 128 dims 455 with 4,096, 398 with 1,024; 8-bit, 32 / 8 heads 271 and 228; 20 of 3,000 + 900 tokens, 16
-// rows 78 with 4,096, 60 with 1,024.
+// them 214 against 264).  And one whose workgroups are alike: the units of a head together (none counted longer than the longer
+// cache) no more than a fifth longer than its caches.  A cache a little longer than a unit, or than the other cache, makes a
+// long and a short workgroup, and the launch ends with the long ones -- 64 sequences of 5K + 5K tokens, 8 heads of 128 dims
+// 455 with 4,096, 398 with 1,024; 8-bit, 32 / 8 heads 271 and 228; 20 of 3,000 + 900 tokens, 16 rows 78 with 4,096, 60 with 1,024;
+// but 64 of 700 + 700, 16 rows 85 with 512, 69 with a unit for each cache.
 // A few sequences are bound by the walk over a unit and not by bandwidth: 256 tokens up to 256 units of 512 (one sequence of 4K
 // tokens: 13.5 against 15.3), 128 up to 32 units (2K tokens: 11.7 against 15.3).
 static inline int decode_unit_tokens(int64_t batch, int hkv, int rows, int max_src, int max_rsn, int pinned, bool fp8 = false) {
     if (pinned) return pinned;               // the caller's choice (st_dual_lens::unit_tokens)
     auto per_head = [&](int unit) { return int64_t((max_src + unit - 1) / unit) + (max_rsn + unit - 1) / unit; };
     auto units = [&](int unit) { return batch * hkv * per_head(unit); };
-    auto even = [&](int unit) { return 5 * per_head(unit) * unit <= 6 * (int64_t(max_src) + max_rsn); };
+    auto even = [&](int unit) { return 5 * per_head(unit) * std::min(unit, std::max(max_src, max_rsn)) <= 6 * (int64_t(max_src) + max_rsn); };
     if (rows > 16 && units(kChunkLong) >= 192) return kChunkLong;
     const int64_t enough = rows > 8 ? 384 : fp8 ? 768 : 2048;
     for (int unit = kChunkLong; unit > kChunk; unit /= 2)

@@ -93,7 +93,7 @@ def _check_long_units(st, bound, unit, q_len, hq, d, rope, fp8, copies):
 
 
 @pytest.mark.parametrize("batch,q_len,hq,src,rsn,units", [(64, 1, 8, 5000, 5000, 5 + 5), (64, 1, 8, 8192, 8192, 2 + 2), (20, 4, 32, 3000, 900, 3 + 1),
-                                                          (20, 4, 32, 4096, 4096, 2 + 2), (64, 1, 8, 500, 6000, 1 + 6)])
+                                                          (20, 4, 32, 4096, 4096, 2 + 2), (64, 1, 8, 500, 6000, 1 + 6), (64, 4, 32, 700, 700, 1 + 1)])
 def test_unit_leaves_no_long_and_short_workgroups(st, batch, q_len, hq, src, rsn, units):
     """Units per sequence and KV head: a unit that the caches fill, not one that leaves a long and a short workgroup of each."""
     hkv, d = 8, 64
