@@ -442,7 +442,7 @@ st_status st_attn_decode_dual_rope(void* out, float* lse, const void* q,
  *   k_new, v_new : [batch, 1, n_kv_heads, head_dim] bf16 device, 16-byte aligned
  *   theta_base   : > 0: q and k_new are UNROTATED and are rotated by the token's position id
  *                  rsn_len[b] - 1 (Sec. 3.2); 0: both are already rotated
- * When both caches are short (max_src_len + max_rsn_len <= 1024; for a few sequences 640) the step is ONE kernel launch:
+ * When both caches are short (max_src_len + max_rsn_len <= 1024; for a few sequences and 128 dims 832) the step is ONE kernel launch:
  * the workgroup that attends for a KV head also stores that head's key and value, and takes the
  * new token from registers.  Longer caches take two launches (the split kernel stores the token
  * through one more work unit per sequence and KV head and merges it as one more partial state;

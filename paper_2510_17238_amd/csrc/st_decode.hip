@@ -362,23 +362,28 @@ template <int D, bool STREAM_KEYS>
 struct Pages16 {
     static constexpr int KS = D / 32, DB = D / 16, KCH = D / 8;
     int my_page;
-    const uint16_t *k_lane, *v_lane;
+    const uint16_t *k_pool, *v_pool;
+    int k_lane, v_lane;                  // this lane's place in a page (the pools are uniform: a lane keeps no address)
     int64_t page_k, page_v;
     __device__ __forceinline__ Pages16(const CacheView& cv, int b, int h, int lane, int tok0, int stride) {
         const int n = lane & 15, g4 = lane >> 4;
         const int page = tok0 / kPage + 2 * stride * (lane >> 1) + (lane & 1);
         const int id = cv.page_table[int64_t(b) * cv.max_pages + min(page, cv.max_pages - 1)];
-        k_lane = cv.k_pool + int64_t(h) * KCH * (kPage * 8) + g4 * (kPage * 8) + (n & 7) * 8;
-        v_lane = cv.v_pool + int64_t(h) * D * kPage + n * kPage + 8 * (g4 & 1);
+        k_pool = cv.k_pool + int64_t(h) * KCH * (kPage * 8);
+        v_pool = cv.v_pool + int64_t(h) * D * kPage;
+        k_lane = g4 * (kPage * 8) + (n & 7) * 8;
+        v_lane = n * kPage + 8 * (g4 & 1);
         page_k = int64_t(cv.n_kv_heads) * KCH * (kPage * 8);
         page_v = int64_t(cv.n_kv_heads) * D * kPage;
         my_page = min(max(id, 0), cv.n_pages - 1);
     }
-    __device__ __forceinline__ void load(int s, Tokens16<D>& t32) const {
+    // step s of this cache, or of the other one where a wave walks both: their pages are alike, the pools and ids are not
+    __device__ __forceinline__ void load(int s, Tokens16<D>& t32) const { load(s, t32, my_page, k_pool, v_pool); }
+    __device__ __forceinline__ void load(int s, Tokens16<D>& t32, int page, const uint16_t* k_of, const uint16_t* v_of) const {
         const int lane = int(threadIdx.x & 63);
-        const int id0 = __builtin_amdgcn_readlane(my_page, 2 * s), id1 = __builtin_amdgcn_readlane(my_page, 2 * s + 1);
-        const uint16_t* kp = k_lane + int64_t(lane & 8 ? id1 : id0) * page_k;
-        const uint16_t* vp = v_lane + int64_t(lane & 32 ? id1 : id0) * page_v;
+        const int id0 = __builtin_amdgcn_readlane(page, 2 * s), id1 = __builtin_amdgcn_readlane(page, 2 * s + 1);
+        const uint16_t* kp = k_of + (int64_t(lane & 8 ? id1 : id0) * page_k + k_lane);
+        const uint16_t* vp = v_of + (int64_t(lane & 32 ? id1 : id0) * page_v + v_lane);
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
             t32.kx[j] = key_load<STREAM_KEYS>(kp + 4 * j * (kPage * 8));
@@ -621,6 +626,8 @@ inline size_t split16_lds_bytes(int rows, int q_len, int d) {
 // tokens, so the tokens of BOTH caches are dealt out in steps of 32 to the waves of the workgroup (reasoning steps from the
 // first wave up, source steps from the last one down -- who takes what is known before the lengths are), and the waves' states
 // meet in LDS, where all threads merge them (log-sum-exp, fixed order) and write the finished rows.
+// Two workgroups per compute unit, which takes 128 registers (with 134 from 257 workgroups on the second half waited for the
+// first: 48 sequences, 32 / 8 heads of 128 dims, 128 tokens 9.9 -> 8.0 us, 640 tokens 26.1 -> 24.2).
 constexpr int kSmallWaves = 8, kTokenWave = 4;
 
 // APPEND (one new token per sequence, q_len = 1): k_new / v_new [batch][Hkv][D] is the token at index
@@ -629,7 +636,7 @@ constexpr int kSmallWaves = 8, kTokenWave = 4;
 // the bf16 operands, as the matrix instruction would -- and walks the cache only up to the token before it; the
 // workgroup of head 0 writes the new length.  Nobody in this launch reads what it writes.
 template <int D, bool APPEND>
-__global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(DecodeArgs a, uint16_t* __restrict__ out, float* __restrict__ lse,
+__global__ __launch_bounds__(64 * kSmallWaves, 4) void decode_small16_kernel(DecodeArgs a, uint16_t* __restrict__ out, float* __restrict__ lse,
                                                                           const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new) {
     constexpr int KS = D / 32, DB = D / 16, KCH = D / 8;
     constexpr int W = kSmallWaves;
@@ -676,8 +683,8 @@ __global__ __launch_bounds__(64 * kSmallWaves) void decode_small16_kernel(Decode
     const int steps_s = (len_s - 32 * (W - 1 - wave) + 32 * W - 1) / (32 * W), steps_r = (len_r - 32 * wave + 32 * W - 1) / (32 * W);
     const int n_steps = steps_r + steps_s;
     auto load = [&](int x, Tokens16<D>& t) {
-        if (x < steps_r) pages_r.load(x, t);
-        else pages_s.load(x - steps_r, t);
+        const bool r = x < steps_r;
+        pages_r.load(r ? x : x - steps_r, t, r ? pages_r.my_page : pages_s.my_page, r ? pages_r.k_pool : pages_s.k_pool, r ? pages_r.v_pool : pages_s.v_pool);
     };
     // the source slice is seen whole; reasoning token j by rows t with j <= len_all - q_len + t
     const int limit = min(max(len_all - a.q_len + t_row + 1, 0), len_r), limit_min = min(max(len_all - a.q_len + 1, 0), len_r);
@@ -1484,12 +1491,14 @@ static inline size_t decode_partial_bytes(int unit, int64_t batch, int hkv, int 
     const size_t slots = size_t(batch) * hkv * nc * rows;
     return align256(slots * d * sizeof(float)) + align256(slots * 2 * sizeof(float)) + 256;
 }
-// Short caches: one workgroup per (sequence, KV head) does everything (no partial results, no merge launch).  A compute unit
-// takes in a cache at about 9 ns per token, so for a few (sequence, KV head) pairs, which leave most of the chip idle, the split
-// and its second launch win from some 640 tokens on (one sequence, 8 KV heads of 128 dims: 400 tokens 8.6 us here, 10.9 split;
-// 1,000 tokens 14.5 here, 11.1 split); larger batches keep it up to 1,024 (16 sequences of up to 900: 15.7 against 21.3).
-static inline bool small_decode(int64_t batch, int hkv, int max_src, int max_rsn) {
-    return max_src + max_rsn <= (batch * hkv <= 32 ? 640 : kSmallDecodeTokens);
+// Short caches: one workgroup per (sequence, KV head) does everything (no partial results, no merge launch).  With heads of 64 dims
+// that wins up to 1,024 tokens at every batch (one sequence, 16 / 8 heads, 900 tokens: 6.9 us against 7.8 replayed from a graph,
+// 7.7 against 10.2 launched one by one).  With heads of 128 a wave's chain of steps is longer, and up to 40 workgroups leave the
+// chip idle: there the split and its second launch win from some 832 tokens on (32 / 8 heads, 4 sequences: 640 tokens 8.1 here,
+// 11.0 split; 832 tokens 11.0, 10.9; 1,024 tokens 12.6, 11.2; launched one by one 8.4 / 12.1, 10.9 / 11.9, 12.3 / 12.0); from 48
+// workgroups on they don't (6 sequences, 1,024 tokens 12.5 / 12.9; 16: 16.0 / 21.4).
+static inline bool small_decode(int64_t batch, int hkv, int d, int max_src, int max_rsn) {
+    return max_src + max_rsn <= (d == 128 && batch * hkv <= 40 ? 832 : kSmallDecodeTokens);
 }
 
 // Tokens per work unit of a split kernel's workgroup.  Every unit pays a prologue (a chain of memory round trips, microseconds
@@ -1651,7 +1660,7 @@ static st_status decode_dual_impl(void* out, float* lse, const void* q, const st
     a.part_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + align256(slots * d * sizeof(float)));
 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    if (!fp8 && a.rows <= 16 && small_decode(batch, hkv, lens->max_src_len, lens->max_rsn_len) && int64_t(batch) * hkv <= 0x7fffffff) {
+    if (!fp8 && a.rows <= 16 && small_decode(batch, hkv, d, lens->max_src_len, lens->max_rsn_len) && int64_t(batch) * hkv <= 0x7fffffff) {
         const size_t smem = (size_t(kSmallWaves + (append ? 1 : 0)) * a.rows * (d + 2) + size_t(a.q_len) * d) * sizeof(float);
         auto launch = [&](auto kernel) -> st_status {
             if (smem > 64 * 1024)                       // beyond the default limit (16 rows of 128 dims only)
