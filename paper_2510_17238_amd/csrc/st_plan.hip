@@ -409,6 +409,8 @@ extern "C" st_status st_plan_create(st_plan** plan_out, const int32_t* segment_i
     for (int b = 0; b < batch; ++b) {
         const int n = p->cu_host[b + 1] - p->cu_host[b];
         p->slot_base_host[b + 1] = p->slot_base_host[b] + (n + kTileM - 1) / kTileM + 1;
+        p->longest = std::max(p->longest, n);
+        p->squared_tokens += double(n) * n;
     }
     p->m_max = p->slot_base_host[batch];   // <= m_max_bound(batch, n_tokens)
     // key tiles of the packed K / V^T buffers: ceil(S / 64) + ceil(R / 64) <= ceil(N / 64) + 1 per sequence

@@ -687,25 +687,29 @@ using namespace st;
 namespace {
 inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 // Workgroups per (128 keys, KV head) of the key-side kernel.  Its work items are KEYS: with few KV heads and many query heads
-// over each, a small batch leaves compute units idle and its few long workgroups end far apart.  The query heads of a group
-// are then split into parts, each with a fp32 partial dK / dV of its own, as long as the launch is no more than so many
-// workgroups per slot of the chip (one per compute unit at 128 dims, two at 64): 2 if a workgroup walks 8,192 rows of its
-// query heads and more, 1.5 from 2,048 on, 1 below -- the shorter the walk, the more the partial sums weigh against it.  us for
-// the gradients, with 1 / 2 / 4 / 8 parts: 1 x 7.5K tokens, 16 / 8 heads of 128 dims (472 workgroups) 699 / 677; 2 x 2.7K (352)
-// 281 / 262; 3 x 2.4K (472) 295 / 314; 8 x 760 (440) 148 / 186; 4 x 3.1K, 16 / 2 of 128 (200) 953 / 615 / 547 / 571; 10 x 1.7K, 16 / 2
-// of 64 (292) 550 / 379 / 307 / 316; 10 x 0.9K, 16 / 8 of 64 (648) 125 / 135.  On sequences of a few tiles the second launch costs
-// more than it gives (17 x 150 tokens, whole step: 129 -> 143 us; 1 x 650: 141 -> 126).
+// over each, a small or a ragged batch leaves compute units idle and its few long workgroups end far apart.  The query heads of a
+// group are then split into parts, each with a fp32 partial dK / dV of its own.  One more step of the split pays while the longest
+// workgroup's walk (rows of the longest sequence times query heads) is longer than an even share of all rows (a workgroup walks
+// half of its sequence's in the mean) plus what the further partial sums cost, 7 rows of a walk for a partial row: fitted to
+// 270 shapes of twelve head geometries, even and ragged, where this is within 0.4 % of the best split in the mean and never loses
+// more than 2 % to no split.  At 64 dims the share counts 1.1 times for 0.9: two workgroups sit on a compute unit, and one
+// left alone there ends sooner.  Beyond two workgroups per slot of the chip nothing is split further, and nothing at all where the
+// sequences have less than 512 tokens in the mean (the second launch: 17 x 150 tokens, whole step: 129 -> 143 us).
+// us for the gradients, with 1 / 2 / 4 / 8 parts: 1 x 7.5K tokens, 16 / 8 heads of 128 dims 690 / 679; 3 x 2.4K 295 / 314; 8 x 760
+// 148 / 186; 10 x 0.9K, 16 / 8 of 64 128 / 137; 4 x 3.1K, 16 / 2 of 128 953 / 615 / 547 / 571; 10 x 1.7K, 16 / 2 of 64
+// 550 / 379 / 307 / 316; ragged: 6,000 and eight of 300 tokens, 8 / 4 of 128 498 / 359, 16 / 2 of 64 1000 / 580 / 384 / 305.
 int dkv_parts(const st_plan* plan, int n_q_heads, int n_kv_heads, int head_dim) {
     const int group = n_q_heads / n_kv_heads;
     if (plan->n_tokens < int64_t(512) * plan->batch) return 1;
     const int64_t workgroups = (plan->n_tokens / kTileM + plan->batch) * n_kv_heads;
     const int64_t slots = 256 * (head_dim == 64 ? 2 : 1);
+    const double share = plan->squared_tokens / (2 * kTileM) * n_q_heads / slots * (head_dim == 64 ? 1.1 : 0.9);
+    const double partial_rows = double(plan->n_tokens) * n_kv_heads / slots;
     int parts = 1;
     for (int p = 2; p <= std::min(group, 8); ++p) {
         if (group % p != 0) continue;
-        const int64_t walk = plan->n_tokens / plan->batch * group / parts;
-        const int half_rounds = walk < 2048 ? 2 : walk < 8192 ? 3 : 4;
-        if (2 * workgroups * parts > half_rounds * slots) break;
+        const double walk = double(plan->longest) * group / parts;
+        if (workgroups * parts >= 2 * slots || walk <= share + 256 + 7 * (p - parts) * partial_rows) break;
         parts = p;
     }
     return parts;

@@ -83,15 +83,18 @@ def test_query_heads_over_waves(st, hq, hkv, d, heads):
     _check(cfg, *_forward_and_backward(st, cfg, heads))
 
 
-@pytest.mark.parametrize("batch,tokens,hq,hkv,d,parts", [(8, 760, 16, 8, 128, 1), (3, 2400, 16, 8, 128, 1), (10, 914, 16, 8, 64, 1), (2, 2700, 16, 8, 128, 2),
-                                                         (1, 6100, 16, 2, 128, 8), (10, 1700, 16, 2, 64, 4), (8, 150, 8, 1, 128, 1)])
-def test_parts_of_the_key_side(st, batch, tokens, hq, hkv, d, parts):
+@pytest.mark.parametrize("lens,hq,hkv,d,parts", [([760] * 8, 16, 8, 128, 1), ([2400] * 3, 16, 8, 128, 1), ([914] * 10, 16, 8, 64, 1), ([2700] * 2, 16, 8, 128, 2),
+                                                 ([6100], 16, 2, 128, 8), ([1700] * 10, 16, 2, 64, 4), ([150] * 8, 8, 1, 128, 1), ([760] * 8, 40, 8, 128, 1),
+                                                 # ragged batches: the longest sequence holds the launch up
+                                                 ([6000] + [300] * 8, 8, 4, 128, 2), ([6000] + [300] * 8, 16, 2, 64, 8), ([3000] + [600] * 10, 16, 8, 64, 2),
+                                                 ([333, 2005, 2327, 387, 925, 1831, 1080, 2878, 503, 1074], 16, 2, 64, 8)])
+def test_parts_of_the_key_side(st, lens, hq, hkv, d, parts):
     """How many ways the key side splits the query heads of a group, as the workspace tells: each part has fp32 sums of its own,
     behind delta, the row statistics and the row tiles of all heads."""
-    cfg = W._assemble("parts", "bf16", hq, hkv, d, [(np.array([tokens // 2]), np.array([tokens - tokens // 2]))] * batch, "grouped", 24)
+    cfg = W._assemble("parts", "bf16", hq, hkv, d, [(np.array([n // 2]), np.array([n - n // 2])) for n in lens], "grouped", 24)
     plan = st.st_plan_create(*ids_to_dev(cfg), cfg.cu_seqlens)
     up = lambda n: (n + 255) // 256 * 256
-    tiles = batch * ((tokens + 63) // 64 + 1)
+    tiles = sum((n + 63) // 64 + 1 for n in lens)
     base = up(cfg.n_tokens * hq * 4) + up(tiles * hq * 1024) + 2 * (up(tiles * hkv * 64 * d * 2) + up(tiles * hq * 64 * d * 2)) + 256
     sums = up(2 * parts * cfg.n_tokens * hkv * d * 4) if parts > 1 else 0
     assert int(st.load_library().st_prefill_bwd_workspace_bytes(plan.handle, hq, hkv, d, st.ST_BF16)) == base + sums
