@@ -226,10 +226,12 @@ st_status st_attn_prefill(void* out, float* lse, const void* q, const void* k, c
 
 /* st_attn_prefill with the rotation of Sec. 3.2 fused in: q and k are UNROTATED and are rotated by
  * positions[token] (device int32 [n_tokens], the stream-local position ids the plan was built
- * from) with base theta_base, as st_rope_apply would -- k on its way into the key tiles, q as the
- * attention kernel loads it -- so neither tensor makes the extra trip through memory.  The angle
- * is reduced in fp64, cos / sin are fp32 (st_rope_apply evaluates them in fp64): a rotated
- * element may differ from st_rope_apply's in its last bf16 bit.  bf16 only (ST_ERR_UNSUPPORTED
+ * from) with base theta_base -- k on its way into the key tiles, q as the attention kernel loads
+ * it -- so neither tensor makes the extra trip through memory.  The angle is reduced in fp64,
+ * cos / sin are fp32 (st_rope_apply evaluates them in fp64): a rotated key may differ from
+ * st_rope_apply's in its last bf16 bit.  A query is rotated and scaled in fp32 and rounded to bf16
+ * once; st_rope_apply and st_attn_prefill round it twice, after the rotation and after the scale.
+ * bf16 only (ST_ERR_UNSUPPORTED
  * for f32: rotate with st_rope_apply); theta_base <= 0 or positions == NULL give
  * ST_ERR_INVALID_ARG.  Everything else as for st_attn_prefill, same workspace. */
 st_status st_attn_prefill_rope(void* out, float* lse, const void* q, const void* k, const void* v,
@@ -259,12 +261,15 @@ st_status st_attn_prefill_ids(void* out, float* lse, const void* q, const void* 
  *   dk, dv       : [N, n_kv_heads, head_dim]   (written; summed over the query heads of a KV group)
  * all of dtype dt, same plan as the forward.  Deterministic (no atomics).
  * ST_BF16: products on the matrix cores (bf16 operands -- P and dS are rounded to bf16 before the
- * second products, as the forward rounds P -- fp32 accumulation); every operand is first gathered
- * into 64-row tiles in the workspace, which therefore holds about 1.1x the bytes of q, k, v, d_out.
+ * second products, as the forward rounds P -- fp32 accumulation).
  * ST_F32: fp32 products and sums (the matrix cores' fp32 instructions); Inf and NaN stay with the
  * pairs that the mask allows, as in the forward.
  * workspace: at least st_prefill_bwd_workspace_bytes(plan, n_q_heads, n_kv_heads, head_dim, dt)
- * bytes, 256-byte aligned.  Errors as for st_attn_prefill, but the tensors need only be aligned to
+ * bytes, 256-byte aligned.  The size depends on the plan, ask for it: ST_BF16 keeps 64-row tiles of
+ * every operand (about 1.1 times the bytes of q, k, v, d_out), ST_F32 4 bytes per token and query
+ * head; and where the query heads of a KV head are split over `parts` workgroups (2 .. 8, for few,
+ * long or ragged sequences) both add 8 * parts * N * n_kv_heads * head_dim bytes of fp32 partial
+ * sums -- with 16 / 2 heads of 128 dims and 8 parts, 1.8 times q, k, v, d_out on top.  Errors as for st_attn_prefill, but the tensors need only be aligned to
  * their elements here (gradients may be slices of a flat buffer).
  * ---------------------------------------------------------------------- */
 size_t st_prefill_bwd_workspace_bytes(const st_plan* plan, int32_t n_q_heads, int32_t n_kv_heads,

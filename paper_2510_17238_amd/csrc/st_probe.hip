@@ -1,7 +1,7 @@
 // Machine probes for the benchmark: what this GPU sustains for the access pattern of the decode kernel and for
 // the instruction the prefill kernel lives on, so that a roofline fraction can be read against a measured ceiling
 // and not only against the data-sheet peak.  They compute nothing of the method.
-//   probe_paged_read_kernel  one wave per workgroup (as the decode kernel); per step a wave reads two 4 KB "key
+//   probe_paged_read_kernel  one wave per workgroup; per step a wave reads two 4 KB "key
 //                            pages" and two 4 KB "value pages" at pseudo-random page indices with the decode
 //                            kernel's per-lane addressing (16 loads of 16 bytes per lane), and folds them with XOR.
 //   probe_mfma_kernel        4 waves per workgroup; every wave issues independent v_mfma_f32_32x32x16_bf16 on

@@ -177,15 +177,15 @@ def test_config3_decode_one_layer(st):
 
 
 def test_config3_decode_one_layer_in_one_call(st):
-    """The same step the way bench.py issues it: st_attn_decode_dual_append stores the token and attends (512-token
-    units chosen by launch size, the token through the split kernel's extra work unit); the whole output, all 32
+    """The same step the way bench.py issues it: st_attn_decode_dual_append stores the token and attends (units of
+    1,024 tokens, chosen by launch size, the token through the split kernel's extra work unit); the whole output, all 32
     sequences, against the oracle."""
     shp = W.config3()
     _decode_full(st, shp, 1, range(shp.batch), seed=33, one_call=True)             # every row of all 32 sequences
 
 
 def test_config5_decode_token_in_one_call(st):
-    """One token of the Qwen3-8B-shaped streaming step (64 streams, caches up to 8K + 16K tokens: 1024-token units), one
+    """One token of the Qwen3-8B-shaped streaming step (64 streams, caches up to 8K + 16K tokens: 4,096-token units), one
     layer, issued as bench.py's streaming-step leg issues it; the whole output, all 64 streams, against the oracle."""
     shp = W.config5()
     _decode_full(st, shp, 1, range(shp.batch), seed=34, one_call=True)             # every row of all 64 streams

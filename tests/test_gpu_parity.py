@@ -439,7 +439,8 @@ def test_prefill_bwd_bf16_tiles(st):
 
 
 def test_prefill_bwd_bf16_agrees_with_plain_kernels(st):
-    """bf16 inputs through the matrix-core backward vs the same values through the fp32 one-thread-per-row kernels."""
+    """bf16 inputs through the bf16 backward vs the same values through the fp32 kernels: two sets of matrix-core kernels that
+    share the segment tables and nothing else (the tests against the oracle are the independent check)."""
     cfg = W.random_prefill(613, 2, 6, (30, 150), (30, 170), 4, 2, 128, "bf16")
     q, k, v = cfg.tensors()
     g = W.normal(np.random.Generator(np.random.PCG64(5)), q.shape, "bf16")
@@ -658,8 +659,9 @@ def test_decode_q_len_8(st):
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("unit", [128, 256, 512, 1024])
 def test_decode_every_unit_size(st, unit, fp8):
-    """The work unit is chosen by launch size (small launches take short units); every size the rule can pick is
-    pinned here on caches that span several units with ragged ends, and gives the same rows."""
+    """The work unit is chosen by launch size (small launches take short units); every size that can be pinned, on caches
+    that span several units with ragged ends, gives the same rows.  (The rule also picks 2,048 and 4,096 tokens, for large
+    launches; those are reached through it, with many sequences over the pages of a few.)"""
     rng = np.random.Generator(np.random.PCG64(413))
     src_lens = np.array([1100, 129, 640]); rsn_lens = np.array([700, 1500, 127]); src_vis = np.array([1025, 128, 0])
     _check_decode(st, rng, 3, 4, 2, 128, src_lens, rsn_lens, src_vis, fp8=fp8, unit_tokens=unit)
