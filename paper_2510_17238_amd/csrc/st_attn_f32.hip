@@ -138,7 +138,7 @@ __device__ __forceinline__ bool prefill_f32_walk(unsigned block, float* __restri
     constexpr int JJ = D / 8, DB = D / 32;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     FwdF32Smem<D>& sm = *reinterpret_cast<FwdF32Smem<D>*>(smem_raw);
-    const unsigned per_item = unsigned(n_q_heads) * (kTileM / kF32Rows);
+    const unsigned per_item = unsigned(n_q_heads) * unsigned(pv.parts32);
     const int rank = int(block / per_item);
     const unsigned rest = block % per_item;
     const int hh = int(rest % unsigned(n_q_heads)), sub = int(rest / unsigned(n_q_heads));
@@ -341,7 +341,7 @@ __device__ __forceinline__ bool bwd_dq_f32_walk(unsigned block, float* __restric
     constexpr int JJ = D / 8, DB = D / 32;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     DqF32Smem<D>& sm = *reinterpret_cast<DqF32Smem<D>*>(smem_raw);
-    const unsigned per_item = unsigned(n_q_heads) * (kTileM / kF32Rows);
+    const unsigned per_item = unsigned(n_q_heads) * unsigned(pv.parts32);
     const int rank = int(block / per_item);
     const unsigned rest = block % per_item;
     const int hh = int(rest % unsigned(n_q_heads)), sub = int(rest / unsigned(n_q_heads));
@@ -525,7 +525,7 @@ __device__ __forceinline__ bool bwd_dkv_f32_walk(unsigned block, float* __restri
     constexpr int JJ = D / 8, DB = D / 32;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     DkvF32Smem<D>& sm = *reinterpret_cast<DkvF32Smem<D>*>(smem_raw);
-    const unsigned per_item = unsigned(n_kv_heads) * (kTileM / kF32Rows) * unsigned(parts);
+    const unsigned per_item = unsigned(n_kv_heads) * unsigned(pv.parts32) * unsigned(parts);
     // (early keys are seen by the most rows: the table, sorted by the forward's cost, is walked backwards)
     const int rank = pv.m_max - 1 - int(block / per_item);
     const unsigned rest = block % per_item;
@@ -745,7 +745,7 @@ static st_status with_smem(K kernel, size_t bytes) {
 
 st_status launch_prefill_f32(float* out, float* lse, const float* q, const float* k, const float* v, const PlanView& pv, int n_q_heads,
                              int n_kv_heads, int head_dim, float scale, hipStream_t s) {
-    const int64_t blocks = int64_t(pv.m_max) * n_q_heads * (kTileM / kF32Rows);
+    const int64_t blocks = int64_t(pv.m_max) * n_q_heads * pv.parts32;
     if (blocks > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_prefill: grid too large");
     auto run = [&](auto dtag) -> st_status {
         constexpr int D = decltype(dtag)::value;
@@ -762,7 +762,7 @@ st_status launch_prefill_f32(float* out, float* lse, const float* q, const float
 st_status launch_bwd_f32(float* dq, float* dk, float* dv, float* delta, const float* d_out, const float* q, const float* k, const float* v,
                          const float* out, const float* lse, const PlanView& pv, int n_q_heads, int n_kv_heads, int head_dim, float scale,
                          int64_t n_tokens, int parts, float* partial, hipStream_t s) {
-    const int64_t qblocks = int64_t(pv.m_max) * n_q_heads * (kTileM / kF32Rows), kblocks = int64_t(pv.m_max) * n_kv_heads * parts * (kTileM / kF32Rows);
+    const int64_t qblocks = int64_t(pv.m_max) * n_q_heads * pv.parts32, kblocks = int64_t(pv.m_max) * n_kv_heads * parts * pv.parts32;
     const int64_t partial_stride = n_tokens * n_kv_heads * head_dim;
     if (qblocks > 0x7fffffff) return fail(ST_ERR_SHAPE, "st_attn_prefill_bwd: grid too large");
     auto run = [&](auto dtag) -> st_status {

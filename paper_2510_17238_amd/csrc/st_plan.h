@@ -1,5 +1,6 @@
 // Device-resident segment tables of one packed batch (internal view of st_plan).
 #pragma once
+#include <algorithm>
 #include <vector>
 
 #include "st_internal.h"
@@ -45,6 +46,11 @@ struct PlanView {  // what kernels need
     // then the reasoning tiles, then spare ones.
     const TileInfo* tiles;     // [pack_tiles]
     int32_t pack_tiles;
+    // 32-row parts of a work item that some sequence has rows for: 4, fewer where no sequence has more than 96 tokens.  A kernel whose
+    // workgroups take a part each launches no more of them -- one that finds no row still waits for its item in a place on the
+    // chip: 300 sequences of 33 tokens, 32 / 8 heads of 64 dims in bf16 128 us with four parts, 75 with two; 64 sequences of one
+    // token, 16 / 8 heads of 128 in fp32 39 with four, 18 with one.
+    int32_t parts32;
 };
 
 // fp32 attention (st_attn_f32.hip); the callers have checked the arguments and ordered `s` behind the plan
@@ -79,5 +85,5 @@ struct st_plan {
     // Orders `s` behind the build of the tables (nothing to do on the stream that built them).
     hipError_t wait_built(hipStream_t s) const { return (s == stream || !built) ? hipSuccess : hipStreamWaitEvent(s, built, 0); }
 
-    st::PlanView view() const { return st::PlanView{cu, n_src, perm, vis, sorted, m_max, tiles, pack_tiles}; }
+    st::PlanView view() const { return st::PlanView{cu, n_src, perm, vis, sorted, m_max, tiles, pack_tiles, std::max((std::min(longest, st::kTileM) + 31) / 32, 1)}; }
 };

@@ -233,10 +233,11 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     // workgroup -> (work item, part of its rows, set of NH x head_waves query heads of one KV head)
     const int heads_here = NH * head_waves;
     const int n_sets = n_q_heads / heads_here;
-    const int per_item = n_sets * head_waves;
+    const int row_parts = item_parts(pv, head_waves);
+    const int per_item = n_sets * row_parts;
     const int rank = blockIdx.x / per_item;
     const int rem = blockIdx.x % per_item;
-    const int hh0 = rem % n_sets, sub = head_waves - 1 - rem / n_sets;              // (later rows have the longer loops: first)
+    const int hh0 = rem % n_sets, sub = row_parts - 1 - rem / n_sets;              // (later rows have the longer loops: first)
     const int group = n_q_heads / n_kv_heads;
     const int hk = hh0 % n_kv_heads;                // consecutive workgroups -> consecutive KV heads
     const int hq0 = hk * group + heads_here * (hh0 / n_kv_heads) + NH * (wave % head_waves);
@@ -823,7 +824,7 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
             ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem)));
             prof_begin(kProfPrefillAttn, s);
             for (int rep = 0; rep < prof_repeat(); ++rep)
-                hipLaunchKernelGGL(kern, dim3((unsigned)(blocks / NH)), dim3(256), smem, s, (uint16_t*)out,
+                hipLaunchKernelGGL(kern, dim3((unsigned)(blocks / (NH * head_waves) * item_parts(pv, head_waves))), dim3(256), smem, s, (uint16_t*)out,
                                    lse, (const uint16_t*)q, kc, vc, pv, n_q_heads, n_kv_heads, scale_log2, (const float2*)tab, head_waves);
             prof_end(kProfPrefillAttn, s);
             return ST_OK;

@@ -52,9 +52,10 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_sets = n_q_heads / head_waves;
-    const int rank = blockIdx.x / n_q_heads;
-    const int rem = blockIdx.x % n_q_heads;
-    const int hh0 = rem % n_sets, sub = head_waves - 1 - rem / n_sets;              // (later rows have the longer loops: first)
+    const int row_parts = item_parts(pv, head_waves);
+    const int rank = blockIdx.x / (n_sets * row_parts);
+    const int rem = blockIdx.x % (n_sets * row_parts);
+    const int hh0 = rem % n_sets, sub = row_parts - 1 - rem / n_sets;              // (later rows have the longer loops: first)
     const int group = n_q_heads / n_kv_heads;
     const int hk = hh0 % n_kv_heads;
     const int hq = hk * group + head_waves * (hh0 / n_kv_heads) + wave % head_waves;
@@ -806,7 +807,7 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
         const int head_waves = group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
         prof_begin(kProfBwdDq, s);
         for (int rep = 0; rep < prof_repeat(); ++rep)
-        hipLaunchKernelGGL((bwd_dq_mfma_kernel<HD>), dim3((unsigned)qblocks), dim3(256), smem_q, s, (uint16_t*)dq, (const uint16_t*)d_out,
+        hipLaunchKernelGGL((bwd_dq_mfma_kernel<HD>), dim3((unsigned)(qblocks / head_waves * item_parts(pv, head_waves))), dim3(256), smem_q, s, (uint16_t*)dq, (const uint16_t*)d_out,
                            (const uint16_t*)q, at(L.krows), at(L.vrows), lse, delta, pv, n_q_heads, n_kv_heads, scale, head_waves);
         prof_end(kProfBwdDq, s);
         prof_begin(kProfBwdDkv, s);

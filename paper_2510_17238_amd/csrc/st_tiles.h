@@ -96,6 +96,8 @@ struct TrOffsets {
     }
 };
 
+// parts of kTileM / head_waves rows of an item that a launch has workgroups for
+__host__ __device__ inline int item_parts(const PlanView& pv, int head_waves) { return (pv.parts32 * head_waves + 3) / 4; }
 // Rows [sub * part_rows, + part_rows) of a work item as an item of their own, with the extents as the plan builds them
 // (n_rows <= 0: no such rows).
 __device__ __forceinline__ WorkItem item_part(WorkItem it, const PlanView& pv, int sub, int part_rows) {

@@ -98,3 +98,14 @@ def test_parts_of_the_key_side(st, lens, hq, hkv, d, parts):
     base = up(cfg.n_tokens * hq * 4) + up(tiles * hq * 1024) + 2 * (up(tiles * hkv * 64 * d * 2) + up(tiles * hq * 64 * d * 2)) + 256
     sums = up(2 * parts * cfg.n_tokens * hkv * d * 4) if parts > 1 else 0
     assert int(st.load_library().st_prefill_bwd_workspace_bytes(plan.handle, hq, hkv, d, st.ST_BF16)) == base + sums
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d", [("bf16", 8, 2, 128), ("bf16", 4, 2, 64), ("bf16", 3, 3, 128), ("f32", 4, 2, 128), ("f32", 2, 1, 64)])
+@pytest.mark.parametrize("longest", [1, 32, 33, 64, 65, 96, 97])
+def test_no_sequence_fills_an_item(st, dtype, hq, hkv, d, longest):
+    """Launches without workgroups for the parts of an item that no sequence has rows for: all of the longest sequence in one stream,
+    in the other, or in both; sequences of one token beside it."""
+    split = lambda s, r: (np.array([s], dtype=np.int64), np.array([r], dtype=np.int64))
+    lists = [split(longest, 0), split(0, longest), split(longest // 2, longest - longest // 2), split(1, 0), split(0, 1)]
+    cfg = W._assemble("short", dtype, hq, hkv, d, lists, "grouped", 25 + longest)
+    _check(cfg, *_forward_and_backward(st, cfg))
