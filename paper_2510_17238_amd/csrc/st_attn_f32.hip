@@ -18,7 +18,7 @@
 // quarter of the row's -- what a small problem is bound by -- and the waves never wait for each other inside the loop.
 // Bound by those chains: one block of 32 x 32 x 128 is 128 instructions of 64 cycles in the forward, and the next block's
 // operands are requested a phase ahead, but a wave has few blocks, the backward's registers leave one wave per SIMD, and the
-// workgroups end in two uneven rounds -- the matrix pipe (fp32: 157 TFLOP/s) is busy 36 to 45 % of the cycles.
+// workgroups end in two uneven rounds -- the matrix pipe (fp32: 157 TFLOP/s) is busy 30 to 37 % of the cycles.
 // Two sequences of about 900 tokens, 16 / 8 heads of 128 dims: forward 2.86 ms (one thread per row, vector ALUs) -> 0.090 ms
 // (58 TFLOP/s of unmasked flop), gradients 19.8 -> 0.35 ms; 128 tokens, 2 heads of 64 dims: 200 -> 8 us.
 #include <math.h>
