@@ -160,6 +160,15 @@ __device__ __forceinline__ void rotate_fragments(bf16x8 (&f)[KS], int off, const
     }
 }
 
+// Unit of a workgroup among the nc of its (sequence, KV head).  Consecutive workgroups go to the eight XCDs in turn: where nc shares a
+// factor g with 8, the same unit of every head would land on the same 8 / g of them -- and with caches of unlike length it is the
+// first units that have tokens (128 sequences of 300 + 300 tokens and one of 12,000, eight slots a head: 163 us, with 72 us of
+// work).  So the units of a head are turned by one place whenever the heads have been once around the XCDs.
+__device__ __forceinline__ int unit_of(unsigned block, int nc) {
+    const unsigned bh = block / unsigned(nc), i = block % unsigned(nc), g = min(unsigned(nc & -nc), 8u);
+    return int(g == 1 ? i : (i + bh * g / 8) % unsigned(nc));
+}
+
 // The decode step with 17 .. 32 query rows q_len * G per sequence and KV head (several tokens in one call, or wide groups) on
 // v_mfma_f32_32x32x16_bf16, whose 32 columns are the query rows.  As in the 16-row kernel below the bytes in flight are what
 // counts -- 4 D bytes per token against 128 flop per byte: the page ids of a wave's run are fetched once, the 16 KB of the next
@@ -182,8 +191,8 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void decode_split32_kernel(Dec
     float2* s_rot = reinterpret_cast<float2*>(s_q + KS * 64);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nc = a.ncs + a.ncr;
-    const int c = int(blockIdx.x % unsigned(nc));
-    const unsigned bh = blockIdx.x / unsigned(nc);
+    const unsigned bh = blockIdx.x / unsigned(nc);       // (sequence, KV head)
+    const int c = unit_of(blockIdx.x, nc);
     const int h = int(bh % unsigned(a.n_kv_heads));
     const int b = int(bh / unsigned(a.n_kv_heads));
     const bool is_src = c < a.ncs;
@@ -508,8 +517,8 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void decode_split16_kernel(Dec
     const WaveStamp stamp(a);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nc = a.ncs + a.ncr + a.append;             // (append: one more slot per sequence and head, the new token's)
-    const int c = int(blockIdx.x % unsigned(nc));
-    const unsigned bh = blockIdx.x / unsigned(nc);
+    const unsigned bh = blockIdx.x / unsigned(nc);       // (sequence, KV head)
+    const int c = unit_of(blockIdx.x, nc);
     const int h = int(bh % unsigned(a.n_kv_heads));
     const int b = int(bh / unsigned(a.n_kv_heads));
     const bool is_src = c < a.ncs;
@@ -812,8 +821,8 @@ __global__ __launch_bounds__(64 * kSplitWaves, 3) void decode_split16_fp8_kernel
     float2* s_rot = reinterpret_cast<float2*>(smem_raw);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nc = a.ncs + a.ncr;
-    const int c = int(blockIdx.x % unsigned(nc));
-    const unsigned bh = blockIdx.x / unsigned(nc);
+    const unsigned bh = blockIdx.x / unsigned(nc);       // (sequence, KV head)
+    const int c = unit_of(blockIdx.x, nc);
     const int h = int(bh % unsigned(a.n_kv_heads));
     const int b = int(bh / unsigned(a.n_kv_heads));
     const bool is_src = c < a.ncs;

@@ -83,3 +83,16 @@ def test_scores_that_fall_for_long(st):
     expect = sum(w @ x[:20, 0] for x in v) / (2 * w.sum())
     assert np.abs(to_f64(out[0, :, 0]) - expect).max() <= 2e-2
     assert np.abs(to_f64(lse[0, :, 0]) - np.log(2 * w.sum())).max() <= 1e-3
+
+
+@pytest.mark.parametrize("units", [2, 4, 6, 8, 12, 16])
+@pytest.mark.parametrize("q_len,hq,hkv,d,fp8", [(1, 4, 2, 128, False), (8, 8, 2, 64, False), (2, 8, 2, 128, True)])
+def test_units_of_a_head_in_turn(st, units, q_len, hq, hkv, d, fp8):
+    """Unit counts that share a factor with the eight XCDs: the units of a head then begin at another one from head to head.  Every
+    unit of every head is still taken once: eleven sequences, one of them full, the others of a unit or two."""
+    rng = np.random.Generator(np.random.PCG64(490 + units))
+    src, rsn = rng.integers(1, 200, 11), rng.integers(q_len, 200, 11)
+    src[3], rsn[3] = 128, 128 * (units - 1)
+    src = np.minimum(src, 128)                                     # one unit of the source, the others of the reasoning cache
+    rsn = np.minimum(rsn, 128 * (units - 1))
+    _check_decode(st, rng, 11, hq, hkv, d, src, rsn, src, q_len=q_len, fp8=fp8, unit_tokens=128)
