@@ -163,7 +163,7 @@ __device__ __forceinline__ void rotate_fragments(bf16x8 (&f)[KS], int off, const
 // Unit of a workgroup among the nc of its (sequence, KV head).  Consecutive workgroups go to the eight XCDs in turn: where nc shares a
 // factor g with 8, the same unit of every head would land on the same 8 / g of them -- and with caches of unlike length it is the
 // first units that have tokens (128 sequences of 300 + 300 tokens and one of 12,000, eight slots a head: 163 us, with 72 us of
-// work).  So the units of a head are turned by one place whenever the heads have been once around the XCDs.
+// work; now 97).  So the units of a head are turned by one place whenever the heads have been once around the XCDs.
 __device__ __forceinline__ int unit_of(unsigned block, int nc) {
     const unsigned bh = block / unsigned(nc), i = block % unsigned(nc), g = min(unsigned(nc & -nc), 8u);
     return int(g == 1 ? i : (i + bh * g / 8) % unsigned(nc));
@@ -180,7 +180,8 @@ __device__ __forceinline__ int unit_of(unsigned block, int nc) {
 // accumulator and cost 4 % of precision against a running maximum; this gives 4 % more.  Error of the rows against 64 bits, 64
 // sequences of up to 8K + 16K tokens: 2.76e-3 with a running maximum over 512 tokens, 2.88e-3, 2.63e-3.  Time: 0 to 2 %.)
 // 64 sequences of up to 8K + 16K tokens, 8 tokens x 4 heads, 8 KV heads of 128 dims (3.78 GB of cache), with the merge
-// of the partial results: 1.50 ms with loads requested when they were needed, 0.89 with a wave per unit of 1,024 tokens, 0.75 ms.
+// of the partial results: 1.50 ms with loads requested when they were needed, 0.89 with a wave per unit of 1,024 tokens, 0.75 with four
+// waves and longer ones, 0.71 with the units spread over the XCDs (unit_of).
 template <int D, bool STREAM_KEYS>
 __global__ __launch_bounds__(64 * kSplitWaves, 2) void decode_split32_kernel(DecodeArgs a) {
     constexpr int KS = D / 16, DB = D / 32, KCH = D / 8;
@@ -1524,7 +1525,8 @@ static inline bool small_decode(int64_t batch, int hkv, int d, int max_src, int 
 // cache) no more than a fifth longer than its caches.  A cache a little longer than a unit, or than the other cache, makes a
 // long and a short workgroup, and the launch ends with the long ones -- 64 sequences of 5K + 5K tokens, 8 heads of 128 dims
 // 455 with 4,096, 398 with 1,024; 8-bit, 32 / 8 heads 271 and 228; 20 of 3,000 + 900 tokens, 16 rows 78 with 4,096, 60 with 1,024;
-// but 64 of 700 + 700, 16 rows 85 with 512, 69 with a unit for each cache.
+// but 64 of 700 + 700, 16 rows 85 with 512, 69 with a unit for each cache.  (Only the bounds are known here: a few long caches among
+// many short ones would take longer units, 128 of 300 tokens with one of 12,000 72 with 4,096 against 97.)
 // A few sequences are bound by the walk over a unit and not by bandwidth: 256 tokens up to 256 units of 512 (one sequence of 4K
 // tokens: 13.5 against 15.3), 128 up to 32 units (2K tokens: 11.7 against 15.3).
 static inline int decode_unit_tokens(int64_t batch, int hkv, int rows, int max_src, int max_rsn, int pinned, bool fp8 = false) {
