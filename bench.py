@@ -203,7 +203,7 @@ def bench_prefill_step(st, torch, W, cfg, steps, warmup, use_graph=True, fused_r
     torch.cuda.synchronize()
     st.st_profile_enable(False)
     kern_ms, n_rec = st.st_profile_read(st.ST_PROF_PREFILL_ATTN)
-    pack_ms, _ = st.st_profile_read(st.ST_PROF_TILE_PACK)
+    pack_ms, n_pack = st.st_profile_read(st.ST_PROF_TILE_PACK)          # (none where the attention kernel gathers its rows itself)
     st.st_profile_read(st.ST_PROF_DECODE_SPLIT)
     assert n_rec == n_prof
     # every stage alone (events on the stream; the launches of one stage back to back)
@@ -218,7 +218,7 @@ def bench_prefill_step(st, torch, W, cfg, steps, warmup, use_graph=True, fused_r
         "decode_token_with_append": _event_ms(torch, lambda: (cr.appended_len.copy_(len_r0),
                                                               st.st_attn_decode_dual_append(q_tok, k_tok, v_tok, caches, src_vis, rsn_len, max_s, max_r, theta_base=cfg.theta,
                                                                                             out=out_tok, workspace=dec_ws)), stage_reps),
-        "tile_pack": pack_ms, "attention": kern_ms,
+        **({"tile_pack": pack_ms} if n_pack else {}), "attention": kern_ms,
     }
     stage_ms["append_source_chunk"] = max(stage_ms["append_source_chunk"] - stage_ms.pop("length_reset_only"), 1e-6)
     # the timed steps, two ways: the whole step (two streams) recorded once into a HIP graph and replayed -- every
@@ -782,11 +782,12 @@ def _prefill_objects(pre, name, fused_rope):
               "ms": {k: round(v, 5) for k, v in ms.items()},
               "rope_qk": {"roofline": _hbm_roofline("rope_kernel<bf16, 128> (st_rope_apply_qk: q and k of all tokens in one launch, read + write)", pre["stage_bytes"]["rope_qk"],
                                                     ms["rope_qk"], f"rope_qk_kernel@{name}")},
-              "tile_pack": {"roofline": _hbm_roofline("tile_pack_kernel (k, v rows gathered into K tiles and V^T tiles)", pre["stage_bytes"]["tile_pack"],
-                                                      ms["tile_pack"], f"tile_pack_kernel@{name}")},
               "append_source_chunk": {"roofline": _hbm_roofline("kv_append_kernel (64-token source chunk per sequence, alone on the GPU)",
                                                                 pre["stage_bytes"]["append_source_chunk"], ms["append_source_chunk"], None,
                                                                 "a launch of a few MB: bound by its own latency, not by bandwidth")}}
+    if "tile_pack" in ms and pre["two_heads"] and not fused_rope:
+        stages["tile_pack"] = {"roofline": _hbm_roofline("tile_pack_kernel (k, v rows gathered into K tiles and V^T tiles)", pre["stage_bytes"]["tile_pack"],
+                                                         ms["tile_pack"], f"tile_pack_kernel@{name}")}
     return tflops_step, roof, stages
 
 

@@ -10,20 +10,20 @@
 // index with a per-row limit, tiles past `total` are never read.
 //
 // Kernels:
-//   tile_pack_kernel   bf16, O(N) bytes: gathers the K rows and the TRANSPOSED V rows of every
-//                         64-row key tile (stream-compact order) into contiguous 16 KB blocks, so
-//                         that the attention kernel streams tiles with plain linear loads and needs
-//                         no per-row token lookup and no transpose in its inner loop.
 //   prefill_attn_kernel<D, NH, ROPE>
 //                         bf16, 4 waves of 32 query rows x NH query heads (1 or 2) of one KV head -- 128 rows of the
-//                         same head(s), or fewer rows of more heads (head_waves); K and V^T
-//                         tiles copied asynchronously into swizzled LDS buffers; QK^T and PV on
+//                         same head(s), or fewer rows of more heads (head_waves); K and V
+//                         tiles copied asynchronously into swizzled LDS buffers, with one head per wave straight from the
+//                         rows of the tensors (no packed copy: 4 x 4K tokens 272 -> 257 us, 96 short sequences
+//                         486 -> 461, results the same bit for bit); QK^T and PV on
 //                         v_mfma_f32_32x32x16_bf16, fp32 softmax state.  Both products are computed
 //                         TRANSPOSED (S^T = K Q^T, O^T = V^T P^T): a lane then owns one query row, so a
 //                         row sum is an in-register reduction plus one exchange with lane^32, and the S^T
 //                         accumulators are already laid out as the B operand of the second product.  The
 //                         loop is software-pipelined by hand (see the kernel).
-//   rope_table_kernel, tile_pack_rope_kernel
+//   tile_pack_kernel      the two-head form's tiles: K rows and TRANSPOSED V rows of every 64-row key tile (stream-compact order)
+//                         gathered into contiguous 16 KB blocks.
+//   rope_table_kernel, key_pack_rope_kernel
 //                         the fused rotation of st_attn_prefill_rope: (cos, sin) of every token once, keys rotated
 //                         on their way into the key tiles; the attention kernel's ROPE form rotates its query rows.
 // (fp32 tensors take the kernel of st_attn_f32.hip, over the same work items.)
@@ -89,12 +89,10 @@ __global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ ta
     }
 }
 
-// Step 2: tile_pack_kernel for UNROTATED keys -- every key row is rotated with its table row on its way into the row
-// tile.  A thread owns two rows x one pair of 8-dim pieces (dims 8 cp .. + 7 and D/2 + the same).
+// Step 2: UNROTATED keys into packed row tiles -- every key row is rotated with its table row on its way.  A thread owns two rows x one pair of 8-dim pieces (dims 8 cp .. + 7 and D/2 + the same).
 template <int D>
-__global__ __launch_bounds__(256) void tile_pack_rope_kernel(uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
-                                                            const float2* __restrict__ tab, const uint16_t* __restrict__ k,
-                                                            const uint16_t* __restrict__ v, PlanView pv, int n_kv_heads) {
+__global__ __launch_bounds__(256) void key_pack_rope_kernel(uint16_t* __restrict__ kc, const float2* __restrict__ tab, const uint16_t* __restrict__ k,
+                                                           PlanView pv, int n_kv_heads) {
     constexpr int KCH = D / 8, CP = KCH / 2;
     constexpr int PER_THREAD = kTileN * CP / 256;
     const int tile = blockIdx.x / n_kv_heads;
@@ -105,7 +103,6 @@ __global__ __launch_bounds__(256) void tile_pack_rope_kernel(uint16_t* __restric
     const int tid = threadIdx.x;
     const uint32_t row_stride = uint32_t(n_kv_heads) * D;
     uint16_t* kdst = kc + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
-    uint16_t* vdst = vc + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
 #pragma unroll
     for (int u = 0; u < PER_THREAD; ++u) {
         const int c = tid + 256 * u;
@@ -134,36 +131,54 @@ __global__ __launch_bounds__(256) void tile_pack_rope_kernel(uint16_t* __restric
         *reinterpret_cast<u32x4*>(kdst + lr * D + (cp ^ swizzle_key<2 * D>(lr)) * 8) = lo;
         *reinterpret_cast<u32x4*>(kdst + lr * D + ((cp + CP) ^ swizzle_key<2 * D>(lr)) * 8) = hi;
     }
-    // V: as in tile_pack_kernel -- 8 keys x 8 d per thread (16-byte loads), transposed in registers to 8 d x 8 keys
-    const int kvb = tid & 7, dq = tid >> 3;
-    if (dq < D / 8) {
-        u32x4 vreg[8];
+}
+
+// V^T tiles (blockIdx.y = 0: [D][64 rows], swizzled) and row tiles of K as it is (1), for the two-head form: with sequences of 8K tokens and
+// more a tile is copied into LDS a hundred times and more, and 16 KB in one piece and operands of one LDS read cost the attention less
+// than rows looked up and read transposed (8 x 16K tokens, 32 / 8 heads: 11.89 ms with this pass over memory, 12.04 with gathered
+// rows, 12.0 with packed row tiles of V).
+template <int D>
+__global__ __launch_bounds__(256) void tile_pack_kernel(uint16_t* __restrict__ vc, const uint16_t* __restrict__ v, uint16_t* __restrict__ kc,
+                                                        const uint16_t* __restrict__ k, PlanView pv, int n_kv_heads) {
+    const int tile = blockIdx.x / n_kv_heads, h = blockIdx.x % n_kv_heads;
+    const TileInfo info = pv.tiles[tile];
+    if (info.valid == 0) return;                    // spare tile of a sequence: never read
+    const int base = info.base, valid = info.valid;
+    const uint32_t row_stride = uint32_t(n_kv_heads) * D;
+    const size_t at = (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
+    if (blockIdx.y == 1) {
+        pack_rows<D>(kc + at, k, pv.perm + base, valid, row_stride, uint32_t(h), [](int, uint32_t, const u32x4&) {});
+        return;
+    }
+    // 8 keys x 8 d per thread (16-byte loads), transposed in registers to 8 d x 8 keys (16-byte stores)
+    const int kvb = threadIdx.x & 7, dq = threadIdx.x >> 3;
+    if (dq >= D / 8) return;
+    u32x4 vreg[8];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int row = kvb * 8 + r;
-            vreg[r] = u32x4{0u, 0u, 0u, 0u};
-            if (row < valid) vreg[r] = *reinterpret_cast<const u32x4*>(v + (uint32_t(pv.perm[base + row]) * row_stride + uint32_t(h) * D + dq * 8));
+    for (int r = 0; r < 8; ++r) {
+        const int row = kvb * 8 + r;
+        vreg[r] = u32x4{0u, 0u, 0u, 0u};
+        if (row < valid) vreg[r] = *reinterpret_cast<const u32x4*>(v + (uint32_t(pv.perm[base + row]) * row_stride + uint32_t(h) * D + dq * 8));
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {                   // word w of every row holds d = 2 w and 2 w + 1
+        u32x4 even, odd;
+#pragma unroll
+        for (int pr = 0; pr < 4; ++pr) {
+            const uint32_t a = vreg[2 * pr][w], bb = vreg[2 * pr + 1][w];
+            even[pr] = __builtin_amdgcn_perm(bb, a, 0x05040100u);   // low halves
+            odd[pr] = __builtin_amdgcn_perm(bb, a, 0x07060302u);    // high halves
         }
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            u32x4 even, odd;
-#pragma unroll
-            for (int pr = 0; pr < 4; ++pr) {
-                const uint32_t a = vreg[2 * pr][w], bb = vreg[2 * pr + 1][w];
-                even[pr] = __builtin_amdgcn_perm(bb, a, 0x05040100u);   // low halves
-                odd[pr] = __builtin_amdgcn_perm(bb, a, 0x07060302u);    // high halves
-            }
-            const int d0 = dq * 8 + 2 * w;
-            *reinterpret_cast<u32x4*>(vdst + d0 * kTileN + (kvb ^ swizzle_key<2 * kTileN>(d0)) * 8) = even;
-            *reinterpret_cast<u32x4*>(vdst + (d0 + 1) * kTileN + (kvb ^ swizzle_key<2 * kTileN>(d0 + 1)) * 8) = odd;
-        }
+        const int d0 = dq * 8 + 2 * w;
+        *reinterpret_cast<u32x4*>(vc + at + d0 * kTileN + (kvb ^ swizzle_key<2 * kTileN>(d0)) * 8) = even;
+        *reinterpret_cast<u32x4*>(vc + at + (d0 + 1) * kTileN + (kvb ^ swizzle_key<2 * kTileN>(d0 + 1)) * 8) = odd;
     }
 }
 
 template <int D, int STAGES>
 struct PipeSmem {
-    uint16_t k[STAGES][kTileN * D];
-    uint16_t vt[STAGES][D * kTileN];
+    uint16_t k[STAGES][kTileN * D], v[STAGES][kTileN * D];       // row tiles (three stages: of V^T)
+    unsigned char tokens[STAGES == 2 ? RowGather<D>::kBytes : 16];       // (gathered rows)
 };
 // --------------------------------------------------------------------------
 // The attention kernel (bf16): NH = 1 or 2 query heads of one KV head per workgroup.
@@ -213,13 +228,14 @@ constexpr float kRiseLog2 = 24.f;
 template <int D, int NH, bool ROPE>
 __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint16_t* __restrict__ out, float* __restrict__ lse,
                                                                    const uint16_t* __restrict__ q,
-                                                                   const uint16_t* __restrict__ kc,
-                                                                   const uint16_t* __restrict__ vc, PlanView pv,
+                                                                   const uint16_t* __restrict__ k,
+                                                                   const uint16_t* __restrict__ v, PlanView pv,
                                                                    int n_q_heads, int n_kv_heads, float scale_log2,
                                                                    const float2* __restrict__ rope_tab, int head_waves) {
     constexpr int KS = D / 16, DB = D / 32, SB = kTileN / 32;
     constexpr int TILE = kTileN * D;
     constexpr int STAGES = NH == 2 ? 3 : 2;
+    constexpr bool PACKED_V = NH == 2, PACKED_K = PACKED_V || ROPE;
     constexpr bool EARLY_K = STAGES == 3;          // K(t + 2) has landed when tile t starts: its first fragments may be read a phase early
     constexpr int PER = 16 / KS;                   // score elements of vector work per matrix instruction (both phases)
     constexpr int kPF = 3;                         // operand fragments read ahead
@@ -247,19 +263,45 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     const int n_tiles = it.a_total + it.b_total;
 
     constexpr int NL = TILE * 2 / 1024 / 4;         // 1 KB copies per wave per tile
-    // a copy instruction takes the tile's address from scalar registers and one 32-bit byte offset per lane
-    const uint16_t* kc_head = kc + size_t(hk) * pv.pack_tiles * TILE;
-    const uint16_t* vc_head = vc + size_t(hk) * pv.pack_tiles * TILE;
+    // K and V tiles: packed ones (NH = 2: K rows, V^T; ROPE: the rotated K rows), each a linear copy, or rows gathered from the tensor.
+    // A copy instruction takes its base from scalar registers and one 32-bit byte offset per lane.
+    const uint16_t* k_head = PACKED_K ? k + size_t(hk) * pv.pack_tiles * TILE : k + hk * D;
+    const uint16_t* v_head = PACKED_V ? v + size_t(hk) * pv.pack_tiles * TILE : v + hk * D;
     const uint32_t lane_off = uint32_t(wave) * (NL * 1024) + uint32_t(lane) * 16;
+    const RowGather<D> rows(sm.tokens, wave, lane, uint32_t(n_kv_heads) * (2 * D));
     auto tile_of = [&](int ti) {
         ti = min(ti, n_tiles - 1);                   // past the end: fetch the last tile again (never used)
         return ti < it.a_total ? it.tile_a0 + ti : it.tile_b0 + (ti - it.a_total);
     };
+    auto copy_tokens = [&](int ti) {
+        const int t = min(ti, n_tiles - 1);
+        const bool in_a = t < it.a_total;
+        rows.copy_tokens(pv.perm + (in_a ? it.a_base : it.b_base), (in_a ? t : t - it.a_total) * kTileN, (in_a ? it.n_stream : it.n_src) - 1, ti);
+    };
     const uint32_t lds_k0 = uint32_t(uintptr_t(&sm.k[0][0])) + uint32_t(wave) * (NL * 1024);
-    const uint32_t lds_v0 = uint32_t(uintptr_t(&sm.vt[0][0])) + uint32_t(wave) * (NL * 1024);
-    auto issue_k = [&](int ti, int stage) { async_copy_rows<NL>(kc_head + size_t(tile_of(ti)) * TILE, lane_off, lds_k0 + stage * (TILE * 2)); };
-    auto issue_v = [&](int ti, int stage) { async_copy_rows<NL>(vc_head + size_t(tile_of(ti)) * TILE, lane_off, lds_v0 + stage * (TILE * 2)); };
-    // The rows' tokens, then their queries and the first key tile, then the other copies: a wait for an ordinary load also waits
+    const uint32_t lds_v0 = uint32_t(uintptr_t(&sm.v[0][0])) + uint32_t(wave) * (NL * 1024);
+    // byte offsets of the lane's pieces of a tile (gathered rows): K's, and V's of the same tile an iteration later
+    uint32_t off_k[NL], off_v[NL];
+    auto issue_k = [&](int ti, int stage) {
+        if constexpr (PACKED_K) async_copy_rows<NL>(k_head + size_t(tile_of(ti)) * TILE, lane_off, lds_k0 + stage * (TILE * 2));
+        else RowGather<D>::copy(RowGather<D>::base(k_head), off_k, lds_k0 + stage * (TILE * 2));
+    };
+    auto issue_v = [&](int ti, int stage) {
+        if constexpr (PACKED_V) async_copy_rows<NL>(v_head + size_t(tile_of(ti)) * TILE, lane_off, lds_v0 + stage * (TILE * 2));
+        else RowGather<D>::copy(RowGather<D>::base(v_head), off_v, lds_v0 + stage * (TILE * 2));
+    };
+    // offsets of tile ti as K's (or V's, where K is packed); V's are K's of an iteration ago
+    auto next_offsets = [&](int ti) {
+        if constexpr (PACKED_K) rows.offsets(off_v, ti);
+        else rows.offsets(off_k, ti);
+    };
+    auto keep_offsets = [&]() {
+        if constexpr (!PACKED_K) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) off_v[i] = off_k[i];
+        }
+    };
+    // The tokens of the rows and of the first tiles, then the queries and the first key tile, then the other copies: a wait for an ordinary load also waits
     // for the copies in flight (they are counted alike), so only what the first scores need is asked for before the queries
     // are there.
     const int row_in_tile = (wave / head_waves) * 32 + n;
@@ -267,6 +309,17 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     const int my_row = it.row0 + min(row_in_tile, it.n_rows - 1);
     const int tok_q = pv.perm[it.a_base + my_row];
     const int my_vis = pv.vis[it.a_base + my_row];
+    constexpr int kAhead = PACKED_K ? 1 : 2;         // an iteration needs the offsets of the tile this far on
+    if constexpr (!PACKED_V) {
+#pragma unroll
+        for (int ti = 0; ti <= kAhead; ++ti) copy_tokens(ti);
+        {
+            int t = tok_q;
+            asm volatile("" : "+v"(t));
+        }
+        wait_vmcnt<0>();                             // (the rows' own tokens are waited for in any case, and nothing else is under way)
+        next_offsets(0);
+    }
 
     bf16x8 qf[NH][KS];
     {
@@ -277,7 +330,7 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
             for (int j = 0; j < KS; ++j) qf[h][j] = *reinterpret_cast<const bf16x8*>(qp + h * D + 16 * j);
     }
     // copy order (tile x lives in buffer x % STAGES):
-    //   three buffers: K0 | V0 K1 K2 V1 | K3 V2 | K4 V3 | ...   K two tiles ahead, V^T one
+    //   three buffers: K0 | V0 K1 K2 V1 | K3 V2 | K4 V3 | ...   K two tiles ahead, V one
     //   two buffers:   K0 | V0 K1       | V1 K2 | V2 K3 | ...   one tile ahead
     issue_k(0, 0);
 #pragma unroll
@@ -288,8 +341,11 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
             asm volatile("" : "+v"(t));
             qf[h][j] = __builtin_bit_cast(bf16x8, t);
         }
+    keep_offsets();
     issue_v(0, 0);
+    if constexpr (!PACKED_K) next_offsets(1);
     issue_k(1, 1);
+    keep_offsets();
     if (STAGES == 3) {
         issue_k(2, 2);
         issue_v(1, 1);
@@ -355,14 +411,17 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
         m_ref[h] = 0.f;
     }
 
-    int koff[KS], voff[4];
+    int koff[KS];
     {
-        const int xk = swizzle_key<2 * D>(n) ^ hg, xv = swizzle_key<2 * kTileN>(n) ^ hg;
+        const int xk = swizzle_key<2 * D>(n) ^ hg;
 #pragma unroll
         for (int j = 0; j < KS; ++j) koff[j] = n * D + ((2 * j) ^ xk) * 8;
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) voff[qd] = n * kTileN + ((2 * qd) ^ xv) * 8;
     }
+    // V^T operands: columns of a row tile, or (packed) rows of a V^T tile
+    const TrOffsets<D> v_cols(lane);
+    int voff[4];
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd) voff[qd] = n * kTileN + ((2 * qd) ^ swizzle_key<2 * kTileN>(n) ^ hg) * 8;
     {
         int t0 = my_vis, t1 = tok_q;
         asm volatile("" : "+v"(t0), "+v"(t1));
@@ -378,7 +437,10 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
 
     // K fragment f of a tile: key block f % SB, k-step f / SB; V^T fragment f: d block f % DB, 16-key step f / DB
     auto ld_k = [&](const uint16_t* kb, int f) { return *reinterpret_cast<const bf16x8*>(kb + 32 * (f % SB) * D + koff[f / SB]); };
-    auto ld_v = [&](const uint16_t* vb, int f) { return *reinterpret_cast<const bf16x8*>(vb + 32 * (f % DB) * kTileN + voff[f / DB]); };
+    auto ld_v = [&](const uint16_t* vb, int f) {
+        if constexpr (PACKED_V) return *reinterpret_cast<const bf16x8*>(vb + 32 * (f % DB) * kTileN + voff[f / DB]);
+        else return v_cols.fragment(vb, f / DB, f % DB);
+    };
 
     struct TileInfo { bool partial; int room; };          // room: columns the row sees from this lane's first one of the tile on
     auto tile_info = [&](int ti) {
@@ -566,12 +628,11 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
         __syncthreads();
         const int stage1 = stage == STAGES - 1 ? 0 : stage + 1;
         const int stage2 = stage1 == STAGES - 1 ? 0 : stage1 + 1;
-        const uint16_t* copy_k = kc_head + size_t(tile_of(ti + (STAGES == 3 ? 3 : 2))) * TILE;
-        const uint16_t* copy_v = vc_head + size_t(tile_of(ti + (STAGES == 3 ? 2 : 1))) * TILE;
-        const uint32_t copy_k_lds = lds_k0 + stage * (TILE * 2);
-        const uint32_t copy_v_lds = lds_v0 + (STAGES == 3 ? (stage == 0 ? 2 : stage - 1) : stage1) * (TILE * 2);
+        if constexpr (!PACKED_V) next_offsets(ti + kAhead);
+        auto copy_k = [&]() { issue_k(ti + STAGES, stage); };
+        auto copy_v = [&]() { issue_v(ti + STAGES - 1, STAGES == 3 ? (stage == 0 ? 2 : stage - 1) : stage1); };
         const uint16_t* kb = &sm.k[0][0] + stage1 * TILE;
-        const uint16_t* vb = &sm.vt[0][0] + stage * TILE;
+        const uint16_t* vb = &sm.v[0][0] + stage * TILE;
         const uint16_t* kb2 = &sm.k[0][0] + stage2 * TILE;        // K(ti+2): the tile of the next round's phase X
         if (!EARLY_K || ti == 0) {
 #pragma unroll
@@ -597,12 +658,13 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
                     s_next[h][sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f], qf[h][j], j > 0 ? s_next[h][sb] : NH == 2 ? s_next[h][SB - 1] : neg_ref, 0, 0, 0);
                     // the copies of this round go out behind the first matrix instructions
                     if (f * NH + h == 0) {
-                        if (STAGES == 3) async_copy_rows<NL>(copy_k, lane_off, copy_k_lds);
-                        else async_copy_rows<NL>(copy_v, lane_off, copy_v_lds);
+                        if constexpr (!PACKED_V) copy_tokens(ti + kAhead + 1);
+                        if (STAGES == 3) copy_k();
+                        else copy_v();
                     }
                     if (f * NH + h == 1) {
-                        if (STAGES == 3) async_copy_rows<NL>(copy_v, lane_off, copy_v_lds);
-                        else async_copy_rows<NL>(copy_k, lane_off, copy_k_lds);
+                        if (STAGES == 3) copy_v();
+                        else copy_k();
                     }
                     exp_slot(f * NH + h);
                     __builtin_amdgcn_sched_barrier(0);
@@ -675,6 +737,7 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
                 for (int i = 0; i < 16; ++i) neg_ref[i] = -m_ref[0];
             }
         }
+        if constexpr (!PACKED_V) keep_offsets();
         const TileInfo fresh = tile_info(ti + 1);
         if (fresh.partial) mask_tile(sv, fresh);
         stage = stage1;
@@ -683,7 +746,7 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     {
         wait_vmcnt<0>();                                 // (also: no copy into LDS may outlive the workgroup)
         __syncthreads();
-        const uint16_t* vb = &sm.vt[0][0] + stage * TILE;
+        const uint16_t* vb = &sm.v[0][0] + stage * TILE;
         constexpr int NF = DB * SB * 2;
         bf16x8 a[NF];
 #pragma unroll
@@ -739,7 +802,7 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
 
 using namespace st;
 
-// packed K and V^T tiles, then the (cos, sin) table of the fused rotation (one float2 per packed row and pair)
+// packed K and V^T tiles (not every form uses them), then the (cos, sin) table of the fused rotation (one float2 per packed row and pair)
 static size_t prefill_tile_bytes(const st_plan* plan, int n_kv_heads, int head_dim) {
     return 2 * size_t(n_kv_heads) * size_t(plan->pack_tiles) * kTileN * size_t(head_dim) * sizeof(uint16_t);
 }
@@ -806,16 +869,19 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
     const int head_waves = sets % 4 == 0 ? 4 : sets % 2 == 0 ? 2 : 1;
     auto launch = [&](auto dtag) -> st_status {
         constexpr int HD = decltype(dtag)::value;
-        prof_begin(kProfTilePack, s);
-        for (int rep = 0; rep < prof_repeat(); ++rep)
+        const bool packs = rope || pair;               // (else the attention kernel takes its rows from the tensors)
+        if (packs) prof_begin(kProfTilePack, s);
+        for (int rep = 0; packs && rep < prof_repeat(); ++rep) {
         if (rope) {
             hipLaunchKernelGGL((rope_table_kernel<HD>), dim3((unsigned)plan->pack_tiles), dim3(256), 0, s, tab, positions, pv, freq);
-            hipLaunchKernelGGL((tile_pack_rope_kernel<HD>), dim3((unsigned)pack_blocks), dim3(256), 0, s, kc, vc, (const float2*)tab,
-                               (const uint16_t*)k, (const uint16_t*)v, pv, n_kv_heads);
-        } else
-            hipLaunchKernelGGL((tile_pack_kernel<HD>), dim3((unsigned)pack_blocks), dim3(256), 0, s, kc, vc, (const uint16_t*)k,
-                               (const uint16_t*)v, pv, n_kv_heads);
-        prof_end(kProfTilePack, s);
+            hipLaunchKernelGGL((key_pack_rope_kernel<HD>), dim3((unsigned)pack_blocks), dim3(256), 0, s, kc, (const float2*)tab,
+                               (const uint16_t*)k, pv, n_kv_heads);
+        }
+        if (pair)
+            hipLaunchKernelGGL((tile_pack_kernel<HD>), dim3((unsigned)pack_blocks, rope ? 1 : 2), dim3(256), 0, s, vc, (const uint16_t*)v, kc,
+                               (const uint16_t*)k, pv, n_kv_heads);
+        }
+        if (packs) prof_end(kProfTilePack, s);
         auto run = [&](auto nh_tag, auto rope_tag) -> st_status {
             constexpr int NH = decltype(nh_tag)::value;
             constexpr bool ROPE = decltype(rope_tag)::value;
@@ -825,7 +891,7 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
             prof_begin(kProfPrefillAttn, s);
             for (int rep = 0; rep < prof_repeat(); ++rep)
                 hipLaunchKernelGGL(kern, dim3((unsigned)(blocks / (NH * head_waves) * item_parts(pv, head_waves))), dim3(256), smem, s, (uint16_t*)out,
-                                   lse, (const uint16_t*)q, kc, vc, pv, n_q_heads, n_kv_heads, scale_log2, (const float2*)tab, head_waves);
+                                   lse, (const uint16_t*)q, rope || pair ? kc : (const uint16_t*)k, pair ? vc : (const uint16_t*)v, pv, n_q_heads, n_kv_heads, scale_log2, (const float2*)tab, head_waves);
             prof_end(kProfPrefillAttn, s);
             return ST_OK;
         };
@@ -836,7 +902,7 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
     };
     const st_status lr = head_dim == 64 ? launch(std::integral_constant<int, 64>{}) : launch(std::integral_constant<int, 128>{});
     if (lr != ST_OK) return lr;
-    ST_LAUNCH_CHECK("tile_pack_kernel / prefill_attn_kernel");
+    ST_LAUNCH_CHECK("key_pack_rope_kernel / prefill_attn_kernel");
     return ST_OK;
 }
 

@@ -1,11 +1,10 @@
 // Packed 64-row operand tiles and their way into LDS, shared by the forward and the backward attention kernels.
 //
-// tile_pack_kernel gathers, for every 64-row tile of a stream (stream-compact order) and every head, the rows of
-// one tensor as a "row tile" ([64 rows][D], rows parked in the order the first-type MFMA wants, 16-byte chunks
-// XOR-swizzled) and the rows of a second tensor as a "transposed tile" ([D][64 rows], swizzled), 16 KB each at
-// D = 128, contiguous -- so that a kernel streams tiles with plain linear copies and needs no per-row token lookup
-// and no transpose in its inner loop.  The forward packs (K rows, V^T); the backward packs row tiles only (K, V, Q, dO:
-// bwd_pack_kernel) and takes its transposed operands out of them with transposing LDS reads (TrOffsets below).
+// A "row tile" holds 64 rows of a stream (stream-compact order) of one head: [64 rows][D], rows parked in the order the first-type MFMA
+// wants, 16-byte chunks XOR-swizzled.  The forward's one-head form gathers row tiles of K and V straight from the tensors into LDS (RowGather); its
+// two-head form and the backward read packed ones (pack_rows; 16 KB each at D = 128, contiguous, so that a tile is a plain linear
+// copy).  Transposed operands come out of a row tile with transposing LDS reads (TrOffsets below), or from a packed "transposed tile" ([D][64
+// rows], swizzled) of the two-head form.
 #pragma once
 #include "st_plan.h"
 
@@ -96,6 +95,65 @@ struct TrOffsets {
     }
 };
 
+// swap bits 2 and 3: the row order in which K is parked in LDS, so that after the
+// first MFMA each half-wave holds 8 CONSECUTIVE keys per 16-key step
+__host__ __device__ __forceinline__ int swap23(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
+
+// A row tile gathered straight out of the caller's tensor: each of the four waves of a workgroup copies 16 of the tile's rows, D / 32
+// copies of 1 KB, and a lane names the address of its own 16 bytes -- the row order and the chunk swizzle of the tile come from
+// which bytes a lane asks for.  (One head's rows lie a token apart: the L2 serves such rows as fast as packed ones, 30 TB/s over the chip either
+// way.)  The tokens of the rows come the same way, 64 bytes per wave and tile, copied into LDS well ahead (copy_tokens) and turned into byte
+// offsets of the lane's pieces by offsets(); tensors of one stride share them.
+template <int D>
+struct RowGather {
+    static constexpr int NL = D / 32;                // copies of a wave per tile
+    static constexpr int kAreas = 4;                 // tiles whose tokens may be under way or in use
+    static constexpr int kBytes = 4 * kAreas * 256;  // LDS of a workgroup's four waves (a copy writes 4 bytes per lane)
+    uint32_t stride, piece, row, lds;                // row bytes; byte of the lane's piece of its row (copy 0); the row whose token this lane fetches
+    const unsigned char* area;
+    __device__ __forceinline__ RowGather(unsigned char* smem, int wave, int lane, uint32_t row_bytes) {
+        // copy i of a wave fills positions R i .. of its 16: lane group g takes position R i + g, which holds row swap23(position)
+        constexpr int R = 16 / NL;
+        const int g = lane / (D / 8), chunk = lane & (D / 8 - 1), slot = lane & 15;
+        stride = row_bytes;
+        piece = uint32_t(chunk ^ swizzle_key<2 * D>(g)) * 16;
+        row = uint32_t(16 * wave + swap23(R * (slot % NL) + slot / NL));              // (slot NL g + i: copy i's row of group g)
+        lds = uint32_t(uintptr_t(smem)) + uint32_t(wave) * (kAreas * 256);
+        area = smem + wave * (kAreas * 256) + 4 * NL * g;
+    }
+    // the tokens of the wave's rows of a tile: rows row0 + .. of the list `perm`, the last one (row `last`) in place of rows past it
+    __device__ __forceinline__ void copy_tokens(const int32_t* perm, int row0, int last, int tile) const {
+        const uint32_t off = uint32_t(min(row0 + int(row), last)) * 4u;
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(perm), "s"(lds + uint32_t(tile % kAreas) * 256u) : "memory", "m0");
+    }
+    // (the copies' immediate offsets move LDS and global address alike: taken back here, with a base (NL - 1) KB below the tensor's)
+    __device__ __forceinline__ void offsets(uint32_t (&off)[NL], int tile) const {
+        uint32_t tok[NL];
+        const unsigned char* p = area + (tile % kAreas) * 256;
+        if constexpr (NL == 4) {
+            const u32x4 x = *reinterpret_cast<const u32x4*>(p);
+#pragma unroll
+            for (int i = 0; i < NL; ++i) tok[i] = x[i];
+        } else {
+            const u32x2 x = *reinterpret_cast<const u32x2*>(p);
+#pragma unroll
+            for (int i = 0; i < NL; ++i) tok[i] = x[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NL; ++i) off[i] = tok[i] * stride + (piece ^ (uint32_t(NL == 4 ? i : 4 * i) * 16)) + 1024u * uint32_t(NL - 1 - i);
+    }
+    static __device__ __forceinline__ const void* base(const uint16_t* tensor) { return reinterpret_cast<const unsigned char*>(tensor) - (NL - 1) * 1024; }
+    static __device__ __forceinline__ void copy(const void* base, const uint32_t (&off)[NL], uint32_t lds_off) {
+        if constexpr (NL == 4)
+            asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %4\n\tglobal_load_lds_dwordx4 %1, %4 offset:1024\n\t"
+                         "global_load_lds_dwordx4 %2, %4 offset:2048\n\tglobal_load_lds_dwordx4 %3, %4 offset:3072"
+                         ::"v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base), "s"(lds_off) : "memory", "m0");
+        else
+            asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024"
+                         ::"v"(off[0]), "v"(off[1]), "s"(base), "s"(lds_off) : "memory", "m0");
+    }
+};
+
 // parts of kTileM / head_waves rows of an item that a launch has workgroups for
 __host__ __device__ inline int item_parts(const PlanView& pv, int head_waves) { return (pv.parts32 * head_waves + 3) / 4; }
 // Rows [sub * part_rows, + part_rows) of a work item as an item of their own, with the extents as the plan builds them
@@ -114,10 +172,6 @@ __device__ __forceinline__ WorkItem item_part(WorkItem it, const PlanView& pv, i
     }
     return it;
 }
-
-// swap bits 2 and 3: the row order in which K is parked in LDS, so that after the
-// first MFMA each half-wave holds 8 CONSECUTIVE keys per 16-key step
-__device__ __forceinline__ int swap23(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 
 // The rows of one tile and head, gathered by a workgroup of 256 threads into a row tile: parked in the row order the first MFMA
 // wants (bits 2 and 3 of the row swapped), with the chunk swizzle of the LDS tile; rows past the end of the stream are zero
@@ -142,47 +196,5 @@ __device__ __forceinline__ void pack_rows(uint16_t* dst, const uint16_t* src, co
         *reinterpret_cast<u32x4*>(dst + lr * D + (ch ^ swizzle_key<2 * D>(lr)) * 8) = val;
     }
 }
-
-template <int D>
-__global__ __launch_bounds__(256) void tile_pack_kernel(uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
-                                                           const uint16_t* __restrict__ k,
-                                                           const uint16_t* __restrict__ v, PlanView pv,
-                                                           int n_kv_heads) {
-    const int tile = blockIdx.x / n_kv_heads;
-    const int h = blockIdx.x % n_kv_heads;
-    const TileInfo info = pv.tiles[tile];
-    if (info.valid == 0) return;                    // spare tile of a sequence: never read
-    const int base = info.base, valid = info.valid;
-    const int tid = threadIdx.x;
-    const uint32_t row_stride = uint32_t(n_kv_heads) * D;
-    uint16_t* kdst = kc + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
-    uint16_t* vdst = vc + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
-    pack_rows<D>(kdst, k, pv.perm + base, valid, row_stride, uint32_t(h), [](int, uint32_t, const u32x4&) {});
-    // V: 8 keys x 8 d per thread (16-byte loads), transposed in registers to 8 d x 8 keys (16-byte stores)
-    const int kvb = tid & 7, dq = tid >> 3;
-    if (dq < D / 8) {
-        u32x4 vreg[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int row = kvb * 8 + r;
-            vreg[r] = u32x4{0u, 0u, 0u, 0u};
-            if (row < valid) vreg[r] = *reinterpret_cast<const u32x4*>(v + (uint32_t(pv.perm[base + row]) * row_stride + uint32_t(h) * D + dq * 8));
-        }
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {                 // word w of every row holds d = 2 w and 2 w + 1
-            u32x4 even, odd;
-#pragma unroll
-            for (int pr = 0; pr < 4; ++pr) {
-                const uint32_t a = vreg[2 * pr][w], bb = vreg[2 * pr + 1][w];
-                even[pr] = __builtin_amdgcn_perm(bb, a, 0x05040100u);   // low halves
-                odd[pr] = __builtin_amdgcn_perm(bb, a, 0x07060302u);    // high halves
-            }
-            const int d0 = dq * 8 + 2 * w;
-            *reinterpret_cast<u32x4*>(vdst + d0 * kTileN + (kvb ^ swizzle_key<2 * kTileN>(d0)) * 8) = even;
-            *reinterpret_cast<u32x4*>(vdst + (d0 + 1) * kTileN + (kvb ^ swizzle_key<2 * kTileN>(d0 + 1)) * 8) = odd;
-        }
-    }
-}
-
 
 }  // namespace st

@@ -1,0 +1,48 @@
+"""GPU, bf16 prefill: the one-head form takes its key and value rows straight from the tensors, token by token.  Streams that end around a
+tile's 64 rows, numbers of KV heads that are no power of two, and neighbours that must not be touched: the sequences before and
+after hold NaN alone, and a row past a stream's end would bring one in."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import streaming_attention as O
+
+from gpu_helpers import DEV, ids_to_dev, to_dev, to_f64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def st():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2510_17238_amd as st_
+    st_.load_library()
+    return st_
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("hq,hkv,d", [(3, 3, 128), (10, 5, 64), (4, 1, 128), (2, 2, 64)])
+@pytest.mark.parametrize("src,rsn", [(1, 1), (63, 65), (64, 128), (65, 63), (129, 0), (0, 191), (200, 257)])
+def test_rows_of_their_own_stream_alone(st, hq, hkv, d, src, rsn, fused):
+    lists = [(np.array([70]), np.array([60])), (np.array([src // 2, src - src // 2]), np.array([rsn // 3, rsn - rsn // 3])), (np.array([5]), np.array([9]))]
+    cfg = W._assemble("gathered", "bf16", hq, hkv, d, lists, "interleaved", 71)
+    q, k, v = cfg.tensors()
+    own = slice(int(cfg.cu_seqlens[1]), int(cfg.cu_seqlens[2]))
+    others = np.r_[0:own.start, own.stop:cfg.n_tokens]
+    tq, tk, tv = (to_dev(x, "bf16") for x in (q, k, v))
+    for t in (tk, tv):
+        t[torch.from_numpy(others).to(DEV)] = float("nan")
+    plan = st.st_plan_create(*ids_to_dev(cfg), cfg.cu_seqlens).heads_per_workgroup(1)
+    lse = torch.empty((cfg.n_tokens, hq), dtype=torch.float32, device=DEV)
+    if fused:
+        out = st.st_attn_prefill_rope(tq, tk, tv, torch.from_numpy(cfg.positions).to(DEV), cfg.theta, plan, lse=lse)
+        q, k = O.rope(q, cfg.positions, cfg.theta), O.rope(k, cfg.positions, cfg.theta)
+    else:
+        out = st.st_attn_prefill(tq, tk, tv, plan, lse=lse)
+    ref, ref_lse = O.attention_dense(q[own], k[own], v[own], cfg.stream_ids[own], cfg.segment_ids[own], cfg.positions[own])
+    # the parity suite's bound of bf16 (rotated keys and queries are rounded once more)
+    tol = 4e-2 if fused else 2e-2
+    assert np.abs(to_f64(out[own]) - ref).max() <= tol
+    assert np.abs(to_f64(lse[own]) - ref_lse).max() <= tol
