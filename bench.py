@@ -203,7 +203,7 @@ def bench_prefill_step(st, torch, W, cfg, steps, warmup, use_graph=True, fused_r
     torch.cuda.synchronize()
     st.st_profile_enable(False)
     kern_ms, n_rec = st.st_profile_read(st.ST_PROF_PREFILL_ATTN)
-    pack_ms, n_pack = st.st_profile_read(st.ST_PROF_TILE_PACK)          # (none where the attention kernel gathers its rows itself)
+    pack_ms, _ = st.st_profile_read(st.ST_PROF_TILE_PACK)
     st.st_profile_read(st.ST_PROF_DECODE_SPLIT)
     assert n_rec == n_prof
     # every stage alone (events on the stream; the launches of one stage back to back)
@@ -218,7 +218,8 @@ def bench_prefill_step(st, torch, W, cfg, steps, warmup, use_graph=True, fused_r
         "decode_token_with_append": _event_ms(torch, lambda: (cr.appended_len.copy_(len_r0),
                                                               st.st_attn_decode_dual_append(q_tok, k_tok, v_tok, caches, src_vis, rsn_len, max_s, max_r, theta_base=cfg.theta,
                                                                                             out=out_tok, workspace=dec_ws)), stage_reps),
-        **({"tile_pack": pack_ms} if n_pack else {}), "attention": kern_ms,
+        # (nothing is packed where the attention kernel gathers its rows itself)
+        **({"tile_pack": pack_ms} if two_heads or fused_rope else {}), "attention": kern_ms,
     }
     stage_ms["append_source_chunk"] = max(stage_ms["append_source_chunk"] - stage_ms.pop("length_reset_only"), 1e-6)
     # the timed steps, two ways: the whole step (two streams) recorded once into a HIP graph and replayed -- every

@@ -870,7 +870,7 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
     auto launch = [&](auto dtag) -> st_status {
         constexpr int HD = decltype(dtag)::value;
         const bool packs = rope || pair;               // (else the attention kernel takes its rows from the tensors)
-        if (packs) prof_begin(kProfTilePack, s);
+        prof_begin(kProfTilePack, s);                  // (a reading per call, of nothing where nothing is packed)
         for (int rep = 0; packs && rep < prof_repeat(); ++rep) {
         if (rope) {
             hipLaunchKernelGGL((rope_table_kernel<HD>), dim3((unsigned)plan->pack_tiles), dim3(256), 0, s, tab, positions, pv, freq);
@@ -881,7 +881,7 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
             hipLaunchKernelGGL((tile_pack_kernel<HD>), dim3((unsigned)pack_blocks, rope ? 1 : 2), dim3(256), 0, s, vc, (const uint16_t*)v, kc,
                                (const uint16_t*)k, pv, n_kv_heads);
         }
-        if (packs) prof_end(kProfTilePack, s);
+        prof_end(kProfTilePack, s);
         auto run = [&](auto nh_tag, auto rope_tag) -> st_status {
             constexpr int NH = decltype(nh_tag)::value;
             constexpr bool ROPE = decltype(rope_tag)::value;
