@@ -30,17 +30,22 @@ namespace st {
 // The kernel fits 256 registers, so TWO workgroups share a CU (two waves per SIMD fill each other's gaps between
 // matrix and vector work); the K and V row tiles are double-buffered and copied one tile ahead (64 KB of LDS per
 // workgroup), one barrier per key tile.
+// The rows of all tiles, here and on the key side, are gathered from the tensors on their way into LDS (RowGather): a pass that packed
+// row tiles and row statistics before took 87 to 100 us of a training step over 4 x 4K tokens, 16 / 8 heads of 128 dims (whole step
+// 1,167 -> 1,075 us with the statistics formed here), 32 of 347 over 10 x 1.7K, 16 / 2 of 64.
 template <int D>
 struct BwdDqSmem {
     uint16_t k[2][kTileN * D];        // K rows
     uint16_t v[2][kTileN * D];        // V rows
+    unsigned char tokens[RowGather<D>::kBytes];
 };
 
-template <int D>
+// GATHER: k and v are the tensors, else their packed row tiles.
+template <int D, bool GATHER>
 __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restrict__ dq, const uint16_t* __restrict__ d_out,
-                                                             const uint16_t* __restrict__ q, const uint16_t* __restrict__ krows,
-                                                             const uint16_t* __restrict__ vrows,
-                                                             const float* __restrict__ lse, const float* __restrict__ delta,
+                                                             const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                                             const uint16_t* __restrict__ v, const uint16_t* __restrict__ out,
+                                                             const float* __restrict__ lse, float* __restrict__ stats,
                                                              PlanView pv, int n_q_heads, int n_kv_heads, float scale, int head_waves) {
     constexpr int KS = D / 16, DB = D / 32, SB = kTileN / 32;
     constexpr int TILE = kTileN * D;
@@ -65,28 +70,48 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
     const int n = lane & 31, hg = lane >> 5;
     const int n_tiles = it.a_total + it.b_total;
 
-    const size_t head_off = size_t(hk) * pv.pack_tiles * TILE + size_t(__builtin_amdgcn_readfirstlane(wave) * NL) * 512;   // (+ 16 bytes per lane)
-    const uint32_t lane_off = uint32_t(lane) * 16u;
+    const uint16_t* k_head = GATHER ? k + hk * D : k + size_t(hk) * pv.pack_tiles * TILE;
+    const uint16_t* v_head = GATHER ? v + hk * D : v + size_t(hk) * pv.pack_tiles * TILE;
+    const uint32_t wave_off = uint32_t(wave) * (NL * 1024), lane_off = wave_off + uint32_t(lane) * 16u;
+    const RowGather<D> rows(sm.tokens, wave, lane, uint32_t(n_kv_heads) * (2 * D));
     auto tile_of = [&](int ti) {
         ti = min(ti, n_tiles - 1);
         return ti < it.a_total ? it.tile_a0 + ti : it.tile_b0 + (ti - it.a_total);
     };
-    const uint32_t wave_off = uint32_t(__builtin_amdgcn_readfirstlane(wave)) * (NL * 1024);
+    auto copy_tokens = [&](int ti) {
+        const int t = min(ti, n_tiles - 1);
+        const bool in_a = t < it.a_total;
+        rows.copy_tokens(pv.perm + (in_a ? it.a_base : it.b_base), (in_a ? t : t - it.a_total) * kTileN, (in_a ? it.n_stream : it.n_src) - 1, ti);
+    };
     const uint32_t lds_k = uint32_t(uintptr_t(&sm.k[0][0])) + wave_off, lds_v = uint32_t(uintptr_t(&sm.v[0][0])) + wave_off;
     auto issue_rows = [&](int ti, int buf) {
-        const size_t off = head_off + size_t(tile_of(ti)) * TILE;
-        async_copy_rows<NL>(krows + off, lane_off, lds_k + buf * (TILE * 2));
-        async_copy_rows<NL>(vrows + off, lane_off, lds_v + buf * (TILE * 2));
+        if constexpr (GATHER) {
+            uint32_t off[NL];
+            rows.offsets(off, ti);
+            RowGather<D>::copy(RowGather<D>::base(k_head), off, lds_k + buf * (TILE * 2));
+            RowGather<D>::copy(RowGather<D>::base(v_head), off, lds_v + buf * (TILE * 2));
+            copy_tokens(ti + 1);
+        } else {
+            const size_t off = size_t(tile_of(ti)) * TILE;
+            async_copy_rows<NL>(k_head + off, lane_off, lds_k + buf * (TILE * 2));
+            async_copy_rows<NL>(v_head + off, lane_off, lds_v + buf * (TILE * 2));
+        }
     };
-    issue_rows(0, 0);
 
     const int row_in_tile = (wave / head_waves) * 32 + n;
     const bool active = row_in_tile < it.n_rows;
     const int my_row = it.row0 + min(row_in_tile, it.n_rows - 1);
     const int tok_q = pv.perm[it.a_base + my_row];
     const int my_vis = pv.vis[it.a_base + my_row];
+    if constexpr (GATHER) {
+        copy_tokens(0);
+        int t = tok_q;
+        asm volatile("" : "+v"(t));
+        wait_vmcnt<0>();             // (the rows' own tokens are waited for in any case, and nothing else is under way)
+    }
+    issue_rows(0, 0);
     const int64_t rowhead = int64_t(tok_q) * n_q_heads + hq;
-    const float lse2 = lse[rowhead] * kLog2e, my_delta = delta[rowhead];
+    const float lse2 = lse[rowhead] * kLog2e;
     const float scale_log2 = scale * kLog2e;
 
     bf16x8 qf[KS], dof[KS];
@@ -94,6 +119,29 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
     for (int j = 0; j < KS; ++j) {
         qf[j] = *reinterpret_cast<const bf16x8_a2*>(q + rowhead * D + 8 * hg + 16 * j);
         dof[j] = *reinterpret_cast<const bf16x8_a2*>(d_out + rowhead * D + 8 * hg + 16 * j);
+    }
+    // delta of the row; what the key side needs of it -- for every 64-row tile of a stream and every query head one 1 KB block of 256 floats:
+    // [0, 64) MINUS lse in base-2 units (-inf for rows past the end of the stream: their probabilities become 0), [64, 128) MINUS
+    // delta, [128, 192) the visible-source count of the row (as int bits) -- comes from here, where dO is at hand.
+    float my_delta = 0.f;
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+        const bf16x8 o = *reinterpret_cast<const bf16x8_a2*>(out + rowhead * D + 8 * hg + 16 * j);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) my_delta = fmaf(float(dof[j][e]), float(o[e]), my_delta);
+    }
+    my_delta += __shfl_xor(my_delta, 32);
+    {
+        auto put_stats = [&](int row, float neg_lse, float neg_delta, int vis) {
+            float* blk = stats + (size_t(hq) * pv.pack_tiles + it.tile_a0 + row / kTileN) * 256 + row % kTileN;
+            blk[0] = neg_lse;
+            blk[64] = neg_delta;
+            blk[128] = __int_as_float(vis);
+        };
+        if (active && hg == 0) put_stats(my_row, -lse2, -my_delta, my_vis);
+        // the wave that holds the stream's last row fills the rest of its tile
+        const int last = it.n_stream - 1 - it.row0, row = it.n_stream + lane;
+        if (last >= (wave / head_waves) * 32 && last < (wave / head_waves) * 32 + 32 && row < (it.n_stream + kTileN - 1) / kTileN * kTileN) put_stats(row, -INFINITY, 0.f, 0);
     }
     // queries times scale * log2(e), rounded to bf16 again (as in the forward kernel): K q' is a score in exponent units
 #pragma unroll
@@ -225,19 +273,12 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
 }
 
 
-// Everything the two gradient kernels stream, in one pass: the row tiles of dO, Q, K and V and, in tile order, the row
-// statistics -- for every 64-row tile of a stream and every query head one 1 KB block of 256 floats: [0, 64) MINUS lse in base-2
-// units (-inf for rows past the end of the stream: their probabilities become 0), [64, 128) MINUS delta, [128, 192) the
-// visible-source count of the row (as int bits) -- so that the key-side kernel fetches them with ONE asynchronous copy per tile.
-// delta is also written in token order for the query-side kernel.
-// A workgroup takes one tile of one head of one tensor, the heads of all four side by side: 0 .. n_q_heads - 1 dO (and the
-// statistics), then Q, then K, then V.  Bound by its bytes (each tensor read and written once, the forward's output read once).
-// As five launches, dO read twice: training step, 4 x 4K tokens, 16 / 8 heads of 128 dims 1181 -> 1154 us; 10 x 1.7K, 16 / 2 of 64 364 -> 347.
+// Row tiles of dO, Q, K and V for tensors that are not aligned to 16 bytes (a gradient may be a slice of a flat buffer): the
+// asynchronous copies of the gradient kernels take aligned pieces, so such tensors are gathered into packed tiles first, in one pass.  A
+// workgroup takes one tile of one head of one tensor, the heads of all four side by side: 0 .. n_q_heads - 1 dO, then Q, then K, then V.
 struct BwdPackArgs {
-    const uint16_t *d_out, *q, *k, *v, *out;
-    const float* lse;
+    const uint16_t *d_out, *q, *k, *v;
     uint16_t *dorows, *qrows, *krows, *vrows;
-    float *stats, *delta;
     int n_q_heads, n_kv_heads;
 };
 template <int D>
@@ -247,42 +288,14 @@ __global__ __launch_bounds__(256) void bwd_pack_kernel(BwdPackArgs a, PlanView p
     int h = int(blockIdx.x) % n_slots;
     const TileInfo info = pv.tiles[tile];
     if (info.valid == 0) return;                    // spare tile of a sequence: never read
-    const int32_t* perm = pv.perm + info.base;
-    if (h < a.n_q_heads) {
-        float* blk = a.stats + (size_t(h) * pv.pack_tiles + tile) * 256;
-        pack_rows<D>(a.dorows + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D), a.d_out, perm, info.valid, uint32_t(a.n_q_heads) * D, uint32_t(h),
-                     [&](int row, uint32_t at, const u32x4& piece) {
-                         float dl = 0.f;
-                         if (row < info.valid) {
-                             const bf16x8 x = __builtin_bit_cast(bf16x8, piece), o = *reinterpret_cast<const bf16x8_a2*>(a.out + at);
-#pragma unroll
-                             for (int e = 0; e < 8; ++e) dl = fmaf(float(x[e]), float(o[e]), dl);
-                         }
-#pragma unroll
-                         for (int s = 1; s < D / 8; s *= 2) dl += __shfl_xor(dl, s);
-                         if (threadIdx.x % (D / 8) != 0) return;
-                         float l2 = INFINITY;
-                         int vs = 0;
-                         if (row < info.valid) {
-                             const int64_t rh = int64_t(perm[row]) * a.n_q_heads + h;
-                             l2 = a.lse[rh] * kLog2e;
-                             vs = pv.vis[info.base + row];
-                             a.delta[rh] = dl;
-                         }
-                         blk[row] = -l2;                             // (negated: where the key-side kernel's accumulators start)
-                         blk[64 + row] = -dl;
-                         blk[128 + row] = __int_as_float(vs);
-                         blk[192 + row] = 0.f;
-                     });
-        return;
-    }
-    h -= a.n_q_heads;
-    const bool is_q = h < a.n_q_heads;
-    if (!is_q) h -= a.n_q_heads;
-    const bool is_v = !is_q && h >= a.n_kv_heads;
-    if (is_v) h -= a.n_kv_heads;
-    uint16_t* dst = (is_q ? a.qrows : is_v ? a.vrows : a.krows) + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
-    pack_rows<D>(dst, is_q ? a.q : is_v ? a.v : a.k, perm, info.valid, uint32_t(is_q ? a.n_q_heads : a.n_kv_heads) * D, uint32_t(h),
+    const bool query_side = h < 2 * a.n_q_heads;
+    if (!query_side) h -= 2 * a.n_q_heads;
+    const int heads = query_side ? a.n_q_heads : a.n_kv_heads;
+    const bool second = h >= heads;                 // Q or V
+    if (second) h -= heads;
+    uint16_t* dst = query_side ? (second ? a.qrows : a.dorows) : second ? a.vrows : a.krows;
+    const uint16_t* src = query_side ? (second ? a.q : a.d_out) : second ? a.v : a.k;
+    pack_rows<D>(dst + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D), src, pv.perm + info.base, info.valid, uint32_t(heads) * D, uint32_t(h),
                  [](int, uint32_t, const u32x4&) {});
 }
 
@@ -295,7 +308,7 @@ __global__ __launch_bounds__(256) void bwd_pack_kernel(BwdPackArgs a, PlanView p
 //   dV^T += dO^T P  (dO^T out of the dO row tile with transposing LDS reads, P from the accumulators, rounded to bf16)
 //   dK^T += Q^T dS  (Q^T out of the Q row tile likewise, dS from the accumulators)
 // Rows run along the accumulator registers here, so lse / delta / visible count of the rows come from the
-// tile's 1 KB statistics block in LDS.  Two buffers per tile kind (66 KB), one barrier per query tile.
+// tile's 1 KB statistics block (written by the query side) in LDS.  Two buffers per tile kind (66 KB), one barrier per query tile.
 // acc += A B with the accumulator in ACCUMULATION registers, whatever form the compiler gives the file's other matrix
 // instructions: the key-side kernel's two output accumulators (128 registers) live there for the whole kernel, the
 // score and dP blocks in vector registers where the exponentials read them -- no copies between the two files.
@@ -308,11 +321,13 @@ struct BwdDkvSmem {
     uint16_t qr[2][kTileN * D];       // Q rows
     uint16_t dor[2][kTileN * D];      // dO rows
     float stats[2][256];
+    unsigned char tokens[RowGather<D>::kBytes];
 };
 
 // parts > 1: the query heads of a KV head are dealt out to `parts` workgroups (a divisor of the group), which leave fp32
 // sums in `partial` ([2: dK, dV][parts][N][n_kv_heads][D]) for bwd_dkv_sum_kernel instead of writing dk / dv -- see dkv_parts.
-template <int D>
+// GATHER: qrows and dorows are the tensors, else their packed row tiles.
+template <int D, bool GATHER>
 __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                                                               const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                               const uint16_t* __restrict__ qrows, const uint16_t* __restrict__ dorows,
@@ -402,10 +417,11 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
     // iteration -> (query tile, head): heads fastest, so that a tile's row statistics change slowest; tiles from the LAST one
     // down (reasoning tiles, then the own stream's) -- every key block of a sequence then starts at the same query tile, and
     // the blocks that start together read the same tiles at about the same time (a quarter less traffic into L2)
-    struct Iter { int tile; int hq; int row0; bool rs; };
+    struct Iter { int tile; int hq; int row0; bool rs; int step; };      // (step: query tiles walked before this one)
     auto iter_at = [&](int t, int g) {                          // (tile count t of the walk, head g of the group)
         Iter r;
         r.hq = hq0 + g;
+        r.step = n_a + n_b - 1 - t;
         if (t < n_a) {
             r.tile = tile_own0 + a_first + t;
             r.row0 = (a_first + t) * kTileN;
@@ -424,17 +440,30 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
     // the copies of one iteration go out in two pieces (one tensor each; the statistics with the first), so that the loop
     // can issue them from the shadows of its first matrix instructions
     const uint32_t lane_off = uint32_t(lane) * 16u;
+    const RowGather<D> rows(sm.tokens, wave_u, lane, uint32_t(n_q_heads) * (2 * D));
+    // (gathered rows) of the next iteration's tile: kept over its heads, or formed for each where that leaves two workgroups per compute unit
+    // (heads of 64: 192 + 64 registers; with three more 133 -> 202 us on 10 x 1.7K tokens, 16 / 2 heads)
+    constexpr bool KEEP_OFFSETS = D == 128;
+    uint32_t row_off[NL];
+    auto copy_tokens = [&](const Iter& r) {
+        rows.copy_tokens(pv.perm + (r.rs ? it.b_base + S : it.a_base), r.row0, (r.rs ? n_rsn : it.n_stream) - 1, r.step);
+    };
     auto issue_piece = [&](const Iter& r, int buf, int piece) {
-        const size_t off = (size_t(r.hq) * pv.pack_tiles + r.tile) * TILE + size_t(wave_u * NL) * 512;      // (+ 16 bytes per lane)
-        if (piece == 0) {
-            if (wave_u == 0) async_copy16(stats + (size_t(r.hq) * pv.pack_tiles + r.tile) * 256 + lane * 4, lds_st + buf * 1024);
-            async_copy_rows<NL>(qrows + off, lane_off, lds_qr + buf * (TILE * 2));
-        } else {
-            async_copy_rows<NL>(dorows + off, lane_off, lds_dor + buf * (TILE * 2));
-        }
+        const uint16_t* tensor = piece == 0 ? qrows : dorows;
+        const uint32_t lds = (piece == 0 ? lds_qr : lds_dor) + buf * (TILE * 2);
+        if (piece == 0 && wave_u == 0) async_copy16(stats + (size_t(r.hq) * pv.pack_tiles + r.tile) * 256 + lane * 4, lds_st + buf * 1024);
+        if (GATHER && !KEEP_OFFSETS && piece == 0) rows.offsets(row_off, r.step);
+        if constexpr (GATHER) RowGather<D>::copy(RowGather<D>::base(tensor + r.hq * D), row_off, lds);
+        else async_copy_rows<NL>(tensor + (size_t(r.hq) * pv.pack_tiles + r.tile) * TILE + size_t(wave_u * NL) * 512, lane_off, lds);
     };
     if (n_iter > 0) {
         const Iter r0 = iter_at(n_a + n_b - 1, 0);
+        if constexpr (GATHER) {
+            copy_tokens(r0);
+            if (n_a + n_b > 1) copy_tokens(iter_at(n_a + n_b - 2, 0));
+            wait_vmcnt<0>();
+            if (KEEP_OFFSETS) rows.offsets(row_off, 0);
+        }
 #pragma unroll
         for (int piece = 0; piece < 2; ++piece) issue_piece(r0, 0, piece);
     }
@@ -447,12 +476,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
             dk_acc[db][i] = 0.f;
             dv_acc[db][i] = 0.f;
         }
-    int koff[KS];
-    {
-        const int xk = swizzle_key<2 * D>(n) ^ hg;
-#pragma unroll
-        for (int j = 0; j < KS; ++j) koff[j] = n * D + ((2 * j) ^ xk) * 8;
-    }
+    // byte of the lane's piece of k-step 0 in a row tile; step j's lies at that XOR 32 j, formed on the tile's LDS address (the tiles begin at
+    // multiples of 256 bytes), so that one register stays instead of one per step
+    const uint32_t piece0 = uint32_t(n * D + (swizzle_key<2 * D>(n) ^ hg) * 8) * 2u;
     const TrOffsets<D> tr(lane);
 
     int t_next = n_a + n_b - 1, g_next = 0;
@@ -469,6 +495,12 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
                 --t_next;
             }
             nxt = iter_at(t_next, g_next);
+            if constexpr (GATHER) {      // (a tile's tokens: asked for while the tile before the last is at its first head)
+                if (g_next == 0) {
+                    if (KEEP_OFFSETS) rows.offsets(row_off, nxt.step);
+                    if (t_next > 0) copy_tokens(iter_at(t_next - 1, 0));
+                }
+            }
         }
 
         // Operands come out of LDS a group of matrix instructions ahead of their use (one wave per SIMD: nobody else
@@ -486,11 +518,14 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
         constexpr int G = DB;                                // fragments per tensor and group; eight score pairs per half go beside 2 G pairs of matrix instructions
         constexpr int PIECES = 4 / G;
         bf16x8 fq[2][G], fo[2][G];
+        typedef bf16x8 lds_bf16x8 __attribute__((address_space(3)));
+        const uint32_t q0 = uint32_t(uintptr_t(qb)) + piece0, o0 = uint32_t(uintptr_t(ob)) - uint32_t(uintptr_t(qb));
         auto load1 = [&](int rb, int g, int slot) {          // Q and dO rows of half rb, k-steps G g .. G g + G - 1
 #pragma unroll
             for (int u = 0; u < G; ++u) {
-                fq[slot][u] = *reinterpret_cast<const bf16x8*>(qb + 32 * rb * D + koff[G * g + u]);
-                fo[slot][u] = *reinterpret_cast<const bf16x8*>(ob + 32 * rb * D + koff[G * g + u]);
+                const uint32_t at = (q0 ^ uint32_t(32 * (G * g + u))) + 64u * rb * D;
+                fq[slot][u] = *(const lds_bf16x8*)(at);
+                fo[slot][u] = *(const lds_bf16x8*)(at + o0);
             }
         };
         auto load2 = [&](int stp, int slot) {                // dO^T and Q^T of rows 16 stp .. 16 stp + 15, all d blocks
@@ -534,20 +569,23 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 const int r0 = 32 * rb + 16 * half + 8 * hg;           // first of the 8 consecutive rows of these registers
-                int vs[8];
+                int limit[8];                                          // keys of the stream that the rows see
+                if (cur.rs) {
 #pragma unroll
-                for (int q4 = 0; q4 < 2; ++q4) {
-                    const f32x4 c2 = *reinterpret_cast<const f32x4*>(st + 128 + r0 + 4 * q4);
+                    for (int q4 = 0; q4 < 2; ++q4) {
+                        const f32x4 c2 = *reinterpret_cast<const f32x4*>(st + 128 + r0 + 4 * q4);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) vs[4 * q4 + e] = __float_as_int(c2[e]);
+                        for (int e = 0; e < 4; ++e) limit[4 * q4 + e] = __float_as_int(c2[e]);
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) limit[e] = cur.row0 + r0 + e + 1;
                 }
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const int i = 8 * half + e;
-                    const int row = cur.row0 + r0 + e;
-                    const bool seen = cur.rs ? vs[e] > my_key : row >= my_key;
                     float p = __builtin_amdgcn_exp2f(s_acc[rb][i]);
-                    p = seen ? p : 0.f;
+                    p = limit[e] > my_key ? p : 0.f;
                     pb[rb][half][e] = (__bf16)p;
                     dsb[rb][half][e] = (__bf16)(p * dp_acc[rb][i]);
                 }
@@ -630,8 +668,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
     // cycles before an ordinary instruction may read them)
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     if (!active) return;
+    const int64_t out_row = int64_t(pv.perm[it.a_base + my_key]) * n_kv_heads + hk;         // (keyhead: not kept in registers over the loop)
     if (parts > 1) {
-        float* pk = partial + part * partial_stride + keyhead * D + 4 * hg;
+        float* pk = partial + part * partial_stride + out_row * D + 4 * hg;
         float* pvv = pk + parts * partial_stride;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -642,8 +681,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
             }
         return;
     }
-    uint16_t* pk = dk + keyhead * D;
-    uint16_t* pvv = dv + keyhead * D;
+    uint16_t* pk = dk + out_row * D;
+    uint16_t* pvv = dv + out_row * D;
     // lane (n, hg), block db, register i  <->  d = 32 db + 8 (i/4) + 4 hg + i%4
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -787,19 +826,22 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
     ST_HIP(plan->wait_built(s));
     const PlanView pv = plan->view();
     float* delta = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + L.delta);
-    // bf16: every operand gathered once into 64-row row tiles (one kernel), then two MFMA kernels
-    auto run_mfma = [&](auto dtag) -> st_status {
+    // bf16: two MFMA kernels over the rows of the tensors, or over packed row tiles where a tensor is not aligned to 16 bytes
+    auto run_mfma = [&](auto dtag, auto gtag) -> st_status {
         constexpr int HD = decltype(dtag)::value;
+        constexpr bool GATHER = decltype(gtag)::value;
         unsigned char* w = static_cast<unsigned char*>(workspace);
         auto at = [&](size_t o) { return reinterpret_cast<uint16_t*>(w + o); };
         float* stats = reinterpret_cast<float*>(w + L.stats);
         float* partial = reinterpret_cast<float*>(w + L.partial);
-        const BwdPackArgs pack{(const uint16_t*)d_out, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)out, lse,
-                               at(L.dorows), at(L.qrows), at(L.krows), at(L.vrows), stats, delta, n_q_heads, n_kv_heads};
-        hipLaunchKernelGGL((bwd_pack_kernel<HD>), dim3((unsigned)pack_blocks), dim3(256), 0, s, pack, pv);
+        if (!GATHER) {
+            const BwdPackArgs pack{(const uint16_t*)d_out, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v,
+                                   at(L.dorows), at(L.qrows), at(L.krows), at(L.vrows), n_q_heads, n_kv_heads};
+            hipLaunchKernelGGL((bwd_pack_kernel<HD>), dim3((unsigned)pack_blocks), dim3(256), 0, s, pack, pv);
+        }
         const size_t smem_q = sizeof(BwdDqSmem<HD>), smem_k = sizeof(BwdDkvSmem<HD>);
-        ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_dq_mfma_kernel<HD>), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem_q)));
-        ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_dkv_mfma_kernel<HD>), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem_k)));
+        ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_dq_mfma_kernel<HD, GATHER>), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem_q)));
+        ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_dkv_mfma_kernel<HD, GATHER>), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem_k)));
         const int group = n_q_heads / n_kv_heads;
         // the waves take as many heads as the group has, as in the forward and for the same reason: fewer rows end closer to
         // their last visible column (training step, 4 x 4K tokens, 16 / 8 heads of 128 dims, 1195 -> 1181 us; 10 x 1.7K, 16 / 2
@@ -807,13 +849,14 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
         const int head_waves = group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
         prof_begin(kProfBwdDq, s);
         for (int rep = 0; rep < prof_repeat(); ++rep)
-        hipLaunchKernelGGL((bwd_dq_mfma_kernel<HD>), dim3((unsigned)(qblocks / head_waves * item_parts(pv, head_waves))), dim3(256), smem_q, s, (uint16_t*)dq, (const uint16_t*)d_out,
-                           (const uint16_t*)q, at(L.krows), at(L.vrows), lse, delta, pv, n_q_heads, n_kv_heads, scale, head_waves);
+        hipLaunchKernelGGL((bwd_dq_mfma_kernel<HD, GATHER>), dim3((unsigned)(qblocks / head_waves * item_parts(pv, head_waves))), dim3(256), smem_q, s, (uint16_t*)dq, (const uint16_t*)d_out,
+                           (const uint16_t*)q, GATHER ? (const uint16_t*)k : at(L.krows), GATHER ? (const uint16_t*)v : at(L.vrows), (const uint16_t*)out, lse, stats, pv,
+                           n_q_heads, n_kv_heads, scale, head_waves);
         prof_end(kProfBwdDq, s);
         prof_begin(kProfBwdDkv, s);
         for (int rep = 0; rep < prof_repeat(); ++rep)
-        hipLaunchKernelGGL((bwd_dkv_mfma_kernel<HD>), dim3((unsigned)(kblocks * L.parts)), dim3(256), smem_k, s, (uint16_t*)dk, (uint16_t*)dv,
-                           (const uint16_t*)k, (const uint16_t*)v, at(L.qrows), at(L.dorows), stats, pv,
+        hipLaunchKernelGGL((bwd_dkv_mfma_kernel<HD, GATHER>), dim3((unsigned)(kblocks * L.parts)), dim3(256), smem_k, s, (uint16_t*)dk, (uint16_t*)dv,
+                           (const uint16_t*)k, (const uint16_t*)v, GATHER ? (const uint16_t*)q : at(L.qrows), GATHER ? (const uint16_t*)d_out : at(L.dorows), stats, pv,
                            n_q_heads, n_kv_heads, scale, L.parts, partial, L.partial_stride);
         prof_end(kProfBwdDkv, s);
         if (L.parts > 1) {
@@ -829,7 +872,12 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
                            static_cast<const float*>(q), static_cast<const float*>(k), static_cast<const float*>(v), static_cast<const float*>(out), lse,
                            pv, n_q_heads, n_kv_heads, head_dim, scale, plan->n_tokens, L.parts,
                            reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + L.partial), s);
-    else r = head_dim == 64 ? run_mfma(std::integral_constant<int, 64>{}) : run_mfma(std::integral_constant<int, 128>{});
+    else {
+        auto run = [&](auto dtag) {
+            return aligned16(q) && aligned16(k) && aligned16(v) && aligned16(d_out) ? run_mfma(dtag, std::true_type{}) : run_mfma(dtag, std::false_type{});
+        };
+        r = head_dim == 64 ? run(std::integral_constant<int, 64>{}) : run(std::integral_constant<int, 128>{});
+    }
     if (r != ST_OK) return r;
     ST_LAUNCH_CHECK("st_attn_prefill_bwd kernels");
     return ST_OK;

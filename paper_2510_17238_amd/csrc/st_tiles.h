@@ -109,27 +109,36 @@ struct RowGather {
     static constexpr int NL = D / 32;                // copies of a wave per tile
     static constexpr int kAreas = 4;                 // tiles whose tokens may be under way or in use
     static constexpr int kBytes = 4 * kAreas * 256;  // LDS of a workgroup's four waves (a copy writes 4 bytes per lane)
-    uint32_t stride, piece, row, lds;                // row bytes; byte of the lane's piece of its row (copy 0); the row whose token this lane fetches
-    const unsigned char* area;
+    uint32_t stride, lds;                            // row bytes; the wave's token areas (LDS address), both uniform
+    const unsigned char* area;                       // ... as a pointer
+    // bits 0-7 byte / 16 of the lane's piece of its row (copy 0), 8-15 the row whose token this lane fetches, 16-23 byte of its rows' tokens
+    // in an area: one register through the kernel instead of three (taken apart where it is used, see part())
+    uint32_t lane_parts;
+    __device__ __forceinline__ uint32_t part(int i) const {
+        uint32_t x = lane_parts;
+        asm volatile("" : "+v"(x));                  // (here, not once and for all)
+        return (x >> (8 * i)) & 255u;
+    }
     __device__ __forceinline__ RowGather(unsigned char* smem, int wave, int lane, uint32_t row_bytes) {
         // copy i of a wave fills positions R i .. of its 16: lane group g takes position R i + g, which holds row swap23(position)
         constexpr int R = 16 / NL;
         const int g = lane / (D / 8), chunk = lane & (D / 8 - 1), slot = lane & 15;
         stride = row_bytes;
-        piece = uint32_t(chunk ^ swizzle_key<2 * D>(g)) * 16;
-        row = uint32_t(16 * wave + swap23(R * (slot % NL) + slot / NL));              // (slot NL g + i: copy i's row of group g)
+        lane_parts = uint32_t(chunk ^ swizzle_key<2 * D>(g)) | uint32_t(16 * wave + swap23(R * (slot % NL) + slot / NL)) << 8        // (slot NL g + i: copy i's row of group g)
+                     | uint32_t(4 * NL * g) << 16;
         lds = uint32_t(uintptr_t(smem)) + uint32_t(wave) * (kAreas * 256);
-        area = smem + wave * (kAreas * 256) + 4 * NL * g;
+        area = smem + wave * (kAreas * 256);
     }
     // the tokens of the wave's rows of a tile: rows row0 + .. of the list `perm`, the last one (row `last`) in place of rows past it
     __device__ __forceinline__ void copy_tokens(const int32_t* perm, int row0, int last, int tile) const {
-        const uint32_t off = uint32_t(min(row0 + int(row), last)) * 4u;
+        const uint32_t off = uint32_t(min(row0 + int(part(1)), last)) * 4u;
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(perm), "s"(lds + uint32_t(tile % kAreas) * 256u) : "memory", "m0");
     }
     // (the copies' immediate offsets move LDS and global address alike: taken back here, with a base (NL - 1) KB below the tensor's)
     __device__ __forceinline__ void offsets(uint32_t (&off)[NL], int tile) const {
         uint32_t tok[NL];
-        const unsigned char* p = area + (tile % kAreas) * 256;
+        const unsigned char* p = area + (tile % kAreas) * 256 + part(2);
+        const uint32_t piece = part(0) * 16;
         if constexpr (NL == 4) {
             const u32x4 x = *reinterpret_cast<const u32x4*>(p);
 #pragma unroll

@@ -1,4 +1,4 @@
-"""GPU, bf16 prefill: the one-head form takes its key and value rows straight from the tensors, token by token.  Streams that end around a
+"""GPU, bf16: the prefill's one-head form and the gradients take their rows straight from the tensors, token by token.  Streams that end around a
 tile's 64 rows, numbers of KV heads that are no power of two, and neighbours that must not be touched: the sequences before and
 after hold NaN alone, and a row past a stream's end would bring one in."""
 import numpy as np
@@ -46,3 +46,25 @@ def test_rows_of_their_own_stream_alone(st, hq, hkv, d, src, rsn, fused):
     tol = 4e-2 if fused else 2e-2
     assert np.abs(to_f64(out[own]) - ref).max() <= tol
     assert np.abs(to_f64(lse[own]) - ref_lse).max() <= tol
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(3, 3, 128), (10, 5, 64), (4, 1, 128), (8, 2, 64)])
+@pytest.mark.parametrize("src,rsn", [(1, 1), (63, 65), (64, 128), (65, 63), (129, 0), (0, 191), (200, 257)])
+def test_gradients_of_their_own_stream_alone(st, hq, hkv, d, src, rsn):
+    lists = [(np.array([70]), np.array([60])), (np.array([src // 2, src - src // 2]), np.array([rsn // 3, rsn - rsn // 3])), (np.array([5]), np.array([9]))]
+    cfg = W._assemble("gathered", "bf16", hq, hkv, d, lists, "interleaved", 72)
+    q, k, v = cfg.tensors()
+    g = W.normal(np.random.Generator(np.random.PCG64(73)), q.shape, "bf16")
+    own = slice(int(cfg.cu_seqlens[1]), int(cfg.cu_seqlens[2]))
+    others = torch.from_numpy(np.r_[0:own.start, own.stop:cfg.n_tokens]).to(DEV)
+    tq, tk, tv, tg = (to_dev(x, "bf16") for x in (q, k, v, g))
+    plan = st.st_plan_create(*ids_to_dev(cfg), cfg.cu_seqlens)
+    lse = torch.empty((cfg.n_tokens, hq), dtype=torch.float32, device=DEV)
+    out = st.st_attn_prefill(tq, tk, tv, plan, lse=lse)
+    for t in (tq, tk, tv, tg, out, lse):
+        t[others] = float("nan")
+    grads = st.st_attn_prefill_bwd(tg, tq, tk, tv, out, lse, plan)
+    refs = O.attention_varlen_backward(q, k, v, g, cfg.stream_ids, cfg.segment_ids, cfg.positions, cfg.cu_seqlens)
+    for name, got, ref in zip(("dq", "dk", "dv"), grads, refs):
+        # (the bound of the row-block tests: P, dS and the result are rounded to 4e-3 of their size)
+        assert np.abs(to_f64(got[own]) - ref[own]).max() <= 6e-2 * max(1.0, np.abs(ref[own]).max()), name
