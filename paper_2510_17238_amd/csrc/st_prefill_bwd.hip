@@ -308,7 +308,7 @@ __global__ __launch_bounds__(256) void bwd_pack_kernel(BwdPackArgs a, PlanView p
 //   dV^T += dO^T P  (dO^T out of the dO row tile with transposing LDS reads, P from the accumulators, rounded to bf16)
 //   dK^T += Q^T dS  (Q^T out of the Q row tile likewise, dS from the accumulators)
 // Rows run along the accumulator registers here, so lse / delta / visible count of the rows come from the
-// tile's 1 KB statistics block (written by the query side) in LDS.  Two buffers per tile kind (66 KB), one barrier per query tile.
+// tile's 1 KB statistics block (written by the query side) in LDS.  Three buffers per tile kind (103 KB), one barrier per query tile.
 // acc += A B with the accumulator in ACCUMULATION registers, whatever form the compiler gives the file's other matrix
 // instructions: the key-side kernel's two output accumulators (128 registers) live there for the whole kernel, the
 // score and dP blocks in vector registers where the exponentials read them -- no copies between the two files.
@@ -318,9 +318,9 @@ __device__ __forceinline__ void mfma_into_agprs(f32x16& acc, const bf16x8& a, co
 
 template <int D>
 struct BwdDkvSmem {
-    uint16_t qr[2][kTileN * D];       // Q rows
-    uint16_t dor[2][kTileN * D];      // dO rows
-    float stats[2][256];
+    uint16_t qr[3][kTileN * D];       // Q rows
+    uint16_t dor[3][kTileN * D];      // dO rows
+    float stats[3][256];
     unsigned char tokens[RowGather<D>::kBytes];
 };
 
@@ -437,36 +437,44 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
     const uint32_t lds_qr = uint32_t(uintptr_t(&sm.qr[0][0])) + wave_off, lds_dor = uint32_t(uintptr_t(&sm.dor[0][0])) + wave_off,
                    lds_st = uint32_t(uintptr_t(&sm.stats[0][0]));
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    // the copies of one iteration go out in two pieces (one tensor each; the statistics with the first), so that the loop
-    // can issue them from the shadows of its first matrix instructions
+    // the copies of one iteration, NL of Q and NL of dO (the statistics with the first): the loop issues them one by one from the shadows of
+    // its first matrix instructions
     const uint32_t lane_off = uint32_t(lane) * 16u;
     const RowGather<D> rows(sm.tokens, wave_u, lane, uint32_t(n_q_heads) * (2 * D));
-    // (gathered rows) of the next iteration's tile: kept over its heads, or formed for each where that leaves two workgroups per compute unit
-    // (heads of 64: 192 + 64 registers; with three more 133 -> 202 us on 10 x 1.7K tokens, 16 / 2 heads)
-    constexpr bool KEEP_OFFSETS = D == 128;
-    uint32_t row_off[NL];
+    uint32_t row_off[NL];                                       // (gathered rows) of the next iteration's tile
     auto copy_tokens = [&](const Iter& r) {
         rows.copy_tokens(pv.perm + (r.rs ? it.b_base + S : it.a_base), r.row0, (r.rs ? n_rsn : it.n_stream) - 1, r.step);
     };
-    auto issue_piece = [&](const Iter& r, int buf, int piece) {
-        const uint16_t* tensor = piece == 0 ? qrows : dorows;
-        const uint32_t lds = (piece == 0 ? lds_qr : lds_dor) + buf * (TILE * 2);
-        if (piece == 0 && wave_u == 0) async_copy16(stats + (size_t(r.hq) * pv.pack_tiles + r.tile) * 256 + lane * 4, lds_st + buf * 1024);
-        if (GATHER && !KEEP_OFFSETS && piece == 0) rows.offsets(row_off, r.step);
-        if constexpr (GATHER) RowGather<D>::copy(RowGather<D>::base(tensor + r.hq * D), row_off, lds);
-        else async_copy_rows<NL>(tensor + (size_t(r.hq) * pv.pack_tiles + r.tile) * TILE + size_t(wave_u * NL) * 512, lane_off, lds);
+    auto issue = [&](const Iter& r, int buf, int c) {
+        const uint16_t* tensor = c < NL ? qrows : dorows;
+        const uint32_t lds = (c < NL ? lds_qr : lds_dor) + buf * (TILE * 2);
+        if (c == 0 && wave_u == 0) async_copy16(stats + (size_t(r.hq) * pv.pack_tiles + r.tile) * 256 + lane * 4, lds_st + buf * 1024);
+        if constexpr (GATHER) RowGather<D>::copy_one(RowGather<D>::base(tensor + r.hq * D), row_off, lds, c % NL);
+        else async_copy_1k(tensor + (size_t(r.hq) * pv.pack_tiles + r.tile) * TILE + size_t(wave_u * NL) * 512, lane_off, lds, c % NL);
     };
-    if (n_iter > 0) {
-        const Iter r0 = iter_at(n_a + n_b - 1, 0);
-        if constexpr (GATHER) {
-            copy_tokens(r0);
-            if (n_a + n_b > 1) copy_tokens(iter_at(n_a + n_b - 2, 0));
-            wait_vmcnt<0>();
-            if (KEEP_OFFSETS) rows.offsets(row_off, 0);
+    // the walk, two iterations ahead of the arithmetic (no division in the loop: it is stepped)
+    int t_copy = n_a + n_b - 1, g_copy = 0;
+    auto step_copy = [&]() {
+        if (++g_copy == group) {
+            g_copy = 0;
+            --t_copy;
         }
+    };
+    if (GATHER && n_iter > 0) {
 #pragma unroll
-        for (int piece = 0; piece < 2; ++piece) issue_piece(r0, 0, piece);
+        for (int t = 0; t < 3; ++t)
+            if (t < n_a + n_b) copy_tokens(iter_at(n_a + n_b - 1 - t, 0));
+        wait_vmcnt<0>();
     }
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+        if (x < n_iter) {
+            const Iter r = iter_at(t_copy, g_copy);
+            if (GATHER && g_copy == 0) rows.offsets(row_off, r.step);
+#pragma unroll
+            for (int c = 0; c < 2 * NL; ++c) issue(r, x, c);
+            step_copy();
+        }
 
     f32x16 dk_acc[DB], dv_acc[DB];
 #pragma unroll
@@ -481,91 +489,93 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
     const uint32_t piece0 = uint32_t(n * D + (swizzle_key<2 * D>(n) ^ hg) * 8) * 2u;
     const TrOffsets<D> tr(lane);
 
-    int t_next = n_a + n_b - 1, g_next = 0;
-    Iter nxt = iter_at(t_next, g_next);
-    for (int x = 0; x < n_iter; ++x) {
-        const int buf = x & 1;
-        wait_vmcnt<0>();                 // the tiles of iteration x have landed; everybody is done with x - 1
-        __syncthreads();
-        const bool more = x + 1 < n_iter;
-        const Iter cur = nxt;
-        if (more) {                      // (no division in the loop: the walk is stepped)
-            if (++g_next == group) {
-                g_next = 0;
-                --t_next;
-            }
-            nxt = iter_at(t_next, g_next);
-            if constexpr (GATHER) {      // (a tile's tokens: asked for while the tile before the last is at its first head)
-                if (g_next == 0) {
-                    if (KEEP_OFFSETS) rows.offsets(row_off, nxt.step);
-                    if (t_next > 0) copy_tokens(iter_at(t_next - 1, 0));
-                }
-            }
+    // Operands come out of LDS a group of matrix instructions ahead of their use (one wave per SIMD: nobody else hides that latency), one
+    // fragment of either tensor behind every pair of instructions.  A tile's two 32-row halves are staggered so that the vector work of one
+    // half runs beside matrix work of the other:
+    //     matrix pipe:  S, dP of half 0 | S, dP of half 1     | dV, dK of half 0    | dV, dK of half 1
+    //     vector ALU :                  | P, dS of half 0     | P, dS of half 1     |
+    // and the first fragments and start values of a tile are read beside the last block of the tile before it: three buffers, so that it has
+    // landed by then.  One piece of each kind of work behind every instruction, no branch between them: 4,580 -> 3,690 cycles per tile of
+    // 64 rows and head of 128 dims (2,048 of the matrix pipe), against fragments and copies a group at a time, the first ones behind the
+    // barrier where all four waves asked for them at once (550 cycles), and a branch per piece of vector work for the masks.  4 x 4K tokens,
+    // 16 / 8 heads: 555 -> 500 us (the chip's clock gives back half of it); 10 x 1.7K, 16 / 2 of 64: 133 -> 126.  The copies still cost 270
+    // cycles: without them 480 us.
+    static_assert(SB == 2 && (DB == 4 || DB == 2) && KS == 2 * DB, "the stagger below is written for 64-row tiles of 64 or 128 dims");
+    constexpr int G = DB;                                    // pairs of matrix instructions per group, two groups per block
+    constexpr int PIECES = 4 / G;                            // (two score pairs per piece: eight per half beside 2 G pairs of instructions)
+    f32x16 s_acc[SB], dp_acc[SB];
+    bf16x8 fq[2][G], fo[2][G];
+    u32x4 pb[SB][2], dsb[SB][2];                             // P and dS, bf16 pairs
+    typedef bf16x8 lds_bf16x8 __attribute__((address_space(3)));
+    typedef f32x4 lds_f32x4 __attribute__((address_space(3)));
+    const uint32_t lds_q = uint32_t(uintptr_t(&sm.qr[0][0])), lds_o = uint32_t(uintptr_t(&sm.dor[0][0]));
+    // Q and dO rows of half rb, k-step G g + u
+    auto load1 = [&](int buf, int rb, int g, int u, int slot) {
+        const uint32_t at = ((lds_q + buf * (TILE * 2) + piece0) ^ uint32_t(32 * (G * g + u))) + 64u * rb * D;
+        fq[slot][u] = *(const lds_bf16x8*)(at);
+        fo[slot][u] = *(const lds_bf16x8*)(at + (lds_o - lds_q));
+    };
+    // lane (n, hg), block rb, register i  <->  query row cur.row0 + 32 rb + 16 (i/8) + 8 hg + i%8, key my_key.
+    // The accumulators start at minus the rows' log-sum-exp (scores) and minus their delta (dP), straight from the
+    // tile's statistics block: what comes out is the exponent of P and dP - delta.  Piece c, 0 .. 7: four registers of either.
+    auto start_values = [&](int buf, int rb, int c) {
+        const int q4 = c >> 1;
+        const f32x4 x = *(const lds_f32x4*)(lds_st + buf * 1024 + 4 * (32 * rb + 16 * (q4 >> 1) + 8 * hg + 4 * (q4 & 1)) + 256 * (c & 1));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) (c & 1 ? dp_acc : s_acc)[rb][4 * q4 + e] = x[e];
+    };
+    auto start_values_beside = [&](int buf, int rb, int i) {         // over the 2 G pairs of a block
+#pragma unroll
+        for (int c = 0; c < PIECES; ++c) start_values(buf, rb, i * PIECES + c);
+    };
+    // P and dS of half rb, the part that goes beside pair i
+    auto soft = [&](int rb, int i) {
+#pragma unroll
+        for (int k = 0; k < PIECES; ++k) {
+            const int e = 2 * (i * PIECES + k);
+            const float p0 = __builtin_amdgcn_exp2f(s_acc[rb][e]), p1 = __builtin_amdgcn_exp2f(s_acc[rb][e + 1]);
+            bf16x2 p, ds;
+            p[0] = (__bf16)p0;
+            p[1] = (__bf16)p1;
+            ds[0] = (__bf16)(p0 * dp_acc[rb][e]);
+            ds[1] = (__bf16)(p1 * dp_acc[rb][e + 1]);
+            uint32_t wp = __builtin_bit_cast(uint32_t, p), wds = __builtin_bit_cast(uint32_t, ds);
+            asm volatile("" : "+v"(wp), "+v"(wds));          // HERE, not in front of their use
+            pb[rb][e >> 3][(e & 7) / 2] = wp;
+            dsb[rb][e >> 3][(e & 7) / 2] = wds;
         }
+    };
 
-        // Operands come out of LDS a group of matrix instructions ahead of their use (one wave per SIMD: nobody else
-        // hides that latency): groups of 4 fragments per tensor, the next group requested before the current one is
-        // multiplied; scheduling barriers keep that order.  The tile's two 32-row halves are staggered so that the
-        // vector work of one half runs beside matrix work of the other:
-        //     matrix pipe:  S, dP of half 0 | S, dP of half 1     | dV, dK of half 0    | dV, dK of half 1
-        //     vector ALU :                  | P, dS of half 0     | P, dS of half 1     |
-        // (two scores' worth of vector work behind every second matrix instruction; tiles on the edge of what the
-        // rows may see form P and dS with their masks between the blocks instead).
-        static_assert(SB == 2 && (DB == 4 || DB == 2) && KS == 2 * DB, "the stagger below is written for 64-row tiles of 64 or 128 dims");
-        f32x16 s_acc[SB], dp_acc[SB];
+    int t_cur = n_a + n_b - 1, g_cur = 0;
+    int buf = 0;
+    if (n_iter > 0) {
+        wait_vmcnt<0>();
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < G; ++u) load1(0, 0, 0, u, 0);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) start_values(0, 0, c);
+    }
+    for (int x = 0; x < n_iter; ++x) {
+        wait_vmcnt<0>();                 // the tiles of iteration x + 1 have landed; everybody is done with x - 1
+        __syncthreads();
+        const Iter cur = iter_at(t_cur, g_cur);
+        if (++g_cur == group) {
+            g_cur = 0;
+            --t_cur;
+        }
+        const Iter ahead = iter_at(max(t_copy, 0), g_copy);              // iteration x + 2 (past the end: some tile again, never used)
+        const int buf1 = buf == 2 ? 0 : buf + 1, buf2 = buf1 == 2 ? 0 : buf1 + 1;
+        if constexpr (GATHER) rows.tokens(row_off, ahead.step);
         const uint16_t* qb = &sm.qr[buf][0];
         const uint16_t* ob = &sm.dor[buf][0];
-        constexpr int G = DB;                                // fragments per tensor and group; eight score pairs per half go beside 2 G pairs of matrix instructions
-        constexpr int PIECES = 4 / G;
-        bf16x8 fq[2][G], fo[2][G];
-        typedef bf16x8 lds_bf16x8 __attribute__((address_space(3)));
-        const uint32_t q0 = uint32_t(uintptr_t(qb)) + piece0, o0 = uint32_t(uintptr_t(ob)) - uint32_t(uintptr_t(qb));
-        auto load1 = [&](int rb, int g, int slot) {          // Q and dO rows of half rb, k-steps G g .. G g + G - 1
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const uint32_t at = (q0 ^ uint32_t(32 * (G * g + u))) + 64u * rb * D;
-                fq[slot][u] = *(const lds_bf16x8*)(at);
-                fo[slot][u] = *(const lds_bf16x8*)(at + o0);
-            }
-        };
-        auto load2 = [&](int stp, int slot) {                // dO^T and Q^T of rows 16 stp .. 16 stp + 15, all d blocks
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                fo[slot][u] = tr.fragment(ob, stp, u);
-                fq[slot][u] = tr.fragment(qb, stp, u);
-            }
-        };
-        // lane (n, hg), block rb, register i  <->  query row cur.row0 + 32 rb + 16 (i/8) + 8 hg + i%8, key my_key.
-        // The accumulators start at minus the rows' log-sum-exp (scores) and minus their delta (dP), straight from the
-        // tile's statistics block: what comes out is the exponent of P and dP - delta.
         const float* st = &sm.stats[buf][0];
-#pragma unroll
-        for (int rb = 0; rb < SB; ++rb)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int r0 = 32 * rb + 16 * (q4 >> 1) + 8 * hg + 4 * (q4 & 1);
-                const f32x4 a = *reinterpret_cast<const f32x4*>(st + r0);
-                const f32x4 b2 = *reinterpret_cast<const f32x4*>(st + 64 + r0);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    s_acc[rb][4 * q4 + e] = a[e];
-                    dp_acc[rb][4 * q4 + e] = b2[e];
-                }
-            }
-        // every row of the tile sees every key of this wave?  (rows are ordered, visible counts do not decrease)
-        const int first_vis = __builtin_amdgcn_readfirstlane(__float_as_int(st[128]));
-        const bool all_seen = cur.rs ? first_vis > wave_last_key : cur.row0 >= wave_last_key;
-        bf16x8 pb[SB][2], dsb[SB][2];
-        // P and dS of two neighbouring registers of half rb (no mask)
-        auto soft2 = [&](int rb, int i) {
-            const float p0 = __builtin_amdgcn_exp2f(s_acc[rb][i]), p1 = __builtin_amdgcn_exp2f(s_acc[rb][i + 1]);
-            pb[rb][i >> 3][i & 7] = (__bf16)p0;
-            pb[rb][i >> 3][(i & 7) + 1] = (__bf16)p1;
-            dsb[rb][i >> 3][i & 7] = (__bf16)(p0 * dp_acc[rb][i]);
-            dsb[rb][i >> 3][(i & 7) + 1] = (__bf16)(p1 * dp_acc[rb][i + 1]);
+        auto load2 = [&](int stp, int u, int slot) {         // dO^T and Q^T of rows 16 stp .. 16 stp + 15, d block u
+            fo[slot][u] = tr.fragment(ob, stp, u);
+            fq[slot][u] = tr.fragment(qb, stp, u);
         };
-        // ... of a whole half, with the rows' masks
-        auto soft_masked = [&](int rb) {
+        // pairs of half rb that the rows do not see: exponent -inf
+        auto mask = [&](int rb) {
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 const int r0 = 32 * rb + 16 * half + 8 * hg;           // first of the 8 consecutive rows of these registers
@@ -582,86 +592,67 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_mfma_kernel(uint16_t* __restri
                     for (int e = 0; e < 8; ++e) limit[e] = cur.row0 + r0 + e + 1;
                 }
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int i = 8 * half + e;
-                    float p = __builtin_amdgcn_exp2f(s_acc[rb][i]);
-                    p = limit[e] > my_key ? p : 0.f;
-                    pb[rb][half][e] = (__bf16)p;
-                    dsb[rb][half][e] = (__bf16)(p * dp_acc[rb][i]);
-                }
+                for (int e = 0; e < 8; ++e) s_acc[rb][8 * half + e] = limit[e] > my_key ? s_acc[rb][8 * half + e] : -INFINITY;
             }
         };
-        // S, dP of half rb: 16 matrix instructions in two groups; `next` requests the fragments that follow the block;
-        // SOFT >= 0: P and dS of that (other) half beside them
-        auto scores = [&](auto soft_tag, int rb, int slot0, auto next) {
-            constexpr int SOFT = decltype(soft_tag)::value;
+        // Blocks of 2 G pairs of matrix instructions: ahead(g, u) requests a fragment of the group after next behind a pair's first instruction,
+        // beside(i) is the other work that goes with pair i
+        auto scores = [&](int rb, auto request, auto beside) {
 #pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const int slot = slot0 ^ g;
-                if (g == 0) load1(rb, 1, slot ^ 1);
-                else next(slot ^ 1);
+            for (int g = 0; g < 2; ++g)
 #pragma unroll
                 for (int u = 0; u < G; ++u) {
-                    s_acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[slot][u], kf[G * g + u], s_acc[rb], 0, 0, 0);
-                    if (SOFT == -2 && u == 0) {              // the first block of an iteration: the next iteration's copies
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (more) issue_piece(nxt, buf ^ 1, g);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (SOFT >= 0) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (all_seen) {                      // (uniform; only the vector work is conditional: a branch
-                                                             //  around matrix instructions makes the compiler copy their accumulators)
-#pragma unroll
-                            for (int k = 0; k < PIECES; ++k) soft2(SOFT, 2 * ((G * g + u) * PIECES + k));
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    dp_acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[slot][u], vf[G * g + u], dp_acc[rb], 0, 0, 0);
+                    s_acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[g][u], kf[G * g + u], s_acc[rb], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    request(g, u);
+                    __builtin_amdgcn_sched_barrier(0);
+                    dp_acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[g][u], vf[G * g + u], dp_acc[rb], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    beside(G * g + u);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            }
         };
-        // dV, dK of half rb: 16 matrix instructions in two groups (rows 16 stp .. + 15 each)
-        auto grads = [&](auto soft_tag, int rb, int slot0, auto next) {
-            constexpr int SOFT = decltype(soft_tag)::value;
+        auto grads = [&](int rb, auto request, auto beside) {
 #pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const int slot = slot0 ^ g;
-                if (g == 0) load2(2 * rb + 1, slot ^ 1);
-                else next(slot ^ 1);
+            for (int g = 0; g < 2; ++g)
 #pragma unroll
                 for (int u = 0; u < G; ++u) {
-                    mfma_into_agprs(dv_acc[u], fo[slot][u], pb[rb][g]);
-                    if (SOFT >= 0) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (all_seen) {                      // (uniform; only the vector work is conditional: a branch
-                                                             //  around matrix instructions makes the compiler copy their accumulators)
-#pragma unroll
-                            for (int k = 0; k < PIECES; ++k) soft2(SOFT, 2 * ((G * g + u) * PIECES + k));
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    mfma_into_agprs(dk_acc[u], fq[slot][u], dsb[rb][g]);
+                    mfma_into_agprs(dv_acc[u], fo[g][u], __builtin_bit_cast(bf16x8, pb[rb][g]));
+                    __builtin_amdgcn_sched_barrier(0);
+                    request(g, u);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma_into_agprs(dk_acc[u], fq[g][u], __builtin_bit_cast(bf16x8, dsb[rb][g]));
+                    __builtin_amdgcn_sched_barrier(0);
+                    beside(G * g + u);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            }
         };
-        using None = std::integral_constant<int, -1>;
-        using Copies = std::integral_constant<int, -2>;
-        using Half0 = std::integral_constant<int, 0>;
-        using Half1 = std::integral_constant<int, 1>;
-        load1(0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        scores(Copies{}, 0, 0, [&](int slot) { load1(1, 0, slot); });
-        scores(Half0{}, 1, 0, [&](int slot) { load2(0, slot); });
-        if (!all_seen) {
-            soft_masked(0);
-            soft_masked(1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        grads(Half1{}, 0, 0, [&](int slot) { load2(2, slot); });
-        grads(None{}, 1, 0, [&](int) {});
+        // the copies of iteration x + 2, one behind every second pair of the two score blocks
+        auto copies = [&](int i) {
+            if (i % 2 == 1) issue(ahead, buf2, i / 2);
+        };
+        static_assert(2 * NL == 2 * G, "as many copies as every second pair of two blocks");
+        scores(0, [&](int g, int u) { g == 0 ? load1(buf, 0, 1, u, 1) : load1(buf, 1, 0, u, 0); }, [&](int i) {
+            if (GATHER && i == 1) rows.form(row_off);
+            copies(i);
+            start_values_beside(buf, 1, i);
+        });
+        // every row of the tile sees every key of this wave?  (rows are ordered, visible counts do not decrease)
+        const int first_vis = __builtin_amdgcn_readfirstlane(__float_as_int(st[128]));
+        const bool all_seen = cur.rs ? first_vis > wave_last_key : cur.row0 >= wave_last_key;
+        // (uniform; only vector work is conditional: a branch around matrix instructions makes the compiler copy their accumulators)
+        if (!all_seen) mask(0);
+        scores(1, [&](int g, int u) { g == 0 ? load1(buf, 1, 1, u, 1) : load2(0, u, 0); }, [&](int i) {
+            copies(2 * G + i);
+            soft(0, i);
+        });
+        if (!all_seen) mask(1);
+        grads(0, [&](int g, int u) { load2(g == 0 ? 1 : 2, u, g == 0 ? 1 : 0); }, [&](int i) { soft(1, i); });
+        // (the tokens of the query tile after `ahead`'s: an iteration before its copies at the latest)
+        if constexpr (GATHER) copy_tokens(iter_at(max(t_copy - 1, 0), 0));
+        grads(1, [&](int g, int u) { g == 0 ? load2(3, u, 1) : load1(buf1, 0, 0, u, 0); }, [&](int i) { start_values_beside(buf1, 0, i); });
+        step_copy();
+        buf = buf1;
     }
     wait_vmcnt<0>();
     // (the matrix instructions above are written as text: the compiler does not know that their results need some

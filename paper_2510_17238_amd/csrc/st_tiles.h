@@ -18,6 +18,16 @@ constexpr float kLn2 = 0.6931471805599453f;
 __device__ __forceinline__ void async_copy16(const void* g, uint32_t lds_off) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_off) : "memory", "m0");
 }
+// The same at base + off (one 32-bit offset per lane), `kb` KB further on both sides: the instruction's immediate offset moves the
+// global address and the LDS address alike.  (kb, 0 .. 3, is a constant once the caller's loop is unrolled.)
+__device__ __forceinline__ void async_copy_1k(const void* base, uint32_t off, uint32_t lds_off, int kb) {
+#define ST_COPY_1K(IMM) asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" IMM ::"v"(off), "s"(base), "s"(lds_off) : "memory", "m0")
+    if (kb == 0) ST_COPY_1K("");
+    else if (kb == 1) ST_COPY_1K(" offset:1024");
+    else if (kb == 2) ST_COPY_1K(" offset:2048");
+    else ST_COPY_1K(" offset:3072");
+#undef ST_COPY_1K
+}
 // NL wave-wide 16-byte copies global -> LDS, 1 KB apart on both sides: the instruction's immediate offset moves
 // the global address and the LDS address alike, so the LDS base goes into m0 once.
 template <int NL>
@@ -134,11 +144,9 @@ struct RowGather {
         const uint32_t off = uint32_t(min(row0 + int(part(1)), last)) * 4u;
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(perm), "s"(lds + uint32_t(tile % kAreas) * 256u) : "memory", "m0");
     }
-    // (the copies' immediate offsets move LDS and global address alike: taken back here, with a base (NL - 1) KB below the tensor's)
-    __device__ __forceinline__ void offsets(uint32_t (&off)[NL], int tile) const {
-        uint32_t tok[NL];
+    // the tokens of the lane's pieces of a tile, out of LDS
+    __device__ __forceinline__ void tokens(uint32_t (&tok)[NL], int tile) const {
         const unsigned char* p = area + (tile % kAreas) * 256 + part(2);
-        const uint32_t piece = part(0) * 16;
         if constexpr (NL == 4) {
             const u32x4 x = *reinterpret_cast<const u32x4*>(p);
 #pragma unroll
@@ -148,10 +156,21 @@ struct RowGather {
 #pragma unroll
             for (int i = 0; i < NL; ++i) tok[i] = x[i];
         }
+    }
+    // their byte offsets (in place), for copies from base(): the copies' immediate offsets move LDS and global address alike, which is taken
+    // back here, with a base (NL - 1) KB below the tensor's
+    __device__ __forceinline__ void form(uint32_t (&off)[NL]) const {
+        const uint32_t piece = part(0) * 16;
 #pragma unroll
-        for (int i = 0; i < NL; ++i) off[i] = tok[i] * stride + (piece ^ (uint32_t(NL == 4 ? i : 4 * i) * 16)) + 1024u * uint32_t(NL - 1 - i);
+        for (int i = 0; i < NL; ++i) off[i] = off[i] * stride + (piece ^ (uint32_t(NL == 4 ? i : 4 * i) * 16)) + 1024u * uint32_t(NL - 1 - i);
+    }
+    __device__ __forceinline__ void offsets(uint32_t (&off)[NL], int tile) const {
+        tokens(off, tile);
+        form(off);
     }
     static __device__ __forceinline__ const void* base(const uint16_t* tensor) { return reinterpret_cast<const unsigned char*>(tensor) - (NL - 1) * 1024; }
+    // copy i alone, and all of them
+    static __device__ __forceinline__ void copy_one(const void* base, const uint32_t (&off)[NL], uint32_t lds_off, int i) { async_copy_1k(base, off[i], lds_off, i); }
     static __device__ __forceinline__ void copy(const void* base, const uint32_t (&off)[NL], uint32_t lds_off) {
         if constexpr (NL == 4)
             asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %4\n\tglobal_load_lds_dwordx4 %1, %4 offset:1024\n\t"
