@@ -39,3 +39,12 @@ def test_more_short_caches_than_compute_units(st, q_len, hq, hkv, d):
     batch = 530 // hkv
     src_lens = rng.choice([0, 1, 17, 64, 129], batch); rsn_lens = rng.choice([q_len, 5, 31, 33, 64, 200], batch)
     _check_decode(st, rng, batch, hq, hkv, d, src_lens, rsn_lens, np.minimum(src_lens, rng.integers(0, 140, batch)), q_len=q_len, rope_theta=1.0e6)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("q_len,hq,hkv", [(1, 7, 1), (1, 9, 1), (3, 3, 1), (5, 1, 1), (3, 10, 2), (13, 1, 1)])
+def test_rows_that_fill_the_merge_in_part(st, q_len, hq, hkv, d):
+    """3 to 15 rows: the merge takes one, two or four dims of a row per thread, the last threads none; an empty and a one-token cache."""
+    rng = np.random.Generator(np.random.PCG64(490 + q_len * hq + d))
+    src_lens, rsn_lens = np.array([0, 70, 33]), np.array([q_len, q_len + 1, 200])
+    _check_decode(st, rng, 3, hq, hkv, d, src_lens, rsn_lens, np.minimum(src_lens, 64), q_len=q_len, rope_theta=1.0e6)
