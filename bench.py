@@ -773,7 +773,7 @@ def _prefill_objects(pre, name, fused_rope):
     cfg = pre["cfg"]
     tflops_step = pre["flops"] / pre["sec_per_step"] / 1e12
     tflops_kernel = pre["flops"] / (pre["prefill_kernel_ms"] * 1e-3) / 1e12
-    kern = f"prefill_attn_kernel<{cfg.head_dim}, {2 if pre['two_heads'] else 1}, {'true' if fused_rope else 'false'}>"
+    kern = f"prefill_attn_kernel<{cfg.head_dim}, {2 if pre['two_heads'] else 1}, {'true' if fused_rope else 'false'}, {'true' if pre['two_heads'] or fused_rope and cfg.head_dim == 128 else 'false'}>"
     roof = {"kernel": kern, "bound": "mfma", "achieved": round(tflops_kernel, 3), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": round(tflops_kernel / PEAK_BF16_TFLOPS, 4), "traffic": measured_traffic(f"prefill_attn_kernel@{name}"),
             "avg_kernel_ms": round(pre["prefill_kernel_ms"], 4), "algorithmic_flops_per_launch": pre["flops"]}

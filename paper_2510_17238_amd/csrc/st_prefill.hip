@@ -10,7 +10,7 @@
 // index with a per-row limit, tiles past `total` are never read.
 //
 // Kernels:
-//   prefill_attn_kernel<D, NH, ROPE>
+//   prefill_attn_kernel<D, NH, ROPE, PACK>
 //                         bf16, 4 waves of 32 query rows x NH query heads (1 or 2) of one KV head -- 128 rows of the
 //                         same head(s), or fewer rows of more heads (head_waves); K and V
 //                         tiles copied asynchronously into swizzled LDS buffers, with one head per wave straight from the
@@ -21,7 +21,7 @@
 //                         row sum is an in-register reduction plus one exchange with lane^32, and the S^T
 //                         accumulators are already laid out as the B operand of the second product.  The
 //                         loop is software-pipelined by hand (see the kernel).
-//   tile_pack_kernel      the two-head form's tiles: K rows and TRANSPOSED V rows of every 64-row key tile (stream-compact order)
+//   tile_pack_kernel      packed tiles (PACK: the two-head form, long sequences): K rows and TRANSPOSED V rows of every 64-row key tile (stream-compact order)
 //                         gathered into contiguous 16 KB blocks.
 //   rope_table_kernel, key_pack_rope_kernel
 //                         the fused rotation of st_attn_prefill_rope: (cos, sin) of every token once, keys rotated
@@ -89,47 +89,62 @@ __global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ ta
     }
 }
 
-// Step 2: UNROTATED keys into packed row tiles -- every key row is rotated with its table row on its way.  A thread owns two rows x one pair of 8-dim pieces (dims 8 cp .. + 7 and D/2 + the same).
+// Step 2: UNROTATED keys into packed row tiles -- every key row is rotated with its table row on its way.  A thread owns two rows (one with
+// heads of 64 dims) x one pair of 8-dim pieces (dims 8 cp .. + 7 and D/2 + the same) of `heads` heads: the table rows, twice the
+// bytes of a key row, are read once for all of them.
 template <int D>
 __global__ __launch_bounds__(256) void key_pack_rope_kernel(uint16_t* __restrict__ kc, const float2* __restrict__ tab, const uint16_t* __restrict__ k,
-                                                           PlanView pv, int n_kv_heads) {
+                                                           PlanView pv, int n_kv_heads, int heads) {
     constexpr int KCH = D / 8, CP = KCH / 2;
     constexpr int PER_THREAD = kTileN * CP / 256;
-    const int tile = blockIdx.x / n_kv_heads;
-    const int h = blockIdx.x % n_kv_heads;
+    const int sets = (n_kv_heads + heads - 1) / heads;
+    const int tile = blockIdx.x / sets, h0 = int(blockIdx.x % sets) * heads, h1 = min(h0 + heads, n_kv_heads);
     const TileInfo info = pv.tiles[tile];
     if (info.valid == 0) return;                    // spare tile of a sequence: never read
-    const int base = info.base, valid = info.valid;
-    const int tid = threadIdx.x;
     const uint32_t row_stride = uint32_t(n_kv_heads) * D;
-    uint16_t* kdst = kc + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
+    const f32x4* tab4 = reinterpret_cast<const f32x4*>(tab);
+    f32x4 cs[PER_THREAD][4];                        // (cos, sin) of pairs 8 cp + 2 w and + 1
+    uint32_t at[PER_THREAD];                        // the piece of head 0
+    bool live[PER_THREAD];
 #pragma unroll
     for (int u = 0; u < PER_THREAD; ++u) {
-        const int c = tid + 256 * u;
-        const int row = c / CP, cp = c % CP;
-        u32x4 lo = {0u, 0u, 0u, 0u}, hi = {0u, 0u, 0u, 0u};
-        if (row < valid) {
-            const uint16_t* kr = k + (uint32_t(pv.perm[base + row]) * row_stride + uint32_t(h) * D + cp * 8);
-            const u32x4 lo_in = *reinterpret_cast<const u32x4*>(kr), hi_in = *reinterpret_cast<const u32x4*>(kr + D / 2);
-            const f32x4* tab4 = reinterpret_cast<const f32x4*>(tab);
+        const int c = int(threadIdx.x) + 256 * u, row = c / CP, cp = c % CP;
+        live[u] = row < info.valid;
+        const int r = min(row, info.valid - 1);
+        at[u] = uint32_t(pv.perm[info.base + r]) * row_stride + uint32_t(cp) * 8;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) cs[u][w] = tab4[rope_table_at<D>(size_t(tile) * kTileN + r, cp >> 1, w, cp & 1)];
+    }
+    for (int h = h0; h < h1; ++h) {
+        uint16_t* kdst = kc + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D);
+        u32x4 lo_in[PER_THREAD], hi_in[PER_THREAD];
+#pragma unroll
+        for (int u = 0; u < PER_THREAD; ++u) {
+            const uint16_t* kr = k + at[u] + uint32_t(h) * D;
+            lo_in[u] = *reinterpret_cast<const u32x4*>(kr);
+            hi_in[u] = *reinterpret_cast<const u32x4*>(kr + D / 2);
+        }
+#pragma unroll
+        for (int u = 0; u < PER_THREAD; ++u) {
+            const int c = int(threadIdx.x) + 256 * u, row = c / CP, cp = c % CP;
+            u32x4 lo, hi;
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                const f32x4 t = tab4[rope_table_at<D>(size_t(tile) * kTileN + row, cp >> 1, w, cp & 1)];      // (cos, sin) of pairs 8 cp + 2 w and + 1
                 uint32_t out_lo = 0, out_hi = 0;
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
-                    const float cs = t[2 * half], sn = t[2 * half + 1];
-                    const float x = bf16_bits_to_f32(uint16_t(lo_in[w] >> (16 * half))), y = bf16_bits_to_f32(uint16_t(hi_in[w] >> (16 * half)));
-                    out_lo |= uint32_t(f32_to_bf16_bits(x * cs - y * sn)) << (16 * half);
-                    out_hi |= uint32_t(f32_to_bf16_bits(y * cs + x * sn)) << (16 * half);
+                    const float c1 = cs[u][w][2 * half], s1 = cs[u][w][2 * half + 1];
+                    const float x = bf16_bits_to_f32(uint16_t(lo_in[u][w] >> (16 * half))), y = bf16_bits_to_f32(uint16_t(hi_in[u][w] >> (16 * half)));
+                    out_lo |= uint32_t(f32_to_bf16_bits(x * c1 - y * s1)) << (16 * half);
+                    out_hi |= uint32_t(f32_to_bf16_bits(y * c1 + x * s1)) << (16 * half);
                 }
-                lo[w] = out_lo;
-                hi[w] = out_hi;
+                lo[w] = live[u] ? out_lo : 0u;
+                hi[w] = live[u] ? out_hi : 0u;
             }
+            const int lr = swap23(row);                                    // row position in the tile
+            *reinterpret_cast<u32x4*>(kdst + lr * D + (cp ^ swizzle_key<2 * D>(lr)) * 8) = lo;
+            *reinterpret_cast<u32x4*>(kdst + lr * D + ((cp + CP) ^ swizzle_key<2 * D>(lr)) * 8) = hi;
         }
-        const int lr = swap23(row);                                    // row position in the tile
-        *reinterpret_cast<u32x4*>(kdst + lr * D + (cp ^ swizzle_key<2 * D>(lr)) * 8) = lo;
-        *reinterpret_cast<u32x4*>(kdst + lr * D + ((cp + CP) ^ swizzle_key<2 * D>(lr)) * 8) = hi;
     }
 }
 
@@ -225,7 +240,8 @@ struct PipeSmem {
 // --------------------------------------------------------------------------
 constexpr float kRiseLog2 = 24.f;
 
-template <int D, int NH, bool ROPE>
+// PACK: K and V^T come as packed tiles (NH = 2 always).
+template <int D, int NH, bool ROPE, bool PACK>
 __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint16_t* __restrict__ out, float* __restrict__ lse,
                                                                    const uint16_t* __restrict__ q,
                                                                    const uint16_t* __restrict__ k,
@@ -235,7 +251,8 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     constexpr int KS = D / 16, DB = D / 32, SB = kTileN / 32;
     constexpr int TILE = kTileN * D;
     constexpr int STAGES = NH == 2 ? 3 : 2;
-    constexpr bool PACKED_V = NH == 2, PACKED_K = PACKED_V || ROPE;
+    static_assert(NH == 1 || PACK, "three buffers, no tokens");
+    constexpr bool PACKED_V = PACK, PACKED_K = PACK || ROPE;
     constexpr bool EARLY_K = STAGES == 3;          // K(t + 2) has landed when tile t starts: its first fragments may be read a phase early
     constexpr int PER = 16 / KS;                   // score elements of vector work per matrix instruction (both phases)
     constexpr int kPF = 3;                         // operand fragments read ahead
@@ -637,7 +654,7 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
                 if (i < NL) async_copy_1k(k_head + size_t(tile_of(ti + 3)) * TILE, lane_off, lds_k0 + stage * (TILE * 2), i);
                 else async_copy_1k(v_head + size_t(tile_of(ti + 2)) * TILE, lane_off, lds_v0 + (stage == 0 ? 2 : stage - 1) * (TILE * 2), i - NL);
             } else if (i == 0) {
-                copy_tokens(ti + kAhead + 1);
+                if constexpr (!PACKED_V) copy_tokens(ti + kAhead + 1);
                 issue_v(ti + 1, stage1);
             } else {
                 issue_k(ti + 2, stage);
@@ -864,6 +881,12 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
     const int heads_wanted = plan->heads_per_workgroup;
     const bool can_pair = (n_q_heads / n_kv_heads) % 2 == 0;
     const bool pair = can_pair && (heads_wanted == 2 || (heads_wanted == 0 && plan->n_tokens / plan->batch >= 8192));
+    // Packed tiles also for one head where the sequences are long enough that a tile's many copies and reads outweigh the pass over memory: the
+    // gathered rows of V cost their transposing reads.  Gathered against packed, batches of 2K / 4K / 8K tokens a sequence, four head
+    // geometries: rotated keys (packed in any case) 0.94 to 0.98 / 0.99 to 1.01 / 1.00 to 1.03 of the time (heads of 64 dims 1.00); plain 0.74 to
+    // 0.92 / 0.90 to 0.99 / 0.97 to 0.99, and 1.02 with eight query heads over a KV head of 128 dims.
+    const int64_t mean_tokens = plan->n_tokens / plan->batch;
+    const bool packed = pair || (head_dim == 128 && mean_tokens >= (rope ? 3500 : n_q_heads / n_kv_heads >= 8 ? 5000 : INT64_MAX));
     // The four waves of a workgroup share the key tiles of one KV head; they take 4, 2 or 1 (sets of) query heads of it and
     // 32, 64 or 128 rows of the item -- as many heads as the group has: fewer rows end closer to their item's last visible
     // column, so less of the issued arithmetic is masked or belongs to no row (useful share 0.89 / 0.93 / 0.95 with 1 / 2 / 4
@@ -873,36 +896,41 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
     const int head_waves = sets % 4 == 0 ? 4 : sets % 2 == 0 ? 2 : 1;
     auto launch = [&](auto dtag) -> st_status {
         constexpr int HD = decltype(dtag)::value;
-        const bool packs = rope || pair;               // (else the attention kernel takes its rows from the tensors)
+        const bool packs = rope || packed;             // (else the attention kernel takes its rows from the tensors)
         prof_begin(kProfTilePack, s);                  // (a reading per call, of nothing where nothing is packed)
         for (int rep = 0; packs && rep < prof_repeat(); ++rep) {
         if (rope) {
             hipLaunchKernelGGL((rope_table_kernel<HD>), dim3((unsigned)plan->pack_tiles), dim3(256), 0, s, tab, positions, pv, freq);
-            hipLaunchKernelGGL((key_pack_rope_kernel<HD>), dim3((unsigned)pack_blocks), dim3(256), 0, s, kc, (const float2*)tab,
-                               (const uint16_t*)k, pv, n_kv_heads);
+            // Four heads per workgroup where that still leaves four workgroups for every compute unit, else one: a small batch would only wait
+            // for one head behind the other (96 sequences of 60 to 900 tokens, 8 KV heads of 128 dims: 57.7 us one by one, 46 by twos, 42.6 by
+            // fours, 42.3 by eights).
+            const int heads = pack_blocks >= 4 * 1024 ? 4 : 1;
+            hipLaunchKernelGGL((key_pack_rope_kernel<HD>), dim3((unsigned)(plan->pack_tiles * ((n_kv_heads + heads - 1) / heads))), dim3(256), 0, s, kc,
+                               (const float2*)tab, (const uint16_t*)k, pv, n_kv_heads, heads);
         }
-        if (pair)
+        if (packed)
             hipLaunchKernelGGL((tile_pack_kernel<HD>), dim3((unsigned)pack_blocks, rope ? 1 : 2), dim3(256), 0, s, vc, (const uint16_t*)v, kc,
                                (const uint16_t*)k, pv, n_kv_heads);
         }
         prof_end(kProfTilePack, s);
-        auto run = [&](auto nh_tag, auto rope_tag) -> st_status {
+        auto run = [&](auto nh_tag, auto rope_tag, auto pack_tag) -> st_status {
             constexpr int NH = decltype(nh_tag)::value;
-            constexpr bool ROPE = decltype(rope_tag)::value;
+            constexpr bool ROPE = decltype(rope_tag)::value, PACK = decltype(pack_tag)::value;
             const size_t smem = sizeof(PipeSmem<HD, NH == 2 ? 3 : 2>);
-            auto* kern = &prefill_attn_kernel<HD, NH, ROPE>;
+            auto* kern = &prefill_attn_kernel<HD, NH, ROPE, PACK>;
             ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, int(smem)));
             prof_begin(kProfPrefillAttn, s);
             for (int rep = 0; rep < prof_repeat(); ++rep)
                 hipLaunchKernelGGL(kern, dim3((unsigned)(blocks / (NH * head_waves) * item_parts(pv, head_waves))), dim3(256), smem, s, (uint16_t*)out,
-                                   lse, (const uint16_t*)q, rope || pair ? kc : (const uint16_t*)k, pair ? vc : (const uint16_t*)v, pv, n_q_heads, n_kv_heads, scale_log2, (const float2*)tab, head_waves);
+                                   lse, (const uint16_t*)q, rope || packed ? kc : (const uint16_t*)k, packed ? vc : (const uint16_t*)v, pv, n_q_heads, n_kv_heads, scale_log2, (const float2*)tab, head_waves);
             prof_end(kProfPrefillAttn, s);
             return ST_OK;
         };
-        using One = std::integral_constant<int, 1>;
-        using Two = std::integral_constant<int, 2>;
-        return rope ? (pair ? run(Two{}, std::true_type{}) : run(One{}, std::true_type{}))
-                    : (pair ? run(Two{}, std::false_type{}) : run(One{}, std::false_type{}));
+        auto heads_of = [&](auto rope_tag) -> st_status {
+            if (pair) return run(std::integral_constant<int, 2>{}, rope_tag, std::true_type{});
+            return packed ? run(std::integral_constant<int, 1>{}, rope_tag, std::true_type{}) : run(std::integral_constant<int, 1>{}, rope_tag, std::false_type{});
+        };
+        return rope ? heads_of(std::true_type{}) : heads_of(std::false_type{});
     };
     const st_status lr = head_dim == 64 ? launch(std::integral_constant<int, 64>{}) : launch(std::integral_constant<int, 128>{});
     if (lr != ST_OK) return lr;

@@ -68,3 +68,25 @@ def test_gradients_of_their_own_stream_alone(st, hq, hkv, d, src, rsn):
     for name, got, ref in zip(("dq", "dk", "dv"), grads, refs):
         # (the bound of the row-block tests: P, dS and the result are rounded to 4e-3 of their size)
         assert np.abs(to_f64(got[own]) - ref[own]).max() <= 6e-2 * max(1.0, np.abs(ref[own]).max()), name
+
+
+@pytest.mark.parametrize("fused,hq,hkv,d,tokens", [(True, 4, 2, 128, 3600), (True, 3, 3, 64, 3600), (False, 8, 1, 128, 5100), (True, 4, 2, 128, 3400)])
+def test_long_sequences_on_either_side_of_the_packed_tiles(st, fused, hq, hkv, d, tokens):
+    """One head per wave over packed tiles and over gathered rows: sampled rows against the oracle."""
+    cfg = W._assemble("long", "bf16", hq, hkv, d, [(np.array([tokens // 4, tokens // 8]), np.array([tokens // 3, tokens - tokens // 4 - tokens // 8 - tokens // 3]))], "interleaved", 74)
+    q, k, v = cfg.tensors()
+    tq, tk, tv = (to_dev(x, "bf16") for x in (q, k, v))
+    plan = st.st_plan_create(*ids_to_dev(cfg), cfg.cu_seqlens).heads_per_workgroup(1)
+    if fused:
+        out = st.st_attn_prefill_rope(tq, tk, tv, torch.from_numpy(cfg.positions).to(DEV), cfg.theta, plan)
+        q, k = O.rope(q, cfg.positions, cfg.theta), O.rope(k, cfg.positions, cfg.theta)
+    else:
+        out = st.st_attn_prefill(tq, tk, tv, plan)
+    got = to_f64(out)
+    mask = O.dense_mask(cfg.stream_ids, cfg.segment_ids, cfg.positions)
+    for row in (0, 1, 63, tokens // 4, tokens // 2, tokens - 65, tokens - 1):
+        for h in range(hq):
+            s = np.where(mask[row], k[:, h // (hq // hkv)].astype(np.float64) @ q[row, h].astype(np.float64) / np.sqrt(d), -np.inf)
+            p = np.exp(s - s.max())
+            ref = (p / p.sum()) @ v[:, h // (hq // hkv)].astype(np.float64)
+            assert np.abs(got[row, h] - ref).max() <= (4e-2 if fused else 2e-2), (row, h)
