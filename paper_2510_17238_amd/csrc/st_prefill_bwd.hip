@@ -84,18 +84,13 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
         rows.copy_tokens(pv.perm + (in_a ? it.a_base : it.b_base), (in_a ? t : t - it.a_total) * kTileN, (in_a ? it.n_stream : it.n_src) - 1, ti);
     };
     const uint32_t lds_k = uint32_t(uintptr_t(&sm.k[0][0])) + wave_off, lds_v = uint32_t(uintptr_t(&sm.v[0][0])) + wave_off;
-    auto issue_rows = [&](int ti, int buf) {
-        if constexpr (GATHER) {
-            uint32_t off[NL];
-            rows.offsets(off, ti);
-            RowGather<D>::copy(RowGather<D>::base(k_head), off, lds_k + buf * (TILE * 2));
-            RowGather<D>::copy(RowGather<D>::base(v_head), off, lds_v + buf * (TILE * 2));
-            copy_tokens(ti + 1);
-        } else {
-            const size_t off = size_t(tile_of(ti)) * TILE;
-            async_copy_rows<NL>(k_head + off, lane_off, lds_k + buf * (TILE * 2));
-            async_copy_rows<NL>(v_head + off, lane_off, lds_v + buf * (TILE * 2));
-        }
+    uint32_t row_off[NL];                                       // (gathered rows) of the tile that is copied
+    // copy c of tile ti, NL of K and NL of V
+    auto issue = [&](int ti, int buf, int c) {
+        const uint16_t* head = c < NL ? k_head : v_head;
+        const uint32_t lds = (c < NL ? lds_k : lds_v) + buf * (TILE * 2);
+        if constexpr (GATHER) RowGather<D>::copy_one(RowGather<D>::base(head), row_off, lds, c % NL);
+        else async_copy_1k(head + size_t(tile_of(ti)) * TILE, lane_off, lds, c % NL);
     };
 
     const int row_in_tile = (wave / head_waves) * 32 + n;
@@ -108,8 +103,11 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
         int t = tok_q;
         asm volatile("" : "+v"(t));
         wait_vmcnt<0>();             // (the rows' own tokens are waited for in any case, and nothing else is under way)
+        rows.offsets(row_off, 0);
+        copy_tokens(1);
     }
-    issue_rows(0, 0);
+#pragma unroll
+    for (int c = 0; c < 2 * NL; ++c) issue(0, 0, c);
     const int64_t rowhead = int64_t(tok_q) * n_q_heads + hq;
     const float lse2 = lse[rowhead] * kLog2e;
     const float scale_log2 = scale * kLog2e;
@@ -154,12 +152,9 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
 
-    int koff[KS];
-    {
-        const int xk = swizzle_key<2 * D>(n) ^ hg;
-#pragma unroll
-        for (int j = 0; j < KS; ++j) koff[j] = n * D + ((2 * j) ^ xk) * 8;
-    }
+    // byte of the lane's piece of k-step 0 in a row tile; step j's lies at that XOR 32 j, formed on the tile's LDS address (the tiles begin at
+    // multiples of 256 bytes)
+    const uint32_t piece0 = uint32_t(n * D + (swizzle_key<2 * D>(n) ^ hg) * 8) * 2u;
     const TrOffsets<D> tr(lane);
     // Score and dP blocks of a tile.  A lane owns one query row, so what has to be taken off every score (the row's
     // log-sum-exp) and off every dP (the row's delta) is one number per lane: between tiles the LAST block of each
@@ -177,83 +172,93 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
         const int buf = ti & 1;
         wait_vmcnt<0>();                 // the row tiles of ti have landed; everybody is done with tile ti - 1
         __syncthreads();
-        issue_rows(ti + 1, buf ^ 1);     // (past the end: the last tile again, never used)
-
+        if constexpr (GATHER) rows.tokens(row_off, ti + 1);       // (past the end: the last tile again, never used)
         const bool in_a = ti < it.a_total;
         const int kt = in_a ? ti : ti - it.a_total;
         const bool partial = kt >= (in_a ? it.a_full : it.b_full) || (kt + 1) * kTileN > (in_a ? it.n_stream : it.n_src);
         const int limit = in_a ? my_row + 1 : my_vis;
 
-        // operands leave LDS a group of matrix instructions ahead of their use (one wave per SIMD: nobody else hides
-        // that latency); scheduling barriers keep the order
+        // The tile's two 32-key halves are staggered, so that the vector work of one runs beside matrix work of the other:
+        //     matrix pipe:  S, dP of half 0 | S, dP of half 1 | dQ of half 0    | dQ of half 1
+        //     vector ALU :                  | dS of half 0    | dS of half 1    | start values
+        // Matrix instructions in pairs: 2 KS of (S, dP), then DB * SB of dQ.  A pair's operands leave LDS two pairs ahead, one copy of the next
+        // tile stands behind every pair from the second on.
+        // (Groups of eight instructions, all dS between the two products, eight copies in one place: 325 us against 312 on 4 x 4K tokens, 16 / 8
+        // heads of 128 dims, 92 against 87 on 10 x 1.7K, 16 / 2 of 64; the other wave of the SIMD already filled most of those gaps.)
+        typedef bf16x8 lds_bf16x8 __attribute__((address_space(3)));
+        const uint32_t k0 = uint32_t(uintptr_t(&sm.k[0][0])) + buf * (TILE * 2) + piece0, dv = uint32_t(uintptr_t(&sm.v[0][0])) - uint32_t(uintptr_t(&sm.k[0][0]));
         const uint16_t* kb = &sm.k[buf][0];
-        const uint16_t* vb = &sm.v[buf][0];
-        constexpr int G = 4, NG1 = SB * KS / G, NG2 = DB * SB * 2 / (2 * G);
-        bf16x8 fk[2][G], fv[2][G];
-        auto load1 = [&](int g, int slot) {
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const int f = g * G + u, sb = f % SB, j = f / SB;
-                fk[slot][u] = *reinterpret_cast<const bf16x8*>(kb + 32 * sb * D + koff[j]);
-                fv[slot][u] = *reinterpret_cast<const bf16x8*>(vb + 32 * sb * D + koff[j]);
+        constexpr int NS = SB * KS, NG = DB * SB, RING = 3;
+        bf16x8 f0[RING], f1[RING];
+        auto request = [&](int p) {
+            if (p < NS) {
+                const uint32_t at = (k0 ^ uint32_t(32 * (p % KS))) + 64u * (p / KS) * D;
+                f0[p % RING] = *(const lds_bf16x8*)(at);
+                f1[p % RING] = *(const lds_bf16x8*)(at + dv);
+            } else if (p < NS + NG) {
+                const int e = 2 * (p - NS);                       // K^T fragments e and e + 1: d block e % DB, 16-key step e / DB
+                f0[p % RING] = tr.fragment(kb, e / DB, e % DB);
+                f1[p % RING] = tr.fragment(kb, (e + 1) / DB, (e + 1) % DB);
             }
         };
-        auto load2 = [&](int g, int slot) {                 // 2 G fragments of K^T (transposing reads of the K rows): fk then fv of the slot
-#pragma unroll
-            for (int u = 0; u < 2 * G; ++u) {
-                const int f = g * 2 * G + u;
-                (u < G ? fk[slot][u] : fv[slot][u - G]) = tr.fragment(kb, f / DB, f % DB);
-            }
-        };
-        load1(0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int g = 0; g < NG1; ++g) {
-            if (g + 1 < NG1) load1(g + 1, (g + 1) & 1);
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const int f = g * G + u, sb = f % SB, j = f / SB;
-                s_acc[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[g & 1][u], qf[j], j == 0 ? s_acc[SB - 1] : s_acc[sb], 0, 0, 0);
-                dp_acc[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv[g & 1][u], dof[j], j == 0 ? dp_acc[SB - 1] : dp_acc[sb], 0, 0, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        u32x4 dsb[SB][2];
         // lane (n, hg), block sb, register i  <->  key column kt*64 + 32 sb + 16 (i/8) + 8 hg + i%8
-        bf16x8 dsb[SB][2];
-        if (partial) {                   // (uniform) only the tiles on the edge of what the rows may see
-            const int c0 = kt * kTileN + 8 * hg;
+        auto mask = [&](int sb) {
+            const int c0 = kt * kTileN + 8 * hg + 32 * sb;
 #pragma unroll
-            for (int sb = 0; sb < SB; ++sb)
+            for (int i = 0; i < 16; ++i) s_acc[sb][i] = c0 + 16 * (i >> 3) + (i & 7) < limit ? s_acc[sb][i] : -INFINITY;
+        };
+        auto soft = [&](int sb, int piece, int pieces) {         // dS of 16 / pieces registers
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int col = c0 + 32 * sb + 16 * (i >> 3) + (i & 7);
-                    s_acc[sb][i] = col < limit ? s_acc[sb][i] : -INFINITY;
-                }
-        }
-#pragma unroll
-        for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float p = __builtin_amdgcn_exp2f(s_acc[sb][i]);
-                dsb[sb][i >> 3][i & 7] = (__bf16)(p * dp_acc[sb][i]);
+            for (int i = piece * 16 / pieces; i < (piece + 1) * 16 / pieces; i += 2) {
+                bf16x2 ds;
+                ds[0] = (__bf16)(__builtin_amdgcn_exp2f(s_acc[sb][i]) * dp_acc[sb][i]);
+                ds[1] = (__bf16)(__builtin_amdgcn_exp2f(s_acc[sb][i + 1]) * dp_acc[sb][i + 1]);
+                uint32_t w = __builtin_bit_cast(uint32_t, ds);
+                asm volatile("" : "+v"(w));                      // HERE, not in front of its use
+                dsb[sb][i >> 3][(i & 7) / 2] = w;
             }
-        // (written as instructions: left to the compiler, the two constant blocks become thirty-two more live registers)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            asm volatile("v_mov_b32 %0, %1" : "=v"(s_acc[SB - 1][i]) : "v"(neg_lse2));
-            asm volatile("v_mov_b32 %0, %1" : "=v"(dp_acc[SB - 1][i]) : "v"(neg_delta));
-        }
-        load2(0, NG1 & 1);
+        };
+        request(0);
+        request(1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g = 0; g < NG2; ++g) {
-            const int slot = (NG1 + g) & 1;
-            if (g + 1 < NG2) load2(g + 1, slot ^ 1);
+        for (int p = 0; p < NS; ++p) {
+            const int sb = p / KS, j = p % KS;
+            s_acc[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f0[p % RING], qf[j], j == 0 ? s_acc[SB - 1] : s_acc[sb], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            request(p + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            dp_acc[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[p % RING], dof[j], j == 0 ? dp_acc[SB - 1] : dp_acc[sb], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (GATHER && p == 0) rows.form(row_off);
+            if (p > 0 && p <= 2 * NL) issue(ti + 1, buf ^ 1, p - 1);
+            if (sb == 1) soft(0, j, KS);
+            __builtin_amdgcn_sched_barrier(0);
+            // (uniform) only the tiles on the edge of what the rows may see
+            if (j == KS - 1 && partial) mask(sb);
+        }
+        static_assert(2 * NL < NS, "a pair for every copy");
 #pragma unroll
-            for (int u = 0; u < 2 * G; ++u) {
-                const int f = g * 2 * G + u, db = f % DB, st = f / DB;
-                acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u < G ? fk[slot][u] : fv[slot][u - G], dsb[st >> 1][st & 1], acc[db], 0, 0, 0);
+        for (int p = 0; p < NG; ++p) {
+            const int e = 2 * p, slot = (NS + p) % RING, half = p / (NG / 2);
+            acc[e % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f0[slot], __builtin_bit_cast(bf16x8, dsb[half][(e / DB) & 1]), acc[e % DB], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            request(NS + p + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            acc[(e + 1) % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[slot], __builtin_bit_cast(bf16x8, dsb[half][((e + 1) / DB) & 1]), acc[(e + 1) % DB], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (half == 0) {
+                soft(1, p, NG / 2);
+            } else {
+                // the start values again (written as instructions: left to the compiler, the two constant blocks become thirty-two more live registers)
+#pragma unroll
+                for (int i = (p - NG / 2) * 32 / NG; i < (p - NG / 2 + 1) * 32 / NG; ++i) {
+                    asm volatile("v_mov_b32 %0, %1" : "=v"(s_acc[SB - 1][i]) : "v"(neg_lse2));
+                    asm volatile("v_mov_b32 %0, %1" : "=v"(dp_acc[SB - 1][i]) : "v"(neg_delta));
+                }
             }
+            if (GATHER && p == 0) copy_tokens(ti + 2);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
