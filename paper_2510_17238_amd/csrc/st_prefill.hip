@@ -886,7 +886,8 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
     // geometries: rotated keys (packed in any case) 0.94 to 0.98 / 0.99 to 1.01 / 1.00 to 1.03 of the time (heads of 64 dims 1.00); plain 0.74 to
     // 0.92 / 0.90 to 0.99 / 0.97 to 0.99, and 1.02 with eight query heads over a KV head of 128 dims.
     const int64_t mean_tokens = plan->n_tokens / plan->batch;
-    const bool packed = pair || (head_dim == 128 && mean_tokens >= (rope ? 3500 : n_q_heads / n_kv_heads >= 8 ? 5000 : INT64_MAX));
+    const bool packed = pair || !gather_fits(plan->n_tokens, n_kv_heads, head_dim) ||
+                        (head_dim == 128 && mean_tokens >= (rope ? 3500 : n_q_heads / n_kv_heads >= 8 ? 5000 : INT64_MAX));
     // The four waves of a workgroup share the key tiles of one KV head; they take 4, 2 or 1 (sets of) query heads of it and
     // 32, 64 or 128 rows of the item -- as many heads as the group has: fewer rows end closer to their item's last visible
     // column, so less of the issued arithmetic is masked or belongs to no row (useful share 0.89 / 0.93 / 0.95 with 1 / 2 / 4

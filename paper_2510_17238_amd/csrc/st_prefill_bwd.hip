@@ -822,7 +822,7 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
     ST_HIP(plan->wait_built(s));
     const PlanView pv = plan->view();
     float* delta = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + L.delta);
-    // bf16: two MFMA kernels over the rows of the tensors, or over packed row tiles where a tensor is not aligned to 16 bytes
+    // bf16: two MFMA kernels over the rows of the tensors, or over packed row tiles (a tensor that is not aligned to 16 bytes, or of 4 GiB)
     auto run_mfma = [&](auto dtag, auto gtag) -> st_status {
         constexpr int HD = decltype(dtag)::value;
         constexpr bool GATHER = decltype(gtag)::value;
@@ -870,7 +870,8 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
                            reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + L.partial), s);
     else {
         auto run = [&](auto dtag) {
-            return aligned16(q) && aligned16(k) && aligned16(v) && aligned16(d_out) ? run_mfma(dtag, std::true_type{}) : run_mfma(dtag, std::false_type{});
+            const bool gather = aligned16(q) && aligned16(k) && aligned16(v) && aligned16(d_out) && gather_fits(plan->n_tokens, n_q_heads, head_dim);
+            return gather ? run_mfma(dtag, std::true_type{}) : run_mfma(dtag, std::false_type{});
         };
         r = head_dim == 64 ? run(std::integral_constant<int, 64>{}) : run(std::integral_constant<int, 128>{});
     }

@@ -182,6 +182,10 @@ struct RowGather {
     }
 };
 
+// A gathered row's byte offset and the 3 KB that take the immediate offsets back have to fit 32 bits together: true of every tensor but one
+// within 4 KB of 4 GiB, which is packed instead.
+inline bool gather_fits(int64_t n_tokens, int n_heads, int head_dim) { return n_tokens * n_heads * head_dim * 2 <= int64_t(0xffffffff) - 4096; }
+
 // parts of kTileM / head_waves rows of an item that a launch has workgroups for
 __host__ __device__ inline int item_parts(const PlanView& pv, int head_waves) { return (pv.parts32 * head_waves + 3) / 4; }
 // Rows [sub * part_rows, + part_rows) of a work item as an item of their own, with the extents as the plan builds them
