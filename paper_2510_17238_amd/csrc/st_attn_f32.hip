@@ -22,7 +22,7 @@
 // stand behind the matrix instructions of the present one (left to the compiler, the two ran one behind the other: key side 168 us
 // against 147).  The workgroups end in two uneven rounds.
 // Two sequences of about 900 tokens, 16 / 8 heads of 128 dims, us: forward 90 with the fp32 instructions -> 62, query side 137 -> 102,
-// key side 212 -> 146; the training step with tables and rotation 432 -> 307.
+// key side 212 -> 146; the training step with tables and rotation 432 -> 317.
 #include <math.h>
 
 #include <type_traits>
@@ -36,7 +36,7 @@ constexpr int kF32Waves = 4, kF32Rows = 32;
 // exp(x) = 2^n 2^f: x log2(e) = n + f with f in [-1/2, 1/2] exact but for its last bit, so that no rounding grows with x (2^(x log2(e)) of
 // the rounded product is off by half a unit of it: 5e-7 at x = -8, 1.8e-6 at -32).  For every x what expf gives: 0.85e-7 at most against 64 bits (expf 0.82e-7)
 // over [-32, 0], subnormal results, Inf and NaN included -- in eight instructions, expf's range checks left to one clamp (the training step
-// below: 307 us, 322 with expf).
+// above: 5 us more than the rounded product, expf 20).
 __device__ __forceinline__ float exp_f32(float x) {
     constexpr float kHi = 1.4426950408889634f, kLo = 1.925963033500e-8f;                   // log2(e) in two terms
     const float n = __builtin_amdgcn_fmed3f(__builtin_rintf(x * kHi), -200.f, 200.f);
@@ -79,12 +79,16 @@ struct RowsLds {
     float x[kF32Rows][D + 4];
 };
 
-// An fp32 operand as three bf16 terms, each the rounded rest of the one before: 8 + 8 + 8 bits, so h + m + l is x to 2^-26 or better.
+// An fp32 operand as three bf16 terms of 2^24 x, each the rounded rest of the one before: 8 + 8 + 8 bits, so h + m + l is 2^24 x to the
+// last bit for every finite x below 2^104 (2e31).  Unscaled, the last terms of an x below 2^-110 would be subnormal and lost: results
+// 1e-3 to 9e-2 off with operands of 2^-118.  From 2^104 on a term is Inf, which shows in the result (see Walk).  Products come out as
+// 2^48 of themselves.  (Two instructions on eleven per pair of values: 307 -> 317 us for the training step above.)
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
 struct Planes {
     bf16x8 h, m, l;
 };
 // Eight values of a lane (the k-values of an operand) on their way into planes, two of them at a time: pair w's first terms and what
-// is left, then its other two.  slot(): the same in six pieces of 6 to 10 instructions, one behind a matrix instruction each.
+// is left, then its other two.  slot(): the same in six pieces of 6 to 14 instructions, one behind a matrix instruction each.
 struct Split8 {
     u32x4 h, m, l;
     f32x4 r0, r1;
@@ -100,10 +104,11 @@ struct Split8 {
     static __device__ __forceinline__ float upper(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
     __device__ __forceinline__ void first(int w, float x0, float x1) {
 #pragma clang fp contract(off)          // (x0 may be a product: fused with the difference it would be split unrounded, here but not there)
-        const uint32_t word = pack(x0, x1);
+        const float y0 = x0 * kUp, y1 = x1 * kUp;
+        const uint32_t word = pack(y0, y1);
         h[w] = word;
-        r0[w] = x0 - lower(word);
-        r1[w] = x1 - upper(word);
+        r0[w] = y0 - lower(word);
+        r1[w] = y1 - upper(word);
     }
     __device__ __forceinline__ void second(int w) {
 #pragma clang fp contract(off)
@@ -206,7 +211,8 @@ __device__ __forceinline__ void park(float (&rows)[kF32Rows][D + 4], const f32x1
 // it.  A NaN stays, so the kernels walk their blocks without a look at this and check what comes out: a workgroup whose result
 // is not finite throws it away and walks again with care -- in blocks with masked pairs the operand rows that hold such
 // a value leave the product and are added to the columns that see them alone.  What that leaves non-finite has seen such a value; as three terms
-// an Inf is Inf and NaNs, and a finite value above 3.389e38 is Inf: those entries are taken from a third walk, on fp32 instructions.
+// an Inf is Inf and NaNs, so is a finite value from 2^104 on (Planes), and a product beyond 2^80 overflows: those entries are taken from a third
+// walk, on fp32 instructions.
 // (Looking at the operands in every such block cost 4 % of the forward and 4 to 14 % of the gradients, most of it in registers; looking
 // at the result costs 1 %, 0.2 us of the smallest forward.)
 enum class Walk { kFast, kCareful, kFp32 };
@@ -235,16 +241,17 @@ __device__ __forceinline__ bool any_wave(const int (&bad)[kF32Waves]) {
     for (int w = 0; w < kF32Waves; ++w) any |= bad[w];
     return any != 0;
 }
-// Sets the rows of an operand that hold a value that is not finite, or is not as bf16 (above 3.389e38), to zero; returned: bit r, row r
+// Sets the rows of an operand that hold a value that is not finite, or not as bf16 terms (SPLIT), to zero; returned: bit r, row r
 // of the block (x[g] holds row acc_row(g, hg)).
-template <int DB>
+template <bool SPLIT, int DB>
 __device__ __forceinline__ uint32_t take_out(float (&x)[16][DB], int hg) {
+    constexpr float kLimit = SPLIT ? kUp * 1.00390625f : 1.f;      // (a value that is rounded up to 2^104 overflows with this)
     uint32_t rows = 0u;
 #pragma unroll
     for (int g = 0; g < 16; ++g) {
         float z = 0.f;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) z = fmaf(x[g][db] * 1.00390625f, 0.f, z);
+        for (int db = 0; db < DB; ++db) z = fmaf(x[g][db] * kLimit, 0.f, z);
         const unsigned long long lanes = __ballot(z != z);
         const bool lower = uint32_t(lanes) != 0u, upper = uint32_t(lanes >> 32) != 0u;
         rows |= (lower ? 1u << acc_row(g, 0) : 0u) | (upper ? 1u << acc_row(g, 1) : 0u);
@@ -253,13 +260,13 @@ __device__ __forceinline__ uint32_t take_out(float (&x)[16][DB], int hg) {
     }
     return rows;
 }
-// weight x row r (uniform; `row` points at its dim 4 hg) added to the columns that see it; w: the block's weights
-template <int D>
+// weight x row r (uniform; `row` points at its dim 4 hg) added to the columns that see it; w: the block's weights; SPLIT: acc is 2^48 of the sum
+template <bool SPLIT, int D>
 __device__ __forceinline__ void add_row(f32x16 (&acc)[D / 32], const f32x16& w, const float* row, int r, int n, bool seen) {
     float weight = w[0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) weight = i == 4 * (r >> 3) + (r & 3) ? w[i] : weight;
-    weight = __shfl(weight, n + 32 * ((r >> 2) & 1));
+    weight = __shfl(weight, n + 32 * ((r >> 2) & 1)) * (SPLIT ? 1.f / kDown : 1.f);
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -290,6 +297,8 @@ __device__ __forceinline__ bool prefill_f32_walk(const HeadRows& at, float* __re
                                                  PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
     constexpr int JJ = D / 8, DB = D / 32, KS = D / 16;
     constexpr bool CAREFUL = WALK != Walk::kFast, FP32 = WALK == Walk::kFp32;
+    constexpr float kUnit = FP32 ? 1.f : kDown;              // a product's unit
+    const float s_scale = scale * kUnit;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     FwdF32Smem<D>& sm = *reinterpret_cast<FwdF32Smem<D>*>(smem_raw);
     const int hk = at.hk, hq = at.hq;
@@ -389,7 +398,7 @@ __device__ __forceinline__ bool prefill_f32_walk(const HeadRows& at, float* __re
         const int limit = in_a ? my_row + 1 : my_vis;                      // columns < limit are visible
         const int limit_min = in_a ? own.first + 1 : first_vis;            // ... to every row
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] *= scale;
+        for (int i = 0; i < 16; ++i) s[i] *= s_scale;
         if (c0 + kF32Rows > limit_min) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[i] = c0 + acc_row(i, hg) < limit ? s[i] : -INFINITY;
@@ -415,9 +424,9 @@ __device__ __forceinline__ bool prefill_f32_walk(const HeadRows& at, float* __re
             l_run += s[i];
         }
         if (CAREFUL && c0 + kF32Rows > limit_min) {
-            for (uint32_t rows = take_out<DB>(vf, hg); rows != 0u; rows &= rows - 1u) {
+            for (uint32_t rows = take_out<!FP32>(vf, hg); rows != 0u; rows &= rows - 1u) {
                 const int r = __ffs(rows) - 1;
-                add_row<D>(o_acc, s, v + __shfl(tok, r) * stride + int64_t(hk) * D + 4 * hg, r, n, c0 + r < limit);
+                add_row<!FP32, D>(o_acc, s, v + __shfl(tok, r) * stride + int64_t(hk) * D + 4 * hg, r, n, c0 + r < limit);
             }
         }
         // ---- O^T += V^T P^T; the next block's keys are requested beside it ----
@@ -485,7 +494,7 @@ __device__ __forceinline__ bool prefill_f32_walk(const HeadRows& at, float* __re
         wt[w] = expf(sm.m[w][row] - m_all);                                // (0 for a wave that saw nothing)
         den = fmaf(wt[w], sm.l[w][row], den);
     }
-    const float inv = 1.f / den;
+    const float inv = kUnit / den;
     f32x4 a[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
@@ -546,6 +555,8 @@ __device__ __forceinline__ bool bwd_dq_f32_walk(const HeadRows& at, float* __res
                                                 PlanView pv, int n_q_heads, int n_kv_heads, float scale) {
     constexpr int JJ = D / 8, DB = D / 32, KS = D / 16;
     constexpr bool CAREFUL = WALK != Walk::kFast, FP32 = WALK == Walk::kFp32;
+    constexpr float kUnit = FP32 ? 1.f : kDown;              // a product's unit
+    const float s_scale = scale * kUnit;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     DqF32Smem<D, HB>& sm = *reinterpret_cast<DqF32Smem<D, HB>*>(smem_raw);
     const int hk = at.hk, hq = at.hq;
@@ -684,15 +695,15 @@ __device__ __forceinline__ bool bwd_dq_f32_walk(const HeadRows& at, float* __res
         for (int h = 0; h < HB; ++h)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                float p = exp_f32(fmaf(s[h][i], scale, -my_lse[h]));
+                float p = exp_f32(fmaf(s[h][i], s_scale, -my_lse[h]));
                 if (partial) p = c0 + acc_row(i, hg) < limit ? p : 0.f;
-                s[h][i] = p * (dp[h][i] - my_delta[h]) * scale;
+                s[h][i] = p * fmaf(dp[h][i], kUnit, -my_delta[h]) * scale;
                 if (CAREFUL) s[h][i] = c0 + acc_row(i, hg) < limit ? s[h][i] : 0.f;
             }
         if (CAREFUL && partial) {
-            for (uint32_t rows = take_out<DB>(kt, hg); rows != 0u; rows &= rows - 1u) {
+            for (uint32_t rows = take_out<!FP32>(kt, hg); rows != 0u; rows &= rows - 1u) {
                 const int r = __ffs(rows) - 1;
-                add_row<D>(acc[0], s[0], k_rows + __shfl(tok, r) * stride, r, n, c0 + r < limit);
+                add_row<!FP32, D>(acc[0], s[0], k_rows + __shfl(tok, r) * stride, r, n, c0 + r < limit);
             }
         }
         // ---- dQ^T += K^T dS^T; the next block's rows are requested beside it ----
@@ -765,6 +776,7 @@ __device__ __forceinline__ bool bwd_dq_f32_walk(const HeadRows& at, float* __res
 #pragma unroll
             for (int w = 1; w < kF32Waves; ++w) a[h][db] += *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][4 * part + 32 * db]);
             z = fold_finite(z, a[h][db]);
+            a[h][db] *= kUnit;
         }
     }
     bool finite = true;
@@ -831,6 +843,8 @@ __device__ __forceinline__ bool bwd_dkv_f32_walk(unsigned block, float* __restri
                                                  int parts, float* __restrict__ partial, int64_t partial_stride) {
     constexpr int JJ = D / 8, DB = D / 32, KS = D / 16;
     constexpr bool CAREFUL = WALK != Walk::kFast, FP32 = WALK == Walk::kFp32;
+    constexpr float kUnit = FP32 ? 1.f : kDown;              // a product's unit
+    const float s_scale = scale * kUnit;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     DkvF32Smem<D>& sm = *reinterpret_cast<DkvF32Smem<D>*>(smem_raw);
     const unsigned per_item = unsigned(n_kv_heads) * unsigned(pv.parts32) * unsigned(parts);
@@ -992,21 +1006,21 @@ __device__ __forceinline__ bool bwd_dkv_f32_walk(unsigned block, float* __restri
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int r = acc_row(i, hg);
-            float p = exp_f32(fmaf(s[i], scale, -__shfl(l_row, r)));
+            float p = exp_f32(fmaf(s[i], s_scale, -__shfl(l_row, r)));
             if (!full) p = my_key < __shfl(lim, r) ? p : 0.f;
             s[i] = p;
-            dp[i] = p * (dp[i] - __shfl(d_row, r)) * scale;
+            dp[i] = p * fmaf(dp[i], kUnit, -__shfl(d_row, r)) * scale;
             if (CAREFUL && !full) dp[i] = my_key < __shfl(lim, r) ? dp[i] : 0.f;
         }
         if (CAREFUL && !full) {
             auto row_of = [&](const float* x, int r) { return x + (int64_t(__shfl(tok, r)) * n_q_heads + cur.hq) * D + 4 * hg; };
-            for (uint32_t rows = take_out<DB>(ot, hg); rows != 0u; rows &= rows - 1u) {
+            for (uint32_t rows = take_out<!FP32>(ot, hg); rows != 0u; rows &= rows - 1u) {
                 const int r = __ffs(rows) - 1;
-                add_row<D>(dv_acc, s, row_of(d_out, r), r, n, my_key < __shfl(lim, r));
+                add_row<!FP32, D>(dv_acc, s, row_of(d_out, r), r, n, my_key < __shfl(lim, r));
             }
-            for (uint32_t rows = take_out<DB>(qt, hg); rows != 0u; rows &= rows - 1u) {
+            for (uint32_t rows = take_out<!FP32>(qt, hg); rows != 0u; rows &= rows - 1u) {
                 const int r = __ffs(rows) - 1;
-                add_row<D>(dk_acc, dp, row_of(q, r), r, n, my_key < __shfl(lim, r));
+                add_row<!FP32, D>(dk_acc, dp, row_of(q, r), r, n, my_key < __shfl(lim, r));
             }
         }
         // ---- dV^T += dO^T P, dK^T += Q^T dS; the next rows are requested beside them ----
@@ -1064,6 +1078,7 @@ __device__ __forceinline__ bool bwd_dkv_f32_walk(unsigned block, float* __restri
 #pragma unroll
             for (int w = 1; w < kF32Waves; ++w) a[which][db] += *reinterpret_cast<const f32x4*>(&sm.merge.o[w][row][4 * part + 32 * db]);
             z = fold_finite(z, a[which][db]);
+            a[which][db] *= kUnit;
         }
     }
     bool finite = true;
