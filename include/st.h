@@ -213,6 +213,10 @@ st_status st_plan_tile_classes(const st_plan* plan, int32_t seq, int32_t block,
  * bf16: in a tile that a row sees in part, a non-finite v of a token that it does not
  * see may reach it (0 x Inf is NaN); the same holds for the gradients.
  *
+ * Results over inputs: bf16, out may be q itself, and out and lse may lie over k and v in any
+ * way (the call then works on packed copies of these).  f32: no result may share memory with an
+ * input.
+ *
  * workspace (bf16 only): at least st_prefill_workspace_bytes(...) bytes, 256-byte
  * aligned; holds K and V^T regrouped into contiguous key tiles for the duration of
  * the call (about the size of k plus v), and room for the rotation table of
@@ -272,6 +276,9 @@ st_status st_attn_prefill_ids(void* out, float* lse, const void* q, const void* 
  * long or ragged sequences) both add 8 * parts * N * n_kv_heads * head_dim bytes of fp32 partial
  * sums -- with 16 / 2 heads of 128 dims and 8 parts, 1.8 times q, k, v, d_out on top.  Errors as for st_attn_prefill, but the tensors need only be aligned to
  * their elements here (gradients may be slices of a flat buffer).
+ * Results over inputs: ST_BF16, dq may be q or d_out itself or lie over `out`, dk and dv may lie over
+ * q, d_out and `out`, and each may be k or v itself (the call then works on packed copies where
+ * rows are read after others are written).  Any other overlap, and any with ST_F32, is not allowed.
  * ---------------------------------------------------------------------- */
 size_t st_prefill_bwd_workspace_bytes(const st_plan* plan, int32_t n_q_heads, int32_t n_kv_heads,
                                       int32_t head_dim, st_dtype dt);

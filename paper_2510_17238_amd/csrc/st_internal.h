@@ -56,6 +56,11 @@ struct WaveTrace {
 WaveTrace prof_wave_trace();
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+// do two ranges of memory share a byte?
+inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + b_bytes && y < x + a_bytes;
+}
 
 // ---- device-side vector types -------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

@@ -885,8 +885,13 @@ static st_status prefill_impl(void* out, float* lse, const void* q, const void* 
     // gathered rows of V cost their transposing reads.  Gathered against packed, batches of 2K / 4K / 8K tokens a sequence, four head
     // geometries: rotated keys (packed in any case) 0.94 to 0.98 / 0.99 to 1.01 / 1.00 to 1.03 of the time (heads of 64 dims 1.00); plain 0.74 to
     // 0.92 / 0.90 to 0.99 / 0.97 to 0.99, and 1.02 with eight query heads over a KV head of 128 dims.
+    // Packed always where a result lies over K or V: workgroups still gather rows that others have written over.
     const int64_t mean_tokens = plan->n_tokens / plan->batch;
-    const bool packed = pair || !gather_fits(plan->n_tokens, n_kv_heads, head_dim) ||
+    const size_t rows = size_t(plan->n_tokens), q_bytes = rows * n_q_heads * head_dim * 2, kv_bytes = rows * n_kv_heads * head_dim * 2;
+    auto written_over = [&](const void* kv) {
+        return overlap(out, q_bytes, kv, kv_bytes) || (lse && overlap(lse, rows * n_q_heads * sizeof(float), kv, kv_bytes));
+    };
+    const bool packed = pair || written_over(k) || written_over(v) || !gather_fits(plan->n_tokens, n_kv_heads, head_dim) ||
                         (head_dim == 128 && mean_tokens >= (rope ? 3500 : n_q_heads / n_kv_heads >= 8 ? 5000 : INT64_MAX));
     // The four waves of a workgroup share the key tiles of one KV head; they take 4, 2 or 1 (sets of) query heads of it and
     // 32, 64 or 128 rows of the item -- as many heads as the group has: fewer rows end closer to their item's last visible

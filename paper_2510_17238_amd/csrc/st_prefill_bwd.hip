@@ -40,13 +40,27 @@ struct BwdDqSmem {
     unsigned char tokens[RowGather<D>::kBytes];
 };
 
-// GATHER: k and v are the tensors, else their packed row tiles.
+// delta of a row, half of it per lane (hg): dims 8 hg + 16 j .. + 7; the two halves are then added.  (One order of the sum for all that form it.)
+template <int KS>
+__device__ __forceinline__ float half_delta(const bf16x8 (&d_out)[KS], const uint16_t* out) {
+    float x = 0.f;
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+        const bf16x8 o = *reinterpret_cast<const bf16x8_a2*>(out + 16 * j);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x = fmaf(float(d_out[j][e]), float(o[e]), x);
+    }
+    return x;
+}
+
+// GATHER: k and v are the tensors, delta is formed from `out`; else k and v are packed row tiles, and delta has been formed with them.
 template <int D, bool GATHER>
 __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restrict__ dq, const uint16_t* __restrict__ d_out,
                                                              const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                              const uint16_t* __restrict__ v, const uint16_t* __restrict__ out,
-                                                             const float* __restrict__ lse, float* __restrict__ stats,
-                                                             PlanView pv, int n_q_heads, int n_kv_heads, float scale, int head_waves) {
+                                                             const float* __restrict__ delta, const float* __restrict__ lse,
+                                                             float* __restrict__ stats, PlanView pv, int n_q_heads, int n_kv_heads,
+                                                             float scale, int head_waves) {
     constexpr int KS = D / 16, DB = D / 32, SB = kTileN / 32;
     constexpr int TILE = kTileN * D;
     constexpr int NL = TILE * 2 / 1024 / 4;
@@ -121,14 +135,13 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
     // delta of the row; what the key side needs of it -- for every 64-row tile of a stream and every query head one 1 KB block of 256 floats:
     // [0, 64) MINUS lse in base-2 units (-inf for rows past the end of the stream: their probabilities become 0), [64, 128) MINUS
     // delta, [128, 192) the visible-source count of the row (as int bits) -- comes from here, where dO is at hand.
-    float my_delta = 0.f;
-#pragma unroll
-    for (int j = 0; j < KS; ++j) {
-        const bf16x8 o = *reinterpret_cast<const bf16x8_a2*>(out + rowhead * D + 8 * hg + 16 * j);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) my_delta = fmaf(float(dof[j][e]), float(o[e]), my_delta);
+    float my_delta;
+    if constexpr (GATHER) {
+        my_delta = half_delta<KS>(dof, out + rowhead * D + 8 * hg);
+        my_delta += __shfl_xor(my_delta, 32);
+    } else {
+        my_delta = delta[rowhead];
     }
-    my_delta += __shfl_xor(my_delta, 32);
     {
         auto put_stats = [&](int row, float neg_lse, float neg_delta, int vis) {
             float* blk = stats + (size_t(hq) * pv.pack_tiles + it.tile_a0 + row / kTileN) * 256 + row % kTileN;
@@ -278,12 +291,14 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(uint16_t* __restric
 }
 
 
-// Row tiles of dO, Q, K and V for tensors that are not aligned to 16 bytes (a gradient may be a slice of a flat buffer): the
-// asynchronous copies of the gradient kernels take aligned pieces, so such tensors are gathered into packed tiles first, in one pass.  A
-// workgroup takes one tile of one head of one tensor, the heads of all four side by side: 0 .. n_q_heads - 1 dO, then Q, then K, then V.
+// Row tiles of dO, Q, K and V, and delta, for tensors that are not aligned to 16 bytes (a gradient may be a slice of a flat buffer): the
+// asynchronous copies of the gradient kernels take aligned pieces; and for gradients that are written over an input, which would be
+// gathered after that.  All is read in one pass before anything is written.  A workgroup takes one tile of one head of one
+// tensor, the heads of all four side by side: 0 .. n_q_heads - 1 dO and delta, then Q, then K, then V.
 struct BwdPackArgs {
-    const uint16_t *d_out, *q, *k, *v;
+    const uint16_t *d_out, *q, *k, *v, *out;
     uint16_t *dorows, *qrows, *krows, *vrows;
+    float* delta;
     int n_q_heads, n_kv_heads;
 };
 template <int D>
@@ -302,6 +317,17 @@ __global__ __launch_bounds__(256) void bwd_pack_kernel(BwdPackArgs a, PlanView p
     const uint16_t* src = query_side ? (second ? a.q : a.d_out) : second ? a.v : a.k;
     pack_rows<D>(dst + (size_t(h) * pv.pack_tiles + tile) * (kTileN * D), src, pv.perm + info.base, info.valid, uint32_t(heads) * D, uint32_t(h),
                  [](int, uint32_t, const u32x4&) {});
+    if (!query_side || second) return;
+    // delta: two lanes per row
+    const int row = int(threadIdx.x) >> 1, hg = int(threadIdx.x) & 1;
+    if (row >= info.valid) return;
+    const int64_t rowhead = int64_t(pv.perm[info.base + row]) * a.n_q_heads + h;
+    bf16x8 x[D / 16];
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j) x[j] = *reinterpret_cast<const bf16x8_a2*>(a.d_out + rowhead * D + 8 * hg + 16 * j);
+    float dl = half_delta<D / 16>(x, a.out + rowhead * D + 8 * hg);
+    dl += __shfl_xor(dl, 1);
+    if (hg == 0) a.delta[rowhead] = dl;
 }
 
 // dK, dV: one workgroup per (128 keys of one stream of one sequence, KV head) -- the forward's work items read
@@ -822,7 +848,8 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
     ST_HIP(plan->wait_built(s));
     const PlanView pv = plan->view();
     float* delta = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + L.delta);
-    // bf16: two MFMA kernels over the rows of the tensors, or over packed row tiles (a tensor that is not aligned to 16 bytes, or of 4 GiB)
+    // bf16: two MFMA kernels over the rows of the tensors, or over packed row tiles (a tensor that is not aligned to 16 bytes, or of 4 GiB, or
+    // that is written over by a gradient while or before its rows are read)
     auto run_mfma = [&](auto dtag, auto gtag) -> st_status {
         constexpr int HD = decltype(dtag)::value;
         constexpr bool GATHER = decltype(gtag)::value;
@@ -831,8 +858,8 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
         float* stats = reinterpret_cast<float*>(w + L.stats);
         float* partial = reinterpret_cast<float*>(w + L.partial);
         if (!GATHER) {
-            const BwdPackArgs pack{(const uint16_t*)d_out, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v,
-                                   at(L.dorows), at(L.qrows), at(L.krows), at(L.vrows), n_q_heads, n_kv_heads};
+            const BwdPackArgs pack{(const uint16_t*)d_out, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)out,
+                                   at(L.dorows), at(L.qrows), at(L.krows), at(L.vrows), delta, n_q_heads, n_kv_heads};
             hipLaunchKernelGGL((bwd_pack_kernel<HD>), dim3((unsigned)pack_blocks), dim3(256), 0, s, pack, pv);
         }
         const size_t smem_q = sizeof(BwdDqSmem<HD>), smem_k = sizeof(BwdDkvSmem<HD>);
@@ -846,7 +873,7 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
         prof_begin(kProfBwdDq, s);
         for (int rep = 0; rep < prof_repeat(); ++rep)
         hipLaunchKernelGGL((bwd_dq_mfma_kernel<HD, GATHER>), dim3((unsigned)(qblocks / head_waves * item_parts(pv, head_waves))), dim3(256), smem_q, s, (uint16_t*)dq, (const uint16_t*)d_out,
-                           (const uint16_t*)q, GATHER ? (const uint16_t*)k : at(L.krows), GATHER ? (const uint16_t*)v : at(L.vrows), (const uint16_t*)out, lse, stats, pv,
+                           (const uint16_t*)q, GATHER ? (const uint16_t*)k : at(L.krows), GATHER ? (const uint16_t*)v : at(L.vrows), (const uint16_t*)out, delta, lse, stats, pv,
                            n_q_heads, n_kv_heads, scale, head_waves);
         prof_end(kProfBwdDq, s);
         prof_begin(kProfBwdDkv, s);
@@ -870,7 +897,15 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
                            reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + L.partial), s);
     else {
         auto run = [&](auto dtag) {
-            const bool gather = aligned16(q) && aligned16(k) && aligned16(v) && aligned16(d_out) && gather_fits(plan->n_tokens, n_q_heads, head_dim);
+            // dq is written while K and V are gathered and before Q and dO are, dk and dv while Q and dO are; a row of `out`, and a
+            // workgroup's own keys and values, are read before the same rows are written.
+            const size_t row_bytes = size_t(plan->n_tokens) * head_dim * 2, q_bytes = row_bytes * n_q_heads, kv_bytes = row_bytes * n_kv_heads;
+            const bool written_over = overlap(dq, q_bytes, q, q_bytes) || overlap(dq, q_bytes, d_out, q_bytes) || overlap(dq, q_bytes, k, kv_bytes) ||
+                                      overlap(dq, q_bytes, v, kv_bytes) || (dq != out && overlap(dq, q_bytes, out, q_bytes)) ||
+                                      overlap(dk, kv_bytes, q, q_bytes) || overlap(dk, kv_bytes, d_out, q_bytes) ||
+                                      overlap(dv, kv_bytes, q, q_bytes) || overlap(dv, kv_bytes, d_out, q_bytes);
+            const bool gather = !written_over && aligned16(q) && aligned16(k) && aligned16(v) && aligned16(d_out) &&
+                                gather_fits(plan->n_tokens, n_q_heads, head_dim);
             return gather ? run_mfma(dtag, std::true_type{}) : run_mfma(dtag, std::false_type{});
         };
         r = head_dim == 64 ? run(std::integral_constant<int, 64>{}) : run(std::integral_constant<int, 128>{});
