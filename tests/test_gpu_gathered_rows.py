@@ -90,3 +90,33 @@ def test_long_sequences_on_either_side_of_the_packed_tiles(st, fused, hq, hkv, d
             p = np.exp(s - s.max())
             ref = (p / p.sum()) @ v[:, h // (hq // hkv)].astype(np.float64)
             assert np.abs(got[row, h] - ref).max() <= (4e-2 if fused else 2e-2), (row, h)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(5, 5, 128), (12, 6, 64), (8, 8, 128), (7, 7, 64), (1, 1, 128)])
+def test_rotated_keys_of_several_heads_per_workgroup(st, hq, hkv, d):
+    """From 4,096 (key tile, head) pairs on a workgroup rotates four heads, the last one what is left of them: the batch as a whole
+    against its parts, which have fewer, bit for bit, and three sequences against the oracle."""
+    rng = np.random.Generator(np.random.PCG64(75))
+    per_part, pairs = -(-4096 // (4 * 2 * hkv)), 0
+    lists = [(rng.integers(0, 60, 2), rng.integers(1, 60, 2)) for _ in range(4 * per_part)]
+    for s, r in lists:
+        pairs += (-(-int(s.sum() + r.sum()) // 64) + 1) * hkv
+    cfg = W._assemble("short", "bf16", hq, hkv, d, lists, "interleaved", 76)
+    q, k, v = cfg.tensors()
+    tq, tk, tv = (to_dev(x, "bf16") for x in (q, k, v))
+    ids = (*ids_to_dev(cfg),)
+
+    def run(b0, b1):
+        sl = slice(int(cfg.cu_seqlens[b0]), int(cfg.cu_seqlens[b1]))
+        plan = st.st_plan_create(*(x[sl].contiguous() for x in ids), cfg.cu_seqlens[b0:b1 + 1] - cfg.cu_seqlens[b0]).heads_per_workgroup(1)
+        return st.st_attn_prefill_rope(tq[sl], tk[sl], tv[sl], ids[2][sl].contiguous(), cfg.theta, plan)
+
+    assert pairs >= 4096 > pairs / 4 * 1.2
+    whole = run(0, len(lists))
+    parts = [run(p * per_part, (p + 1) * per_part) for p in range(4)]
+    assert torch.equal(whole, torch.cat(parts))
+    for b in (0, len(lists) // 2, len(lists) - 1):
+        sl = slice(int(cfg.cu_seqlens[b]), int(cfg.cu_seqlens[b + 1]))
+        ref, _ = O.attention_dense(O.rope(q[sl], cfg.positions[sl], cfg.theta), O.rope(k[sl], cfg.positions[sl], cfg.theta), v[sl], cfg.stream_ids[sl],
+                                   cfg.segment_ids[sl], cfg.positions[sl])
+        assert np.abs(to_f64(whole[sl]) - ref).max() <= 4e-2, b
