@@ -207,8 +207,10 @@ st_status st_plan_tile_classes(const st_plan* plan, int32_t seq, int32_t block,
  * fp32 accumulation and fp32 softmax state; the queries carry the softmax scale
  * (q * scale * log2(e), rounded to bf16 once more: a perturbation of q of at most
  * half a bf16 unit in the last place, the size of its own quantisation), the
- * probabilities are rounded to bf16 before the second product.  f32: fp32 products
- * and sums.
+ * probabilities are rounded to bf16 before the second product.  f32: operands and
+ * weights are multiplied with all their 24 bits (as three bf16 terms each on the matrix cores;
+ * what is left out of a product is below 2^-26 of it), fp32 sums; finite values from 2^104 on and
+ * products from 2^80 on, which the terms cannot hold, by fp32 instructions, several times slower.
  * Inf and NaN: f32, a token's values reach the rows that see the token and no others.
  * bf16: in a tile that a row sees in part, a non-finite v of a token that it does not
  * see may reach it (0 x Inf is NaN); the same holds for the gradients.
@@ -218,9 +220,11 @@ st_status st_plan_tile_classes(const st_plan* plan, int32_t seq, int32_t block,
  * input.
  *
  * workspace (bf16 only): at least st_prefill_workspace_bytes(...) bytes, 256-byte
- * aligned; holds K and V^T regrouped into contiguous key tiles for the duration of
- * the call (about the size of k plus v), and room for the rotation table of
- * st_attn_prefill_rope (head_dim * 4 bytes per token).  Not needed for f32 (may be NULL).
+ * aligned, room for K and V^T regrouped into contiguous key tiles (about the size of k plus v) and
+ * for the rotation table of st_attn_prefill_rope (head_dim * 4 bytes per token).  Touched for the
+ * duration of the call as far as its form needs: tiles of both for long sequences and where a
+ * result lies over k or v, tiles of k and the table where keys are rotated, else nothing.  Not
+ * needed for f32 (may be NULL).
  * ---------------------------------------------------------------------- */
 size_t st_prefill_workspace_bytes(const st_plan* plan, int32_t n_kv_heads, int32_t head_dim, st_dtype dt);
 
@@ -267,12 +271,13 @@ st_status st_attn_prefill_ids(void* out, float* lse, const void* q, const void* 
  * all of dtype dt, same plan as the forward.  Deterministic (no atomics).
  * ST_BF16: products on the matrix cores (bf16 operands -- P and dS are rounded to bf16 before the
  * second products, as the forward rounds P -- fp32 accumulation).
- * ST_F32: fp32 products and sums (the matrix cores' fp32 instructions); Inf and NaN stay with the
- * pairs that the mask allows, as in the forward.
+ * ST_F32: products of 24 bits as three bf16 terms and fp32 sums, as in the forward; Inf and NaN stay
+ * with the pairs that the mask allows, as in the forward.
  * workspace: at least st_prefill_bwd_workspace_bytes(plan, n_q_heads, n_kv_heads, head_dim, dt)
- * bytes, 256-byte aligned.  The size depends on the plan, ask for it: ST_BF16 keeps 64-row tiles of
- * every operand (about 1.1 times the bytes of q, k, v, d_out), ST_F32 4 bytes per token and query
- * head; and where the query heads of a KV head are split over `parts` workgroups (2 .. 8, for few,
+ * bytes, 256-byte aligned.  The size depends on the plan, ask for it: ST_BF16 has room for 64-row
+ * tiles of every operand (about 1.1 times the bytes of q, k, v, d_out; touched where a tensor is not
+ * aligned to 16 bytes or lies under a result, which the size does not know) and keeps 1 KB of row
+ * statistics per 64 rows and query head, ST_F32 4 bytes per token and query head; and where the query heads of a KV head are split over `parts` workgroups (2 .. 8, for few,
  * long or ragged sequences) both add 8 * parts * N * n_kv_heads * head_dim bytes of fp32 partial
  * sums -- with 16 / 2 heads of 128 dims and 8 parts, 1.8 times q, k, v, d_out on top.  Errors as for st_attn_prefill, but the tensors need only be aligned to
  * their elements here (gradients may be slices of a flat buffer).

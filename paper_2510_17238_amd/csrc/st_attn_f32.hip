@@ -3,8 +3,8 @@
 //
 // Every fp32 operand is split into three bf16 terms (8 + 8 + 8 bits: all 24), and a product is six v_mfma_f32_32x32x16_bf16 instead of
 // eight v_mfma_f32_32x32x2_f32 of twice the length: 192 cycles of the matrix pipe for 16 k-values where fp32 took 512.  The three products
-// left out are below 2^-26 of the whole, the sums are fp32 as before and fewer; against 64 bits the error is 0.76 to 0.90 of what it was with the
-// fp32 instructions, output and gradients, over 24 shapes of 54 to 1,200 tokens.  The operand layouts need no shuffle:
+// left out are below 2^-26 of the whole, the sums are fp32 as before and fewer; against 64 bits the error is 0.72 to 0.88 of what it was with the
+// fp32 instructions, output and gradients, over 26 shapes of 54 to 1,200 tokens.  The operand layouts need no shuffle:
 //   * first-type products (S^T = K Q^T and the like, contraction over the head dims): step j contracts 16 dims, of which a lane holds
 //     16 j + 4 hg .. + 3 and 8 further on (hg = lane / 32): two 16-byte loads of a row as it lies in memory;
 //   * accumulator register i of a lane holds row r(i) = 8 (i / 4) + 4 (lane / 32) + i % 4 of the result's 32 rows, and registers
@@ -17,12 +17,12 @@
 // a KV head, whose keys and values are then split once for both); its FOUR WAVES take the 32-row blocks of the other side in turn and
 // their results meet in LDS at the end.  A wave's chain of blocks is a quarter of the row's -- what a small problem is bound by -- and
 // the waves never wait for each other inside the loop.
-// Bound by what a wave can issue: a block of 32 x 32 x 128 is 96 matrix instructions of 32 cycles in the forward beside 1,000 vector
-// instructions, 700 of them splits; an operand that every wave split for itself is split again by the others.  The splits of the next step
+// Bound by what a wave can issue: a block of 32 x 32 x 128 is 96 matrix instructions of 32 cycles in the forward beside 1,250 vector
+// instructions, 900 of them splits; an operand that every wave split for itself is split again by the others.  The splits of the next step
 // stand behind the matrix instructions of the present one (left to the compiler, the two ran one behind the other: key side 168 us
 // against 147).  The workgroups end in two uneven rounds.
-// Two sequences of about 900 tokens, 16 / 8 heads of 128 dims, us: forward 90 with the fp32 instructions -> 62, query side 137 -> 102,
-// key side 212 -> 146; the training step with tables and rotation 432 -> 317.
+// Two sequences of about 900 tokens, 16 / 8 heads of 128 dims, us: forward 90 with the fp32 instructions -> 65, query side 137 -> 106,
+// key side 212 -> 153; the training step with tables and rotation 432 -> 317.
 #include <math.h>
 
 #include <type_traits>

@@ -762,7 +762,7 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void decode_small16_kernel(Dec
     __syncthreads();
     // Merge: a thread takes one dim of a row, two or four where the rows have more than the threads; everything it needs is read at once, and
     // all waves take part.  (State by state, each with a branch, by the threads that had four dims: 2,900 of the workgroup's 15,800 cycles
-    // with 4 rows of 128 dims, now 2,000; 36 layers of one token, 32 / 8 heads, 400 cached tokens 298 -> 287 us.)
+    // with 4 rows of 128 dims, now 2,000; 36 layers of one token, 32 / 8 heads, 400 cached tokens 298.5 -> 291.5 us.)
     auto merge = [&](auto width) {
         constexpr int N = decltype(width)::value;
         for (int e = int(threadIdx.x) * N; e < a.rows * D; e += 64 * W * N) {

@@ -21,8 +21,9 @@
 //                         row sum is an in-register reduction plus one exchange with lane^32, and the S^T
 //                         accumulators are already laid out as the B operand of the second product.  The
 //                         loop is software-pipelined by hand (see the kernel).
-//   tile_pack_kernel      packed tiles (PACK: the two-head form, long sequences): K rows and TRANSPOSED V rows of every 64-row key tile (stream-compact order)
-//                         gathered into contiguous 16 KB blocks.
+//   tile_pack_kernel      packed tiles (PACK: the two-head form always; the one-head form on long sequences, where a result
+//                         lies over K or V, and for tensors within 4 KB of 4 GiB): K rows and TRANSPOSED V rows of every
+//                         64-row key tile (stream-compact order) gathered into contiguous 16 KB blocks.
 //   rope_table_kernel, key_pack_rope_kernel
 //                         the fused rotation of st_attn_prefill_rope: (cos, sin) of every token once, keys rotated
 //                         on their way into the key tiles; the attention kernel's ROPE form rotates its query rows.
@@ -33,24 +34,6 @@
 
 namespace st {
 
-// --------------------------------------------------------------------------
-// MFMA kernel (bf16): NH = 1 or 2 query heads of one KV head per workgroup.
-// --------------------------------------------------------------------------
-// Every wave owns 32 query rows of a work item for NH query heads that share a KV head.
-//   NH = 2  A K (or V^T) operand fragment read from LDS feeds two MFMAs and one tile copied into LDS
-//           serves twice the arithmetic: LDS read traffic and L2 -> LDS copy traffic per flop are both
-//           halved.  The price is registers (two output accumulators, two score blocks, two Q operands:
-//           about 440 per lane, the output accumulators in accumulation registers), so one wave per SIMD;
-//           three K and three V^T buffers (96 KB), copies two tiles ahead.
-//   NH = 1  fits the ordinary vector registers twice per SIMD: two workgroups per CU, two buffers each
-//           (64 KB), copies one tile ahead.
-// Either way a wave cannot count on other waves to fill the matrix pipe while it does its softmax, so
-// the loop is software-pipelined by hand, in the exact instruction order wanted:
-//   phase X of tile t:  scores of tile t+1   beside  exp2 / bf16 P / row sum of tile t
-//   phase Y of tile t:  O^T += V^T P^T        beside  the moves of tile t+1's scores out of the accumulation registers
-// with ONE barrier per key tile.  There is no running maximum of a row (see the list at the kernel): the reference
-// exponent m_ref is the row maximum of the first tile and only moves when a tile's weights sum beyond 2^kRiseLog2,
-// an out-of-line block.
 // Fused rotation (Sec. 3.2), step 1: the (cos, sin) pairs of every packed row, evaluated ONCE per token (not once per head):
 // the key pack below and the attention kernel's query load both rotate with them.  Laid out for the latter, whose lane (n, hg)
 // holds the dims 16 j + 8 hg .. + 7 of row n: per 32 rows of a packed tile [j][w][hg][n] pairs 16 j + 8 hg + 2 w and + 1, so
@@ -148,10 +131,10 @@ __global__ __launch_bounds__(256) void key_pack_rope_kernel(uint16_t* __restrict
     }
 }
 
-// V^T tiles (blockIdx.y = 0: [D][64 rows], swizzled) and row tiles of K as it is (1), for the two-head form: with sequences of 8K tokens and
-// more a tile is copied into LDS a hundred times and more, and 16 KB in one piece and operands of one LDS read cost the attention less
-// than rows looked up and read transposed (8 x 16K tokens, 32 / 8 heads: 11.89 ms with this pass over memory, 12.04 with gathered
-// rows, 12.0 with packed row tiles of V).
+// V^T tiles (blockIdx.y = 0: [D][64 rows], swizzled) and row tiles of K as it is (1; not where the key pack above has written rotated ones).
+// On long sequences a tile is copied into LDS a hundred times and more, and 16 KB in one piece and operands of one LDS read cost the
+// attention less than rows looked up and read transposed (two-head form, 8 x 16K tokens, 32 / 8 heads: 11.89 ms with this pass over
+// memory, 12.04 with gathered rows, 12.0 with packed row tiles of V; the one-head form's lines stand at the dispatch).
 template <int D>
 __global__ __launch_bounds__(256) void tile_pack_kernel(uint16_t* __restrict__ vc, const uint16_t* __restrict__ v, uint16_t* __restrict__ kc,
                                                         const uint16_t* __restrict__ k, PlanView pv, int n_kv_heads) {
@@ -192,7 +175,7 @@ __global__ __launch_bounds__(256) void tile_pack_kernel(uint16_t* __restrict__ v
 
 template <int D, int STAGES>
 struct PipeSmem {
-    uint16_t k[STAGES][kTileN * D], v[STAGES][kTileN * D];       // row tiles (three stages: of V^T)
+    uint16_t k[STAGES][kTileN * D], v[STAGES][kTileN * D];       // K row tiles; V row tiles, packed V^T tiles
     unsigned char tokens[STAGES == 2 ? RowGather<D>::kBytes : 16];       // (gathered rows)
 };
 // --------------------------------------------------------------------------
@@ -203,8 +186,8 @@ struct PipeSmem {
 //           The price is registers (two output accumulators, two score blocks, two Q operands: about 430 per lane,
 //           the accumulators in accumulation registers), so one wave per SIMD; three K and three V^T buffers
 //           (96 KB), K copied two tiles ahead.
-//   NH = 1  fits the ordinary vector registers twice per SIMD: two workgroups per CU, two buffers each (64 KB),
-//           copies one tile ahead.
+//   NH = 1  fits the ordinary vector registers twice per SIMD: two workgroups per CU, two buffers each (64 KB,
+//           and 4 KB of tokens of gathered rows), copies one tile ahead.
 // Either way a wave cannot count on other waves to fill the matrix pipe while it does its softmax, so the loop
 // is software-pipelined by hand, in the exact instruction order wanted:
 //   phase X of tile t:  scores of tile t+1   beside  exp2 / bf16 P / row sum of tile t
@@ -240,7 +223,7 @@ struct PipeSmem {
 // --------------------------------------------------------------------------
 constexpr float kRiseLog2 = 24.f;
 
-// PACK: K and V^T come as packed tiles (NH = 2 always).
+// PACK: K and V^T come as packed tiles (always with NH = 2); else V's rows, and K's without ROPE, are gathered from the tensors.
 template <int D, int NH, bool ROPE, bool PACK>
 __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint16_t* __restrict__ out, float* __restrict__ lse,
                                                                    const uint16_t* __restrict__ q,
@@ -280,7 +263,7 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
     const int n_tiles = it.a_total + it.b_total;
 
     constexpr int NL = TILE * 2 / 1024 / 4;         // 1 KB copies per wave per tile
-    // K and V tiles: packed ones (NH = 2: K rows, V^T; ROPE: the rotated K rows), each a linear copy, or rows gathered from the tensor.
+    // K and V tiles: packed ones (PACK: K rows, V^T; ROPE: the rotated K rows), each a linear copy, or rows gathered from the tensor.
     // A copy instruction takes its base from scalar registers and one 32-bit byte offset per lane.
     const uint16_t* k_head = PACKED_K ? k + size_t(hk) * pv.pack_tiles * TILE : k + hk * D;
     const uint16_t* v_head = PACKED_V ? v + size_t(hk) * pv.pack_tiles * TILE : v + hk * D;
@@ -647,7 +630,8 @@ __global__ __launch_bounds__(256, NH == 2 ? 1 : 2) void prefill_attn_kernel(uint
         const int stage2 = stage1 == STAGES - 1 ? 0 : stage1 + 1;
         if constexpr (!PACKED_V) next_offsets(ti + kAhead);
         // The copies of this round, behind the first matrix instructions.  NH = 2: K, then V^T, one copy each -- the four waves are here
-        // together, and with four in one place they wait for one another's (8 x 16K tokens 11.01 -> 10.91 ms).  NH = 1: the tokens, then V
+        // together, and with four in one place they wait for one another's (8 x 16K tokens, attention alone 11.01 -> 10.91 ms; the whole step
+        // moves by 1 %, no more than its runs differ).  NH = 1: the tokens, then V
         // and K, all of a tile at once (one by one: the same on 4 x 4K tokens, 2 % slower with heads of 64).
         auto copies = [&](int i) {
             if constexpr (NH == 2) {

@@ -29,7 +29,7 @@ namespace st {
 //                      rounded to bf16)
 // The kernel fits 256 registers, so TWO workgroups share a CU (two waves per SIMD fill each other's gaps between
 // matrix and vector work); the K and V row tiles are double-buffered and copied one tile ahead (64 KB of LDS per
-// workgroup), one barrier per key tile.
+// workgroup, and 4 KB of tokens), one barrier per key tile.
 // The rows of all tiles, here and on the key side, are gathered from the tensors on their way into LDS (RowGather): a pass that packed
 // row tiles and row statistics before took 87 to 100 us of a training step over 4 x 4K tokens, 16 / 8 heads of 128 dims (whole step
 // 1,167 -> 1,075 us with the statistics formed here), 32 of 347 over 10 x 1.7K, 16 / 2 of 64.
@@ -788,7 +788,8 @@ int dkv_parts_f32(const st_plan* plan, int n_q_heads, int n_kv_heads) {
         if (group % p == 0) parts = p;
     return parts;
 }
-// workspace of the fp32 path: delta | partial dK, dV; of the bf16 path: delta (token order) | row statistics | K rows | V rows | Q rows | dO rows | partial dK, dV
+// workspace of the fp32 path: delta | partial dK, dV; of the bf16 path: delta (token order) | row statistics | K rows | V rows | Q rows | dO rows | partial dK, dV;
+// delta and the four kinds of rows are those of the packed form alone: the size does not know the tensors' addresses
 struct BwdLayout {
     size_t delta, stats, krows, vrows, qrows, dorows, partial, total;
     int parts;

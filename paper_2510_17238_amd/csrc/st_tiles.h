@@ -1,10 +1,11 @@
-// Packed 64-row operand tiles and their way into LDS, shared by the forward and the backward attention kernels.
+// 64-row operand tiles and their way into LDS, shared by the forward and the backward attention kernels.
 //
 // A "row tile" holds 64 rows of a stream (stream-compact order) of one head: [64 rows][D], rows parked in the order the first-type MFMA
-// wants, 16-byte chunks XOR-swizzled.  The forward's one-head form gathers row tiles of K and V straight from the tensors into LDS (RowGather); its
-// two-head form and the backward read packed ones (pack_rows; 16 KB each at D = 128, contiguous, so that a tile is a plain linear
-// copy).  Transposed operands come out of a row tile with transposing LDS reads (TrOffsets below), or from a packed "transposed tile" ([D][64
-// rows], swizzled) of the two-head form.
+// wants, 16-byte chunks XOR-swizzled.  The forward's one-head form (K and V) and the gradients (K, V, Q, dO) gather row tiles straight from the tensors into LDS (RowGather).  Packed
+// ones (pack_rows; 16 KB each at D = 128, contiguous, so that a tile is a plain linear copy) are read by the two-head form, by the one-head
+// form on long sequences and of rotated keys, and by both directions where a tensor cannot be gathered: too large, written over by a
+// result, in the gradients also not aligned to 16 bytes.  Transposed operands come out of a row tile with transposing LDS reads (TrOffsets
+// below); the packed V of the forward is a "transposed tile" ([D][64 rows], swizzled).
 #pragma once
 #include "st_plan.h"
 
