@@ -898,11 +898,11 @@ extern "C" st_status st_attn_prefill_bwd(void* dq, void* dk, void* dv, const voi
                            reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + L.partial), s);
     else {
         auto run = [&](auto dtag) {
-            // dq is written while K and V are gathered and before Q and dO are, dk and dv while Q and dO are; a row of `out`, and a
-            // workgroup's own keys and values, are read before the same rows are written.
+            // dq is written while K, V and the rows of `out` are read and before Q and dO are gathered, dk and dv while Q and dO are.  (A
+            // workgroup's own keys and values are read before they may be written over.)
             const size_t row_bytes = size_t(plan->n_tokens) * head_dim * 2, q_bytes = row_bytes * n_q_heads, kv_bytes = row_bytes * n_kv_heads;
             const bool written_over = overlap(dq, q_bytes, q, q_bytes) || overlap(dq, q_bytes, d_out, q_bytes) || overlap(dq, q_bytes, k, kv_bytes) ||
-                                      overlap(dq, q_bytes, v, kv_bytes) || (dq != out && overlap(dq, q_bytes, out, q_bytes)) ||
+                                      overlap(dq, q_bytes, v, kv_bytes) || overlap(dq, q_bytes, out, q_bytes) ||
                                       overlap(dk, kv_bytes, q, q_bytes) || overlap(dk, kv_bytes, d_out, q_bytes) ||
                                       overlap(dv, kv_bytes, q, q_bytes) || overlap(dv, kv_bytes, d_out, q_bytes);
             const bool gather = !written_over && aligned16(q) && aligned16(k) && aligned16(v) && aligned16(d_out) &&

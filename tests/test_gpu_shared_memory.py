@@ -75,3 +75,32 @@ def test_gradients_over_an_input(st, hq, hkv, d, shared, shift):
     assert status == 0
     for c in want:
         assert torch.equal(view[c], want[c]), c
+
+
+@pytest.mark.parametrize("at", [0, 1024])
+def test_gradient_over_the_output_while_kernels_are_timed(st, at):
+    """Timed kernels are launched several times: the second launch must not read an output that the first has written over."""
+    cfg, x, plan = _case(st, 4, 2, 128)
+    lse = torch.empty((cfg.n_tokens, 4), dtype=torch.float32, device=DEV)
+    out = st.st_attn_prefill(x["q"], x["k"], x["v"], plan, lse=lse)
+    want = st.st_attn_prefill_bwd(x["d_out"], x["q"], x["k"], x["v"], out, lse, plan)
+    flat = torch.zeros(2 * out.numel(), dtype=torch.bfloat16, device=DEV)
+    view = flat[at:at + out.numel()].view(out.shape)
+    view.copy_(out)
+    dq, dk, dv = flat[:out.numel()].view(out.shape), torch.empty_like(x["k"]), torch.empty_like(x["v"])
+    lib = st.load_library()
+    ws = torch.empty(int(lib.st_prefill_bwd_workspace_bytes(plan.handle, 4, 2, 128, st.ST_BF16)), dtype=torch.uint8, device=DEV)
+    st.st_profile_repeat(4)
+    st.st_profile_enable(True)
+    try:
+        status = lib.st_attn_prefill_bwd(*(t.data_ptr() for t in (dq, dk, dv, x["d_out"], x["q"], x["k"], x["v"], view)), lse.data_ptr(), plan.handle, 4, 2,
+                                         128, 0.0, st.ST_BF16, ws.data_ptr(), ws.nbytes, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        for which in (st.ST_PROF_BWD_DQ, st.ST_PROF_BWD_DKV):
+            st.st_profile_read(which)
+        st.st_profile_enable(False)
+        st.st_profile_repeat(1)
+    assert status == 0
+    for got, ref in zip((dq, dk, dv), want):
+        assert torch.equal(got, ref)
