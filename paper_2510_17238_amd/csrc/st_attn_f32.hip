@@ -21,8 +21,8 @@
 // instructions, 900 of them splits; an operand that every wave split for itself is split again by the others.  The splits of the next step
 // stand behind the matrix instructions of the present one (left to the compiler, the two ran one behind the other: key side 168 us
 // against 147).  The workgroups end in two uneven rounds.
-// Two sequences of about 900 tokens, 16 / 8 heads of 128 dims, us: forward 90 with the fp32 instructions -> 65, query side 137 -> 106,
-// key side 212 -> 153; the training step with tables and rotation 432 -> 317.
+// Two sequences of about 900 tokens, 16 / 8 heads of 128 dims, us: forward 90 with the fp32 instructions -> 66, query side 137 -> 107,
+// key side 212 -> 154; the training step with tables and rotation 432 -> 317.
 #include <math.h>
 
 #include <type_traits>
